@@ -353,9 +353,10 @@ def exact(case, seed):
 def tolerance(case):
     """Measured against exact(): outputs rounded to bf16 are 1.7e-3 off, products left in fp32 1e-5 to 4e-5
     (their cases also return the bf16 O_A), three bf16 gradients added in bf16 2.8e-3, sums of AdamW 4e-8,
-    Ritz values 3e-8; four times the bf16 rounding, and 1e-5 for plain fp32 sums.  A chained step adds the casts of O_A, where a last-bit difference can move a code (6 per cent of a
-    term) and, if it is the maximum, the scale; folded rows and codes may differ where a value sits on
-    the edge between two codes or two scores are equal to that precision."""
+    Ritz values 3e-8; four times the bf16 rounding, and 1e-5 for plain fp32 sums.  A chained step adds the
+    casts of O_A, where a last-bit difference can move a code (6 per cent of a term) and, if it is the
+    maximum, the scale; folded rows and codes may differ where a value sits on the edge between two codes
+    or two scores are equal to that precision."""
     op = case["op"]
     if op == "optim":
         return {"rel": 1e-5, "max": 1e-3, "differ": 1e-3}
