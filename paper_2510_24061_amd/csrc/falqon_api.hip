@@ -3,11 +3,20 @@
 #include <cmath>
 
 #include "falqon_internal.h"
+#include "gemm_mid.h"
 #include "row_scores.h"
 
 namespace falqon {
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+// Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not.
+static int mid_db_parts(int64_t T, int64_t n, int64_t m)
+{
+    if (!gemm_mid_supported(T, n)) return 0;
+    const int64_t rows = mid_tile_rows(T, n, m), parts = (T + rows - 1) / rows;
+    return parts <= kDbSplitMax ? static_cast<int>(parts) : 0;
+}
 
 WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r)
 {
@@ -19,6 +28,7 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r)
     int oa_parts = oa_splits(T, r), db_parts = db_splits(T, m);
     if (po.use && po.splits > oa_parts) oa_parts = po.splits;
     if (pd.use && pd.groups > db_parts) db_parts = pd.groups;
+    if (mid_db_parts(T, n, m) > db_parts) db_parts = mid_db_parts(T, n, m);
     w.amax_partials = off; off = align_up(off + sizeof(float) * kMaxAmaxBlocks, 256);
     w.scores = off;        off = align_up(off + sizeof(double) * static_cast<size_t>(m + (m + 63) / 64), 256);
     w.delta_sel = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r), 256);
@@ -133,13 +143,14 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
                      : launch_zero_word(reinterpret_cast<uint32_t*>(amax_oa), st);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
-    // O_merged <- x~ W~'^T / (s_w s_x), split into y and O_A.  When the r adapter columns fit
-    // into the last, partly empty tile column of the backbone product they ride along in the one
-    // GEMM, whose epilogue splits them off; otherwise they would add a whole, almost empty tile
-    // column (a second round over the CUs) and are formed from the same x~ by a split-K launch of
-    // the same kernel on the adapter rows instead.
+    // O_merged <- x~ W~'^T / (s_w s_x), split into y and O_A.  Small and medium products run on small tiles
+    // that finish O_A in the same launch.  On the large tiles the r adapter columns ride along in the one
+    // GEMM, whose epilogue splits them off, when they fit into the last, partly empty tile column of the
+    // backbone product; otherwise they would add a whole, almost empty tile column (a second round over
+    // the CUs) and are formed by the backbone tiles' workgroups or by tiles of their own.
+    const bool mid = gemm_mid_supported(T, m);
     const int64_t tile = gemm_tile_n(T, m + r);
-    const bool merged = (m + r + tile - 1) / tile == (m + tile - 1) / tile;
+    const bool merged = !mid && (m + r + tile - 1) / tile == (m + tile - 1) / tile;
     GemmArgs g;
     g.a = xq; g.lda = n; g.a_fmt = 0;
     g.b = wq; g.ldb = n; g.b_is_kn = 0;
@@ -147,6 +158,12 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     g.sa = s_x; g.sb = s_w;
     g.c0 = y; g.ldc0 = m; g.c0_is_f32 = (yt == FALQON_F32); g.n_split = m;
     g.c1 = o_a; g.ldc1 = r; g.amax1 = reinterpret_cast<uint32_t*>(amax_oa);
+    if (mid) {
+        MidSide side;
+        side.rows = wq + m * n; side.r = r;
+        e = launch_gemm_mid(g, side, -1, st);
+        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    }
     if (merged) {
         e = launch_gemm(g, st);
         return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
@@ -169,7 +186,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
         return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
     }
     // Otherwise: the same GEMM kernel on the adapter rows, K split over workgroups.  Nothing orders
-    // the two products, so when the backbone product runs on the large tiles both go out as one launch.
+    // the two products, so both go out as one launch.
     const int splits = oa_splits(T, r);
     int64_t kps = (n + splits - 1) / splits;
     kps = (kps + 127) / 128 * 128;
@@ -181,12 +198,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     h.c0 = part; h.ldc0 = r; h.c0_is_f32 = 1; h.n_split = r;
     h.c1 = nullptr; h.ldc1 = 0; h.amax1 = nullptr;
     h.splits = splits; h.k_per_split = kps;
-    if (gemm_fwd_pair_supported(g, h)) {
-        e = launch_gemm_fwd_pair(g, h, st);
-    } else {
-        e = launch_gemm(g, st);
-        if (e == hipSuccess) e = launch_gemm(h, st);
-    }
+    e = launch_gemm_fwd_pair(g, h, st);
     if (e != hipSuccess) return FALQON_ERR_HIP;
     e = launch_sum_partials_bf16(part, splits, T * r, static_cast<uint16_t*>(o_a),
                                  reinterpret_cast<uint32_t*>(amax_oa), st);
@@ -217,12 +229,13 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t* w8 = static_cast<uint8_t*>(ws);
 
-    // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by side jobs of the dX tiles, the
+    // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
     // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
     const DbTailPlan pd = dx ? plan_db_tail(T, n, m, r) : DbTailPlan{false, 0};
+    const int mid_parts = dx ? mid_db_parts(T, n, m) : 0;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
-                                   reinterpret_cast<float*>(w8 + L.amax_partials), nullptr, st, pd.use ? &sc : nullptr);
+                                   reinterpret_cast<float*>(w8 + L.amax_partials), nullptr, st, pd.use || mid_parts ? &sc : nullptr);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
     // dX <- dy~ W~ / (s_dy s_w): the backbone rows of the concatenated weight, read as [K = m, N = n]
@@ -236,8 +249,12 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     // dB <- dy~^T O_A~ / (s_dy s_oa);  DeltaBuffer += -lr dB.  Its partial pass reads only dy~ and
     // O_A, so nothing orders it against the dX product: on the large tiles both go out as one launch.
     const DbArgs d = make_db_args(dyq, o_a, amax_oa, T, m, r, reinterpret_cast<float*>(w8 + L.db_partials),
-                                  pd.use ? pd.groups : db_splits(T, m));
-    if (pd.use) {
+                                  pd.use ? pd.groups : mid_parts ? mid_parts : db_splits(T, m));
+    if (mid_parts) {
+        MidSide side;
+        side.r = r; side.oaq = w8 + L.oa_codes; side.db_partial = d.partial;
+        e = launch_gemm_mid(g, side, -1, st);
+    } else if (pd.use) {
         TailArgs t;
         t.side = w8 + L.oa_codes; t.r = r; t.partial = d.partial; t.splits = 0; t.steps_per_split = 0; t.row_parts = 1;
         e = launch_gemm_dx_tail(g, t, st);

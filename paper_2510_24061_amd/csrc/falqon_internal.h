@@ -58,7 +58,6 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 int64_t gemm_tile_n(int64_t M, int64_t N);   // width of the output tiles launch_gemm picks for an M x N product
 // g (large product, 256x256 tiles) and h (a split-K product on 128x128 tiles) in one launch; both
 // [N,K], E4M3.  Results are those of launch_gemm(g) and launch_gemm(h).
-bool gemm_fwd_pair_supported(const GemmArgs& g, const GemmArgs& h);
 hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t stream);
 
 // What every 256x256 backbone tile does for the adapter besides its own tile (gemm.hip).

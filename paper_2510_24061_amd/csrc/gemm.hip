@@ -28,60 +28,11 @@
 
 #include "db_tile.h"
 #include "falqon_internal.h"
+#include "gemm_common.h"
+#include "gemm_mid.h"
 
 namespace falqon {
 namespace {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-#define FQ_GLOBAL_PTR(p) ((const void __attribute__((address_space(1)))*)(p))
-#define FQ_LDS_PTR(p) ((void __attribute__((address_space(3)))*)(p))
-
-__device__ __attribute__((aligned(16))) uint8_t g_zero16[16];
-
-constexpr int BK = 128;   // bytes of K per step (two 64-deep MFMAs)
-
-// Swizzle of a K-contiguous tile (128 B = 8 chunks of 16 B per row): the physical chunk of
-// logical chunk c in row `row` is c ^ swz_kc(row).  Any 8 or 16 consecutive rows land on
-// distinct 16-byte bank groups for a fixed logical chunk.
-__device__ __forceinline__ int swz_kc(int row) { return ((row >> 1) ^ ((row & 1) << 2)) & 7; }
-
-// Swizzle of a [K][N] tile with CH chunks of 16 B per K-row.
-template <int CH>
-__device__ __forceinline__ int swz_kn(int krow) { return CH >= 16 ? ((krow & 7) << 1) : (krow & (CH - 1)); }
-
-__device__ __forceinline__ const uint8_t* opaque_uniform(const uint8_t* p)
-{
-    const uint64_t u = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
-    return reinterpret_cast<const uint8_t*>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits for every
-// outstanding global access, which would drain the global_load_lds fetches that are meant to
-// stay in flight across the barrier; their completion is awaited explicitly where needed.
-__device__ __forceinline__ void barrier_lds_only()
-{
-    asm volatile("" ::: "memory");               // compiler-level: no LDS access moves across
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-}
-
-// two fp32 -> two bf16 (round to nearest even) in one dword: v_cvt_pk_bf16_f32
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
-{
-    typedef float v2f __attribute__((ext_vector_type(2)));
-    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-    const v2f f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
-}
 
 // ---- side jobs of a 256x256 backbone tile ---------------------------------------------------------
 // The adapter's two small products (O_A = x~ A~^T in the forward launch, dB = dy~^T O_A~ in the
@@ -954,7 +905,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream)
 
 }  // namespace
 
-static bool use_big_tiles(int64_t M, int64_t N)
+bool use_big_tiles(int64_t M, int64_t N)
 {
     // Large problems: 256x256 tiles, one workgroup per CU.  Small ones: 128x128 so that more
     // than a handful of CUs take part.
@@ -962,11 +913,6 @@ static bool use_big_tiles(int64_t M, int64_t N)
 }
 
 int64_t gemm_tile_n(int64_t M, int64_t N) { return use_big_tiles(M, N) ? 256 : 128; }
-
-bool gemm_fwd_pair_supported(const GemmArgs& g, const GemmArgs& h)
-{
-    return use_big_tiles(g.M, g.N) && g.splits == 1 && !g.b_is_kn && !h.b_is_kn && g.a_fmt == 0 && h.a_fmt == 0;
-}
 
 hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t stream)
 {
@@ -1070,11 +1016,17 @@ hipError_t launch_gemm_dx_db_pair(const GemmArgs& g, const DbArgs& d, hipStream_
     return hipGetLastError();
 }
 
+hipError_t launch_gemm_tiles(const GemmArgs& g, hipStream_t stream)
+{
+    if (use_big_tiles(g.M, g.N)) return launch_cfg<2, 2, 4, 4>(g, stream);
+    return launch_cfg<2, 2, 2, 2>(g, stream);
+}
+
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    if (use_big_tiles(g.M, g.N)) return launch_cfg<2, 2, 4, 4>(g, stream);
-    return launch_cfg<2, 2, 2, 2>(g, stream);
+    if (g.splits == 1 && gemm_mid_supported(g.M, g.N)) return launch_gemm_mid(g, MidSide{}, -1, stream);
+    return launch_gemm_tiles(g, stream);
 }
 
 }  // namespace falqon

@@ -1,0 +1,61 @@
+// Device helpers shared by the two families of FP8 product kernels (gemm.hip: tiles of 256 and more
+// tokens; gemm_mid.hip: small tiles on deep rings).
+#pragma once
+#include "falqon_internal.h"
+
+namespace falqon {
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+#define FQ_GLOBAL_PTR(p) ((const void __attribute__((address_space(1)))*)(p))
+#define FQ_LDS_PTR(p) ((void __attribute__((address_space(3)))*)(p))
+
+__device__ __attribute__((aligned(16))) uint8_t g_zero16[16];
+
+constexpr int BK = 128;   // bytes of K per step (two 64-deep MFMAs)
+
+// Swizzle of a K-contiguous tile (128 B = 8 chunks of 16 B per row): the physical chunk of
+// logical chunk c in row `row` is c ^ swz_kc(row).  Any 8 or 16 consecutive rows land on
+// distinct 16-byte bank groups for a fixed logical chunk.
+__device__ __forceinline__ int swz_kc(int row) { return ((row >> 1) ^ ((row & 1) << 2)) & 7; }
+
+// Swizzle of a [K][N] tile with CH chunks of 16 B per K-row.
+template <int CH>
+__device__ __forceinline__ int swz_kn(int krow) { return CH >= 16 ? ((krow & 7) << 1) : (krow & (CH - 1)); }
+
+__device__ __forceinline__ const uint8_t* opaque_uniform(const uint8_t* p)
+{
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
+    return reinterpret_cast<const uint8_t*>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits for every
+// outstanding global access, which would drain the global_load_lds fetches that are meant to
+// stay in flight across the barrier; their completion is awaited explicitly where needed.
+__device__ __forceinline__ void barrier_lds_only()
+{
+    asm volatile("" ::: "memory");               // compiler-level: no LDS access moves across
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
+// two fp32 -> two bf16 (round to nearest even) in one dword: v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    const v2f f = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
+}
+
+}  // namespace
+}  // namespace falqon
