@@ -10,12 +10,14 @@ namespace falqon {
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not.
+// Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not, because
+// the ordered sum of that many partials would cost more than the launch it saves (7 to 12 us).
+constexpr int64_t kMidDbMax = 64;
 static int mid_db_parts(int64_t T, int64_t n, int64_t m)
 {
     if (!gemm_mid_supported(T, n)) return 0;
     const int64_t rows = mid_tile_rows(T, n, m), parts = (T + rows - 1) / rows;
-    return parts <= kDbSplitMax ? static_cast<int>(parts) : 0;
+    return parts <= kMidDbMax ? static_cast<int>(parts) : 0;
 }
 
 WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r)
@@ -148,9 +150,10 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     // GEMM, whose epilogue splits them off, when they fit into the last, partly empty tile column of the
     // backbone product; otherwise they would add a whole, almost empty tile column (a second round over
     // the CUs) and are formed by the backbone tiles' workgroups or by tiles of their own.
-    const bool mid = gemm_mid_supported(T, m);
-    const int64_t tile = gemm_tile_n(T, m + r);
-    const bool merged = !mid && (m + r + tile - 1) / tile == (m + tile - 1) / tile;
+    const OaTailPlan po = plan_oa_tail(T, n, m, r);
+    const bool fits = (m + r + 255) / 256 == (m + 255) / 256;
+    const bool mid = gemm_mid_supported(T, m) || (!use_big_tiles(T, m) && !fits && !po.use);
+    const bool merged = !mid && fits;
     GemmArgs g;
     g.a = xq; g.lda = n; g.a_fmt = 0;
     g.b = wq; g.ldb = n; g.b_is_kn = 0;
@@ -173,11 +176,10 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     // side job ahead of the tile that leaves fp32 partials over K slices, which one more pass adds
     // in order, rounds to bf16 and takes the maximum of.
     float* part = reinterpret_cast<float*>(w8 + L.oa_partials);
-    const OaTailPlan po = plan_oa_tail(T, n, m, r);
     if (po.use) {
         TailArgs t;
         t.side = wq + m * n; t.r = r; t.partial = part; t.splits = po.splits; t.steps_per_split = po.steps_per_split;
-        t.row_parts = po.row_parts;
+        t.row_parts = po.row_parts; t.tile_rows = po.tile_rows;
         e = launch_gemm_fwd_tail(g, t, st);
         if (e != hipSuccess) return FALQON_ERR_HIP;
         if (po.splits > 0)                                       // (no partials: the launch wrote O_A and its maximum)
@@ -231,7 +233,7 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
 
     // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
     // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
-    const DbTailPlan pd = dx ? plan_db_tail(T, n, m, r) : DbTailPlan{false, 0};
+    const DbTailPlan pd = dx ? plan_db_tail(T, n, m, r) : DbTailPlan{false, 0, 256};
     const int mid_parts = dx ? mid_db_parts(T, n, m) : 0;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
@@ -257,6 +259,7 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     } else if (pd.use) {
         TailArgs t;
         t.side = w8 + L.oa_codes; t.r = r; t.partial = d.partial; t.splits = 0; t.steps_per_split = 0; t.row_parts = 1;
+        t.tile_rows = pd.tile_rows;
         e = launch_gemm_dx_tail(g, t, st);
     } else if (!dx) {
         e = launch_db_partial(d, st);                      // the layer's input needs no gradient
@@ -403,13 +406,13 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
     uint8_t* w8 = static_cast<uint8_t*>(side_ws);
     TailArgs t;
     t.side = side; t.r = r; t.splits = 0; t.steps_per_split = 0; t.row_parts = 1;
+    if (!use_big_tiles(M, N)) return FALQON_ERR_SHAPE;
     hipError_t e;
     if (!b_is_kn) {
         const OaTailPlan po = plan_oa_tail(M, n, m, r);
-        const int64_t tile = gemm_tile_n(M, m + r);
-        if (!po.use || (m + r + tile - 1) / tile == (m + tile - 1) / tile) return FALQON_ERR_SHAPE;
+        if (!po.use || (m + r + 255) / 256 == (m + 255) / 256) return FALQON_ERR_SHAPE;
         t.partial = reinterpret_cast<float*>(w8 + L.oa_partials); t.splits = po.splits; t.steps_per_split = po.steps_per_split;
-        t.row_parts = po.row_parts;
+        t.row_parts = po.row_parts; t.tile_rows = po.tile_rows;
         if (po.splits == 0) {                                    // O_A (bf16) instead of partials
             g.c1 = w8 + L.oa_partials; g.ldc1 = r;
         }
@@ -417,7 +420,7 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
     } else {
         const DbTailPlan pd = plan_db_tail(M, n, m, r);
         if (!pd.use) return FALQON_ERR_SHAPE;
-        t.partial = reinterpret_cast<float*>(w8 + L.db_partials);
+        t.partial = reinterpret_cast<float*>(w8 + L.db_partials); t.tile_rows = pd.tile_rows;
         e = launch_gemm_dx_tail(g, t, st);
     }
     return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;

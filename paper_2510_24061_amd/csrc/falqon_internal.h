@@ -55,7 +55,6 @@ struct GemmArgs {
     int splits = 1; int64_t k_per_split = int64_t(1) << 40;   // split K: c0 becomes [splits][M][ldc0] partials
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream);
-int64_t gemm_tile_n(int64_t M, int64_t N);   // width of the output tiles launch_gemm picks for an M x N product
 // g (large product, 256x256 tiles) and h (a split-K product on 128x128 tiles) in one launch; both
 // [N,K], E4M3.  Results are those of launch_gemm(g) and launch_gemm(h).
 hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t stream);
@@ -72,9 +71,10 @@ hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_
 //                          partial[groups][m][r], raw sums; splits / steps_per_split unused
 struct TailArgs {
     const uint8_t* side; int64_t r; float* partial; int splits; int steps_per_split; int row_parts;
+    int tile_rows = 256;     // token rows of the tiles: 128, 192 or 256
 };
-struct OaTailPlan { bool use; int splits; int steps_per_split; int row_parts; };
-struct DbTailPlan { bool use; int groups; };
+struct OaTailPlan { bool use; int splits; int steps_per_split; int row_parts; int tile_rows; };
+struct DbTailPlan { bool use; int groups; int tile_rows; };
 OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r);     // forward of a [T,n] x [m+r,n] layer
 DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r);     // backward of the same layer
 hipError_t launch_gemm_fwd_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream);

@@ -179,15 +179,16 @@ __device__ __forceinline__ void oa_side_run(const TailArgs& t, const GemmArgs& g
     __syncthreads();                                              // the share's LDS reads are done: the tile may overwrite
 }
 
-// Input gradient: token tile rows are paired into groups of 512 tokens; the workgroups of a group
+// Input gradient: token tile rows (BM tokens) are paired into groups; the workgroups of a group
 // divide the output features (the K dimension of this launch) among themselves in steps of 128.  A
-// workgroup multiplies, per feature step, dy~[512 tokens][128 features] with O_A~[512 tokens][rank]
+// workgroup multiplies, per feature step, dy~[2 BM tokens][128 features] with O_A~[2 BM tokens][rank]
 // over the tokens and writes raw sums to partial[group][feature][rank].  Both tiles sit in LDS as
 // [token][feature] and are read with the transposing LDS read (dbt::read_tokens_of_feature).
-constexpr int kDbTailTokens = 512, kDbTailGroupRows = 2;
+constexpr int kDbTailGroupRows = 2;                               // a group: 2 BM tokens
 
 struct DbTailGeom { int group, f_begin, f_end; int64_t t0, t_end; };
 
+template <int BM>
 __device__ __forceinline__ DbTailGeom db_side_geom(const GemmArgs& g, int tile_m, int tile_n, int tiles_m, int tiles_n)
 {
     DbTailGeom q;
@@ -200,17 +201,20 @@ __device__ __forceinline__ DbTailGeom db_side_geom(const GemmArgs& g, int tile_m
     const int w = (tile_m - q.group * kDbTailGroupRows) * tiles_n + tile_n;
     q.f_begin = w * per;
     q.f_end = q.f_begin + per < F ? q.f_begin + per : F;
-    q.t0 = static_cast<int64_t>(q.group) * kDbTailTokens;
-    q.t_end = q.t0 + kDbTailTokens < g.M ? q.t0 + kDbTailTokens : g.M;
+    constexpr int TOKENS = kDbTailGroupRows * BM;
+    q.t0 = static_cast<int64_t>(q.group) * TOKENS;
+    q.t_end = q.t0 + TOKENS < g.M ? q.t0 + TOKENS : g.M;
     return q;
 }
 
+template <int BM>
 __device__ __forceinline__ void db_side_fetch(const TailArgs& t, const GemmArgs& g, const DbTailGeom& q, int c, bool with_oa,
                                               uint8_t* lds_dy, uint8_t* lds_oa, int wave, int lane)
 {
+    constexpr int TOKENS = kDbTailGroupRows * BM;
     const int64_t i0 = static_cast<int64_t>(q.f_begin + c) * 128;
 #pragma unroll
-    for (int it = 0; it < kDbTailTokens / 8 / 4; ++it) {         // dy~: 8 token rows of 128 bytes per wave instruction
+    for (int it = 0; it < TOKENS / 8 / 4; ++it) {         // dy~: 8 token rows of 128 bytes per wave instruction
         const int i = it * 4 + wave;
         const int trow = i * 8 + (lane >> 3);
         const int64_t gt = q.t0 + trow, gi = i0 + (((lane & 7) ^ dbt::swz_t<8>(trow)) << 4);
@@ -219,7 +223,7 @@ __device__ __forceinline__ void db_side_fetch(const TailArgs& t, const GemmArgs&
     if (!with_oa) return;
     const int64_t r = t.r;
 #pragma unroll
-    for (int it = 0; it < kDbTailTokens / 16 / 4; ++it) {        // O_A~: 16 token rows of 64 bytes per wave instruction
+    for (int it = 0; it < TOKENS / 16 / 4; ++it) {        // O_A~: 16 token rows of 64 bytes per wave instruction
         const int i = it * 4 + wave;
         const int trow = i * 16 + (lane >> 2);
         const int64_t gt = q.t0 + trow, gp = ((lane & 3) ^ dbt::swz_t<4>(trow)) << 4;
@@ -228,6 +232,7 @@ __device__ __forceinline__ void db_side_fetch(const TailArgs& t, const GemmArgs&
 }
 
 // Step 0 (with O_A~) has been issued by the caller, followed by the tile's first stage.
+template <int BM>
 __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g, const DbTailGeom& q,
                                             uint8_t* lds_dy, uint8_t* lds_oa, int wave, int lane)
 {
@@ -237,7 +242,7 @@ __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g
     for (int c = 0; q.f_begin + c < q.f_end; ++c) {
         if (c > 0) {
             __syncthreads();                                      // every wave has read the previous feature step
-            db_side_fetch(t, g, q, c, false, lds_dy, lds_oa, wave, lane);
+            db_side_fetch<BM>(t, g, q, c, false, lds_dy, lds_oa, wave, lane);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -256,9 +261,10 @@ __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g
                 acc[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bb, acc[b], 1 /* E5M2 */, 0 /* E4M3 */, 0, 0, 0, 0);
             }
         };
-        if (k_blocks == kDbTailTokens / 64) {                     // a full group: unrolled, so that LDS reads run ahead
+        constexpr int BLOCKS = kDbTailGroupRows * BM / 64;
+        if (k_blocks == BLOCKS) {                                 // a full group: unrolled, so that LDS reads run ahead
 #pragma unroll
-            for (int kb = 0; kb < kDbTailTokens / 64; ++kb) k_block(kb);
+            for (int kb = 0; kb < BLOCKS; ++kb) k_block(kb);
         } else {
             for (int kb = 0; kb < k_blocks; ++kb) k_block(kb);
         }
@@ -278,9 +284,16 @@ __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g
 }
 
 // LDS of one workgroup: operand rings, the left operand three stages deep, the right operand two
-// (160 KB at 256x256).
+// (160 KB at 256x256), or three where a tile of 128 rows leaves the room (144 KB, and 12 KB for the adapter
+// rows that ride along): its half-step is too short to hide a fetch.
+template <int MB, int NB>
+constexpr int right_ring() { return MB == 2 && NB == 4 ? 3 : 2; }
+constexpr int kRideStage = 32 * BK;                               // 32 adapter rows of one stage
 template <int WM, int WN, int MB, int NB>
-constexpr int gemm_lds_bytes() { return (3 * WM * MB + 2 * WN * NB) * 32 * BK; }
+constexpr int gemm_lds_bytes()
+{
+    return (3 * WM * MB + right_ring<MB, NB>() * WN * NB) * 32 * BK + (right_ring<MB, NB>() == 3 ? 3 * kRideStage : 0);
+}
 
 // One output tile.  `bid` is the workgroup's index in a grid of 8 * chunk workgroups whose index
 // modulo 8 is the XCD it runs on, `split` its K split; `lds` is gemm_lds_bytes() of LDS, 1 KB aligned.
@@ -294,7 +307,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
                                           const int bid, const int split, uint8_t* const lds,
                                           const TailArgs* const tail = nullptr)
 {
-    static_assert(TAIL == 0 || (WM == 2 && WN == 2 && MB == 4 && NB == 4), "side jobs ride on the 256x256 tile only");
+    static_assert(TAIL == 0 || (WM == 2 && WN == 2 && NB == 4), "the adapter's products ride on the 256-column tiles only");
+    static_assert(TAIL != 1 || MB == 4, "the O_A side job is laid out for 256 token rows");
     static_assert((TAIL != 1 && TAIL != 3 && TAIL != 4 && TAIL != 5) || (!B_KN && A_FMT == 0), "the adapter product belongs to the forward product");
     static_assert(TAIL != 2 || (B_KN && A_FMT == 1), "the dB slice belongs to the input-gradient product");
     constexpr int BM = WM * MB * 32, BN = WN * NB * 32, NW = WM * WN;
@@ -327,8 +341,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     const uint8_t* const gb = B_KN ? g.b + kbeg * g.ldb : g.b + kbeg;
     uint8_t* const c0p = static_cast<uint8_t*>(g.c0) +
                          static_cast<int64_t>(split) * M * g.ldc0 * (g.c0_is_f32 ? 4 : 2);
-    // rescale factor: read here, where the two loads hide under the first operand fetches, and kept in
-    // a scalar register (read at the top of the epilogue they cost every tile a memory round trip)
+    // rescale factor: kept in a scalar register (read at the top of the epilogue it costs every tile a
+    // memory round trip)
     const float inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / ((*g.sa) * (*g.sb)))));
 
     // ---- global -> LDS ----------------------------------------------------------------------
@@ -338,6 +352,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     // products land in output elements that are never stored.  The K tail cannot be clamped
     // (it would add foreign terms to valid outputs); its step fetches out-of-range chunks from
     // a block of zeros instead (slow path, at most one step per tile).
+    constexpr int BR = right_ring<MB, NB>();
     constexpr int IT_A = BM / 8 / NW, IT_B = B_BYTES / 1024 / NW;
     constexpr int CH = BN / 16;                               // [K][N] tile: chunks per K-row
     constexpr int RPI = 64 / CH;                              // [K][N] tile: K-rows per wave instruction
@@ -488,6 +503,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
         if (!B_KN) return read_kc(sB, wn * NB * 32 + ni * 32 + (lane & 31), kh);
         return read_kn(sB, wn * NB * 32 + ni * 32, kh);
     };
+    constexpr bool RIDE = TAIL == 3 || TAIL == 4 || TAIL == 5;
+    constexpr int RB = TAIL == 5 ? 4 : TAIL == 4 ? 2 : 1;
+    // On the 128-row tiles the adapter operand takes the way of the others, through the LDS: the four
+    // waves of a workgroup share their rank blocks, and read straight from memory (16 bytes of a row per
+    // lane) it would take the vector-memory path longer than the tile's own operands.
+    constexpr bool RIDE_LDS = RIDE && BR == 3 && RB <= 2;
     constexpr int N_MFMA = MB * NB, N_FRAG = MB + NB;
     constexpr int A_PER_SLOT = (IT_A + N_MFMA - 1) / N_MFMA, B_PER_SLOT = (IT_B + N_MFMA - 1) / N_MFMA;
     constexpr int FRAGS_PER_SLOT = (N_FRAG + N_MFMA - 1) / N_MFMA;
@@ -495,7 +516,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     constexpr int WAIT_ALL = 0;
     constexpr int WAIT_LDS = 0xC07F;                                                            // lgkmcnt 0 only
     constexpr int WAIT_BUT_A = (IT_A & 15) | (7 << 4) | ((IT_A >> 4) << 14);                    // lgkmcnt 0
-    constexpr int WAIT_BUT_STAGE = ((IT_A + IT_B) & 15) | (7 << 4) | (((IT_A + IT_B) >> 4) << 14);
+    constexpr int STAGE_FETCHES = IT_A + IT_B + (RIDE_LDS ? 1 : 0);
+    constexpr int WAIT_BUT_STAGE = (STAGE_FETCHES & 15) | (7 << 4) | ((STAGE_FETCHES >> 4) << 14);
 
     v8i af[2][MB], bf[2][NB];
     // read fragment f (right-operand fragments first) of half kh from a stage
@@ -505,23 +527,23 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     };
 
     // ---- adapter product riding on the tile's own K-steps (TAIL == 3, 4) -------------------------
-    // O_A of a tile row is 16 blocks of 16 token rows by r / 16 blocks of 16 ranks.  Wave w of tile
-    // column c takes, of token rows [16 (u % 16), +16) of the tile row, u = 4 c + w, the RB rank
-    // blocks from RB (u / 16) on (RB = 1, 2, 4 for TAIL == 3, 4, 5), over all of K.  Its token
+    // O_A of a tile row is TB = BM / 16 blocks of 16 token rows by r / 16 blocks of 16 ranks.  Wave w of
+    // tile column c takes, of token rows [16 (u % TB), +16) of the tile row, u = 4 c + w, the RB rank
+    // blocks from RB (u / TB) on (RB = 1, 2, 4 for TAIL == 3, 4, 5), over all of K.  Its token
     // operand is read from the left tile that sits in LDS for the tile's own product, its adapter
     // operands straight from memory one step ahead; RB 16x16x128 MFMAs per K-step and no partial
     // results.  Waves without a block run the same instructions on clamped rows and store nothing, so
     // the loop carries no branch for it.
-    constexpr bool RIDE = TAIL == 3 || TAIL == 4 || TAIL == 5;
-    constexpr int RB = TAIL == 5 ? 4 : TAIL == 4 ? 2 : 1;
     v4f accx[RB];
 #pragma unroll
     for (int j = 0; j < RB; ++j) accx[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     float ride_max = 0.0f;
     v8i sb[RB];
     const int ride_u = tile_n * NW + wave;
-    const int ride_row = (ride_u & 15) * 16 + (lane & 15);     // row of the left tile
-    const int ride_blk0 = (ride_u >> 4) * RB;                  // first rank block of the wave
+    constexpr int TB = BM / 16;                                // token blocks of a tile row
+    const int ride_tb = ride_u % TB;
+    const int ride_row = ride_tb * 16 + (lane & 15);           // row of the left tile
+    const int ride_blk0 = (ride_u / TB) * RB;                  // first rank block of the wave
     // adapter operand of stage s: lane part of the address, and the wave's rank blocks (a block
     // beyond the rank is clamped to the last one)
     const uint8_t* ride_src = nullptr;
@@ -565,7 +587,34 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
         for (int j = 0; j < RB; ++j)
             asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+v"(accx[j]) : "v"(sb[j]), "v"(xa));
     };
-    if constexpr (RIDE) ride_load(0, false);
+    // the same operands by way of the LDS (RIDE_LDS): 32 adapter rows per stage from the first rank block on
+    uint8_t* const lds_r = lds_b + BR * B_BYTES;
+    uint32_t off_r = 0;
+    const uint8_t* base_r = nullptr;
+    if constexpr (RIDE_LDS) {
+        const int row = wave * 8 + (lane >> 3);
+        int rr = ride_blk0 * 16 + row;
+        if (rr >= tail->r) rr = static_cast<int>(tail->r) - 1;
+        off_r = static_cast<uint32_t>(rr) * static_cast<uint32_t>(g.ldb) + (((lane & 7) ^ swz_kc(row)) << 4);
+        base_r = tail->side;
+    }
+    auto fetch_r = [&](int s, uint8_t* dst, bool inside) {
+        const int64_t gk = static_cast<int64_t>(s) * BK + (((lane & 7) ^ swz_kc(wave * 8 + (lane >> 3))) << 4);
+        dma16(inside || gk < g.K ? base_r + static_cast<int64_t>(s) * BK + off_r : g_zero16, dst + wave * 1024);
+    };
+    auto ride_read_adapter = [&](const uint8_t* tile) {
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            const int row = (j & 1) * 16 + (lane & 15), cb = (lane >> 4) * 2;
+            const uint8_t* base = tile + row * BK;
+            const v4i lo = *reinterpret_cast<const v4i*>(base + ((cb ^ swz_kc(row)) << 4));
+            const v4i hi = *reinterpret_cast<const v4i*>(base + (((cb + 1) ^ swz_kc(row)) << 4));
+            sb[j][0] = lo[0]; sb[j][1] = lo[1]; sb[j][2] = lo[2]; sb[j][3] = lo[3];
+            sb[j][4] = hi[0]; sb[j][5] = hi[1]; sb[j][6] = hi[2]; sb[j][7] = hi[3];
+        }
+    };
+    if constexpr (RIDE_LDS) fetch_r(0, lds_r, false);
+    else if constexpr (RIDE) ride_load(0, false);
 
     // The side job's first operand fetches go out ahead of the tile's first stage; the job itself
     // runs while that stage is in flight or has landed, and ends with a barrier, after which the
@@ -583,12 +632,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
             fetch_b_all(0, lds_b);
         }
     } else if constexpr (TAIL == 2) {
-        const DbTailGeom q = db_side_geom(g, tile_m, tile_n, tiles_m, tiles_n);
+        const DbTailGeom q = db_side_geom<BM>(g, tile_m, tile_n, tiles_m, tiles_n);
         if (q.f_begin < q.f_end) {
-            db_side_fetch(*tail, g, q, 0, true, lds + A_BYTES, lds_b + B_BYTES, wave, lane);
+            db_side_fetch<BM>(*tail, g, q, 0, true, lds + A_BYTES, lds_b + B_BYTES, wave, lane);
             fetch_a_all(0, lds);
             fetch_b_all(0, lds_b);
-            db_side_run(*tail, g, q, lds + A_BYTES, lds_b + B_BYTES, wave, lane);
+            db_side_run<BM>(*tail, g, q, lds + A_BYTES, lds_b + B_BYTES, wave, lane);
         } else {
             fetch_a_all(0, lds);
             fetch_b_all(0, lds_b);
@@ -600,6 +649,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     if (KT > 1) {
         fetch_a_all(1, lds + A_BYTES);
         fetch_b_all(1, lds_b + B_BYTES);
+        if constexpr (RIDE_LDS) fetch_r(1, lds_r + kRideStage, false);
         __builtin_amdgcn_s_waitcnt(WAIT_BUT_STAGE);           // stage 0 has landed
     } else {
         __builtin_amdgcn_s_waitcnt(WAIT_ALL);
@@ -609,8 +659,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     for (int f = 0; f < N_FRAG; ++f) read_frag(lds, lds_b, 0, f);
     if constexpr (RIDE) {
         xa = ride_read(lds);
+        if constexpr (RIDE_LDS) ride_read_adapter(lds_r);
         ride_mfma();
-        if (KT > 1) ride_load(1, false);
+        if (!RIDE_LDS && KT > 1) ride_load(1, false);
     }
     __builtin_amdgcn_s_waitcnt(WAIT_LDS);
 
@@ -622,9 +673,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
         constexpr bool STEADY = decltype(steady_tag)::value;
         const int ia1 = ia == 2 ? 0 : ia + 1, ia2 = ia1 == 2 ? 0 : ia1 + 1;
         const uint8_t* sA = lds + ia * A_BYTES;
-        const uint8_t* sB = lds_b + (kt & 1) * B_BYTES;
+        const uint8_t* sB = lds_b + (BR == 3 ? ia : (kt & 1)) * B_BYTES;
         uint8_t* nA = lds + ia2 * A_BYTES;                     // destination of stage k+2, left
-        uint8_t* nB = lds_b + (kt & 1) * B_BYTES;              // destination of stage k+2, right
+        uint8_t* nB = lds_b + (BR == 3 ? ia2 : (kt & 1)) * B_BYTES;   // destination of stage k+2, right
         const bool fetch = STEADY || kt + 2 < KT;
         const bool fast = STEADY || (fetch && (static_cast<int64_t>(kt + 3) * BK <= K));
         const bool next = STEADY || kt + 1 < KT;
@@ -632,6 +683,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
         const uint8_t* pb = opaque_uniform(base_b + (kt + 2) * kstep_b);
         // ---- half 0 ----
         if (!STEADY && fetch && !fast) fetch_a_all(kt + 2, nA); // K tail: zero-filled slow path
+        if (BR == 3 && !STEADY && fetch && !fast) {
+            fetch_b_all(kt + 2, nB);
+            if constexpr (RIDE_LDS) fetch_r(kt + 2, lds_r + ia2 * kRideStage, false);
+        }
 #pragma unroll
         for (int mi = 0; mi < MB; ++mi) {
 #pragma unroll
@@ -642,39 +697,54 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
                 acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                     bf[0][ni], af[0][mi], acc[mi][ni], 0 /* E4M3 */, A_FMT, 0, 0, 0, 0);
                 if (STEADY || fast) {
+                    if constexpr (BR == 3) {                       // the whole stage: a step and more to land
+                        constexpr int PER = (STAGE_FETCHES + N_MFMA - 1) / N_MFMA;
 #pragma unroll
-                    for (int u = 0; u < A_PER_SLOT; ++u)
-                        if (q * A_PER_SLOT + u < IT_A) fetch_a_one(pa, nA, q * A_PER_SLOT + u);
+                        for (int u = 0; u < PER; ++u) {
+                            const int j = q * PER + u;
+                            if (j < IT_B) fetch_b_one(pb, nB, j);
+                            else if (j < IT_B + IT_A) fetch_a_one(pa, nA, j - IT_B);
+                            else if (RIDE_LDS && j < STAGE_FETCHES) fetch_r(kt + 2, lds_r + ia2 * kRideStage, true);
+                        }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < A_PER_SLOT; ++u)
+                            if (q * A_PER_SLOT + u < IT_A) fetch_a_one(pa, nA, q * A_PER_SLOT + u);
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < FRAGS_PER_SLOT; ++u) read_frag(sA, sB, 1, q * FRAGS_PER_SLOT + u);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // half 1's operands are in registers and stage k+1 has landed (only the left-tile fetches
-        // of stage k+2, issued last, may still be in flight)
-        if (STEADY || fetch) __builtin_amdgcn_s_waitcnt(WAIT_BUT_A);
+        // half 1's operands are in registers and stage k+1 has landed (only the fetches of stage k+2 made
+        // in this half may still be in flight)
+        if (STEADY || fetch) __builtin_amdgcn_s_waitcnt(BR == 3 ? WAIT_BUT_STAGE : WAIT_BUT_A);
         else __builtin_amdgcn_s_waitcnt(WAIT_ALL);
         barrier_lds_only();                                    // ... for every wave
         // ---- half 1 ----
         const uint8_t* tA = lds + ia1 * A_BYTES;                // stage k+1
-        const uint8_t* tB = lds_b + ((kt + 1) & 1) * B_BYTES;
-        if (!STEADY && fetch && !fast) fetch_b_all(kt + 2, nB);
+        const uint8_t* tB = lds_b + (BR == 3 ? ia1 : ((kt + 1) & 1)) * B_BYTES;
+        if (BR == 2 && !STEADY && fetch && !fast) fetch_b_all(kt + 2, nB);
 #pragma unroll
         for (int mi = 0; mi < MB; ++mi) {
 #pragma unroll
             for (int ni = 0; ni < NB; ++ni) {
                 const int q = mi * NB + ni;
                 if (RIDE && (STEADY || next)) {                    // the adapter product's share of stage k+1
-                    if (q == N_FRAG) xa = ride_read(tA);           // behind the reads of the next half-step's operands
-                    if (q == N_FRAG + 4) {
+                    constexpr int RIDE_READ = N_FRAG < N_MFMA - 4 ? N_FRAG : N_MFMA - 4;
+                    if (q == RIDE_READ) {                          // behind the reads of the next half-step's operands
+                        xa = ride_read(tA);
+                        if constexpr (RIDE_LDS) ride_read_adapter(lds_r + ia1 * kRideStage);
+                    }
+                    if (q == (RIDE_READ + 4 < N_MFMA ? RIDE_READ + 4 : N_MFMA - 1)) {
                         ride_mfma();
-                        if (STEADY || fetch) ride_load(kt + 2, STEADY);
+                        if (!RIDE_LDS && (STEADY || fetch)) ride_load(kt + 2, STEADY);
                     }
                 }
                 acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                     bf[1][ni], af[1][mi], acc[mi][ni], 0 /* E4M3 */, A_FMT, 0, 0, 0, 0);
-                if (STEADY || fast) {
+                if (BR == 2 && (STEADY || fast)) {
 #pragma unroll
                     for (int u = 0; u < B_PER_SLOT; ++u)
                         if (q * B_PER_SLOT + u < IT_B) fetch_b_one(pb, nB, q * B_PER_SLOT + u);
@@ -697,7 +767,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     if constexpr (RIDE) {
         // lane l holds token row l % 16 of the block and ranks [4 (l / 16), +4)
         const int r = static_cast<int>(tail->r);
-        const int64_t row = m0 + (ride_u & 15) * 16 + (lane & 15);
+        const int64_t row = m0 + ride_tb * 16 + (lane & 15);
 #pragma unroll
         for (int j = 0; j < RB; ++j) {
             const int col = (ride_blk0 + j) * 16 + (lane >> 4) * 4;
@@ -829,20 +899,21 @@ gemm_fwd_tail_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, con
 }
 
 // The same product with the adapter product riding on the K-steps of the tiles themselves: writes
-// O_A (bf16) and its running maximum, no partial results.
-template <int RB>
+// O_A (bf16) and its running maximum, no partial results.  64 MB token rows per tile.
+template <int MB, int RB>
 __global__ void __launch_bounds__(256)
 gemm_fwd_ride_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int chunk, const TailArgs t)
 {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[gemm_lds_bytes<2, 2, 4, 4>()];
-    gemm_tile<2, 2, 4, 4, false, 0, RB == 4 ? 5 : RB == 2 ? 4 : 3>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[gemm_lds_bytes<2, 2, MB, 4>()];
+    gemm_tile<2, 2, MB, 4, false, 0, RB == 4 ? 5 : RB == 2 ? 4 : 3>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
 }
 
+template <int MB>
 __global__ void __launch_bounds__(256)
 gemm_dx_tail_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int chunk, const TailArgs t)
 {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[gemm_lds_bytes<2, 2, 4, 4>()];
-    gemm_tile<2, 2, 4, 4, true, 1, 2>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[gemm_lds_bytes<2, 2, MB, 4>()];
+    gemm_tile<2, 2, MB, 4, true, 1, 2>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
 }
 
 // Forward product and the adapter's split-K product in one launch.  Both read only x~ and the
@@ -907,12 +978,29 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream)
 
 bool use_big_tiles(int64_t M, int64_t N)
 {
-    // Large problems: 256x256 tiles, one workgroup per CU.  Small ones: 128x128 so that more
-    // than a handful of CUs take part.
+    // Large problems: 256x256 tiles, one workgroup per CU.
     return ((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
-int64_t gemm_tile_n(int64_t M, int64_t N) { return use_big_tiles(M, N) ? 256 : 128; }
+// Token rows of the large tiles (their columns are always 256), by the time a launch takes: a full round
+// of 256 tiles takes 30, 40 or 52 us (128, 192, 256 rows; K = 4096), a last round that fills only a part p of
+// the CUs 0.65 + 0.3 p of that (fewer busy CUs, higher clock).  Measured at T x 4096 x N, us with 128 / 192 /
+// 256 rows: 2048 x 4096 29.8 / 35.3 / 42.3; 3000 x 4096 53 / 40 / 45; 4096 x 4096 60 / 69 / 52; 4096 x 5120
+// (K = 5120) 115 / 94 / 112; 6000 x 4096 87 / 79 / 90; 4096 x 11008 178 / 154 / 148.
+static double big_tile_us(int64_t M, int64_t N, int rows)
+{
+    const int64_t tiles = (M + rows - 1) / rows * ((N + 255) / 256), part = tiles % 256;
+    const double rounds = static_cast<double>(tiles / 256) + (part ? 0.65 + 0.3 / 256.0 * static_cast<double>(part) : 0.0);
+    return rounds * (rows == 128 ? 30.0 : rows == 192 ? 40.0 : 52.0);
+}
+
+static int big_tile_rows(int64_t M, int64_t N)
+{
+    int best = 256;
+    for (int rows = 128; rows < 256; rows += 64)
+        if (big_tile_us(M, N, rows) < big_tile_us(M, N, best)) best = rows;
+    return best;
+}
 
 hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t stream)
 {
@@ -937,23 +1025,33 @@ hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_
 // of tiles).
 OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r)
 {
-    OaTailPlan p{false, 0, 0, 1};
-    if (!use_big_tiles(T, m)) return p;
+    OaTailPlan p{false, 0, 0, 1, 256};
+    if (gemm_mid_supported(T, m)) return p;
     const int tiles_n = static_cast<int>((m + 255) / 256);
     const int KT = static_cast<int>((n + BK - 1) / BK);
     const int rank_blocks = static_cast<int>((r + 15) / 16);
-    for (int rb = 1; rb <= 4; rb *= 2) {
-        // wave u of a tile row takes token block u % 16 and the rank blocks from rb (u / 16) on: the
-        // 4 tiles_n waves must reach every token block for every group of rb rank blocks
-        if (4 * tiles_n >= 16 * ((rank_blocks + rb - 1) / rb)) {
+    double best_us = 0.0;
+    for (int rows = 128; rows <= 256; rows += 64) {
+        for (int rb = 1; rb <= 4; rb *= 2) {
+            // wave u of a tile row takes one of its rows / 16 token blocks and rb rank blocks: the
+            // 4 tiles_n waves must reach every token block for every group of rb rank blocks
+            if (4 * tiles_n < rows / 16 * ((rank_blocks + rb - 1) / rb)) continue;
+            // Riding along costs 4 .. 10 %, and 30 % and more with four rank blocks per wave (r = 256 at
+            // 4096 x 4096 x 4096: 66.5 us with 128 rows, 69.2 with 256, where the operands of four blocks
+            // do not fit the registers beside the tile's).
+            const double us = big_tile_us(T, m, rows) * (rb == 4 ? 1.3 : rows == 192 ? 1.1 : rb == 2 ? 1.1 : 1.05);
+            if (p.use && us >= best_us) break;
+            best_us = us;
             p.use = true;
             p.splits = 0;
             p.steps_per_split = rb;                                       // rank blocks per wave
             p.row_parts = 0;
-            return p;
+            p.tile_rows = rows;
+            break;
         }
     }
-    if (r > 64) return p;
+    if (p.use) return p;
+    if (r > 64 || !use_big_tiles(T, m)) return p;
     p.row_parts = tiles_n >= 2 ? 2 : 1;
     int s0 = tiles_n / p.row_parts < 8 ? tiles_n / p.row_parts : 8;
     if (s0 > KT) s0 = KT;
@@ -967,38 +1065,60 @@ OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r)
 // workgroup of a full group and eight in a last group of a single tile row.
 DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r)
 {
-    DbTailPlan p{false, 0};
-    if (!use_big_tiles(T, n) || r > 64) return p;
-    const int tiles_m = static_cast<int>((T + 255) / 256), tiles_n = static_cast<int>((n + 255) / 256);
-    p.groups = (tiles_m + kDbTailGroupRows - 1) / kDbTailGroupRows;
-    const int F = static_cast<int>((m + 127) / 128);
-    const int per_full = (F + kDbTailGroupRows * tiles_n - 1) / (kDbTailGroupRows * tiles_n);
-    const int per_last = (tiles_m % kDbTailGroupRows) ? (F + tiles_n - 1) / tiles_n : per_full;
-    p.use = p.groups <= kDbSplitMax && per_full <= 4 && per_last <= 8;
+    DbTailPlan p{false, 0, 256};
+    if (gemm_mid_supported(T, n) || r > 64) return p;
+    for (int rows = big_tile_rows(T, n); rows <= 256; rows += 64) {      // the best one, else fewer, larger groups
+        const int tiles_m = static_cast<int>((T + rows - 1) / rows), tiles_n = static_cast<int>((n + 255) / 256);
+        p.groups = (tiles_m + kDbTailGroupRows - 1) / kDbTailGroupRows;
+        const int F = static_cast<int>((m + 127) / 128);
+        const int per_full = (F + kDbTailGroupRows * tiles_n - 1) / (kDbTailGroupRows * tiles_n);
+        const int per_last = (tiles_m % kDbTailGroupRows) ? (F + tiles_n - 1) / tiles_n : per_full;
+        p.tile_rows = rows;
+        p.use = p.groups <= kDbSplitMax && per_full <= 4 && per_last <= 8;
+        if (p.use) break;
+    }
     return p;
+}
+
+template <int MB>
+static hipError_t launch_fwd_ride(const GemmArgs& g, const TailArgs& t, int rb, hipStream_t stream)
+{
+    const int tiles_m = static_cast<int>((g.M + 64 * MB - 1) / (64 * MB)), tiles_n = static_cast<int>((g.N + 255) / 256);
+    const int chunk = (tiles_m * tiles_n + 7) / 8;
+    const dim3 grid(static_cast<unsigned>(8 * chunk)), block(256);
+    if (rb == 4) gemm_fwd_ride_kernel<MB, 4><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    else if (rb == 2) gemm_fwd_ride_kernel<MB, 2><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    else gemm_fwd_ride_kernel<MB, 1><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    return hipGetLastError();
 }
 
 hipError_t launch_gemm_fwd_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream)
 {
+    if (t.row_parts == 0) {
+        if (t.tile_rows == 128) return launch_fwd_ride<2>(g, t, t.steps_per_split, stream);
+        if (t.tile_rows == 192) return launch_fwd_ride<3>(g, t, t.steps_per_split, stream);
+        return launch_fwd_ride<4>(g, t, t.steps_per_split, stream);
+    }
     const int tiles_m = static_cast<int>((g.M + 255) / 256), tiles_n = static_cast<int>((g.N + 255) / 256);
     const int chunk = (tiles_m * tiles_n + 7) / 8;
-    if (t.row_parts == 0 && t.steps_per_split == 4)
-        gemm_fwd_ride_kernel<4><<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
-    else if (t.row_parts == 0 && t.steps_per_split == 2)
-        gemm_fwd_ride_kernel<2><<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
-    else if (t.row_parts == 0)
-        gemm_fwd_ride_kernel<1><<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
-    else
-        gemm_fwd_tail_kernel<<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    gemm_fwd_tail_kernel<<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    return hipGetLastError();
+}
+
+template <int MB>
+static hipError_t launch_dx_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream)
+{
+    const int tiles_m = static_cast<int>((g.M + 64 * MB - 1) / (64 * MB)), tiles_n = static_cast<int>((g.N + 255) / 256);
+    const int chunk = (tiles_m * tiles_n + 7) / 8;
+    gemm_dx_tail_kernel<MB><<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_dx_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream)
 {
-    const int tiles_m = static_cast<int>((g.M + 255) / 256), tiles_n = static_cast<int>((g.N + 255) / 256);
-    const int chunk = (tiles_m * tiles_n + 7) / 8;
-    gemm_dx_tail_kernel<<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
-    return hipGetLastError();
+    if (t.tile_rows == 128) return launch_dx_tail<2>(g, t, stream);
+    if (t.tile_rows == 192) return launch_dx_tail<3>(g, t, stream);
+    return launch_dx_tail<4>(g, t, stream);
 }
 
 bool gemm_dx_db_pair_supported(const GemmArgs& g)
@@ -1018,14 +1138,17 @@ hipError_t launch_gemm_dx_db_pair(const GemmArgs& g, const DbArgs& d, hipStream_
 
 hipError_t launch_gemm_tiles(const GemmArgs& g, hipStream_t stream)
 {
-    if (use_big_tiles(g.M, g.N)) return launch_cfg<2, 2, 4, 4>(g, stream);
-    return launch_cfg<2, 2, 2, 2>(g, stream);
+    const int rows = big_tile_rows(g.M, g.N);
+    if (rows == 128) return launch_cfg<2, 2, 2, 4>(g, stream);
+    if (rows == 192) return launch_cfg<2, 2, 3, 4>(g, stream);
+    return launch_cfg<2, 2, 4, 4>(g, stream);
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    if (g.splits == 1 && gemm_mid_supported(g.M, g.N)) return launch_gemm_mid(g, MidSide{}, -1, stream);
+    if (g.splits > 1) return launch_cfg<2, 2, 2, 2>(g, stream);        // split K: small output, 128x128 tiles
+    if (gemm_mid_supported(g.M, g.N)) return launch_gemm_mid(g, MidSide{}, -1, stream);
     return launch_gemm_tiles(g, stream);
 }
 

@@ -89,7 +89,6 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     const int64_t n0 = static_cast<int64_t>(adapter ? tile_n - t.tiles_n : tile_n) * BN;
     const int64_t M = g.M, N = adapter ? t.r : g.N, K = g.K;
     const uint8_t* const gb = adapter ? t.side : g.b;
-    const float inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / ((*g.sa) * (*g.sb)))));
 
     // ---- global -> LDS ----------------------------------------------------------------------
     // As in the large tiles: uniform base + 32-bit lane offset while a stage lies inside K, rows and
@@ -346,6 +345,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
             }
         }
     };
+    float inv;
     {
         const int first = KT < S ? KT : S;
         if constexpr (DB) {
@@ -359,6 +359,8 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
             }
         }
         for (int s = 0; s < first; ++s) fetch(s, lds + s * STAGE);
+        // rescale factor: read behind the first fetches, so that its memory round trip hides under theirs
+        inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / ((*g.sa) * (*g.sb)))));
         WaitStages<S - 1>::template run<LPW>(first - 1);
         barrier_lds_only();
         read_stage(std::integral_constant<int, 0>{}, lds);
@@ -533,7 +535,13 @@ hipError_t launch_cfg(MidArgs t, hipStream_t stream)
 
 }  // namespace
 
-bool gemm_mid_supported(int64_t M, int64_t N) { return !use_big_tiles(M, N); }
+// Small tiles while all of them (128x128 at the largest) find a CU; beyond that tiles of 128 x 256 and up
+// are faster (us with dB or O_A: 1024 x 4096 x 4096 forward 27.7 here, 27.6 there, input gradient 24.6 and
+// 30.1; 1500 x 4096 x 4096 43 and 30, 44 and 32).
+bool gemm_mid_supported(int64_t M, int64_t N)
+{
+    return !use_big_tiles(M, N) && ((M + 127) / 128) * ((N + 127) / 128) <= kMidCus;
+}
 
 // Tile configuration by size: the least of rounds over the CUs x K-steps x time of a step, plus what a
 // launch takes beside its steps (us, measured at full and nearly full rounds, 0.5 us accuracy).  Small tiles
@@ -542,7 +550,7 @@ bool gemm_mid_supported(int64_t M, int64_t N) { return !use_big_tiles(M, N); }
 static int mid_config(int64_t M, int64_t N, int64_t K)
 {
     struct { int bm, bn; double step, fixed; } const cfg[kMidConfigs] = {
-        {32, 64, 0.17, 3.9}, {64, 64, 0.20, 4.2}, {64, 128, 0.32, 5.0}, {128, 128, 0.60, 6.3}};
+        {32, 64, 0.30, 3.9}, {64, 64, 0.34, 4.2}, {64, 128, 0.42, 5.0}, {128, 128, 0.58, 6.3}};
     int best = 0;
     double best_us = 0.0;
     for (int c = 0; c < kMidConfigs; ++c) {
