@@ -20,17 +20,21 @@ static int mid_db_parts(int64_t T, int64_t n, int64_t m)
     return parts <= kMidDbMax ? static_cast<int>(parts) : 0;
 }
 
-WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r)
+// least: the layout of a workspace that has room for no more partials of dB than the launches need that
+// form it apart from small dX tiles.  Every call also works in such a workspace; falqon_melded_bwd then takes
+// those launches.
+WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least)
 {
     WsLayout w;
     size_t off = 0;
-    // partial counts: the larger of what the two ways of forming each adapter product need
+    // partial counts: the larger of what the ways of forming each adapter product need
     const OaTailPlan po = plan_oa_tail(T, n, m, r);
-    const DbTailPlan pd = plan_db_tail(T, n, m, r);
+    const DbTailPlan p256 = plan_db_tail(T, n, m, r, 256), pd = plan_db_tail(T, n, m, r, 0);
     int oa_parts = oa_splits(T, r), db_parts = db_splits(T, m);
     if (po.use && po.splits > oa_parts) oa_parts = po.splits;
-    if (pd.use && pd.groups > db_parts) db_parts = pd.groups;
-    if (mid_db_parts(T, n, m) > db_parts) db_parts = mid_db_parts(T, n, m);
+    if (p256.use && p256.groups > db_parts) db_parts = p256.groups;
+    if (!least && pd.use && pd.groups > db_parts) db_parts = pd.groups;
+    if (!least && mid_db_parts(T, n, m) > db_parts) db_parts = mid_db_parts(T, n, m);
     w.amax_partials = off; off = align_up(off + sizeof(float) * kMaxAmaxBlocks, 256);
     w.scores = off;        off = align_up(off + sizeof(double) * static_cast<size_t>(m + (m + 63) / 64), 256);
     w.delta_sel = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r), 256);
@@ -84,7 +88,7 @@ const char* falqon_status_string(falqon_status s)
 size_t falqon_workspace_bytes(int64_t T, int64_t n, int64_t m, int64_t r)
 {
     if (bad_layer_shape(T, n, m, r)) return 0;
-    return ws_layout(T, n, m, r).total;
+    return ws_layout(T, n, m, r, false).total;
 }
 
 size_t falqon_row_score_bytes(int64_t m)
@@ -131,7 +135,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     if ((reinterpret_cast<uintptr_t>(s_w) & 3u) || (reinterpret_cast<uintptr_t>(s_x) & 3u) ||
         (reinterpret_cast<uintptr_t>(amax_oa) & 3u))
         return FALQON_ERR_ALIGN;
-    const WsLayout L = ws_layout(T, n, m, r);
+    const WsLayout L = ws_layout(T, n, m, r, true);
     if (!ws || ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
     if (misaligned(ws)) return FALQON_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -225,7 +229,9 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     if ((reinterpret_cast<uintptr_t>(s_w) & 3u) || (reinterpret_cast<uintptr_t>(s_dy) & 3u) ||
         (reinterpret_cast<uintptr_t>(amax_oa) & 3u))
         return FALQON_ERR_ALIGN;
-    const WsLayout L = ws_layout(T, n, m, r);
+    WsLayout L = ws_layout(T, n, m, r, false);
+    const bool least = ws_bytes < L.total;
+    if (least) L = ws_layout(T, n, m, r, true);
     if (!ws || ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
     if (misaligned(ws)) return FALQON_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -233,8 +239,8 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
 
     // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
     // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
-    const DbTailPlan pd = dx ? plan_db_tail(T, n, m, r) : DbTailPlan{false, 0, 256};
-    const int mid_parts = dx ? mid_db_parts(T, n, m) : 0;
+    const DbTailPlan pd = dx ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
+    const int mid_parts = dx && !least ? mid_db_parts(T, n, m) : 0;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
                                    reinterpret_cast<float*>(w8 + L.amax_partials), nullptr, st, pd.use || mid_parts ? &sc : nullptr);
@@ -283,7 +289,7 @@ falqon_status falqon_db_bf16(const uint8_t* dyq, const float* s_dy, const void* 
     if (misaligned(dyq) || misaligned(o_a) || misaligned(d_b) || (delta_buf && misaligned(delta_buf)) ||
         (reinterpret_cast<uintptr_t>(s_dy) & 3u))
         return FALQON_ERR_ALIGN;
-    const WsLayout L = ws_layout(T, 16, m, r);
+    const WsLayout L = ws_layout(T, 16, m, r, true);
     if (!ws || ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
     if (misaligned(ws)) return FALQON_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -305,7 +311,7 @@ falqon_status falqon_da(const uint8_t* dyq, const float* s_dy, const uint8_t* bt
         (reinterpret_cast<uintptr_t>(s_x) & 3u) || (reinterpret_cast<uintptr_t>(amax_g) & 3u))
         return FALQON_ERR_ALIGN;
     // the second product has the layer's input width in the place of its output width
-    const WsLayout L = ws_layout(T, m, n, r);
+    const WsLayout L = ws_layout(T, m, n, r, true);
     if (!ws || ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
     if (misaligned(ws)) return FALQON_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -347,7 +353,7 @@ falqon_status falqon_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int6
     if (misaligned(delta_buf) || misaligned(wq) || (reinterpret_cast<uintptr_t>(idx_out) & 3u) ||
         (reinterpret_cast<uintptr_t>(row_scores) & 7u))
         return FALQON_ERR_ALIGN;
-    const WsLayout L = ws_layout(1, n, m, r);
+    const WsLayout L = ws_layout(1, n, m, r, true);
     if (!ws || ws_bytes < L.db_partials) return FALQON_ERR_WORKSPACE;
     if (misaligned(ws)) return FALQON_ERR_ALIGN;
     uint8_t* w8 = static_cast<uint8_t*>(ws);
@@ -400,7 +406,9 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
     if (bad_layer_shape(M, n, m, r)) return FALQON_ERR_SHAPE;
     if ((b_is_kn != 0) != (a_fmt == FALQON_E5M2)) return FALQON_ERR_ENUM;
     if (misaligned(side)) return FALQON_ERR_ALIGN;
-    const WsLayout L = ws_layout(M, n, m, r);
+    WsLayout L = ws_layout(M, n, m, r, false);
+    const bool least = side_ws_bytes < L.total;
+    if (least) L = ws_layout(M, n, m, r, true);
     if (!side_ws || side_ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
     if (misaligned(side_ws)) return FALQON_ERR_ALIGN;
     uint8_t* w8 = static_cast<uint8_t*>(side_ws);
@@ -418,7 +426,7 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
         }
         e = launch_gemm_fwd_tail(g, t, st);
     } else {
-        const DbTailPlan pd = plan_db_tail(M, n, m, r);
+        const DbTailPlan pd = plan_db_tail(M, n, m, r, least ? 256 : 0);
         if (!pd.use) return FALQON_ERR_SHAPE;
         t.partial = reinterpret_cast<float*>(w8 + L.db_partials); t.tile_rows = pd.tile_rows;
         e = launch_gemm_dx_tail(g, t, st);

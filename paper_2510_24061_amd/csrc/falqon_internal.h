@@ -23,7 +23,7 @@ struct WsLayout {
     size_t oa_codes;        // uint8[T][r]: the saved O_A cast to E4M3 for the adapter gradient
     size_t total;
 };
-WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r);
+WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least);
 int db_splits(int64_t T, int64_t m);
 
 // ---- quantizer (quantize.hip) ------------------------------------------------------------
@@ -76,7 +76,8 @@ struct TailArgs {
 struct OaTailPlan { bool use; int splits; int steps_per_split; int row_parts; int tile_rows; };
 struct DbTailPlan { bool use; int groups; int tile_rows; };
 OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r);     // forward of a [T,n] x [m+r,n] layer
-DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r);     // backward of the same layer
+// backward of the same layer; rows: token rows of the tiles, 0 to choose by size
+DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r, int rows);
 hipError_t launch_gemm_fwd_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream);
 hipError_t launch_gemm_dx_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream);
 

@@ -1063,11 +1063,11 @@ OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r)
 
 // Input gradient: groups of two token tile rows; at most kDbSplitMax groups, four feature steps per
 // workgroup of a full group and eight in a last group of a single tile row.
-DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r)
+DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_rows)
 {
     DbTailPlan p{false, 0, 256};
-    if (gemm_mid_supported(T, n) || r > 64) return p;
-    for (int rows = big_tile_rows(T, n); rows <= 256; rows += 64) {      // the best one, else fewer, larger groups
+    if (gemm_mid_supported(T, n) || r > 64 || (only_rows && !use_big_tiles(T, n))) return p;
+    for (int rows = only_rows ? only_rows : big_tile_rows(T, n); rows <= 256; rows += 64) {   // the best one, else larger groups
         const int tiles_m = static_cast<int>((T + rows - 1) / rows), tiles_n = static_cast<int>((n + 255) / 256);
         p.groups = (tiles_m + kDbTailGroupRows - 1) / kDbTailGroupRows;
         const int F = static_cast<int>((m + 127) / 128);

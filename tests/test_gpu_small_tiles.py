@@ -2,7 +2,9 @@
 product as tile columns of its own or riding on the backbone's, and the adapter gradient formed inside the
 input-gradient tiles, on exact-integer data (fp32 outputs bit for bit)."""
 import pytest
+import torch
 
+import paper_2510_24061_amd as fq
 from test_gpu_layer import _exact_integer_layer
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +45,31 @@ def test_exact_integer_layer_is_bit_exact(T, n, m, r):
 ])
 def test_tiles_of_128_and_192_rows_exact_integer_layer_is_bit_exact(T, n, m, r):
     _exact_integer_layer(T, n, m, r)
+
+
+@pytest.mark.parametrize("T,n,m,r", [(512, 1024, 1040, 64), (2100, 2048, 528, 48)])
+def test_backward_also_works_in_the_smallest_workspace(T, n, m, r):
+    """A workspace without room for the partial sums that the small or 128- and 192-row tiles would leave: the call
+    takes the launches that need less.  Same dX; dB up to the order of fp32 sums."""
+    g = torch.Generator().manual_seed(T)
+    layer = fq.MeldedLinear(T, n, m, r, 8)
+    layer.init_weights(torch.randn(m, n, generator=g).cuda() * 0.02, torch.randn(r, n, generator=g).cuda() / r)
+    layer.forward(torch.randn(T, n, generator=g).bfloat16().cuda())
+    dy = torch.randn(T, m, generator=g).bfloat16().cuda()
+    layer.backward(dy, accumulate=False)
+    dx, d_b = layer.dx.clone(), layer.d_b.clone()
+    lo, hi, full = 0, layer.ws.numel(), layer.ws
+    while hi - lo > 256:                           # the smallest workspace that the call accepts
+        mid = (lo + hi) // 2 // 256 * 256
+        layer.ws = full[:mid]
+        try:
+            layer.backward(dy, accumulate=False)
+            hi = mid
+        except fq.FalqonError:
+            lo = mid
+    assert hi < full.numel()
+    layer.ws = torch.empty(hi, dtype=torch.uint8, device="cuda")
+    layer.dx.zero_(), layer.d_b.zero_()
+    layer.backward(dy, accumulate=False)
+    assert torch.equal(layer.dx, dx)
+    assert float((layer.d_b - d_b).norm() / d_b.norm()) < 1e-4      # fp32 matrix-core sums: 2e-5 of the result
