@@ -40,30 +40,40 @@ __device__ __forceinline__ float buffer_step(float buf, float lr, float g)
 }
 
 // dB = (sum of partials, split ascending) / (s_dy * s_oa);  delta_buf += -lr * dB.
-// A workgroup owns 64 rows of dB.  With `score` set (only together with delta_buf) it keeps the new
-// buffer rows in LDS and leaves their L1 norms and the block's largest norm for the proxy update.
-__global__ void __launch_bounds__(kThreads)
+// A workgroup owns 64 rows of dB, a thread U runs of four columns at a time.  With `score` set (only
+// together with delta_buf) it keeps the new rows in LDS and leaves their L1 norms and the largest one
+// (row_scores.h).  Bound by latency: 1024 threads, so that all of a workgroup's loads are in flight at once
+// up to rank 64 (a quarter of the threads took four round trips, 7.0 against 4.4 us at 4096 x 64 x 8 splits).
+constexpr int kReduceThreads = 1024;
+
+template <int U>
+__global__ void __launch_bounds__(kReduceThreads)
 db_reduce_kernel(const float* __restrict__ partial, int splits, int64_t m, int r,
                  const float* __restrict__ s_dy, const float* __restrict__ amax_oa,
                  float* __restrict__ d_b, float* delta_buf, float lr, double* __restrict__ score)
 {
     extern __shared__ float s_rows[];                                              // 64 x (r + 4) floats when score is set
-    const float s_oa_scale = amax_oa ? 448.0f / fmaxf(*amax_oa, 1e-12f) : 1.0f;    // no amax: O_A was not cast
-    const float inv = 1.0f / ((*s_dy) * s_oa_scale);
     const int64_t count = m * r;
     const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kScoreRows;
     const int64_t e0 = row0 * r;
     int64_t e_end = e0 + static_cast<int64_t>(kScoreRows) * r;
     if (e_end > count) e_end = count;
     const int r4 = r / 4, pitch = r + 4;
-    constexpr int B = 8, U = 4;                                    // splits per batch, float4 positions per thread and pass
-    for (int64_t base = e0 + threadIdx.x * 4; base < e_end; base += static_cast<int64_t>(U) * kThreads * 4) {
-        float4 s[U];
+    constexpr int B = 8;                                           // splits per batch
+    for (int64_t base = e0 + threadIdx.x * 4; base < e_end; base += static_cast<int64_t>(U) * kReduceThreads * 4) {
+        float4 s[U], d[U];
+        if (delta_buf) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t e = base + static_cast<int64_t>(u) * kReduceThreads * 4;
+                if (e < e_end) d[u] = *reinterpret_cast<const float4*>(delta_buf + e);
+            }
+        }
         for (int sp0 = 0; sp0 < splits; sp0 += B) {
             float4 v[U][B];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t e = base + static_cast<int64_t>(u) * kThreads * 4;
+                const int64_t e = base + static_cast<int64_t>(u) * kReduceThreads * 4;
                 const int64_t ee = e < e_end ? e : e0;                   // beyond the block: a valid address, value unused
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
@@ -79,23 +89,25 @@ db_reduce_kernel(const float* __restrict__ partial, int splits, int64_t m, int r
                     else if (sp0 + b < splits) { s[u].x += v[u][b].x; s[u].y += v[u][b].y; s[u].z += v[u][b].z; s[u].w += v[u][b].w; }
                 }
         }
+        const float s_oa_scale = amax_oa ? 448.0f / fmaxf(*amax_oa, 1e-12f) : 1.0f;    // no amax: O_A was not cast
+        const float inv = 1.0f / ((*s_dy) * s_oa_scale);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t e = base + static_cast<int64_t>(u) * kThreads * 4;
+            const int64_t e = base + static_cast<int64_t>(u) * kReduceThreads * 4;
             if (e >= e_end) continue;
             float4 g = s[u];
             g.x *= inv; g.y *= inv; g.z *= inv; g.w *= inv;
             *reinterpret_cast<float4*>(d_b + e) = g;
             if (delta_buf) {
-                float4 d = *reinterpret_cast<const float4*>(delta_buf + e);
-                d.x = buffer_step(d.x, lr, g.x);
-                d.y = buffer_step(d.y, lr, g.y);
-                d.z = buffer_step(d.z, lr, g.z);
-                d.w = buffer_step(d.w, lr, g.w);
-                *reinterpret_cast<float4*>(delta_buf + e) = d;
+                float4 n = d[u];
+                n.x = buffer_step(n.x, lr, g.x);
+                n.y = buffer_step(n.y, lr, g.y);
+                n.z = buffer_step(n.z, lr, g.z);
+                n.w = buffer_step(n.w, lr, g.w);
+                *reinterpret_cast<float4*>(delta_buf + e) = n;
                 if (score) {
-                    const int64_t q4 = (e - e0) / 4;
-                    *reinterpret_cast<float4*>(s_rows + (q4 / r4) * pitch + (q4 % r4) * 4) = d;
+                    const int q4 = static_cast<int>(e - e0) / 4;
+                    *reinterpret_cast<float4*>(s_rows + (q4 / r4) * pitch + (q4 % r4) * 4) = n;
                 }
             }
         }
@@ -150,13 +162,19 @@ hipError_t launch_db_reduce(const DbArgs& d, const float* s_dy, float* d_b, floa
     if (d.splits < 1) return hipErrorInvalidValue;
     if (!delta_buf) score = nullptr;                              // the scores are those of the buffer the step leaves
     const size_t lds = score ? sizeof(float) * kScoreRows * (static_cast<size_t>(d.r) + 4) : 0;
+    const dim3 grid(static_cast<unsigned>(score_blocks(d.m)));
+    if (d.r <= 64) {
+        db_reduce_kernel<1><<<grid, kReduceThreads, lds, stream>>>(d.partial, d.splits, d.m, static_cast<int>(d.r), s_dy,
+                                                                   d.amax_oa, d_b, delta_buf, lr, score);
+        return hipGetLastError();
+    }
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&db_reduce_kernel),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&db_reduce_kernel<2>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) return e;
     }
-    db_reduce_kernel<<<static_cast<unsigned>(score_blocks(d.m)), kThreads, lds, stream>>>(
-        d.partial, d.splits, d.m, static_cast<int>(d.r), s_dy, d.amax_oa, d_b, delta_buf, lr, score);
+    db_reduce_kernel<2><<<grid, kReduceThreads, lds, stream>>>(d.partial, d.splits, d.m, static_cast<int>(d.r), s_dy,
+                                                               d.amax_oa, d_b, delta_buf, lr, score);
     return hipGetLastError();
 }
 

@@ -1,24 +1,19 @@
 // Row-wise proxy update (update equation; last two lines of the backward-and-update loop):
 //   k = topk( sum_j |dB_ij| ; k ),   W~[k] = W~[k] + DeltaBuffer[k] A
 //
-// Three small launches, all latency bound (the update touches k of m rows), so each is shaped to
-// have its loads in flight together rather than one after the other:
-//   1. row scores: L1 norm of every buffer row, fp64, columns ascending, and the largest score of
-//      every block of 64 rows (row_scores.h).  Skipped when the kernel that wrote the buffer has
-//      already left them (falqon_melded_bwd with its buffer step).
-//   2. selection: the rank of a row is the number of rows that beat it (larger score, or equal
-//      score and smaller index); a row of rank c < k is selected and its index goes to idx[c].
-//      Counting is exact and order free, so the result is deterministic and already sorted: no
-//      sort, no atomics, no host round trip.  Only rows that can be selected are ranked: the k-th
-//      largest of the block maxima is a lower bound on the k-th largest score (each of those maxima
-//      is the score of a different row), so a row below it has at least k rows above it.  The wave
-//      that finds a selected row also moves that buffer row to a compact staging array (and clears
-//      it in the buffer), which lets the third launch spread one row over several workgroups
-//      without a hazard on the buffer.  (Requantizing in the same launch was built and measured
-//      slower: the one workgroup that finds a row then walks the whole weight row alone.)
-//   3. requantize: value(W~[i,j]) + sum_p delta[p] * value(A~[p,j]) in fp64 (p ascending),
-//      rounded to fp32, cast to E4M3, written back.  A~ is rows [m, m+r) of the concatenated
-//      weight, in the same scaled domain as W~, so the backbone's scale never enters.
+// Small launches, all latency bound (the update touches k of m rows), so each is shaped to have its loads
+// in flight together rather than one after the other:
+//   1. row scores: L1 norm of every buffer row, fp64, columns ascending (row_scores.h).  Skipped when the
+//      kernel that wrote the buffer has already left them (falqon_melded_bwd with its buffer step).
+//   2. selection: the rank of a row is the number of rows that beat it (larger score, or equal score and
+//      smaller index): exact and order free, so the result is deterministic and already sorted, with no
+//      sort, no atomics on results, no host round trip.  Only rows that can be selected are ranked: the k-th
+//      largest of the maxima of disjoint groups of rows is a lower bound on the k-th largest score.  The
+//      selected buffer row moves to a compact staging array (and is cleared in the buffer), which lets the
+//      third launch spread one row over several workgroups without a hazard on the buffer.
+//   3. requantize: value(W~[i,j]) + sum_p delta[p] * value(A~[p,j]) in fp64 (p ascending), rounded to
+//      fp32, cast to E4M3, written back.  A~ is rows [m, m+r) of the concatenated weight, in the same
+//      scaled domain as W~, so the backbone's scale never enters.
 #include <mutex>
 
 #include "falqon_internal.h"
@@ -37,15 +32,17 @@ constexpr size_t kStaticScoreBytes = sizeof(double) * (kStaticMaxRows + kStaticM
 constexpr size_t kStaticBytes = kStaticScoreBytes + sizeof(float) * kStaticMaxSelected;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
-// grid: ceil(m / 64); dynamic LDS: 64 * (r + 4) floats
-__global__ void __launch_bounds__(kThreads)
+// grid: ceil(m / 64); dynamic LDS: 64 * (r + 4) floats.  1024 threads: one round trip up to rank 64.
+constexpr int kScoreThreads = 1024;
+
+__global__ void __launch_bounds__(kScoreThreads)
 row_score_kernel(const float* __restrict__ buf, int64_t m, int r, double* __restrict__ score)
 {
     extern __shared__ float s_rows[];
     const int pitch = r + 4;                                         // +16 B: rows start on different banks
     const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kScoreRows;
     const int r4 = r / 4;
-    for (int e = threadIdx.x; e < kScoreRows * r4; e += kThreads) {
+    for (int e = threadIdx.x; e < kScoreRows * r4; e += kScoreThreads) {
         const int row = e / r4, c4 = e - row * r4;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (row0 + row < m) v = *reinterpret_cast<const float4*>(buf + (row0 + row) * r + c4 * 4);
@@ -63,11 +60,188 @@ __device__ __forceinline__ void decode4_e4m3(uint32_t w, double (&d)[4])
     d[3] = static_cast<double>(__builtin_amdgcn_cvt_f32_fp8(static_cast<int>(w), 3));
 }
 
-// A workgroup owns 16 rows (4 waves x 4 consecutive rows).
-// Scores are non-negative doubles, so their bit patterns order them as 64-bit integers.  Row j
-// beats row i if key_j > key_i, or key_j == key_i and j < i: for all j below the wave's rows that
-// is "key_j >= key_i", for all j above them "key_j > key_i", so the inner loop is one integer
-// comparison per pair; only the wave's own four rows need the index compared.
+__device__ __forceinline__ uint32_t encode4_e4m3(const double (&acc)[4])
+{
+    float f[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = __builtin_amdgcn_fmed3f(static_cast<float>(acc[e]), -448.0f, 448.0f);
+    int w = 0;
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], w, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], w, true);
+    return static_cast<uint32_t>(w);
+}
+
+// ---- selection ------------------------------------------------------------------------------------------
+// grid (k): workgroup c finds the row of rank c, stages its buffer row and clears it.  Scores are
+// non-negative doubles, so their bit patterns order them as 64-bit integers.  Thread t holds the keys of rows
+// t, t + 256, ...; threads t and t ^ 1 form one of 128 groups.  The k-th largest group maximum bounds the
+// k-th largest key from below, and so does any number below it: tau, its leading bits (every wave finds them
+// by bisection on its own, two maxima per lane).  The rows whose high word reaches tau, a few dozen, contain
+// the k selected ones; they are ranked pairwise.  If too many reach it (long runs of equal scores, such as
+// an untouched buffer) the row is found by bisection on the key and, among equals, by index.
+//
+// All latency: one round trip for the scores, one for the buffer row, and 2 us of comparisons.  Every
+// workgroup repeats the comparisons; nothing is exchanged.  us by kernel trace, against ranking 16 rows per workgroup
+// or, beyond 4096 rows, ranking whole blocks: 6.0 (8.0) at 4096 rows, 8.8 (18.5) at 11008, k = 32.
+// (Requantizing in the same launch was built too: the workgroups that share a row have to agree on when
+// its buffer row may be cleared, and their device-scope atomics cost more, 6 us, than the launch saved.)
+constexpr int kSelectGroups = 128, kSelectCands = 256, kSelectMaxK = 96, kSelectMaxRows = 64 * kThreads;
+constexpr int kTauLowBit = 14;                                       // tau keeps a score's exponent and 6 bits behind it
+
+template <int U>                                                     // U keys per thread: m <= 256 U
+__global__ void __launch_bounds__(kThreads)
+select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int32_t* __restrict__ idx, float* buf,
+              float* __restrict__ delta_sel, int clear_selected)
+{
+    __shared__ uint32_t s_max[kSelectGroups];
+    __shared__ uint64_t s_ckey[kSelectCands];
+    __shared__ int s_cidx[kSelectCands];
+    __shared__ int s_ncand, s_row, s_count[2][kThreads / 64], s_equal[U][kThreads / 64];
+    __shared__ unsigned long long s_all, s_any;
+    const uint64_t* key = reinterpret_cast<const uint64_t*>(score);
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int rank = static_cast<int>(blockIdx.x);
+
+    uint64_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t i = static_cast<int64_t>(u) * kThreads + t;
+        v[u] = i < m ? key[i] : 0;
+    }
+    if (t == 0) { s_ncand = 0; s_row = -1; }
+    uint32_t hi = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t h = static_cast<uint32_t>(v[u] >> 32);
+        hi = h > hi ? h : hi;
+    }
+    const uint32_t other = __shfl_xor(hi, 1, 64);
+    hi = other > hi ? other : hi;
+    if ((t & 1) == 0) s_max[t >> 1] = hi;
+    __syncthreads();
+
+    // ---- tau: the k-th largest of the maxima, rounded down to its leading bits -------------------------
+    uint32_t tau = 0;
+    {
+        const uint32_t a = s_max[lane], b = s_max[lane + 64];
+#pragma unroll
+        for (int bit = 30; bit >= kTauLowBit; --bit) {
+            const uint32_t trial = tau | (1u << bit);
+            if (__popcll(__ballot(a >= trial)) + __popcll(__ballot(b >= trial)) >= k) tau = trial;
+        }
+    }
+    // ---- the rows that reach it ---------------------------------------------------------------------------
+    int found_here = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool in = static_cast<int64_t>(u) * kThreads + t < m && static_cast<uint32_t>(v[u] >> 32) >= tau;
+        found_here += in ? 1 : 0;
+    }
+    if (found_here) {
+        int pos = atomicAdd(&s_ncand, found_here);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = static_cast<int64_t>(u) * kThreads + t < m && static_cast<uint32_t>(v[u] >> 32) >= tau;
+            if (in && pos < kSelectCands) { s_ckey[pos] = v[u]; s_cidx[pos] = u * kThreads + t; }
+            pos += in ? 1 : 0;
+        }
+    }
+    __syncthreads();
+    const int nc = s_ncand;
+    if (nc <= kSelectCands) {
+        // four threads per listed row, four others at a time
+        for (int c0 = 0; c0 < nc; c0 += kThreads / 4) {
+            const int c = c0 + t / 4;
+            const bool in = c < nc;
+            const uint64_t kc = s_ckey[in ? c : 0];
+            const int ic = s_cidx[in ? c : 0];
+            int beat = 0;
+            for (int j0 = t & 3; j0 < nc; j0 += 16) {
+                uint64_t kj[4];
+                int ij[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int j = j0 + 4 * q < nc ? j0 + 4 * q : c;  // beyond the list: the row itself, which does not beat itself
+                    kj[q] = s_ckey[in ? j : 0];
+                    ij[q] = s_cidx[in ? j : 0];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) beat += (kj[q] > kc || (kj[q] == kc && ij[q] < ic)) ? 1 : 0;
+            }
+            beat += __shfl_xor(beat, 1, 64);
+            beat += __shfl_xor(beat, 2, 64);
+            if (in && (t & 3) == 0 && beat == rank) s_row = ic;
+        }
+    } else {
+        // largest key that more than `rank` rows reach: the key of the row looked for
+        unsigned long long all = ~0ull, any = 0;
+        auto count_reaching = [&](uint64_t bound, int which) {       // rows with key >= bound, over the workgroup
+            int c = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                c += (static_cast<int64_t>(u) * kThreads + t < m && v[u] >= bound) ? 1 : 0;
+            for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+            if (lane == 0) s_count[which][wave] = c;
+            __syncthreads();
+            return s_count[which][0] + s_count[which][1] + s_count[which][2] + s_count[which][3];
+        };
+        // bits that all listed rows share (equal scores: every bit) need no count
+        if (t == 0) { s_all = ~0ull; s_any = 0; }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (static_cast<int64_t>(u) * kThreads + t < m && static_cast<uint32_t>(v[u] >> 32) >= tau) {
+                all &= v[u];
+                any |= v[u];
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            all &= __shfl_xor(all, off, 64);
+            any |= __shfl_xor(any, off, 64);
+        }
+        if (lane == 0) { atomicAnd(&s_all, all); atomicOr(&s_any, any); }
+        __syncthreads();
+        all = s_all;
+        any = s_any;
+        uint64_t found = 0;
+        for (int bit = 63; bit >= 0; --bit) {                        // (every thread takes the same path)
+            const uint64_t trial = found | (uint64_t(1) << bit);
+            if ((all & trial & ~found) || ((any & trial & ~found) && count_reaching(trial, bit & 1) > rank)) found = trial;
+        }
+        __syncthreads();
+        const int greater = found == ~uint64_t(0) ? 0 : count_reaching(found + 1, 0);
+        __syncthreads();
+        int left = rank - greater;                                   // equal rows of smaller index
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t mask = __ballot(static_cast<int64_t>(u) * kThreads + t < m && v[u] == found);
+            if (lane == 0) s_equal[u][wave] = __popcll(mask);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool eq = static_cast<int64_t>(u) * kThreads + t < m && v[u] == found;
+            int before = __popcll(__ballot(eq) & ((uint64_t(1) << lane) - 1)), total = 0;
+            for (int w = 0; w < kThreads / 64; ++w) {
+                const int c = s_equal[u][w];
+                if (w < wave) before += c;
+                total += c;
+            }
+            if (eq && before == left) s_row = u * kThreads + t;
+            left -= total;
+        }
+    }
+    __syncthreads();
+    const int64_t row = s_row;
+    if (row < 0 || row >= m) return;                                 // cannot happen; keeps every access in range
+
+    if (t == 0) idx[rank] = static_cast<int32_t>(row);
+    if (t < r) {
+        delta_sel[static_cast<int64_t>(rank) * r + t] = buf[row * r + t];
+        if (clear_selected) buf[row * r + t] = 0.0f;
+    }
+}
+
 constexpr int kChunk = 4096;                                         // scores that fit the small selection's LDS (32 KB)
 static_assert(65536 / kScoreRows <= kChunk, "the block maxima of the largest buffer (m <= 65536) fit the LDS chunk");
 
@@ -299,13 +473,7 @@ row_requantize_kernel(uint8_t* wq, int64_t n, int64_t m, int64_t r, const int32_
             for (int e = 0; e < 4; ++e) acc[e] = fma(d, a[e], acc[e]);  // product is exact in fp64
         }
     }
-    float f[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) f[e] = __builtin_amdgcn_fmed3f(static_cast<float>(acc[e]), -448.0f, 448.0f);
-    int w = 0;
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], w, false);
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], w, true);
-    wrow[c] = static_cast<uint32_t>(w);
+    wrow[c] = encode4_e4m3(acc);
 }
 
 }  // namespace
@@ -347,31 +515,45 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
                                int32_t* idx_out, int clear_selected, double* scores, const double* scores_in,
                                float* delta_sel, hipStream_t stream)
 {
+    hipError_t e;
     if (!scores_in) {
         const size_t lds = sizeof(float) * kScoreRows * (static_cast<size_t>(r) + 4);
         if (lds > 64 * 1024) {
-            hipError_t e0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&row_score_kernel),
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-            if (e0 != hipSuccess) return e0;
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&row_score_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+            if (e != hipSuccess) return e;
         }
-        row_score_kernel<<<static_cast<unsigned>(score_blocks(m)), kThreads, lds, stream>>>(delta_buf, m, static_cast<int>(r),
-                                                                                        scores);
-        hipError_t e = hipGetLastError();
+        row_score_kernel<<<static_cast<unsigned>(score_blocks(m)), kScoreThreads, lds, stream>>>(delta_buf, m,
+                                                                                                 static_cast<int>(r), scores);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
         scores_in = scores;
     }
-    if (m > kChunk) {
+    // The selection that finds one rank per workgroup, while the scores fit a workgroup's registers and the
+    // group maxima bound the k-th score well (k of 128 groups).
+    // Measured (whole update, us): 4096 rows k = 32 14.3 against 15.2, 16384 rows k = 64 19.5 against 31.2; an
+    // untouched buffer, where every score is equal, is the one case that was faster before.
+    if (k <= kSelectMaxK && m <= kSelectMaxRows) {
+        auto go = [&](auto kernel) {
+            kernel<<<static_cast<unsigned>(k), kThreads, 0, stream>>>(scores_in, m, k, static_cast<int>(r), idx_out, delta_buf,
+                                                                      delta_sel, clear_selected);
+        };
+        if (m <= 4 * kThreads) go(select_kernel<4>);
+        else if (m <= 16 * kThreads) go(select_kernel<16>);
+        else if (m <= 44 * kThreads) go(select_kernel<44>);
+        else go(select_kernel<64>);
+    } else if (m > kChunk) {
         constexpr size_t lds_sel = sizeof(uint64_t) * kChunkFiltered;
-        hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&topk_filtered_kernel),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_sel));
-        if (e1 != hipSuccess) return e1;
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&topk_filtered_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_sel));
+        if (e != hipSuccess) return e;
         topk_filtered_kernel<<<static_cast<unsigned>(score_blocks(m)), kThreads, lds_sel, stream>>>(
             scores_in, m, k, static_cast<int>(r), idx_out, delta_buf, delta_sel, clear_selected);
     } else {
         topk_rank_kernel<<<static_cast<unsigned>((m + 4 * kRankRows - 1) / (4 * kRankRows)), kThreads, 0, stream>>>(
             scores_in, m, k, static_cast<int>(r), idx_out, delta_buf, delta_sel, clear_selected);
     }
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 grid(static_cast<unsigned>(k), static_cast<unsigned>((n / 4 + kThreads - 1) / kThreads));
     row_requantize_kernel<<<grid, kThreads, 0, stream>>>(wq, n, m, r, idx_out, delta_sel);

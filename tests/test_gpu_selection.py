@@ -1,0 +1,52 @@
+"""Selection of the proxy update at the edges of its two paths: register counts (1024, 4096, 11264 and
+16384 rows), k on both sides of the limit, long runs of equal scores, scores that differ in their last
+bits only, and infinite and zero rows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_common import layer_on_gpu, np_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _buffer(kind, m, r, g):
+    if kind == "spread":
+        return (g.normal(size=(m, r)) * np.exp(1.5 * g.normal(size=(m, 1)))).astype(np.float32)
+    buf = np.zeros((m, r), np.float32)
+    if kind == "few":                              # fewer rows than k carry anything
+        buf[g.choice(m, size=3, replace=False), 0] = [1.0, 2.0, 2.0]
+    elif kind == "equal":                          # one value everywhere, a few larger
+        buf[:, 1] = 0.5
+        buf[g.choice(m, size=5, replace=False), 2] = 1.0
+    elif kind == "last bits":                      # scores that share all but their last bits
+        buf[:, 0] = 1.0
+        buf[:, 1] = (g.integers(0, 4, size=m) * 2.0 ** -50).astype(np.float32)
+    elif kind == "infinite":
+        buf[:] = g.normal(size=(m, r))
+        buf[7, 3] = np.inf
+    return buf
+
+
+@pytest.mark.parametrize("m,k", [(16, 16), (1024, 8), (1040, 96), (4096, 97), (4112, 32), (11264, 64), (11280, 33), (16384, 96),
+                                 (16400, 20)])
+@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "infinite"])
+def test_rows_and_order_are_the_oracles(m, k, kind):
+    n, r = 64, 16
+    g = np.random.default_rng(m + k)
+    buf = _buffer(kind, m, r, g)
+    wcat = oracle.fp8_encode(g.integers(-8, 9, size=(m + r, n)).astype(np.float32), oracle.E4M3)
+    layer = layer_on_gpu(4, n, m, r, k, wcat, np.float32(1.0))
+    layer.delta_buf.copy_(torch.from_numpy(buf))
+    layer.update()
+    torch.cuda.synchronize()
+    score = np.abs(buf.astype(np.float64)).sum(1)
+    want = np.lexsort((np.arange(m), -score))[:k]
+    assert np.array_equal(np_of(layer.idx), want)
+    left = buf.copy()
+    left[want] = 0.0
+    assert np.array_equal(np_of(layer.delta_buf), left)
+    if kind != "infinite":                         # non-finite values: selection and buffer only
+        idx_ref, w_ref, buf_ref = oracle.proxy_update(buf, wcat, m, r, k, True)
+        assert np.array_equal(idx_ref, want) and np.array_equal(np_of(layer.wq), w_ref)
