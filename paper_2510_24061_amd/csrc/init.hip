@@ -126,21 +126,38 @@ apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* 
         for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
     const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 
-    for (int64_t i0 = i_begin; i0 < i_end; i0 += 8) {
+    // Operands of the next step are requested before this step's products (92 -> 76 us at 4096 x 4096, l = 72; the
+    // other product, whose loads are 16 bytes of a row each, is faster without, 50 against 100 us).
+    float ev[4], ev2[4];
+    float4 yv[NBV], yv2[NBV];
+    auto fetch = [&](int64_t i0, float (&ef)[4], float4 (&yf)[NBV]) {
         const int64_t ii = i0 + 4 * h;                               // m and per_slice are multiples of 4 and 8
         const bool in = ii < i_end;
-        float ev[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) ev[t] = (in && col < n) ? ecol[(ii + t) * n] : 0.0f;
+        for (int t = 0; t < 4; ++t) ef[t] = (in && col < n) ? ecol[(ii + t) * n] : 0.0f;
 #pragma unroll
         for (int b = 0; b < NBV; ++b) {
             const int c = b * 32 + (lane & 31);
-            const float4 yv = (in && c < l) ? *reinterpret_cast<const float4*>(y + static_cast<int64_t>(c) * m + ii) : zero;
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv.x, ev[0], acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv.y, ev[1], acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv.z, ev[2], acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv.w, ev[3], acc[b], 0, 0, 0);
+            yf[b] = (in && c < l) ? *reinterpret_cast<const float4*>(y + static_cast<int64_t>(c) * m + ii) : zero;
         }
+    };
+    auto multiply = [&](const float (&ef)[4], const float4 (&yf)[NBV]) {
+#pragma unroll
+        for (int b = 0; b < NBV; ++b) {
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].x, ef[0], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].y, ef[1], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].z, ef[2], acc[b], 0, 0, 0);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].w, ef[3], acc[b], 0, 0, 0);
+        }
+    };
+    fetch(i_begin, ev, yv);
+    for (int64_t i0 = i_begin; i0 < i_end; i0 += 16) {
+        fetch(i0 + 8, ev2, yv2);                                     // (zeros beyond the slice)
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ev, yv);
+        fetch(i0 + 16, ev, yv);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ev2, yv2);
     }
     if (col >= n) return;
     float* const out = part + static_cast<int64_t>(blockIdx.y) * l * n;
@@ -168,67 +185,139 @@ sum_slices_kernel(const float* __restrict__ part, int slices, int64_t count, flo
 }
 
 // Orthonormalisation of the l rows of V[l][len] by Cholesky QR, applied twice: G = V V^T (fp64,
-// gram_kernel), G = L L^T, V <- L^-1 V by forward substitution.  Everything of size len runs over
-// the whole chip; only the l x l factorisation is one workgroup.  The second application brings the
-// rows to orthonormal at the precision they are stored in whenever cond(V) < 1e8, which a product
-// with E of a set of orthonormal vectors is far from reaching.  A row whose pivot is not positive
-// (a vector in the span of the earlier ones) is set to zero.
+// gram_kernel), G = L L^T and its inverse factor (inverse_factor_kernel), V <- L^-1 V
+// (apply_lower_kernel).  Everything of size len runs over the whole chip; only the l x l factorisation is
+// one workgroup.  The second application brings the rows to orthonormal at the precision they are stored in
+// whenever cond(V) < 1e8, which a product with E of a set of orthonormal vectors is far from reaching.  A
+// row whose pivot is not positive (a vector in the span of the earlier ones) is set to zero.
 //
-// Right-looking factorisation in LDS.  Output: the strict lower triangle of L, and on the diagonal
-// the reciprocal of the pivot (0 for a dropped row).
-__global__ void __launch_bounds__(kThreads)
-cholesky_kernel(const double* __restrict__ g, int l, double* __restrict__ lfac)
+// L^-1 by elimination on [G | I]: step c subtracts G[k][c] / d_c times row c from every row k > c, d_c the
+// pivot; the right half becomes the inverse of the unit factor L', and L = L' D^(1/2).  Column j of the left
+// half is finished in step j, where column j of the right one begins, so one lower triangle of registers
+// holds both, in blocks of 4 x 4, one per thread: a step reads eight LDS values per sixteen updates (one
+// element per thread and update reads two for each, and the LDS then takes longer than the arithmetic:
+// 55 us at l = 72).  A step publishes row c of the right half and column c of the left one in one LDS vector
+// and costs a barrier, a reciprocal and the update: a chain of l of them is all there is: 29 us at l = 72, where a factorisation with its trailing block in LDS took
+// 130 us and a forward substitution per column of V another 113 us.
+constexpr int kFactorThreads = 576;                                   // 32 * 33 / 2 blocks at l = 128, in whole waves
+
+__global__ void __launch_bounds__(kFactorThreads)
+inverse_factor_kernel(const double* __restrict__ g, int l, double* __restrict__ linv)
 {
-    extern __shared__ double s_l[];                                   // [l][l]
-    for (int q = threadIdx.x; q < l * l; q += kThreads) s_l[q] = g[q];
-    __syncthreads();
-    const double tiny = 1e-28 * fmax(s_l[0], 1e-300);
-    for (int c = 0; c < l; ++c) {
-        const double d = s_l[c * l + c];
-        const bool dead = !(d > tiny);
-        const double rinv = dead ? 0.0 : 1.0 / sqrt(d);
-        __syncthreads();                                              // everyone has read the pivot
-        for (int k = c + threadIdx.x; k < l; k += kThreads)
-            s_l[k * l + c] = (k == c) ? rinv : s_l[k * l + c] * rinv;
-        __syncthreads();
-        const int rem = l - 1 - c;                                    // trailing block, lower half only
-        for (int q = threadIdx.x; q < rem * rem; q += kThreads) {
-            const int k = c + 1 + q / rem, j = c + 1 + q % rem;
-            if (j <= k) s_l[k * l + j] -= s_l[k * l + c] * s_l[j * l + c];
+    __shared__ __attribute__((aligned(32))) double s_vec[2][kMaxL];
+    __shared__ double s_root[kMaxL];
+    const int t = threadIdx.x, nb = l / 4;                            // l is a multiple of 8
+    int R = static_cast<int>((sqrtf(8.0f * static_cast<float>(t) + 1.0f) - 1.0f) * 0.5f);
+    if (R * (R + 1) / 2 > t) --R;
+    if ((R + 1) * (R + 2) / 2 <= t) ++R;
+    const int C = t - R * (R + 1) / 2;
+    const bool live = R < nb;                                         // block row R, block column C <= R
+    double x[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[i][j] = live ? g[(4 * R + i) * l + 4 * C + j] : 0.0;
+    const double tiny = 1e-28 * fmax(g[0], 1e-300);
+    for (int cb = 0; cb < nb; ++cb) {
+#pragma unroll
+        for (int ci = 0; ci < 4; ++ci) {
+            const int c = 4 * cb + ci;
+            double* const vec = s_vec[ci & 1];                        // (the buffers alternate: one barrier per step)
+            if (live && C == cb) {                                    // the pivot and the column below it
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (R > cb || i >= ci) vec[4 * R + i] = x[i][ci];
+            }
+            if (live && R == cb) {                                    // L'^-1[c][.] before the pivot
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (C < cb || j < ci) vec[4 * C + j] = x[ci][j];
+            }
+            __syncthreads();
+            const double d = vec[c];
+            double dinv = __builtin_amdgcn_rcp(d);                    // and two Newton steps: full precision
+            dinv = fma(fma(-d, dinv, 1.0), dinv, dinv);
+            dinv = fma(fma(-d, dinv, 1.0), dinv, dinv);
+            if (!(d > tiny)) dinv = 0.0;                              // a dead row takes no part
+            if (t == 0) s_root[c] = dinv;
+            if (live && R >= cb) {
+                double f[4], v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { f[i] = vec[4 * R + i] * dinv; v[i] = vec[4 * C + i]; }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (R == cb && i <= ci) continue;                 // rows up to c are finished
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[i][j] = C == cb && j == ci ? -f[i] : x[i][j] - f[i] * v[j];
+                }
+                if (R == cb && C == cb) x[ci][ci] = 1.0;
+            }
         }
-        __syncthreads();
     }
-    for (int q = threadIdx.x; q < l * l; q += kThreads) lfac[q] = (q % l <= q / l) ? s_l[q] : 0.0;
+    __syncthreads();
+    if (t < l) s_root[t] = sqrt(s_root[t]);
+    __syncthreads();
+    if (!live) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (R > C || j <= i) linv[(4 * R + i) * l + 4 * C + j] = x[i][j] * s_root[4 * R + i];
 }
 
-// V <- L^-1 V in place: one lane per column of V, rows solved in order; the column lives in LDS.
-__global__ void __launch_bounds__(64)
-solve_lower_kernel(float* __restrict__ v, int l, int64_t len, const double* __restrict__ lfac)
+// V <- L^-1 V in place: a workgroup owns 64 columns of V, a wave four rows of the result at a time, whose
+// factors are uniform over the wave (scalar loads) and share each element of V read from LDS: 9.6 us at
+// 72 x 4096.
+constexpr int kLowerCols = 64, kLowerThreads = 1024;
+
+__global__ void __launch_bounds__(kLowerThreads)
+apply_lower_kernel(float* __restrict__ v, int l, int64_t len, const double* __restrict__ linv)
 {
-    __shared__ float s_q[kMaxL][64];
-    const int tj = threadIdx.x;
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * 64 + tj;
-    if (j >= len) return;                                             // no barrier below: a lane only touches its own column
-    for (int c = 0; c < l; ++c) s_q[c][tj] = v[static_cast<int64_t>(c) * len + j];
-    for (int c = 0; c < l; ++c) {
-        const double* row = lfac + static_cast<int64_t>(c) * l;
-        double acc = static_cast<double>(s_q[c][tj]);
-        for (int p = 0; p < c; ++p) acc -= row[p] * static_cast<double>(s_q[p][tj]);
-        const float q = static_cast<float>(acc * row[c]);
-        s_q[c][tj] = q;
-        v[static_cast<int64_t>(c) * len + j] = q;
+    extern __shared__ double s_v[];                                   // [l][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * kLowerCols + lane;
+    for (int c = wave; c < l; c += kLowerThreads / 64)
+        s_v[c * kLowerCols + lane] = j < len ? static_cast<double>(v[static_cast<int64_t>(c) * len + j]) : 0.0;
+    __syncthreads();
+    for (int c0 = 4 * wave; c0 < l; c0 += 4 * (kLowerThreads / 64)) { // l is a multiple of 8
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        const double* const f = linv + static_cast<int64_t>(c0) * l;
+        for (int p = 0; p < c0; p += 4) {
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = s_v[(p + u) * kLowerCols + lane];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[q] = fma(f[q * l + p + u], x[u], acc[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)                                   // the diagonal block
+#pragma unroll
+            for (int u = 0; u <= q; ++u) acc[q] = fma(f[q * l + c0 + u], s_v[(c0 + u) * kLowerCols + lane], acc[q]);
+        if (j < len) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[static_cast<int64_t>(c0 + q) * len + j] = static_cast<float>(acc[q]);
+        }
     }
 }
 
-// H[a][b] = sum_i Y[a][i] Y[b][i] in fp64; grid (l, l)
+// H[a][b] = sum_i Y[a][i] Y[b][i] in fp64; grid (l, l), the upper half leaves, the lower one writes both
 __global__ void __launch_bounds__(kThreads)
 gram_kernel(const float* __restrict__ y, int l, int64_t m, double* __restrict__ h)
 {
     __shared__ double s_red[kThreads / 64];
+    if (blockIdx.y > blockIdx.x) return;
     const float* ya = y + static_cast<int64_t>(blockIdx.x) * m;
     const float* yb = y + static_cast<int64_t>(blockIdx.y) * m;
     double d = 0.0;
-    for (int64_t i = threadIdx.x; i < m; i += kThreads) d += static_cast<double>(ya[i]) * static_cast<double>(yb[i]);
+    for (int64_t i = 4 * threadIdx.x; i < m; i += 4 * kThreads) {     // m is a multiple of 4
+        const float4 p = *reinterpret_cast<const float4*>(ya + i), q = *reinterpret_cast<const float4*>(yb + i);
+        d += static_cast<double>(p.x) * static_cast<double>(q.x);
+        d += static_cast<double>(p.y) * static_cast<double>(q.y);
+        d += static_cast<double>(p.z) * static_cast<double>(q.z);
+        d += static_cast<double>(p.w) * static_cast<double>(q.w);
+    }
     for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off, 64);
     if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = d;
     __syncthreads();
@@ -236,105 +325,145 @@ gram_kernel(const float* __restrict__ y, int l, int64_t m, double* __restrict__ 
         double t = 0.0;
         for (int w = 0; w < kThreads / 64; ++w) t += s_red[w];
         h[static_cast<int64_t>(blockIdx.x) * l + blockIdx.y] = t;
+        h[static_cast<int64_t>(blockIdx.y) * l + blockIdx.x] = t;
     }
 }
 
 // Symmetric eigen-decomposition of H (l x l, l even, fp64) by two-sided Jacobi with the round-robin
-// ordering: each round rotates l/2 disjoint index pairs at once.  One workgroup; H lives in LDS,
-// the eigenvectors P (columns) beside it where both fit (P_IN_LDS, l <= 96: a round then touches no
-// memory), in global memory otherwise.  Stops after the first sweep without a rotation, or after
-// `sweeps`.  On exit lambda[i] = H[i][i] and order[k] is the
-// index of the k-th largest eigenvalue.
-// 1024 threads: a round is three short LDS-bound phases between barriers, the more lanes the shorter
+// ordering: each round rotates l/2 disjoint index pairs at once.  One workgroup; H lives in LDS, the
+// eigenvectors (rows of pt) beside it where both fit (P_IN_LDS, l <= 96: a round then touches no memory), in
+// global memory otherwise.  A round is two phases between barriers: one pass that applies the rotations to H
+// from both sides at once (a thread owns the 2 x 2 block of two pairs, in the lower half, and writes its
+// mirror image too); then the eigenvectors' rotation by fifteen waves, while the first one forms the next
+// round's rotations, a chain of fp64 roots and a division.  Rows of H at an odd pitch: at a pitch of 72
+// doubles a column sits in four LDS banks.  Stops after the first sweep without a rotation, or after
+// `sweeps`.  On exit lambda[i] = H[i][i] and order[k] is the index of the k-th largest eigenvalue.
+// 1024 threads; a chain of l - 1 rounds per sweep, 1.4 us each (l = 72: 0.78 ms for the
+// whole; 2.85 ms with columns, rows and rotations as three phases at an even pitch).
 constexpr int kJacobiThreads = 1024;
 
 template <bool P_IN_LDS>
 __global__ void __launch_bounds__(kJacobiThreads)
-jacobi_eig_kernel(const double* __restrict__ h_in, int l, double* __restrict__ p, double* __restrict__ lambda,
+jacobi_eig_kernel(const double* __restrict__ h_in, int l, double* __restrict__ pt, double* __restrict__ lambda,
                   int* __restrict__ order, int sweeps)
 {
-    extern __shared__ double s_h[];                                   // [l][l], (P [l][l],) then c[l/2], s[l/2], pairs
-    double* const s_p = P_IN_LDS ? s_h + l * l : p;                   // the eigenvectors while they are rotated
-    double* const s_c = s_h + (P_IN_LDS ? 2 : 1) * l * l;
-    double* const s_s = s_c + l / 2;
-    int* const s_pp = reinterpret_cast<int*>(s_s + l / 2);            // pairs of this round: p[k], q[k]
-    int* const s_rot = s_pp + l;                                      // rotations taken in this sweep
-    for (int q = threadIdx.x; q < l * l; q += kJacobiThreads) {
-        s_h[q] = h_in[q];
+    extern __shared__ double s_h[];                                   // [l][l + 1], (pt [l][l],) then rotations and pairs
+    const int pitch = l + 1, t = threadIdx.x;
+    double* const s_p = P_IN_LDS ? s_h + l * pitch : pt;              // the eigenvectors while they are rotated
+    double* const s_cs = s_h + l * pitch + (P_IN_LDS ? l * l : 0);    // two sets of l/2 cosines, l/2 sines
+    int* const s_pairs = reinterpret_cast<int*>(s_cs + 2 * l);        // and of l/2 pairs
+    int* const s_rot = s_pairs + 2 * l;                               // rotations taken in this sweep and the next
+    for (int q = t; q < l * l; q += kJacobiThreads) {
+        s_h[q / l * pitch + q % l] = h_in[q];
         s_p[q] = (q / l == q % l) ? 1.0 : 0.0;
     }
-    __syncthreads();
     const int half = l / 2;
+    // this thread's blocks (k >= j) of H, and its columns of pairs of eigenvectors, as two 16-bit indices
+    constexpr int EB = 3, EP = 9;                                     // l <= 128: 2080 blocks, 8192 columns
+    int blk[EB], vec[EP];
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+        const int q = t + e * kJacobiThreads;
+        int k = static_cast<int>((sqrtf(8.0f * static_cast<float>(q) + 1.0f) - 1.0f) * 0.5f);
+        if (k * (k + 1) / 2 > q) --k;
+        if ((k + 1) * (k + 2) / 2 <= q) ++k;
+        blk[e] = k < half ? k << 16 | (q - k * (k + 1) / 2) : -1;
+    }
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {                                    // the first wave forms rotations instead
+        const int q = t - 64 + e * (kJacobiThreads - 64);
+        vec[e] = t >= 64 && q < half * l ? (q / l) << 16 | q % l : -1;
+    }
+    if (t == 0) s_rot[0] = s_rot[1] = 0;
+    __syncthreads();
     // round-robin ordering: position 0 keeps index 0, positions 1 .. l-1 rotate by one per round
-    auto at = [&](int pos, int round) { return pos == 0 ? 0 : (pos - 1 + (l - 1) - round % (l - 1)) % (l - 1) + 1; };
+    auto at = [&](int pos, int round) { return pos == 0 ? 0 : (pos - 1 >= round ? pos - round : pos - round + l - 1); };
+    // pairs (positions k and l-1-k) of a round and their rotations from the current 2x2 blocks
+    auto form = [&](int round, int set, int* rot) {
+        if (t >= half) return;
+        int a = at(t, round), b = at(l - 1 - t, round);
+        if (a > b) { const int x = a; a = b; b = x; }
+        s_pairs[set * l + 2 * t] = a; s_pairs[set * l + 2 * t + 1] = b;
+        const double haa = s_h[a * pitch + a], hbb = s_h[b * pitch + b], hab = s_h[a * pitch + b];
+        double c = 1.0, s = 0.0;
+        // an off-diagonal entry below the rounding level of its two diagonal ones is left alone
+        if (fabs(hab) > 1e-300 && fabs(hab) > 1e-16 * sqrt(fabs(haa * hbb))) {
+            atomicAdd(rot, 1);
+            // tangent of the smaller angle: 2 hab / (d +- sqrt(d^2 + 4 hab^2)), d = hbb - haa
+            const double d = hbb - haa, x = 2.0 * hab;
+            const double root = sqrt(d * d + x * x);
+            const double tn = x / (d >= 0.0 ? d + root : d - root);
+            c = rsqrt(1.0 + tn * tn);
+            s = tn * c;
+        }
+        s_cs[set * l + t] = c; s_cs[set * l + half + t] = s;
+    };
+    form(0, 0, s_rot);
+    __syncthreads();
+    int set = 0;
     for (int sweep = 0; sweep < sweeps; ++sweep) {
-        if (threadIdx.x == 0) *s_rot = 0;
-        __syncthreads();
-        for (int round = 0; round < l - 1; ++round) {
-            // pairs (positions k and l-1-k) and their rotations from the current 2x2 blocks
-            for (int k = threadIdx.x; k < half; k += kJacobiThreads) {
-                int a = at(k, round), b = at(l - 1 - k, round);
-                if (a > b) { const int t = a; a = b; b = t; }
-                s_pp[2 * k] = a; s_pp[2 * k + 1] = b;
-                const double haa = s_h[a * l + a], hbb = s_h[b * l + b], hab = s_h[a * l + b];
-                double c = 1.0, s = 0.0;
-                // an off-diagonal entry below the rounding level of its two diagonal ones is left alone
-                if (fabs(hab) > 1e-300 && fabs(hab) > 1e-16 * sqrt(fabs(haa * hbb))) {
-                    atomicAdd(s_rot, 1);
-                    const double tau = (hbb - haa) / (2.0 * hab);
-                    const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
+        for (int round = 0; round < l - 1; ++round, set ^= 1) {
+            const double* const s_c = s_cs + set * l;
+            const double* const s_s = s_c + half;
+            const int* const s_pp = s_pairs + set * l;
+            const bool last = round == l - 2;
+            if (last && t == 0) s_rot[(sweep + 1) & 1] = 0;
+            // H <- J^T H J   (pairs are disjoint, so all of them at once)
+#pragma unroll
+            for (int e = 0; e < EB; ++e) {
+                if (blk[e] < 0) continue;
+                const int k = blk[e] >> 16, j = blk[e] & 0xffff;
+                const int ak = s_pp[2 * k], bk = s_pp[2 * k + 1], aj = s_pp[2 * j], bj = s_pp[2 * j + 1];
+                const double ck = s_c[k], sk = s_s[k], cj = s_c[j], sj = s_s[j];
+                const double x00 = s_h[ak * pitch + aj], x01 = s_h[ak * pitch + bj];
+                const double x10 = s_h[bk * pitch + aj], x11 = s_h[bk * pitch + bj];
+                const double y00 = cj * x00 - sj * x01, y01 = sj * x00 + cj * x01;
+                const double y10 = cj * x10 - sj * x11, y11 = sj * x10 + cj * x11;
+                const double z00 = ck * y00 - sk * y10, z01 = ck * y01 - sk * y11;
+                const double z10 = sk * y00 + ck * y10, z11 = sk * y01 + ck * y11;
+                s_h[ak * pitch + aj] = z00; s_h[ak * pitch + bj] = z01;
+                s_h[bk * pitch + aj] = z10; s_h[bk * pitch + bj] = z11;
+                if (k != j) {
+                    s_h[aj * pitch + ak] = z00; s_h[bj * pitch + ak] = z01;
+                    s_h[aj * pitch + bk] = z10; s_h[bj * pitch + bk] = z11;
                 }
-                s_c[k] = c; s_s[k] = s;
             }
             __syncthreads();
-            // columns: H <- H J, P <- P J   (pairs are disjoint, so all of them at once)
-            for (int q = threadIdx.x; q < half * l; q += kJacobiThreads) {
-                const int k = q / l, i = q - k * l;
-                const int a = s_pp[2 * k], b = s_pp[2 * k + 1];
-                const double c = s_c[k], s = s_s[k];
-                const double ha = s_h[i * l + a], hb = s_h[i * l + b];
-                s_h[i * l + a] = c * ha - s * hb;
-                s_h[i * l + b] = s * ha + c * hb;
-                const double pa = s_p[i * l + a], pb = s_p[i * l + b];
-                s_p[i * l + a] = c * pa - s * pb;
-                s_p[i * l + b] = s * pa + c * pb;
-            }
-            __syncthreads();
-            // rows: H <- J^T H
-            for (int q = threadIdx.x; q < half * l; q += kJacobiThreads) {
-                const int k = q / l, j = q - k * l;
-                const int a = s_pp[2 * k], b = s_pp[2 * k + 1];
-                const double c = s_c[k], s = s_s[k];
-                const double ha = s_h[a * l + j], hb = s_h[b * l + j];
-                s_h[a * l + j] = c * ha - s * hb;
-                s_h[b * l + j] = s * ha + c * hb;
+            // the next round's rotations (first wave) beside pt <- J^T pt (the others)
+            form(last ? 0 : round + 1, set ^ 1, s_rot + ((sweep + (last ? 1 : 0)) & 1));
+#pragma unroll
+            for (int e = 0; e < EP; ++e) {
+                if (vec[e] < 0) continue;
+                const int k = vec[e] >> 16, i = vec[e] & 0xffff;
+                double* const pa = s_p + s_pp[2 * k] * l + i;
+                double* const pb = s_p + s_pp[2 * k + 1] * l + i;
+                const double c = s_c[k], s = s_s[k], va = *pa, vb = *pb;
+                *pa = c * va - s * vb;
+                *pb = s * va + c * vb;
             }
             __syncthreads();
         }
-        if (*s_rot == 0) break;                                       // converged (same value in every lane)
-        __syncthreads();
+        if (s_rot[sweep & 1] == 0) break;                             // converged (same value in every lane)
     }
     if (P_IN_LDS)
-        for (int q = threadIdx.x; q < l * l; q += kJacobiThreads) p[q] = s_p[q];
-    for (int i = threadIdx.x; i < l; i += kJacobiThreads) lambda[i] = s_h[i * l + i];
+        for (int q = t; q < l * l; q += kJacobiThreads) pt[q] = s_p[q];
+    for (int i = t; i < l; i += kJacobiThreads) lambda[i] = s_h[i * pitch + i];
     __syncthreads();
     // rank by eigenvalue, larger first, equal values by smaller index
-    for (int i = threadIdx.x; i < l; i += kJacobiThreads) {
-        const double li = s_h[i * l + i];
+    for (int i = t; i < l; i += kJacobiThreads) {
+        const double li = s_h[i * pitch + i];
         int rank = 0;
         for (int j = 0; j < l; ++j) {
-            const double lj = s_h[j * l + j];
+            const double lj = s_h[j * pitch + j];
             rank += (lj > li || (lj == li && j < i)) ? 1 : 0;
         }
         order[rank] = i;
     }
 }
 
-// A^[k][j] = lambda_k^(1/4) * sum_c P[c][order[k]] Z[c][j];  sigma[k] = sqrt(lambda_k)
+// A^[k][j] = lambda_k^(1/4) * sum_c pt[order[k]][c] Z[c][j];  sigma[k] = sqrt(lambda_k)
 __global__ void __launch_bounds__(kThreads)
-rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __restrict__ p,
+rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __restrict__ pt,
               const double* __restrict__ lambda, const int* __restrict__ order, int r,
               float* __restrict__ a_out, float* __restrict__ sigma_out, int inverse_scale)
 {
@@ -348,7 +477,7 @@ rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __res
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     if (j < n) {
         double acc = 0.0;
-        for (int c = 0; c < l; ++c) acc += p[c * l + col] * static_cast<double>(z[static_cast<int64_t>(c) * n + j]);
+        for (int c = 0; c < l; ++c) acc += pt[col * l + c] * static_cast<double>(z[static_cast<int64_t>(c) * n + j]);
         a_out[static_cast<int64_t>(k) * n + j] = static_cast<float>(scale * acc);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && sigma_out) sigma_out[k] = static_cast<float>(sqrt(lam));
@@ -386,14 +515,12 @@ SvdLayout svd_layout(int64_t m, int64_t n, int64_t r)
 // rows of v[l][len] <- orthonormal (Cholesky QR twice); h and lfac are l x l fp64 scratch
 static hipError_t orthonormalize_rows(float* v, int l, int64_t len, double* h, double* lfac, hipStream_t stream)
 {
-    const size_t lds = sizeof(double) * static_cast<size_t>(l) * l;
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&cholesky_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (err != hipSuccess) return err;
+    const size_t lds = sizeof(double) * static_cast<size_t>(l) * kLowerCols;                  // 64 KB at most
+    hipError_t err;
     for (int pass = 0; pass < 2; ++pass) {
         gram_kernel<<<dim3(l, l), kThreads, 0, stream>>>(v, l, len, h);
-        cholesky_kernel<<<1, kThreads, lds, stream>>>(h, l, lfac);
-        solve_lower_kernel<<<static_cast<unsigned>((len + 63) / 64), 64, 0, stream>>>(v, l, len, lfac);
+        inverse_factor_kernel<<<1, kFactorThreads, 0, stream>>>(h, l, lfac);
+        apply_lower_kernel<<<static_cast<unsigned>((len + kLowerCols - 1) / kLowerCols), kLowerThreads, lds, stream>>>(v, l, len, lfac);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
@@ -459,7 +586,7 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     FQ_CHECK_LAUNCH();
     // H, and the eigenvectors too while both fit the LDS (l <= 96; rotated in memory otherwise)
     const size_t mat = sizeof(double) * static_cast<size_t>(l) * l;
-    const size_t rest = sizeof(double) * static_cast<size_t>(l) + sizeof(int) * (static_cast<size_t>(l) + 4);
+    const size_t rest = sizeof(double) * 3 * static_cast<size_t>(l) + sizeof(int) * (2 * static_cast<size_t>(l) + 2);
     const bool p_in_lds = 2 * mat + rest <= 160 * 1024;
     const size_t lds = (p_in_lds ? 2 : 1) * mat + rest;
     const void* jacobi = p_in_lds ? reinterpret_cast<const void*>(&jacobi_eig_kernel<true>)

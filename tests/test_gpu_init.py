@@ -110,3 +110,24 @@ def test_factor_of_a_quantization_residual_and_the_layer_it_initializes():
     torch.cuda.synchronize()
     f = oracle.layer_fwd(x.float().numpy(), np_of(layer.wq), ref["s_w"], m, r)
     assert np.linalg.norm(np_of(layer.o_a) - f["o_a"]) <= 1e-3 * np.linalg.norm(f["o_a"])
+
+
+@pytest.mark.parametrize("m,n,r", [(272, 400, 88), (272, 400, 96)])      # eigenvectors just inside the LDS, and in memory
+def test_largest_subspaces(m, n, r):
+    g = np.random.default_rng(r)
+    e = g.normal(size=(m, n)).astype(np.float32) * np.linspace(3.0, 0.01, n, dtype=np.float32) ** 4
+    a, sig = _factor(e, r, iters=4, seed=r)
+    sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)
+    assert np.all(sig <= sv[:r] * (1 + 1e-4)) and np.sum(sig ** 2) >= 0.97 * np.sum(sv[:r] ** 2)
+    assert np.max(np.abs(a @ a.T - np.diag(sig))) <= 1e-4 * sig[0]
+
+
+@pytest.mark.parametrize("rank", [0, 5])
+def test_matrix_of_lower_rank_than_asked_for(rank):
+    """Vectors in the span of the others drop out (all of them for a zero matrix); nothing becomes NaN."""
+    g = np.random.default_rng(3)
+    e = (g.normal(size=(200, rank)) @ g.normal(size=(rank, 320))).astype(np.float32)
+    a, sig = _factor(e, 16, iters=2, seed=1)
+    assert np.all(np.isfinite(a)) and np.all(np.isfinite(sig))
+    sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)
+    assert np.max(np.abs(sig - sv[:16])) <= 1e-4 * max(sv[0], 1e-30)
