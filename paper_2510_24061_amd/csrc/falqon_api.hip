@@ -32,7 +32,7 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least)
     const DbTailPlan p256 = plan_db_tail(T, n, m, r, 256), pd = plan_db_tail(T, n, m, r, 0);
     int oa_parts = oa_splits(T, r), db_parts = db_splits(T, m);
     if (po.use && po.splits > oa_parts) oa_parts = po.splits;
-    if (p256.use && p256.groups > db_parts) db_parts = p256.groups;
+    if (r <= 64 && p256.use && p256.groups > db_parts) db_parts = p256.groups;
     if (!least && pd.use && pd.groups > db_parts) db_parts = pd.groups;
     if (!least && mid_db_parts(T, n, m) > db_parts) db_parts = mid_db_parts(T, n, m);
     w.amax_partials = off; off = align_up(off + sizeof(float) * kMaxAmaxBlocks, 256);
@@ -239,7 +239,7 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
 
     // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
     // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
-    const DbTailPlan pd = dx ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
+    const DbTailPlan pd = dx && !(least && r > 64) ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
     const int mid_parts = dx && !least ? mid_db_parts(T, n, m) : 0;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
@@ -427,7 +427,7 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
         e = launch_gemm_fwd_tail(g, t, st);
     } else {
         const DbTailPlan pd = plan_db_tail(M, n, m, r, least ? 256 : 0);
-        if (!pd.use) return FALQON_ERR_SHAPE;
+        if (!pd.use || r > 64) return FALQON_ERR_SHAPE;
         t.partial = reinterpret_cast<float*>(w8 + L.db_partials); t.tile_rows = pd.tile_rows;
         e = launch_gemm_dx_tail(g, t, st);
     }

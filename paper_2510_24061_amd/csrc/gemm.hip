@@ -208,8 +208,7 @@ __device__ __forceinline__ DbTailGeom db_side_geom(const GemmArgs& g, int tile_m
 }
 
 template <int BM>
-__device__ __forceinline__ void db_side_fetch(const TailArgs& t, const GemmArgs& g, const DbTailGeom& q, int c, bool with_oa,
-                                              uint8_t* lds_dy, uint8_t* lds_oa, int wave, int lane)
+__device__ __forceinline__ void db_side_fetch_dy(const GemmArgs& g, const DbTailGeom& q, int c, uint8_t* lds_dy, int wave, int lane)
 {
     constexpr int TOKENS = kDbTailGroupRows * BM;
     const int64_t i0 = static_cast<int64_t>(q.f_begin + c) * 128;
@@ -220,18 +219,26 @@ __device__ __forceinline__ void db_side_fetch(const TailArgs& t, const GemmArgs&
         const int64_t gt = q.t0 + trow, gi = i0 + (((lane & 7) ^ dbt::swz_t<8>(trow)) << 4);
         dma16_to_lds((gt < q.t_end && gi < g.K) ? g.a + gt * g.lda + gi : g_zero16, lds_dy + i * 1024);
     }
-    if (!with_oa) return;
+}
+
+// ranks [64 rc, +64) of O_A~
+template <int BM>
+__device__ __forceinline__ void db_side_fetch_oa(const TailArgs& t, const DbTailGeom& q, int rc, uint8_t* lds_oa, int wave, int lane)
+{
+    constexpr int TOKENS = kDbTailGroupRows * BM;
     const int64_t r = t.r;
 #pragma unroll
-    for (int it = 0; it < TOKENS / 16 / 4; ++it) {        // O_A~: 16 token rows of 64 bytes per wave instruction
+    for (int it = 0; it < TOKENS / 16 / 4; ++it) {               // 16 token rows of 64 bytes per wave instruction
         const int i = it * 4 + wave;
         const int trow = i * 16 + (lane >> 2);
-        const int64_t gt = q.t0 + trow, gp = ((lane & 3) ^ dbt::swz_t<4>(trow)) << 4;
+        const int64_t gt = q.t0 + trow, gp = rc * 64 + (((lane & 3) ^ dbt::swz_t<4>(trow)) << 4);
         dma16_to_lds((gt < q.t_end && gp < r) ? t.side + gt * r + gp : g_zero16, lds_oa + i * 1024);
     }
 }
 
-// Step 0 (with O_A~) has been issued by the caller, followed by the tile's first stage.
+// Feature step 0 and the first 64 ranks of O_A~ have been issued by the caller, followed by the tile's first
+// stage.  Ranks beyond 64 take a round trip for each further 64 of them, with dy~ kept: at 4096 x 4096 x 4096
+// and r = 256 the launch takes 73.8 us (66.5 at r = 64, same run), 85 with tiles of their own for dB.
 template <int BM>
 __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g, const DbTailGeom& q,
                                             uint8_t* lds_dy, uint8_t* lds_oa, int wave, int lane)
@@ -239,10 +246,14 @@ __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g
     const int64_t m = g.K, r = t.r;
     const int k_blocks = static_cast<int>((q.t_end - q.t0 + 63) / 64);
     float* out = t.partial + static_cast<int64_t>(q.group) * m * r;
-    for (int c = 0; q.f_begin + c < q.f_end; ++c) {
-        if (c > 0) {
-            __syncthreads();                                      // every wave has read the previous feature step
-            db_side_fetch<BM>(t, g, q, c, false, lds_dy, lds_oa, wave, lane);
+    const int chunks = static_cast<int>((r + 63) / 64);
+    for (int step = 0; q.f_begin + step / chunks < q.f_end; ++step) {
+        const int c = step / chunks, rc = step - c * chunks;
+        const int64_t p0 = rc * 64;
+        if (step > 0) {
+            __syncthreads();                                      // every wave has read the previous operands
+            if (rc == 0) db_side_fetch_dy<BM>(g, q, c, lds_dy, wave, lane);
+            if (chunks > 1) db_side_fetch_oa<BM>(t, q, rc, lds_oa, wave, lane);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -256,7 +267,7 @@ __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g
             const dbt::v8i a = dbt::read_tokens_of_feature<8>(lds_dy, wave * 32, kb, lane);
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                if (b * 32 >= r) continue;
+                if (p0 + b * 32 >= r) continue;
                 const dbt::v8i bb = dbt::read_tokens_of_feature<4>(lds_oa, b * 32, kb, lane);
                 acc[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bb, acc[b], 1 /* E5M2 */, 0 /* E4M3 */, 0, 0, 0, 0);
             }
@@ -271,7 +282,7 @@ __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g
         const int64_t i0 = static_cast<int64_t>(q.f_begin + c) * 128 + wave * 32;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int64_t p = b * 32 + (lane & 31);
+            const int64_t p = p0 + b * 32 + (lane & 31);
             if (p >= r) continue;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -634,7 +645,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     } else if constexpr (TAIL == 2) {
         const DbTailGeom q = db_side_geom<BM>(g, tile_m, tile_n, tiles_m, tiles_n);
         if (q.f_begin < q.f_end) {
-            db_side_fetch<BM>(*tail, g, q, 0, true, lds + A_BYTES, lds_b + B_BYTES, wave, lane);
+            db_side_fetch_dy<BM>(g, q, 0, lds + A_BYTES, wave, lane);
+            db_side_fetch_oa<BM>(*tail, q, 0, lds_b + B_BYTES, wave, lane);
             fetch_a_all(0, lds);
             fetch_b_all(0, lds_b);
             db_side_run<BM>(*tail, g, q, lds + A_BYTES, lds_b + B_BYTES, wave, lane);
@@ -1061,12 +1073,13 @@ OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r)
     return p;
 }
 
-// Input gradient: groups of two token tile rows; at most kDbSplitMax groups, four feature steps per
-// workgroup of a full group and eight in a last group of a single tile row.
+// Input gradient: groups of two token tile rows; at most kDbSplitMax groups, four round trips (feature steps
+// times chunks of 64 ranks) per workgroup of a full group and eight in a last group of a single tile row.
 DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_rows)
 {
     DbTailPlan p{false, 0, 256};
-    if (gemm_mid_supported(T, n) || r > 64 || (only_rows && !use_big_tiles(T, n))) return p;
+    if (gemm_mid_supported(T, n) || (only_rows && !use_big_tiles(T, n))) return p;
+    const int chunks = static_cast<int>((r + 63) / 64);
     for (int rows = only_rows ? only_rows : big_tile_rows(T, n); rows <= 256; rows += 64) {   // the best one, else larger groups
         const int tiles_m = static_cast<int>((T + rows - 1) / rows), tiles_n = static_cast<int>((n + 255) / 256);
         p.groups = (tiles_m + kDbTailGroupRows - 1) / kDbTailGroupRows;
@@ -1074,7 +1087,7 @@ DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_row
         const int per_full = (F + kDbTailGroupRows * tiles_n - 1) / (kDbTailGroupRows * tiles_n);
         const int per_last = (tiles_m % kDbTailGroupRows) ? (F + tiles_n - 1) / tiles_n : per_full;
         p.tile_rows = rows;
-        p.use = p.groups <= kDbSplitMax && per_full <= 4 && per_last <= 8;
+        p.use = p.groups <= kDbSplitMax && per_full * chunks <= 4 && per_last * chunks <= 8;
         if (p.use) break;
     }
     return p;

@@ -41,7 +41,9 @@ def test_exact_integer_layer_is_bit_exact(T, n, m, r):
     (2900, 1040, 4096, 32),       # ... two rank blocks
     (1900, 4096, 400, 64),        # input gradient: 128-row tiles, dB over groups of 256 tokens, the last one short
     (2900, 4080, 528, 48),        # ... 192-row tiles, groups of 384 tokens
-    (1700, 4352, 272, 128),       # ... rank above the side job's: dB in a launch of its own
+    (1700, 4352, 272, 128),       # ... rank 128: two chunks of ranks per feature step
+    (2300, 4096, 400, 208),       # ... four chunks, the last one 16 wide, 256-row tiles
+    (1100, 4352, 4240, 256),      # ... four chunks and more feature steps than a workgroup takes: tiles of their own for dB
 ])
 def test_tiles_of_128_and_192_rows_exact_integer_layer_is_bit_exact(T, n, m, r):
     _exact_integer_layer(T, n, m, r)
