@@ -10,14 +10,22 @@ namespace falqon {
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not, because
-// the ordered sum of that many partials would cost more than the launch it saves (7 to 12 us).
+// Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not.  The tiles
+// of a tile row share out the steps of 128 features among themselves, about 1.2 us for each (operands, matrix
+// instructions, 32 KB of stores), and the ordered sum reads one partial per tile row at about 4 TB/s; a launch of
+// its own takes 7 us, reads dy~ again and leaves fewer partials.  (us for product, dB and sum: 512 x 4096 x 4096,
+// r = 64, 1 step per tile, 8 partials: 25 inside, 36 apart; 6479 x 272 x 5328, 14 steps, 51 partials: 79 inside,
+// 64 apart.)
 constexpr int64_t kMidDbMax = 64;
-static int mid_db_parts(int64_t T, int64_t n, int64_t m)
+static int mid_db_parts(int64_t T, int64_t n, int64_t m, int64_t r)
 {
     if (!gemm_mid_supported(T, n)) return 0;
     const int64_t rows = mid_tile_rows(T, n, m), parts = (T + rows - 1) / rows;
-    return parts <= kMidDbMax ? static_cast<int>(parts) : 0;
+    const int64_t cols = mid_tile_columns(T, n, m), steps = ((m + 127) / 128 + cols - 1) / cols;
+    const double partial_us = static_cast<double>(m) * static_cast<double>(r) * 4.0 / 4e6;
+    const double inside = 1.2 * static_cast<double>(steps) + static_cast<double>(parts) * partial_us;
+    const double apart = 7.0 + static_cast<double>(T) * static_cast<double>(m) / 4e6 + db_splits(T, m) * partial_us;
+    return parts <= kMidDbMax && inside < apart ? static_cast<int>(parts) : 0;
 }
 
 // least: the layout of a workspace that has room for no more partials of dB than the launches need that
@@ -34,7 +42,7 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least)
     if (po.use && po.splits > oa_parts) oa_parts = po.splits;
     if (r <= 64 && p256.use && p256.groups > db_parts) db_parts = p256.groups;
     if (!least && pd.use && pd.groups > db_parts) db_parts = pd.groups;
-    if (!least && mid_db_parts(T, n, m) > db_parts) db_parts = mid_db_parts(T, n, m);
+    if (!least && mid_db_parts(T, n, m, r) > db_parts) db_parts = mid_db_parts(T, n, m, r);
     w.amax_partials = off; off = align_up(off + sizeof(float) * kMaxAmaxBlocks, 256);
     w.scores = off;        off = align_up(off + sizeof(double) * static_cast<size_t>(m + (m + 63) / 64), 256);
     w.delta_sel = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r), 256);
@@ -240,7 +248,7 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
     // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
     const DbTailPlan pd = dx && !(least && r > 64) ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
-    const int mid_parts = dx && !least ? mid_db_parts(T, n, m) : 0;
+    const int mid_parts = dx && !least ? mid_db_parts(T, n, m, r) : 0;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
                                    reinterpret_cast<float*>(w8 + L.amax_partials), nullptr, st, pd.use || mid_parts ? &sc : nullptr);

@@ -18,6 +18,7 @@ struct MidSide {
 constexpr int kMidConfigs = 4;
 bool gemm_mid_supported(int64_t M, int64_t N);                   // products of this size run on the small tiles
 int mid_tile_rows(int64_t M, int64_t N, int64_t K);              // tokens per tile row of the configuration chosen by size
+int64_t mid_tile_columns(int64_t M, int64_t N, int64_t K);       // tile columns of it
 // cfg: tile configuration, -1 to choose by size
 hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, int cfg, hipStream_t stream);
 

@@ -567,6 +567,13 @@ int mid_tile_rows(int64_t M, int64_t N, int64_t K)
     return rows[mid_config(M, N, K)];
 }
 
+int64_t mid_tile_columns(int64_t M, int64_t N, int64_t K)
+{
+    const int cols[kMidConfigs] = {64, 64, 128, 128};
+    const int64_t c = cols[mid_config(M, N, K)];
+    return (N + c - 1) / c;
+}
+
 hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, int cfg, hipStream_t stream)
 {
     MidArgs t;

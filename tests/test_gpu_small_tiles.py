@@ -25,7 +25,7 @@ pytestmark = pytest.mark.gpu
     (1024, 400, 4096, 64),        # 128 x 128 tiles, adapter rows riding
     (1000, 4112, 400, 16),        # 128 x 128 tiles in the input gradient
     (1500, 272, 4112, 128),       # more than one round of tiles
-    (9000, 272, 144, 256),        # more than 64 tile rows: the adapter gradient in a launch of its own
+    (9000, 272, 144, 256),        # the adapter gradient in a launch of its own
 ])
 def test_exact_integer_layer_is_bit_exact(T, n, m, r):
     _exact_integer_layer(T, n, m, r)
