@@ -27,8 +27,8 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least);
 int db_splits(int64_t T, int64_t m);
 
 // ---- quantizer (quantize.hip) ------------------------------------------------------------
-// Two launches: per-block partial maxima, then scale + cast.  `zero_word` (nullable) is a
-// device word the cast pass clears, used to reset the running maximum of O_A.
+// Two launches, per-block partial maxima, then scale + cast; one for small tensors.  `zero_word` (nullable)
+// is a device word that the call clears, used to reset the running maximum of O_A.
 // `side` (nullable): a small dense bf16 tensor of `count` elements (a multiple of 16) with a known
 // maximum that the cast pass casts to E4M3 along the way, q = cast(x * (448 / max(*amax, 1e-12f))).
 struct SideCast { const uint16_t* x; const float* amax; uint8_t* q; int64_t count; };

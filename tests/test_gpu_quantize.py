@@ -160,3 +160,27 @@ def test_quantize_row_strided_input_and_output(fmt, dtype, rows, cols, pad_x, pa
     got = np_of(qbig)
     assert np.array_equal(got[:, :cols], q_ref)
     assert np.all(got[:, cols:] == 0xAA)
+
+
+@pytest.mark.parametrize("fmt", [fq.E4M3, fq.E5M2])
+@pytest.mark.parametrize("dtype,rows,cols", [(torch.bfloat16, 64, 4096), (torch.bfloat16, 64, 4112),    # at and beyond the
+                                             (torch.float32, 32, 4096), (torch.float32, 33, 4096),      # one-launch limit
+                                             (torch.bfloat16, 1, 16384), (torch.bfloat16, 1025, 16)])
+def test_one_launch_and_two_launches_match_the_oracle(fmt, dtype, rows, cols):
+    """Dense and with padded rows (values in the padding must not reach the scale), the maximum in the first,
+    last and a middle element, with and without a given scale."""
+    g = torch.Generator().manual_seed(rows + cols)
+    x = torch.randn(rows, cols, generator=g).to(dtype)
+    for at in (0, x.numel() - 1, x.numel() // 2 + 5):
+        y = x.clone()
+        y.view(-1)[at] = -77.0
+        _check(y, fmt)
+        _check(y, fmt, scale_in=np.float32(3.7))
+    wide = torch.full((rows, cols + 32), 1e4, dtype=dtype)
+    wide[:, :cols] = x
+    wg, q = wide.cuda(), torch.zeros(rows, cols + 16, dtype=torch.uint8, device="cuda")
+    s, ws = torch.zeros(1, device="cuda"), torch.empty(8192, dtype=torch.uint8, device="cuda")
+    fq.quantize(wg[:, :cols], fmt, q[:, :cols], s, ws)
+    q_ref, s_ref, _ = oracle.quantize(x.float().numpy(), fmt)
+    assert np.array_equal(np_of(q)[:, :cols], q_ref) and not np_of(q)[:, cols:].any()
+    assert np.float32(s.item()).tobytes() == s_ref.tobytes()
