@@ -88,12 +88,14 @@ def workspace_bytes(T: int, n: int, m: int, r: int) -> int:
     return int(lib().falqon_workspace_bytes(T, n, m, r))
 
 
+# A call of a small layer takes less time on the GPU than its arguments take here, so they go to ctypes as
+# plain integers (the prototypes make pointers of them) and the stream comes from the raw accessor.
 def _p(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -111,7 +113,7 @@ def _check(status: int, where: str):
 
 def _dev(*tensors):
     for t in tensors:
-        if t is not None and not (t.is_cuda and t.is_contiguous()):
+        if t is not None and (not t.is_cuda or not t.is_contiguous()):
             raise ValueError("tensors must be contiguous GPU tensors")
 
 
