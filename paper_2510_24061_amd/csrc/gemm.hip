@@ -11,7 +11,8 @@
 // Design for CDNA4:
 //   - v_mfma_f32_32x32x64_f8f6f4 (the 8-bit path that runs at the full FP8 rate; the older
 //     32x32x16 FP8 instruction runs at half of it), fp32 accumulators in registers.
-//   - A workgroup owns a BM x BN output tile and walks K in steps of 128 bytes.  Operand
+//   - A workgroup owns a BM x BN output tile (256 columns; 256, 192 or 128 rows, chosen by rounds over the
+//     CUs, big_tile_us; smaller products in gemm_mid.hip) and walks K in steps of 128 bytes.  Operand
 //     tiles go HBM/L2 -> LDS with global_load_lds (16 B per lane, no register staging) into
 //     rings three (left operand) and two (right operand) stages deep: the fetches of step k+2
 //     are issued while step k is multiplied.
@@ -1160,7 +1161,14 @@ hipError_t launch_gemm_tiles(const GemmArgs& g, hipStream_t stream)
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    if (g.splits > 1) return launch_cfg<2, 2, 2, 2>(g, stream);        // split K: small output, 128x128 tiles
+    if (g.splits > 1) {                                                // split K: few output columns, 128x128 tiles
+        if (g.b_is_kn || g.a_fmt != 1) return hipErrorInvalidValue;    // (the inner gradient of A is the one such product)
+        const int tiles_m = static_cast<int>((g.M + 127) / 128), tiles_n = static_cast<int>((g.N + 127) / 128);
+        const int chunk = (tiles_m * tiles_n + 7) / 8;
+        gemm_fp8_kernel<2, 2, 2, 2, false, 1><<<dim3(static_cast<unsigned>(8 * chunk), static_cast<unsigned>(g.splits)), dim3(256), 0,
+                                                stream>>>(g, tiles_m, tiles_n, chunk);
+        return hipGetLastError();
+    }
     if (gemm_mid_supported(g.M, g.N)) return launch_gemm_mid(g, MidSide{}, -1, stream);
     return launch_gemm_tiles(g, stream);
 }
