@@ -41,15 +41,21 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least)
     int oa_parts = oa_splits(T, r), db_parts = db_splits(T, m);
     if (po.use && po.splits > oa_parts) oa_parts = po.splits;
     if (r <= 64 && p256.use && p256.groups > db_parts) db_parts = p256.groups;
-    if (!least && pd.use && pd.groups > db_parts) db_parts = pd.groups;
-    if (!least && mid_db_parts(T, n, m, r) > db_parts) db_parts = mid_db_parts(T, n, m, r);
+    int wide_parts = mid_db_parts(T, n, m, r);
+    if (pd.use && pd.groups > wide_parts) wide_parts = pd.groups;
     w.amax_partials = off; off = align_up(off + sizeof(float) * kMaxAmaxBlocks, 256);
     w.scores = off;        off = align_up(off + sizeof(double) * static_cast<size_t>(m + (m + 63) / 64), 256);
     w.delta_sel = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r), 256);
-    w.db_partials = off;   off = align_up(off + sizeof(float) * static_cast<size_t>(db_parts) *
-                                                    static_cast<size_t>(m) * static_cast<size_t>(r), 256);
-    w.oa_partials = off;   off = align_up(off + sizeof(float) * static_cast<size_t>(oa_parts) *
-                                                    static_cast<size_t>(T) * static_cast<size_t>(r), 256);
+    // The partials of O_A follow (sizes of [m, r] floats are multiples of 1 KB, so without a gap).  No call uses
+    // them beside more partials of dB than the least layout has, and a forward and a backward call cannot share a
+    // workspace at one time anyway (amax_partials): what dB needs beyond its own room lies there first.
+    const size_t db_one = sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r);
+    const size_t oa_bytes = sizeof(float) * static_cast<size_t>(oa_parts) * static_cast<size_t>(T) * static_cast<size_t>(r);
+    size_t db_bytes = db_one * static_cast<size_t>(db_parts);
+    const size_t wide_bytes = least ? 0 : db_one * static_cast<size_t>(wide_parts);
+    while (db_bytes + oa_bytes < wide_bytes) db_bytes += db_one;
+    w.db_partials = off;   off = align_up(off + db_bytes, 256);
+    w.oa_partials = off;   off = align_up(off + oa_bytes, 256);
     w.oa_codes = off;      off = align_up(off + static_cast<size_t>(T) * static_cast<size_t>(r), 256);
     w.total = off;
     return w;
