@@ -431,8 +431,9 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
     if (!use_big_tiles(M, N)) return FALQON_ERR_SHAPE;
     hipError_t e;
     if (!b_is_kn) {
+        // the shapes are those at which tiles of 256 tokens have room for the side job, whatever rows it runs on
         const OaTailPlan po = plan_oa_tail(M, n, m, r);
-        if (!po.use || (m + r + 255) / 256 == (m + 255) / 256) return FALQON_ERR_SHAPE;
+        if (!po.use || !plan_oa_tail(M, n, m, r, 256).use || (m + r + 255) / 256 == (m + 255) / 256) return FALQON_ERR_SHAPE;
         t.partial = reinterpret_cast<float*>(w8 + L.oa_partials); t.splits = po.splits; t.steps_per_split = po.steps_per_split;
         t.row_parts = po.row_parts; t.tile_rows = po.tile_rows;
         if (po.splits == 0) {                                    // O_A (bf16) instead of partials
@@ -441,7 +442,7 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
         e = launch_gemm_fwd_tail(g, t, st);
     } else {
         const DbTailPlan pd = plan_db_tail(M, n, m, r, least ? 256 : 0);
-        if (!pd.use || r > 64) return FALQON_ERR_SHAPE;
+        if (!pd.use || !plan_db_tail(M, n, m, r, 256).use || r > 64) return FALQON_ERR_SHAPE;
         t.partial = reinterpret_cast<float*>(w8 + L.db_partials); t.tile_rows = pd.tile_rows;
         e = launch_gemm_dx_tail(g, t, st);
     }

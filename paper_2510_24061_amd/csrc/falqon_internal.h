@@ -75,7 +75,7 @@ struct TailArgs {
 };
 struct OaTailPlan { bool use; int splits; int steps_per_split; int row_parts; int tile_rows; };
 struct DbTailPlan { bool use; int groups; int tile_rows; };
-OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r);     // forward of a [T,n] x [m+r,n] layer
+OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_rows = 0);     // forward of a [T,n] x [m+r,n] layer
 // backward of the same layer; rows: token rows of the tiles, 0 to choose by size
 DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r, int rows);
 hipError_t launch_gemm_fwd_tail(const GemmArgs& g, const TailArgs& t, hipStream_t stream);

@@ -1036,15 +1036,15 @@ hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_
 // one K slice per set, at most 8 slices, each a whole number of K-steps and none empty; used when a
 // slice is at most four chunks (beyond that the exposed fetch round trips outweigh the saved round
 // of tiles).
-OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r)
+OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_rows)
 {
     OaTailPlan p{false, 0, 0, 1, 256};
-    if (gemm_mid_supported(T, m)) return p;
+    if (gemm_mid_supported(T, m) || (only_rows && !use_big_tiles(T, m))) return p;
     const int tiles_n = static_cast<int>((m + 255) / 256);
     const int KT = static_cast<int>((n + BK - 1) / BK);
     const int rank_blocks = static_cast<int>((r + 15) / 16);
     double best_us = 0.0;
-    for (int rows = 128; rows <= 256; rows += 64) {
+    for (int rows = only_rows ? only_rows : 128; rows <= 256; rows += 64) {
         for (int rb = 1; rb <= 4; rb *= 2) {
             // wave u of a tile row takes one of its rows / 16 token blocks and rb rank blocks: the
             // 4 tiles_n waves must reach every token block for every group of rb rank blocks
