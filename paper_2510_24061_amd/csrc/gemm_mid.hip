@@ -5,9 +5,9 @@
 // through the LDS, and the latency of getting them there:
 //   - a workgroup is alone on its CU and spends the whole LDS on one ring of S stages (S = 4 .. 8) that
 //     holds both operands, so that 100 to 130 KB are in flight while one stage is multiplied.
-//   - fetches write the LDS at 64 B/clk and operand reads take 128 B/clk of the same port (measured: a
-//     K-step costs the sum of the two, 385 / 470 / 655 / 940 clk for the four tiles below, against 64 to
-//     512 clk of matrix instructions).  So the four waves split the tile 2 (columns) x 2 (K): each
+//   - fetches write the LDS at 64 B/clk per CU, reads take about 200 B/clk and hide under them (measured:
+//     8 fetches per wave 514 clk, with 16 reads beside them 515), so the fetches are what a K-step costs as
+//     long as reads and matrix instructions stay beside them.  The four waves split the tile 2 (columns) x 2 (K): each
 //     multiplies 32 MB tokens x 32 NB columns over one 64-byte half of every K-step, which reads a third
 //     less than a 2 x 2 split of the tile; the two halves meet once, after the loop.
 //   - operands of step k + 1 are read into registers under the matrix instructions of step k, so a
@@ -17,9 +17,10 @@
 //     multiply one more 32-column block, or, where a tile row has too few tile columns or the chip has
 //     idle CUs, the adapter has tile columns of its own.  O_A and its maximum leave the launch finished.
 //   - input gradient: the stages of the left operand also hold what dB needs (see db_stage below).
-// Measured against the 128x128 tiles used before plus their launches for the adapter (us, weights from
-// HBM): 512 x 4096 x 4096, r = 64: forward 20.5 (25.4 + 7.1 + 3.9), input gradient with dB 18.4 (25.1 + 7.0);
-// 8 x 4096 x 11008 forward 13.3 (26.7 + 5.6 + 2.5); 256 x 512 x 512: 4.7 (6.0 + 5.5 + 3.2).
+// Measured against the 128x128 tiles used before plus their launches for the adapter (us, kernel trace of
+// both in one run): 512 x 4096 x 4096, r = 64: forward 18.5 (19.9 + 7.5 + 3.8), input gradient with dB 21.1
+// (20.3 + 7.2); 8 x 4096 x 11008 forward 10.7 (19.3 + 5.9 + 3.9); 256 x 512 x 512 forward 5.2 (6.8 + 5.4 + 3.1),
+// input gradient with dB 5.8 (6.9 + 6.1).
 #include <type_traits>
 
 #include "falqon_internal.h"
