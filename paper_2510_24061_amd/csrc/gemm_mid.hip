@@ -185,8 +185,9 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         return x;
     };
     // The transposing read goes out as inline assembly (through the builtin the compiler makes it wait
-    // for every fetch in flight).  Its results are only touched behind the lgkmcnt(0) at the top of the
-    // next step, which names them as operands so that no use or copy can move ahead of it.
+    // for every fetch in flight), so the compiler takes its results as there at once.  It copies registers
+    // where control flow meets, so no read stays in flight across a branch: the reads of a stage, the matrix
+    // instructions that hide them and the wait that names their results (landed) are one straight run.
     auto read_kn = [&](const uint8_t* tile, int ncol_base, v2i (&d)[4]) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -224,6 +225,18 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     auto read_stage = [&](auto parity, const uint8_t* st) {
 #pragma unroll
         for (int f = 0; f < N_FRAG; ++f) read_frag(parity, st, f);
+    };
+    auto landed = [&](auto parity) {
+        if constexpr (B_KN) {
+            constexpr int P = decltype(parity)::value;
+            __builtin_amdgcn_sched_barrier(0);                    // behind the matrix instructions
+#pragma unroll
+            for (int ni = 0; ni < NB; ++ni) {
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bt[P][ni][0]), "+v"(bt[P][ni][1]), "+v"(bt[P][ni][2]), "+v"(bt[P][ni][3]));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { bf[P][ni][2 * q] = bt[P][ni][q][0]; bf[P][ni][2 * q + 1] = bt[P][ni][q][1]; }
+            }
+        }
     };
     // ---- adapter gradient: dB = dy~^T O_A~ over this tile's tokens ---------------------------------
     // The stages of the left operand are dy~ [tokens][128 features]; the tiles of a tile row share the
@@ -283,31 +296,23 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         }
     };
     int slot = 0;                                                 // ring slot of stage kt
-    // STEADY: stage kt + S exists and lies inside K, so that the body carries no branch.
+    // STEADY: stage kt + S exists and lies inside K, so that the body carries no branch.  The others read a
+    // stage kt + 1 too where there is none (bytes of the ring that nothing uses): a branch around the reads
+    // would end the straight run.
     auto step = [&](auto parity, auto steady_tag, int kt) {
         constexpr int P = decltype(parity)::value;
         constexpr bool STEADY = decltype(steady_tag)::value;
-        const bool next = STEADY || kt + 1 < KT;
-        // stage kt + 1 has landed (of the stages behind it, those already fetched stay in flight) ...
+        // the operands of kt are in registers, stage kt + 1 has landed (of the stages behind it, those already
+        // fetched stay in flight) ...
         if constexpr (STEADY) {
             __builtin_amdgcn_s_waitcnt((((S - 2) * LPW) & 15) | (7 << 4) | ((((S - 2) * LPW) >> 4) << 14));
         } else {
             const int out = (KT - 1 < kt + S - 1 ? KT - 1 : kt + S - 1) - (kt + 1);
-            WaitStages<S - 2>::template run<LPW>(next ? out : 0);
-            __builtin_amdgcn_s_waitcnt(0xC07F);                   // ... and the operands of kt are in registers
-        }
-        if constexpr (B_KN) {
-#pragma unroll
-            for (int ni = 0; ni < NB; ++ni) {
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bt[P][ni][0]), "+v"(bt[P][ni][1]), "+v"(bt[P][ni][2]), "+v"(bt[P][ni][3]));
-#pragma unroll
-                for (int q = 0; q < 4; ++q) { bf[P][ni][2 * q] = bt[P][ni][q][0]; bf[P][ni][2 * q + 1] = bt[P][ni][q][1]; }
-            }
+            WaitStages<S - 2>::template run<LPW>(out > 0 ? out : 0);
         }
         barrier_lds_only();                                       // ... for every wave: the slot of stage kt is free
         uint8_t* const freed = lds + slot * STAGE;
         slot = slot + 1 == S ? 0 : slot + 1;
-        if (!STEADY && next) read_stage(std::integral_constant<int, 1 - P>{}, lds + slot * STAGE);
         const uint8_t *pa = nullptr, *pb = nullptr, *pr = nullptr;
         if constexpr (STEADY) {
             pa = inside_a(kt + S); pb = inside_b(kt + S); pr = inside_r(kt + S);
@@ -317,6 +322,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         if constexpr (DB) {
             if (kt + 1 >= db_begin && kt + 1 < db_end) db_stage(lds + slot * STAGE, kt + 1);
         }
+        if constexpr (!STEADY) read_stage(std::integral_constant<int, 1 - P>{}, lds + slot * STAGE);
         // The fetches are spread over the matrix instructions: a wave that issues them back to back, ahead
         // of its LDS reads, stalls on the CU's 64 B/clk vector-memory path.
         constexpr int PER = (LPW + MB * NB - 1) / (MB * NB), FPER = (N_FRAG + MB * NB - 1) / (MB * NB);
@@ -345,6 +351,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
                     rf[P], af[P][j], acc[MB * NB + j], 0, 0, 0, 0, 0, 0);
             }
         }
+        landed(std::integral_constant<int, 1 - P>{});
     };
     float inv;
     {
@@ -365,6 +372,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         WaitStages<S - 1>::template run<LPW>(first - 1);
         barrier_lds_only();
         read_stage(std::integral_constant<int, 0>{}, lds);
+        landed(std::integral_constant<int, 0>{});
         if constexpr (DB) {
             if (db_begin == 0 && db_end > 0) db_stage(lds, 0);
         }
