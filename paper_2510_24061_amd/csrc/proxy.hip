@@ -179,7 +179,12 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
     } else {
         // largest key that more than `rank` rows reach: the key of the row looked for
         unsigned long long all = ~0ull, any = 0;
-        auto count_reaching = [&](uint64_t bound, int which) {       // rows with key >= bound, over the workgroup
+        // rows with key >= bound, over the workgroup.  One barrier per call: the sums of a call may still be read
+        // while the next one writes, so the two use different buffers, and the barrier of the next keeps the one
+        // after it apart.  All waves make the same calls.
+        int which = 0;
+        auto count_reaching = [&](uint64_t bound) {
+            which ^= 1;
             int c = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -210,11 +215,9 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
         uint64_t found = 0;
         for (int bit = 63; bit >= 0; --bit) {                        // (every thread takes the same path)
             const uint64_t trial = found | (uint64_t(1) << bit);
-            if ((all & trial & ~found) || ((any & trial & ~found) && count_reaching(trial, bit & 1) > rank)) found = trial;
+            if ((all & trial & ~found) || ((any & trial & ~found) && count_reaching(trial) > rank)) found = trial;
         }
-        __syncthreads();
-        const int greater = found == ~uint64_t(0) ? 0 : count_reaching(found + 1, 0);
-        __syncthreads();
+        const int greater = found == ~uint64_t(0) ? 0 : count_reaching(found + 1);
         int left = rank - greater;                                   // equal rows of smaller index
 #pragma unroll
         for (int u = 0; u < U; ++u) {

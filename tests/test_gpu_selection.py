@@ -1,6 +1,6 @@
 """Selection of the proxy update at the edges of its two paths: register counts (1024, 4096, 11264 and
-16384 rows), k on both sides of the limit, long runs of equal scores, scores that differ in their last
-bits only, and infinite and zero rows."""
+16384 rows), k on both sides of the limit, long runs of equal scores, scores that share all but a few
+neighbouring or separate bits, and infinite and zero rows."""
 import numpy as np
 import pytest
 import torch
@@ -23,6 +23,10 @@ def _buffer(kind, m, r, g):
     elif kind == "last bits":                      # scores that share all but their last bits
         buf[:, 0] = 1.0
         buf[:, 1] = (g.integers(0, 4, size=m) * 2.0 ** -50).astype(np.float32)
+    elif kind.startswith("bits"):                  # ... that differ in single bits of the fp64 pattern, none adjacent
+        buf[:, 0] = 1.0
+        for bit in kind.split()[1:]:
+            buf[:, 1] += (g.integers(0, 2, size=m) * 2.0 ** (int(bit) - 52)).astype(np.float32)
     elif kind == "infinite":
         buf[:] = g.normal(size=(m, r))
         buf[7, 3] = np.inf
@@ -31,7 +35,7 @@ def _buffer(kind, m, r, g):
 
 @pytest.mark.parametrize("m,k", [(16, 16), (1024, 8), (1040, 96), (4096, 97), (4112, 32), (11264, 64), (11280, 33), (16384, 96),
                                  (16400, 20)])
-@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "infinite"])
+@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "bits 2 0", "bits 40 38 31", "infinite"])
 def test_rows_and_order_are_the_oracles(m, k, kind):
     n, r = 64, 16
     g = np.random.default_rng(m + k)
