@@ -15,6 +15,7 @@
 //      fp32, cast to E4M3, written back.  A~ is rows [m, m+r) of the concatenated weight, in the same
 //      scaled domain as W~, so the backbone's scale never enters.
 #include <mutex>
+#include <type_traits>
 
 #include "falqon_internal.h"
 #include "row_scores.h"
@@ -80,27 +81,94 @@ __device__ __forceinline__ uint32_t encode4_e4m3(const double (&acc)[4])
 // non-negative doubles, so their bit patterns order them as 64-bit integers.  Thread t holds the keys of rows
 // t, t + 256, ...; threads t and t ^ 1 form one of 128 groups.  The k-th largest group maximum bounds the
 // k-th largest key from below, and so does any number below it: tau, its leading bits (every wave finds them
-// by bisection on its own, two maxima per lane).  The rows whose high word reaches tau, a few dozen, contain
-// the k selected ones; they are ranked pairwise.  If too many reach it (long runs of equal scores, such as
-// an untouched buffer) the row is found by bisection on the key and, among equals, by index.
+// by bisection on its own, two maxima per lane).  The rows that reach tau, a few dozen, contain the k selected
+// ones; they are ranked pairwise.
+//
+// tau has 12 bits from the first one in which the maxima differ: the exponent and some bits behind it where the
+// rows have learned at different rates, bits far behind it where they are alike (the first step of AdamW moves
+// every element by about the learning rate).  If far more rows than are looked for reach tau, 12 more bits,
+// until tau is the k-th maximum itself; what is left then are equal scores (an untouched buffer), and the row is
+// found among those above tau, or by its index among the equal ones.  Only where many rows are above tau (all that
+// is large sits in a few threads) is it found by counting over all rows, bit by bit.
 //
 // All latency: one round trip for the scores, one for the buffer row, and 2 us of comparisons.  Every
-// workgroup repeats the comparisons; nothing is exchanged.  us by kernel trace, against ranking 16 rows per workgroup
-// or, beyond 4096 rows, ranking whole blocks: 6.0 (8.0) at 4096 rows, 8.8 (18.5) at 11008, k = 32.
+// workgroup repeats the comparisons; nothing is exchanged.  Whole update in us (graph of 20, n = 256), against
+// ranking 16 rows per workgroup or, beyond 4096 rows, whole blocks:
+//                       rows learned at different rates   after the first AdamW step   untouched
+//   512 x 16, k = 8              8.5 (9.0)                        8.5 (9.0)              8.0 (9.4)
+//   4096 x 64, k = 32           12.0 (15.1)                      12.0 (15.0)            10.5 (15.2)
+//   11008 x 64, k = 32          14.6 (25.7)                      14.8 (25.7)            12.5 (132)
+// Slower than before only where many of few rows are equal and reach tau: 256 of 512 rows 10.7 (9.4), a third of
+// 2000 rows 12.8 (12.3).
 // (Requantizing in the same launch was built too: the workgroups that share a row have to agree on when
 // its buffer row may be cleared, and their device-scope atomics cost more, 6 us, than the launch saved.)
-constexpr int kSelectGroups = 128, kSelectCands = 256, kSelectMaxK = 96, kSelectMaxRows = 64 * kThreads;
-constexpr int kTauLowBit = 14;                                       // tau keeps a score's exponent and 6 bits behind it
+constexpr int kSelectGroups = 128, kSelectMaxK = 96, kSelectCands = 2 * kSelectMaxK + 32, kSelectMaxRows = 64 * kThreads;
+constexpr int kTauBits = 12;                                         // bits of tau found at a time
+constexpr int kTauRounds = 6;                                        // that many cover a key
+
+// bitwise or over the wave, the same in every lane
+__device__ __forceinline__ uint32_t wave_or(uint32_t x)
+{
+    const auto v = [](uint32_t u) { return static_cast<int>(u); };
+    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8: rows of 16 lanes
+    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x112, 0xf, 0xf, true);
+    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x114, 0xf, 0xf, true);
+    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x118, 0xf, 0xf, true);
+    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x142, 0xa, 0xf, true);   // row_bcast 15, 31: across rows
+    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x143, 0xc, 0xf, true);
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(v(x), 63));
+}
+
+__device__ __forceinline__ uint64_t read_lane64(uint64_t x, int lane)
+{
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x)), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x >> 32)), lane);
+    return static_cast<uint64_t>(hi) << 32 | lo;
+}
+
+// The next kTauBits bits of the k-th largest of 128 maxima, two per lane (a, b).  tau: its bits outside `open`,
+// zeros inside; open: the low bits not yet known.
+template <bool FIRST>                                                // nothing is known yet
+__device__ __forceinline__ void extend_tau(uint64_t a, uint64_t b, int k, uint64_t& tau, uint64_t& open)
+{
+    bool in_a = true, in_b = true;                                   // maxima that share what is known, and one of them
+    uint64_t ref;
+    if constexpr (FIRST) {
+        ref = read_lane64(a, 0);
+    } else {
+        in_a = ((a ^ tau) & ~open) == 0; in_b = ((b ^ tau) & ~open) == 0;
+        const uint64_t mask_a = __ballot(in_a), mask_b = __ballot(in_b);
+        ref = mask_a ? read_lane64(a, __builtin_ctzll(mask_a)) : mask_b ? read_lane64(b, __builtin_ctzll(mask_b)) : tau;
+    }
+    const uint64_t diff = (in_a ? a ^ ref : 0) | (in_b ? b ^ ref : 0);
+    const uint64_t all = static_cast<uint64_t>(wave_or(static_cast<uint32_t>(diff >> 32))) << 32 | wave_or(static_cast<uint32_t>(diff));
+    if (all == 0) { tau = ref; open = 0; return; }
+    const int top = 63 - __builtin_clzll(all), low = top < kTauBits ? 0 : top - (kTauBits - 1);
+    const uint64_t below_top = (uint64_t(2) << top) - 1;             // (keys have no sign bit: top <= 62)
+    // the window [low, top] of each maximum; those above or below what is known count always or never
+    const uint32_t wa = in_a ? static_cast<uint32_t>((a & below_top) >> low) : a > tau ? ~0u : 0u;
+    const uint32_t wb = in_b ? static_cast<uint32_t>((b & below_top) >> low) : b > tau ? ~0u : 0u;
+    uint32_t w = 0;
+#pragma unroll
+    for (int bit = kTauBits - 1; bit >= 0; --bit) {
+        const uint32_t trial = w | (1u << bit);
+        if (__popcll(__ballot(wa >= trial)) + __popcll(__ballot(wb >= trial)) >= k) w = trial;
+    }
+    tau = (ref & ~below_top) | static_cast<uint64_t>(w) << low;
+    open = (uint64_t(1) << low) - 1;
+}
 
 template <int U>                                                     // U keys per thread: m <= 256 U
 __global__ void __launch_bounds__(kThreads)
 select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int32_t* __restrict__ idx, float* buf,
               float* __restrict__ delta_sel, int clear_selected)
 {
-    __shared__ uint32_t s_max[kSelectGroups];
+    static_assert(U <= 64, "one lane per key of a thread");
+    __shared__ uint64_t s_max[kSelectGroups];
     __shared__ uint64_t s_ckey[kSelectCands];
     __shared__ int s_cidx[kSelectCands];
-    __shared__ int s_ncand, s_row, s_count[2][kThreads / 64], s_equal[U][kThreads / 64];
+    __shared__ int s_listed[kTauRounds + 1], s_row, s_count[2][kThreads / 64];
+    __shared__ __attribute__((aligned(16))) int s_equal[64][kThreads / 64];
     __shared__ unsigned long long s_all, s_any;
     const uint64_t* key = reinterpret_cast<const uint64_t*>(score);
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
@@ -110,50 +178,45 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t i = static_cast<int64_t>(u) * kThreads + t;
-        v[u] = i < m ? key[i] : 0;
-    }
-    if (t == 0) { s_ncand = 0; s_row = -1; }
-    uint32_t hi = 0;
+        v[u] = i < m ? key[i] : 0;                                   // (0 also stands for the rows behind the last one:
+    }                                                                // none is looked for but among equals, by index)
+    if (t <= kTauRounds) s_listed[t] = 0;
+    if (t == 0) s_row = -1;
+    double mx = 0.0;                                                 // (a NaN is left out: tau stays a lower bound)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t h = static_cast<uint32_t>(v[u] >> 32);
-        hi = h > hi ? h : hi;
-    }
-    const uint32_t other = __shfl_xor(hi, 1, 64);
-    hi = other > hi ? other : hi;
-    if ((t & 1) == 0) s_max[t >> 1] = hi;
+    for (int u = 0; u < U; ++u) mx = fmax(mx, __longlong_as_double(static_cast<long long>(v[u])));
+    mx = fmax(mx, __shfl_xor(mx, 1, 64));
+    if ((t & 1) == 0) s_max[t >> 1] = static_cast<uint64_t>(__double_as_longlong(mx));
     __syncthreads();
 
-    // ---- tau: the k-th largest of the maxima, rounded down to its leading bits -------------------------
-    uint32_t tau = 0;
-    {
-        const uint32_t a = s_max[lane], b = s_max[lane + 64];
-#pragma unroll
-        for (int bit = 30; bit >= kTauLowBit; --bit) {
-            const uint32_t trial = tau | (1u << bit);
-            if (__popcll(__ballot(a >= trial)) + __popcll(__ballot(b >= trial)) >= k) tau = trial;
-        }
-    }
-    // ---- the rows that reach it ---------------------------------------------------------------------------
-    int found_here = 0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const bool in = static_cast<int64_t>(u) * kThreads + t < m && static_cast<uint32_t>(v[u] >> 32) >= tau;
-        found_here += in ? 1 : 0;
-    }
-    if (found_here) {
-        int pos = atomicAdd(&s_ncand, found_here);
+    // Ranking is quadratic: with far more rows listed than are looked for, tau gets more bits, or is the k-th
+    // maximum itself and many of the listed ones equal it.
+    const int limit = 2 * static_cast<int>(k) + 32;
+    // rows with key >= bound > 0 (above: > bound) into the list, as far as it goes; which: the counter, used once per
+    // launch.  Keys are compared as doubles, in one instruction; a NaN counts as above, as its bits do.
+    auto list_rows = [&](uint64_t bound, auto above_tag, int which) __attribute__((always_inline)) {
+        constexpr bool ABOVE = decltype(above_tag)::value;
+        const double reach = __longlong_as_double(static_cast<long long>(bound));
+        uint32_t in[2] = {0, 0};                                     // bit u: key u of this thread
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = static_cast<int64_t>(u) * kThreads + t < m && static_cast<uint32_t>(v[u] >> 32) >= tau;
-            if (in && pos < kSelectCands) { s_ckey[pos] = v[u]; s_cidx[pos] = u * kThreads + t; }
-            pos += in ? 1 : 0;
+            const double x = __longlong_as_double(static_cast<long long>(v[u]));
+            in[u / 32] |= (ABOVE ? !(x <= reach) : !(x < reach)) ? 1u << (u % 32) : 0u;
         }
-    }
-    __syncthreads();
-    const int nc = s_ncand;
-    if (nc <= kSelectCands) {
-        // four threads per listed row, four others at a time
+        if (in[0] | in[1]) {
+            int pos = atomicAdd(&s_listed[which], __popc(in[0]) + __popc(in[1]));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int listed = in[u / 32] >> (u % 32) & 1;
+                if (listed && pos < limit) { s_ckey[pos] = v[u]; s_cidx[pos] = u * kThreads + t; }
+                pos += listed;
+            }
+        }
+        __syncthreads();
+        return s_listed[which];
+    };
+    // the row of rank `rank` among the nc listed ones: four threads per listed row, four others at a time
+    auto rank_listed = [&](int nc) __attribute__((always_inline)) {
         for (int c0 = 0; c0 < nc; c0 += kThreads / 4) {
             const int c = c0 + t / 4;
             const bool in = c < nc;
@@ -176,30 +239,80 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
             beat += __shfl_xor(beat, 2, 64);
             if (in && (t & 3) == 0 && beat == rank) s_row = ic;
         }
+    };
+    // the row with `left` rows of the same key before it
+    auto index_among_equal = [&](uint64_t value, int left) __attribute__((always_inline)) {
+        uint64_t equal = 0;                                          // bit u: key u of this thread
+        int mine = 0;                                                // lane u: rows of the wave's share of key u
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool eq = v[u] == value;
+            const int count = __popcll(__ballot(eq));
+            equal |= eq ? uint64_t(1) << u : 0;
+            mine = lane == u ? count : mine;
+        }
+        s_equal[lane][wave] = mine;
+        __syncthreads();
+        const int4 c = *reinterpret_cast<const int4*>(s_equal[lane]);
+        int upto = c.x + c.y + c.z + c.w;                            // rows of keys 0 .. lane
+        for (int off = 1; off < 64; off <<= 1) {
+            const int below = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += below;
+        }
+        const uint64_t reached = __ballot(upto > left);
+        if (!reached) return;                                        // (value is a key of more than `left` rows)
+        const int u = __builtin_ctzll(reached);
+        int before = __shfl(upto - (c.x + c.y + c.z + c.w), u, 64);
+        before += wave > 0 ? __shfl(c.x, u, 64) : 0;
+        before += wave > 1 ? __shfl(c.y, u, 64) : 0;
+        before += wave > 2 ? __shfl(c.z, u, 64) : 0;
+        const bool eq = equal >> u & 1;
+        before += __popcll(__ballot(eq) & ((uint64_t(1) << lane) - 1));
+        if (eq && before == left) s_row = u * kThreads + t;
+    };
+
+    uint64_t tau = 0, open = ~uint64_t(0);
+    int nc;
+    {
+        const uint64_t a = s_max[lane], b = s_max[lane + 64];
+        extend_tau<true>(a, b, static_cast<int>(k), tau, open);
+        nc = tau ? list_rows(tau, std::false_type{}, 0) : limit + 1;                // (every row reaches 0)
+        for (int round = 1; nc > limit && open != 0 && round < kTauRounds; ++round) {
+            const uint64_t before = tau;
+            extend_tau<false>(a, b, static_cast<int>(k), tau, open);
+            if (tau != before) nc = list_rows(tau, std::false_type{}, round);
+        }
+    }
+    const int above = nc > limit ? list_rows(tau, std::true_type{}, kTauRounds) : 0;
+    if (nc <= limit) {
+        rank_listed(nc);
+    } else if (rank >= above) {
+        index_among_equal(tau, rank - above);
+    } else if (above <= limit) {
+        rank_listed(above);
     } else {
-        // largest key that more than `rank` rows reach: the key of the row looked for
-        unsigned long long all = ~0ull, any = 0;
-        // rows with key >= bound, over the workgroup.  One barrier per call: the sums of a call may still be read
-        // while the next one writes, so the two use different buffers, and the barrier of the next keeps the one
-        // after it apart.  All waves make the same calls.
+        // largest key that more than `rank` rows reach: the key of the row looked for.  One barrier per count:
+        // the sums of a count may still be read while the next one writes, so the two use different buffers, and
+        // the barrier of the next keeps the one after it apart.  All waves make the same counts.
         int which = 0;
-        auto count_reaching = [&](uint64_t bound) {
+        auto count_reaching = [&](uint64_t bound) __attribute__((always_inline)) {
             which ^= 1;
             int c = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                c += (static_cast<int64_t>(u) * kThreads + t < m && v[u] >= bound) ? 1 : 0;
+                c += v[u] >= bound ? 1 : 0;
             for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
             if (lane == 0) s_count[which][wave] = c;
             __syncthreads();
             return s_count[which][0] + s_count[which][1] + s_count[which][2] + s_count[which][3];
         };
-        // bits that all listed rows share (equal scores: every bit) need no count
+        // bits that all rows from tau on share need no count
+        unsigned long long all = ~0ull, any = 0;
         if (t == 0) { s_all = ~0ull; s_any = 0; }
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (static_cast<int64_t>(u) * kThreads + t < m && static_cast<uint32_t>(v[u] >> 32) >= tau) {
+            if (v[u] >= tau) {
                 all &= v[u];
                 any |= v[u];
             }
@@ -217,26 +330,7 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
             const uint64_t trial = found | (uint64_t(1) << bit);
             if ((all & trial & ~found) || ((any & trial & ~found) && count_reaching(trial) > rank)) found = trial;
         }
-        const int greater = found == ~uint64_t(0) ? 0 : count_reaching(found + 1);
-        int left = rank - greater;                                   // equal rows of smaller index
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint64_t mask = __ballot(static_cast<int64_t>(u) * kThreads + t < m && v[u] == found);
-            if (lane == 0) s_equal[u][wave] = __popcll(mask);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool eq = static_cast<int64_t>(u) * kThreads + t < m && v[u] == found;
-            int before = __popcll(__ballot(eq) & ((uint64_t(1) << lane) - 1)), total = 0;
-            for (int w = 0; w < kThreads / 64; ++w) {
-                const int c = s_equal[u][w];
-                if (w < wave) before += c;
-                total += c;
-            }
-            if (eq && before == left) s_row = u * kThreads + t;
-            left -= total;
-        }
+        index_among_equal(found, rank - count_reaching(found + 1));
     }
     __syncthreads();
     const int64_t row = s_row;
@@ -544,8 +638,7 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
     }
     // The selection that finds one rank per workgroup, while the scores fit a workgroup's registers and the
     // group maxima bound the k-th score well (k of 128 groups).
-    // Measured (whole update, us): 4096 rows k = 32 14.3 against 15.2, 16384 rows k = 64 19.5 against 31.2; an
-    // untouched buffer, where every score is equal, is the one case that was faster before.
+    // Figures at the kernel; at the edge, 16384 rows and k = 96: 22.9 us against 31.4 for the whole update.
     if (k <= kSelectMaxK && m <= kSelectMaxRows) {
         auto go = [&](auto kernel) {
             kernel<<<static_cast<unsigned>(k), kThreads, 0, stream>>>(scores_in, m, k, static_cast<int>(r), idx_out, delta_buf,

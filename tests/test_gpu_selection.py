@@ -1,6 +1,7 @@
 """Selection of the proxy update at the edges of its two paths: register counts (1024, 4096, 11264 and
 16384 rows), k on both sides of the limit, long runs of equal scores, scores that share all but a few
-neighbouring or separate bits, and infinite and zero rows."""
+neighbouring or separate bits, rows that are nearly alike (with and without a few far larger ones), large rows
+that all sit in a few threads, and infinite and zero rows."""
 import numpy as np
 import pytest
 import torch
@@ -27,15 +28,27 @@ def _buffer(kind, m, r, g):
         buf[:, 0] = 1.0
         for bit in kind.split()[1:]:
             buf[:, 1] += (g.integers(0, 2, size=m) * 2.0 ** (int(bit) - 52)).astype(np.float32)
+    elif kind in ("alike", "outliers"):            # as the first step of AdamW leaves them; a few far larger
+        buf[:] = 2e-4 * (1.0 + 1e-5 * g.normal(size=(m, r)))
+        if kind == "outliers":
+            buf[g.choice(m, size=5, replace=False)] *= 1e6
+    elif kind == "clustered":                      # all that is large in the first 16 of every 256 rows
+        buf[:, 0] = 0.5
+        top = np.arange(m) % 256 < 16
+        buf[top] = 1.0 + np.abs(g.normal(size=(int(top.sum()), r)))
     elif kind == "infinite":
         buf[:] = g.normal(size=(m, r))
         buf[7, 3] = np.inf
+    elif kind == "half infinite":
+        buf[:] = g.normal(size=(m, r))
+        buf[1::2, 3] = np.inf
     return buf
 
 
 @pytest.mark.parametrize("m,k", [(16, 16), (1024, 8), (1040, 96), (4096, 97), (4112, 32), (11264, 64), (11280, 33), (16384, 96),
                                  (16400, 20)])
-@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "bits 2 0", "bits 40 38 31", "infinite"])
+@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "bits 2 0", "bits 40 38 31", "alike", "outliers",
+                                  "clustered", "infinite", "half infinite"])
 def test_rows_and_order_are_the_oracles(m, k, kind):
     n, r = 64, 16
     g = np.random.default_rng(m + k)
@@ -51,6 +64,6 @@ def test_rows_and_order_are_the_oracles(m, k, kind):
     left = buf.copy()
     left[want] = 0.0
     assert np.array_equal(np_of(layer.delta_buf), left)
-    if kind != "infinite":                         # non-finite values: selection and buffer only
+    if "infinite" not in kind:                      # non-finite values: selection and buffer only
         idx_ref, w_ref, buf_ref = oracle.proxy_update(buf, wcat, m, r, k, True)
         assert np.array_equal(idx_ref, want) and np.array_equal(np_of(layer.wq), w_ref)
