@@ -13,6 +13,7 @@
 // Products with E accumulate in fp32 (matrix cores, slices of the contraction added in order);
 // everything l x l (Gram matrices, Cholesky factors, the eigenproblem) is fp64.
 #include "falqon_internal.h"
+#include "jacobi_rotation.h"
 
 namespace falqon {
 namespace {
@@ -385,17 +386,8 @@ jacobi_eig_kernel(const double* __restrict__ h_in, int l, double* __restrict__ p
         if (a > b) { const int x = a; a = b; b = x; }
         s_pairs[set * l + 2 * t] = a; s_pairs[set * l + 2 * t + 1] = b;
         const double haa = s_h[a * pitch + a], hbb = s_h[b * pitch + b], hab = s_h[a * pitch + b];
-        double c = 1.0, s = 0.0;
-        // an off-diagonal entry below the rounding level of its two diagonal ones is left alone
-        if (fabs(hab) > 1e-300 && fabs(hab) > 1e-16 * sqrt(fabs(haa * hbb))) {
-            atomicAdd(rot, 1);
-            // tangent of the smaller angle: 2 hab / (d +- sqrt(d^2 + 4 hab^2)), d = hbb - haa
-            const double d = hbb - haa, x = 2.0 * hab;
-            const double root = sqrt(d * d + x * x);
-            const double tn = x / (d >= 0.0 ? d + root : d - root);
-            c = rsqrt(1.0 + tn * tn);
-            s = tn * c;
-        }
+        double c, s;
+        if (jacobi_rotation(haa, hbb, hab, c, s)) atomicAdd(rot, 1);
         s_cs[set * l + t] = c; s_cs[set * l + half + t] = s;
     };
     form(0, 0, s_rot);
