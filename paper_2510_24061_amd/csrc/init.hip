@@ -441,12 +441,14 @@ jacobi_eig_kernel(const double* __restrict__ h_in, int l, double* __restrict__ p
         for (int q = t; q < l * l; q += kJacobiThreads) pt[q] = s_p[q];
     for (int i = t; i < l; i += kJacobiThreads) lambda[i] = s_h[i * pitch + i];
     __syncthreads();
-    // rank by eigenvalue, larger first, equal values by smaller index
+    // rank by eigenvalue, larger first, equal values by smaller index.  A NaN (a matrix that is not finite) ranks
+    // last: the ranks have to be a permutation, since the entries of `order` are used as indices.
+    auto value = [&](int i) { const double x = s_h[i * pitch + i]; return x == x ? x : -HUGE_VAL; };
     for (int i = t; i < l; i += kJacobiThreads) {
-        const double li = s_h[i * pitch + i];
+        const double li = value(i);
         int rank = 0;
         for (int j = 0; j < l; ++j) {
-            const double lj = s_h[j * pitch + j];
+            const double lj = value(j);
             rank += (lj > li || (lj == li && j < i)) ? 1 : 0;
         }
         order[rank] = i;

@@ -131,3 +131,23 @@ def test_matrix_of_lower_rank_than_asked_for(rank):
     assert np.all(np.isfinite(a)) and np.all(np.isfinite(sig))
     sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)
     assert np.max(np.abs(sig - sv[:16])) <= 1e-4 * max(sv[0], 1e-30)
+
+
+@pytest.mark.parametrize("r", [16, 96])                                   # eigenvectors in the LDS, and in memory
+def test_matrix_that_is_not_finite_leaves_the_next_one_alone(r):
+    """What comes out for it is unspecified; no index is formed from it, and the same workspace serves the next matrix."""
+    g = np.random.default_rng(r)
+    m, n = 200, 320
+    e = g.normal(size=(m, n)).astype(np.float32)
+    bad = e.copy()
+    bad[3, 5], bad[7, 11] = np.nan, np.inf
+    omega = torch.randn(r + 8, n, generator=torch.Generator().manual_seed(r)).cuda()
+    a, sig = torch.empty(r, n, device="cuda"), torch.empty(r, device="cuda")
+    ws = torch.full((fq.svd_workspace_bytes(m, n, r),), 0x7f, dtype=torch.uint8, device="cuda")
+    fq.svd_right_factor(torch.from_numpy(bad).cuda(), r, omega, 1, a, sig, ws)
+    torch.cuda.synchronize()
+    fq.svd_right_factor(torch.from_numpy(e).cuda(), r, omega, 4, a, sig, ws)
+    torch.cuda.synchronize()
+    sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)
+    sig = np_of(sig).astype(np.float64)
+    assert np.all(sig <= sv[:r] * (1 + 1e-4)) and np.sum(sig ** 2) >= 0.9 * np.sum(sv[:r] ** 2)
