@@ -192,7 +192,8 @@ quantize_one_kernel(const T* __restrict__ x, int n_vecs, int64_t vecs_per_row, i
     }
     float m = 0.0f;
     constexpr int B = 4;                                             // vectors in flight per thread
-    for (int v0 = threadIdx.x; v0 < n_vecs; v0 += B * kOneThreads) {
+    // (a given scale needs no maximum unless it is asked for)
+    for (int v0 = scale_in && !amax_out ? n_vecs : static_cast<int>(threadIdx.x); v0 < n_vecs; v0 += B * kOneThreads) {
         float f[B][kVec];
 #pragma unroll
         for (int b = 0; b < B; ++b) {

@@ -184,3 +184,8 @@ def test_one_launch_and_two_launches_match_the_oracle(fmt, dtype, rows, cols):
     q_ref, s_ref, _ = oracle.quantize(x.float().numpy(), fmt)
     assert np.array_equal(np_of(q)[:, :cols], q_ref) and not np_of(q)[:, cols:].any()
     assert np.float32(s.item()).tobytes() == s_ref.tobytes()
+    given = torch.full((1,), 3.7, device="cuda")
+    fq.quantize(wg[:, :cols], fmt, q[:, :cols], s, ws, scale_in=given)     # a scale, and no maximum asked for
+    q_ref, _, _ = oracle.quantize(x.float().numpy(), fmt, scale_in=np.float32(3.7))
+    assert np.array_equal(np_of(q)[:, :cols], q_ref) and not np_of(q)[:, cols:].any()
+    assert s.item() == given.item()
