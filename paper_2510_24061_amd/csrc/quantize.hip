@@ -165,11 +165,14 @@ scale_cast_kernel(const T* __restrict__ x, int64_t n_vecs, int64_t vecs_per_row,
 
 // Both passes in one launch for small tensors: every workgroup takes the maximum of the whole tensor itself
 // (it is order free, so all of them and the two-launch form agree to the bit) and casts its share, one vector
-// per thread.  The last side_blocks workgroups cast the side tensor.  A launch costs the host about 5 us and
-// the device 3; reading 512 KB through one CU's 64 B/clk takes 3.4 us, so that is the limit (kOneLaunchBytes).
-// 256 x 512 bf16: 5.8 us on the device against 3.0 + 3.5 and a launch; a step of 256 x 512 x 512 48.3 -> 41.7 us.
+// per thread.  The last side_blocks workgroups cast the side tensor.  Bound by reading the tensor through one CU
+// (fp32 lanes read 64 bytes each, four instructions over the same lines, at about half the rate), so the limit
+// is where the device takes as long as for two launches; the host saves one at any size.  us on the device, one launch
+// against two: bf16 16 KB 2.8 (4.2), 128 KB 3.7 (5.2), 256 KB 4.75 (5.3), 512 KB 6.85 (5.4); fp32 16 KB 2.7 (3.9),
+// 128 KB 4.8 (5.3), 192 KB 6.5 (5.4), 512 KB 10.1 (5.6).
 constexpr int kOneThreads = 1024;
-constexpr int64_t kOneLaunchBytes = 512 * 1024;
+template <typename T>
+constexpr int64_t one_launch_bytes() { return (sizeof(T) == 2 ? 256 : 128) * 1024; }
 
 template <typename T, int FMT>
 __global__ void __launch_bounds__(kOneThreads)
@@ -191,7 +194,7 @@ quantize_one_kernel(const T* __restrict__ x, int n_vecs, int64_t vecs_per_row, i
         return;
     }
     float m = 0.0f;
-    constexpr int B = 4;                                             // vectors in flight per thread
+    constexpr int B = sizeof(T) == 2 ? 4 : 2;                        // vectors in flight per thread: 128 KB per workgroup
     // (a given scale needs no maximum unless it is asked for)
     for (int v0 = scale_in && !amax_out ? n_vecs : static_cast<int>(threadIdx.x); v0 < n_vecs; v0 += B * kOneThreads) {
         float f[B][kVec];
@@ -243,7 +246,7 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     }
     const int64_t vecs_per_row = cols / kVec;
     const int64_t n_vecs = rows * vecs_per_row;
-    if (n_vecs * kVec * static_cast<int64_t>(sizeof(T)) <= kOneLaunchBytes && side.count / kVec <= 64 * kOneThreads) {
+    if (n_vecs * kVec * static_cast<int64_t>(sizeof(T)) <= one_launch_bytes<T>() && side.count / kVec <= 64 * kOneThreads) {
         const int64_t main_blocks = n_vecs > 0 ? (n_vecs + kOneThreads - 1) / kOneThreads : 1;
         side_blocks = static_cast<int>((side.count / kVec + kOneThreads - 1) / kOneThreads);
         const dim3 grid(static_cast<unsigned>(main_blocks + side_blocks));

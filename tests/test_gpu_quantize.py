@@ -163,8 +163,10 @@ def test_quantize_row_strided_input_and_output(fmt, dtype, rows, cols, pad_x, pa
 
 
 @pytest.mark.parametrize("fmt", [fq.E4M3, fq.E5M2])
-@pytest.mark.parametrize("dtype,rows,cols", [(torch.bfloat16, 64, 4096), (torch.bfloat16, 64, 4112),    # at and beyond the
-                                             (torch.float32, 32, 4096), (torch.float32, 33, 4096),      # one-launch limit
+@pytest.mark.parametrize("dtype,rows,cols", [(torch.bfloat16, 32, 4096), (torch.bfloat16, 32, 4112),    # at and beyond the
+                                             (torch.float32, 8, 4096), (torch.float32, 8, 4112),        # one-launch limit
+                                             (torch.bfloat16, 64, 4096), (torch.bfloat16, 64, 4112),
+                                             (torch.float32, 32, 4096), (torch.float32, 33, 4096),
                                              (torch.bfloat16, 1, 16384), (torch.bfloat16, 1025, 16)])
 def test_one_launch_and_two_launches_match_the_oracle(fmt, dtype, rows, cols):
     """Dense and with padded rows (values in the padding must not reach the scale), the maximum in the first,
