@@ -551,11 +551,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     for (int j = 0; j < RB; ++j) accx[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     float ride_max = 0.0f;
     v8i sb[RB];
-    const int ride_u = tile_n * NW + wave;
-    constexpr int TB = BM / 16;                                // token blocks of a tile row
-    const int ride_tb = ride_u % TB;
+    const unsigned ride_u = static_cast<unsigned>(tile_n * NW + wave);
+    constexpr unsigned TB = BM / 16;                           // token blocks of a tile row
+    const int ride_tb = static_cast<int>(ride_u % TB);
     const int ride_row = ride_tb * 16 + (lane & 15);           // row of the left tile
-    const int ride_blk0 = (ride_u / TB) * RB;                  // first rank block of the wave
+    const int ride_blk0 = static_cast<int>(ride_u / TB) * RB;                  // first rank block of the wave
     // adapter operand of stage s: lane part of the address, and the wave's rank blocks (a block
     // beyond the rank is clamped to the last one)
     const uint8_t* ride_src = nullptr;
