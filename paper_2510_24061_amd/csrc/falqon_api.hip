@@ -11,20 +11,23 @@ namespace falqon {
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not.  The tiles
-// of a tile row share out the steps of 128 features among themselves, about 1.2 us for each (operands, matrix
-// instructions, 32 KB of stores), and the ordered sum reads one partial per tile row at about 4 TB/s; a launch of
-// its own takes 7 us, reads dy~ again and leaves fewer partials.  (us for product, dB and sum: 512 x 4096 x 4096,
-// r = 64, 1 step per tile, 8 partials: 25 inside, 36 apart; 6479 x 272 x 5328, 14 steps, 51 partials: 79 inside,
-// 64 apart.)
+// of a tile row share out the steps of 128 features among themselves; a step takes 0.5 us and 0.3 us for each 32 ranks
+// (operands, matrix instructions, stores).  The ordered sum reads one partial per tile row, at 5 TB/s or, as a workgroup
+// owns 64 rows of dB, at 87 GB/s each.  A launch of its own reads dy~ again, once for each 64 ranks, leaves fewer
+// partials, lets the product take any tiles, and costs the host another 2 us at the least.  Fitted to 1100 calls
+// (20 sizes, features 64 to 8192, r = 16, 64, 256; the choice by it is 0.7 % slower than the better one on average).
+// us for the call: 512 x 4096 x 4096, r = 64: 33 inside, 39 apart; 4000 x 1024 x 512, r = 256: 78 inside, 56 apart.
 constexpr int64_t kMidDbMax = 64;
 static int mid_db_parts(int64_t T, int64_t n, int64_t m, int64_t r)
 {
     if (!gemm_mid_supported(T, n)) return 0;
-    const int64_t rows = mid_tile_rows(T, n, m), parts = (T + rows - 1) / rows;
-    const int64_t cols = mid_tile_columns(T, n, m), steps = ((m + 127) / 128 + cols - 1) / cols;
-    const double partial_us = static_cast<double>(m) * static_cast<double>(r) * 4.0 / 4e6;
-    const double inside = 1.2 * static_cast<double>(steps) + static_cast<double>(parts) * partial_us;
-    const double apart = 7.0 + static_cast<double>(T) * static_cast<double>(m) / 4e6 + db_splits(T, m) * partial_us;
+    const MidPlan p = plan_mid(T, n, m, true, 0);
+    const int64_t parts = (T + p.rows - 1) / p.rows, steps = ((m + 127) / 128 + p.columns - 1) / p.columns;
+    const double bytes = static_cast<double>(m) * static_cast<double>(r) * 4.0;
+    const double sum_us = bytes / 5.4e6 > static_cast<double>(r) / 340.0 ? bytes / 5.4e6 : static_cast<double>(r) / 340.0;   // of one partial
+    const double inside = p.us + static_cast<double>(steps) * (0.5 + 0.3 * static_cast<double>((r + 31) / 32)) + static_cast<double>(parts) * sum_us;
+    const double apart = product_us(T, n, m, true) + 6.7 + static_cast<double>(T * m * ((r + 63) / 64)) / 3e6 +
+                         db_splits(T, m) * (bytes / 11.7e6 + sum_us);
     return parts <= kMidDbMax && inside < apart ? static_cast<int>(parts) : 0;
 }
 
@@ -182,7 +185,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     if (mid) {
         MidSide side;
         side.rows = wq + m * n; side.r = r;
-        e = launch_gemm_mid(g, side, -1, st);
+        e = launch_gemm_mid(g, side, st);
         return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
     }
     if (merged) {
@@ -275,7 +278,7 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     if (mid_parts) {
         MidSide side;
         side.r = r; side.oaq = w8 + L.oa_codes; side.db_partial = d.partial;
-        e = launch_gemm_mid(g, side, -1, st);
+        e = launch_gemm_mid(g, side, st);
     } else if (pd.use) {
         TailArgs t;
         t.side = w8 + L.oa_codes; t.r = r; t.partial = d.partial; t.splits = 0; t.steps_per_split = 0; t.row_parts = 1;
@@ -432,8 +435,11 @@ falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t*
     hipError_t e;
     if (!b_is_kn) {
         // the shapes are those at which tiles of 256 tokens have room for the side job, whatever rows it runs on
-        const OaTailPlan po = plan_oa_tail(M, n, m, r);
-        if (!po.use || !plan_oa_tail(M, n, m, r, 256).use || (m + r + 255) / 256 == (m + 255) / 256) return FALQON_ERR_SHAPE;
+        // (or the melded call prefers tiles of its own for the adapter)
+        const OaTailPlan p256 = plan_oa_tail(M, n, m, r, 256);
+        if (!p256.use || (m + r + 255) / 256 == (m + 255) / 256) return FALQON_ERR_SHAPE;
+        OaTailPlan po = plan_oa_tail(M, n, m, r);
+        if (!po.use) po = p256;
         t.partial = reinterpret_cast<float*>(w8 + L.oa_partials); t.splits = po.splits; t.steps_per_split = po.steps_per_split;
         t.row_parts = po.row_parts; t.tile_rows = po.tile_rows;
         if (po.splits == 0) {                                    // O_A (bf16) instead of partials

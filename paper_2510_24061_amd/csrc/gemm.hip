@@ -11,8 +11,8 @@
 // Design for CDNA4:
 //   - v_mfma_f32_32x32x64_f8f6f4 (the 8-bit path that runs at the full FP8 rate; the older
 //     32x32x16 FP8 instruction runs at half of it), fp32 accumulators in registers.
-//   - A workgroup owns a BM x BN output tile (256 columns; 256, 192 or 128 rows, chosen by rounds over the
-//     CUs, big_tile_us; smaller products in gemm_mid.hip) and walks K in steps of 128 bytes.  Operand
+//   - A workgroup owns a BM x BN output tile (256 columns; 256, 192 or 128 rows, wide_us; 128x128, two workgroups per
+//     CU, where K is short, tiles128_us; small products in gemm_mid.hip) and walks K in steps of 128 bytes.  Operand
 //     tiles go HBM/L2 -> LDS with global_load_lds (16 B per lane, no register staging) into
 //     rings three (left operand) and two (right operand) stages deep: the fetches of step k+2
 //     are issued while step k is multiplied.
@@ -995,25 +995,65 @@ bool use_big_tiles(int64_t M, int64_t N)
     return ((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
-// Token rows of the large tiles (their columns are always 256), by the time a launch takes: a full round
-// of 256 tiles takes 30, 40 or 52 us (128, 192, 256 rows; K = 4096), a last round that fills only a part p of
-// the CUs 0.65 + 0.3 p of that (fewer busy CUs, higher clock).  Measured at T x 4096 x N, us with 128 / 192 /
-// 256 rows: 2048 x 4096 29.8 / 35.3 / 42.3; 3000 x 4096 53 / 40 / 45; 4096 x 4096 60 / 69 / 52; 4096 x 5120
-// (K = 5120) 115 / 94 / 112; 6000 x 4096 87 / 79 / 90; 4096 x 11008 178 / 154 / 148.
-static double big_tile_us(int64_t M, int64_t N, int rows)
+// Time of a launch on tiles of 128, 192 or 256 rows (their columns are always 256), us: launch + rounds over the CUs x
+// (round + K-steps x step), a last round that fills only a part p of the CUs counting 0.75 to 0.8 + 0.1 p (fewer
+// busy CUs, higher clock).  ride: rank blocks per wave that ride along (0: none); what they add to a step they add in
+// any round, since it is latency: with four, and with two beside 192 and 256 rows, the adapter operands come straight from
+// memory, 16 bytes of a row per lane (256 rows: two blocks spill 19 registers and four 38, too).  Fitted to 16 sizes from
+// 1024 x 4096 to 8192 x 5120 with K from 256 to 8192, within 3 to 4 %; the choice by it is 0.4 % slower than the best
+// on average.
+static double wide_us(int64_t M, int64_t N, int64_t K, int rows, int ride = 0)
 {
+    struct Ride { double launch, step, step_full; };
+    struct Cost { double launch, round, step, part, part_full; Ride ride[3]; };
+    const Cost cost[3] = {{3.9, 4.4, 0.713, 0.81, 0.083, {{0.9, 0.002, 0.062}, {1.1, 0.037, 0.045}, {0.2, 0.874, -0.166}}},
+                          {4.0, 6.2, 0.910, 0.74, 0.174, {{0.4, 0.114, 0.006}, {0.2, 0.363, -0.073}, {0.2, 0.857, -0.184}}},
+                          {4.7, 7.8, 1.175, 0.75, 0.137, {{1.0, -0.013, 0.090}, {1.3, 0.165, 0.022}, {2.6, 0.631, -0.112}}}};
+    const Cost& c = cost[rows / 64 - 2];
     const int64_t tiles = (M + rows - 1) / rows * ((N + 255) / 256), part = tiles % 256;
-    const double rounds = static_cast<double>(tiles / 256) + (part ? 0.65 + 0.3 / 256.0 * static_cast<double>(part) : 0.0);
-    return rounds * (rows == 128 ? 30.0 : rows == 192 ? 40.0 : 52.0);
+    const double steps = static_cast<double>((K + BK - 1) / BK);
+    const double rounds = static_cast<double>(tiles / 256) + (part ? c.part + c.part_full / 256.0 * static_cast<double>(part) : 0.0);
+    const double us = c.launch + rounds * (c.round + steps * c.step);
+    if (!ride) return us;
+    const Ride& d = c.ride[ride == 4 ? 2 : ride - 1];
+    const double busy = tiles < 256 ? static_cast<double>(tiles) / 256.0 : 1.0;
+    return us + d.launch + static_cast<double>((tiles + 255) / 256) * steps * (d.step + d.step_full * busy);
 }
 
-static int big_tile_rows(int64_t M, int64_t N)
+// Time of a launch on 128x128 tiles, two workgroups per CU: one's way in and out hides under the other's steps.
+// (us against the best of the other tiles: 1024 x 4096 K = 128 6.2 and 7.6, K = 2048 12.2 and 13.8, K = 8192 37.9 and
+// 35; 6000 x 800 K = 512 8.4 and 9.3, K = 8192 50.5 and 49.5.)
+static double tiles128_us(int64_t M, int64_t N, int64_t K)
+{
+    const double load = static_cast<double>((M + 127) / 128 * ((N + 127) / 128)) / 256.0;
+    return 5.1 + 0.5 * load + static_cast<double>((K + BK - 1) / BK) * (0.33 + 0.19 * load) * (load > 1.0 ? 1.35 : 1.0);
+}
+
+static int big_tile_rows(int64_t M, int64_t N, int64_t K)
 {
     int best = 256;
     for (int rows = 128; rows < 256; rows += 64)
-        if (big_tile_us(M, N, rows) < big_tile_us(M, N, best)) best = rows;
+        if (wide_us(M, N, K, rows) < wide_us(M, N, K, best)) best = rows;
     return best;
 }
+
+// Tiles of launch_gemm and their time.  From 128 tiles of 256x256 on the wide tiles; below, what takes least.
+struct ProductPlan { enum { WIDE, TILES128, MID } kind; int rows; double us; };
+static ProductPlan plan_product(int64_t M, int64_t N, int64_t K, bool b_is_kn)
+{
+    const int rows = big_tile_rows(M, N, K);
+    ProductPlan p{ProductPlan::WIDE, rows, wide_us(M, N, K, rows)};
+    if (use_big_tiles(M, N)) return p;
+    const double us = tiles128_us(M, N, K);
+    if (us < p.us) p = ProductPlan{ProductPlan::TILES128, 128, us};
+    if (gemm_mid_supported(M, N)) {
+        const double mid = plan_mid(M, N, K, b_is_kn, 0).us;
+        if (mid < p.us) p = ProductPlan{ProductPlan::MID, 0, mid};
+    }
+    return p;
+}
+
+double product_us(int64_t M, int64_t N, int64_t K, bool b_is_kn) { return plan_product(M, N, K, b_is_kn).us; }
 
 hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t stream)
 {
@@ -1035,11 +1075,14 @@ hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_
 // side job: the tile columns of a tile row in sets of two (one where a tile row has a single tile),
 // one K slice per set, at most 8 slices, each a whole number of K-steps and none empty; used when a
 // slice is at most four chunks (beyond that the exposed fetch round trips outweigh the saved round
-// of tiles).
+// of tiles).  Four blocks per wave take long where K is long: not used where the adapter's product in tiles of its own,
+// ahead of the 256x256 ones (r > 64), or the small tiles (below 128 tiles of 256x256) are faster (us: 6000 x 8192 x 2048, r = 256
+// 197 riding on 128 rows, 117 in tiles of its own; 5000 x 8192 x 1024, r = 128 101 riding, 73 on small tiles).
 OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_rows)
 {
     OaTailPlan p{false, 0, 0, 1, 256};
-    if (gemm_mid_supported(T, m) || (only_rows && !use_big_tiles(T, m))) return p;
+    const bool big = use_big_tiles(T, m);
+    if (gemm_mid_supported(T, m) || (only_rows && !big)) return p;
     const int tiles_n = static_cast<int>((m + 255) / 256);
     const int KT = static_cast<int>((n + BK - 1) / BK);
     const int rank_blocks = static_cast<int>((r + 15) / 16);
@@ -1049,11 +1092,8 @@ OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_row
             // wave u of a tile row takes one of its rows / 16 token blocks and rb rank blocks: the
             // 4 tiles_n waves must reach every token block for every group of rb rank blocks
             if (4 * tiles_n < rows / 16 * ((rank_blocks + rb - 1) / rb)) continue;
-            // Riding along costs 4 .. 10 %, and 30 % and more with four rank blocks per wave (r = 256 at
-            // 4096 x 4096 x 4096: 66.5 us with 128 rows, 69.2 with 256, where the operands of four blocks
-            // do not fit the registers beside the tile's).
-            const double us = big_tile_us(T, m, rows) * (rb == 4 ? 1.3 : rows == 192 ? 1.1 : rb == 2 ? 1.1 : 1.05);
-            if (p.use && us >= best_us) break;
+            const double us = wide_us(T, m, n, rows, rb);
+            if (p.use && us >= 1.03 * best_us) break;                     // (larger tiles move less: they win a draw)
             best_us = us;
             p.use = true;
             p.splits = 0;
@@ -1063,8 +1103,18 @@ OaTailPlan plan_oa_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_row
             break;
         }
     }
+    if (p.use && !only_rows) {
+        if (!big) {
+            p.use = best_us <= plan_mid(T, m, n, false, r).us;
+        } else if (p.steps_per_split == 4 && r > 64) {
+            const int splits = oa_splits(T, r);
+            const double rank_tiles = static_cast<double>((T + 127) / 128 * ((r + 127) / 128));
+            p.use = best_us <= wide_us(T, m, n, 256) + 8.0 + static_cast<double>(splits * T * r) / 3.4e5 + rank_tiles * KT / 256.0;
+        }
+        return p;
+    }
     if (p.use) return p;
-    if (r > 64 || !use_big_tiles(T, m)) return p;
+    if (r > 64 || !big) return p;
     p.row_parts = tiles_n >= 2 ? 2 : 1;
     int s0 = tiles_n / p.row_parts < 8 ? tiles_n / p.row_parts : 8;
     if (s0 > KT) s0 = KT;
@@ -1081,7 +1131,7 @@ DbTailPlan plan_db_tail(int64_t T, int64_t n, int64_t m, int64_t r, int only_row
     DbTailPlan p{false, 0, 256};
     if (gemm_mid_supported(T, n) || (only_rows && !use_big_tiles(T, n))) return p;
     const int chunks = static_cast<int>((r + 63) / 64);
-    for (int rows = only_rows ? only_rows : big_tile_rows(T, n); rows <= 256; rows += 64) {   // the best one, else larger groups
+    for (int rows = only_rows ? only_rows : big_tile_rows(T, n, m); rows <= 256; rows += 64) {   // the best one, else larger groups
         const int tiles_m = static_cast<int>((T + rows - 1) / rows), tiles_n = static_cast<int>((n + 255) / 256);
         p.groups = (tiles_m + kDbTailGroupRows - 1) / kDbTailGroupRows;
         const int F = static_cast<int>((m + 127) / 128);
@@ -1150,27 +1200,16 @@ hipError_t launch_gemm_dx_db_pair(const GemmArgs& g, const DbArgs& d, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_tiles(const GemmArgs& g, hipStream_t stream)
-{
-    const int rows = big_tile_rows(g.M, g.N);
-    if (rows == 128) return launch_cfg<2, 2, 2, 4>(g, stream);
-    if (rows == 192) return launch_cfg<2, 2, 3, 4>(g, stream);
-    return launch_cfg<2, 2, 4, 4>(g, stream);
-}
-
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    if (g.splits > 1) {                                                // split K: few output columns, 128x128 tiles
-        if (g.b_is_kn || g.a_fmt != 1) return hipErrorInvalidValue;    // (the inner gradient of A is the one such product)
-        const int tiles_m = static_cast<int>((g.M + 127) / 128), tiles_n = static_cast<int>((g.N + 127) / 128);
-        const int chunk = (tiles_m * tiles_n + 7) / 8;
-        gemm_fp8_kernel<2, 2, 2, 2, false, 1><<<dim3(static_cast<unsigned>(8 * chunk), static_cast<unsigned>(g.splits)), dim3(256), 0,
-                                                stream>>>(g, tiles_m, tiles_n, chunk);
-        return hipGetLastError();
-    }
-    if (gemm_mid_supported(g.M, g.N)) return launch_gemm_mid(g, MidSide{}, -1, stream);
-    return launch_gemm_tiles(g, stream);
+    if (g.splits > 1) return launch_cfg<2, 2, 2, 2>(g, stream);          // split K: few output columns
+    const ProductPlan p = plan_product(g.M, g.N, g.K, g.b_is_kn != 0);
+    if (p.kind == ProductPlan::MID) return launch_gemm_mid(g, MidSide{}, stream);
+    if (p.kind == ProductPlan::TILES128) return launch_cfg<2, 2, 2, 2>(g, stream);
+    if (p.rows == 128) return launch_cfg<2, 2, 2, 4>(g, stream);
+    if (p.rows == 192) return launch_cfg<2, 2, 3, 4>(g, stream);
+    return launch_cfg<2, 2, 4, 4>(g, stream);
 }
 
 }  // namespace falqon

@@ -5,7 +5,8 @@
 namespace falqon {
 
 bool use_big_tiles(int64_t M, int64_t N);    // gemm.hip: the 256x256 tiles fill the chip
-hipError_t launch_gemm_tiles(const GemmArgs& g, hipStream_t stream);   // gemm.hip: the large-tile family whatever the size
+// gemm.hip: time of launch_gemm for this product, by the cost rules of both families
+double product_us(int64_t M, int64_t N, int64_t K, bool b_is_kn);
 
 // What a launch does for the adapter besides the product g.
 struct MidSide {
@@ -15,11 +16,10 @@ struct MidSide {
     const uint8_t* oaq = nullptr;    // input gradient (E5M2 left operand): O_A codes [M][r]; partial sums of
     float* db_partial = nullptr;     // dy~^T O_A~ go to db_partial[tile row][K][r], not rescaled
 };
-constexpr int kMidConfigs = 4;
-bool gemm_mid_supported(int64_t M, int64_t N);                   // products of this size run on the small tiles
-int mid_tile_rows(int64_t M, int64_t N, int64_t K);              // tokens per tile row of the configuration chosen by size
-int64_t mid_tile_columns(int64_t M, int64_t N, int64_t K);       // tile columns of it
-// cfg: tile configuration, -1 to choose by size
-hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, int cfg, hipStream_t stream);
+bool gemm_mid_supported(int64_t M, int64_t N);                   // the 128x128 tiles of a product of this size all find a CU
+// Tile configuration of a product, the one of least time; r: rank of the adapter whose O_A it forms along (0: none).
+struct MidPlan { int config; int rows; int64_t columns; double us; };   // tokens per tile row, tile columns
+MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_is_kn, int64_t r);
+hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, hipStream_t stream);
 
 }  // namespace falqon

@@ -515,6 +515,15 @@ gemm_mid_kernel(const MidArgs t)
     mid_tile<MB, NB, S, B_KN, A_FMT, false, DB>(t, tile_m, tile_n, tile_n >= t.tiles_n, lds);
 }
 
+// Adapter columns of their own cost nothing while they make no further round over the CUs; a step of a tile that
+// carries them along takes 1.7 times as long.  Returns the extra tile columns, 0: they ride.
+int own_columns(int64_t tiles_m, int64_t tiles_n, int64_t r, int bn)
+{
+    const int64_t own = (r + bn - 1) / bn;
+    const bool fits = (tiles_m * (tiles_n + own) - 1) / kMidCus == (tiles_m * tiles_n - 1) / kMidCus;
+    return tiles_n < (r + 31) / 32 || fits ? static_cast<int>(own) : 0;
+}
+
 template <int MB, int NB, int S_FWD, int S_KN, int S_DB>
 hipError_t launch_cfg(MidArgs t, hipStream_t stream)
 {
@@ -523,11 +532,8 @@ hipError_t launch_cfg(MidArgs t, hipStream_t stream)
     t.tiles_n = static_cast<int>((t.g.N + BN - 1) / BN);
     t.tiles_a = t.ride = 0;
     if (t.side) {
-        const int own = static_cast<int>((t.r + BN - 1) / BN), blocks = static_cast<int>((t.r + 31) / 32);
-        // Adapter columns of their own cost nothing while they find idle CUs; a tile that carries them
-        // along takes a quarter more matrix work.
-        if (t.tiles_n < blocks || t.tiles_m * (t.tiles_n + own) <= kMidCus) t.tiles_a = own;
-        else t.ride = blocks;
+        t.tiles_a = own_columns(t.tiles_m, t.tiles_n, t.r, BN);
+        if (!t.tiles_a) t.ride = static_cast<int>((t.r + 31) / 32);
     }
     t.chunk = (t.tiles_m * (t.tiles_n + t.tiles_a) + 7) / 8;
     const dim3 grid(static_cast<unsigned>(8 * t.chunk)), block(256);
@@ -544,50 +550,46 @@ hipError_t launch_cfg(MidArgs t, hipStream_t stream)
 
 }  // namespace
 
-// Small tiles while all of them (128x128 at the largest) find a CU; beyond that tiles of 128 x 256 and up
-// are faster (us with dB or O_A: 1024 x 4096 x 4096 forward 27.7 here, 27.6 there, input gradient 24.6 and
-// 30.1; 1500 x 4096 x 4096 43 and 30, 44 and 32).
 bool gemm_mid_supported(int64_t M, int64_t N)
 {
     return !use_big_tiles(M, N) && ((M + 127) / 128) * ((N + 127) / 128) <= kMidCus;
 }
 
-// Tile configuration by size: the least of rounds over the CUs x K-steps x time of a step, plus what a
-// launch takes beside its steps (us, measured at full and nearly full rounds, 0.5 us accuracy).  Small tiles
-// win while all of them find a CU (512 x 4096 x 4096: 18.2 with 64x128, 22.4 with 64x64 in two rounds, 20.4
-// with 128x128 on half the chip).
-static int mid_config(int64_t M, int64_t N, int64_t K)
+// us = launch + rounds over the CUs x (round + K-steps x (step + step_full x part of the CUs that are busy)): a
+// workgroup is alone on its CU, so every round pays the way into its rings and out again, and a step takes longer
+// the more CUs draw on the memory.  Fitted to products of 20 sizes with K from 64 to 8192 (graphs of 10; the fit is
+// within 5 %, and the choice by it 0.2 % slower than the best of all on average).  Tiles that find room in one
+// round win; 2 to 8 rounds of smaller ones take up to twice as long (1024 x 4096, K = 128: 12.2 us in four rounds of
+// 64x64, 7.7 with 128x128).
+MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_is_kn, int64_t r)
 {
-    struct { int bm, bn; double step, fixed; } const cfg[kMidConfigs] = {
-        {32, 64, 0.30, 3.9}, {64, 64, 0.34, 4.2}, {64, 128, 0.42, 5.0}, {128, 128, 0.58, 6.3}};
-    int best = 0;
-    double best_us = 0.0;
-    for (int c = 0; c < kMidConfigs; ++c) {
-        const int64_t tiles = ((M + cfg[c].bm - 1) / cfg[c].bm) * ((N + cfg[c].bn - 1) / cfg[c].bn);
-        const double us = static_cast<double>((tiles + kMidCus - 1) / kMidCus) * ((K + BK - 1) / BK) * cfg[c].step + cfg[c].fixed;
-        if (c == 0 || us < best_us) { best = c; best_us = us; }
+    struct Cost { double launch, round, step, step_full; };
+    struct { int bm, bn; Cost nk, kn; } const cfg[] = {
+        {32, 64, {2.2, 2.1, 0.114, 0.041}, {2.2, 2.15, 0.143, 0.105}},
+        {64, 64, {2.1, 2.4, 0.138, 0.071}, {2.1, 2.5, 0.178, 0.134}},
+        {64, 128, {2.0, 3.3, 0.198, 0.103}, {1.8, 3.6, 0.253, 0.104}},
+        {128, 128, {2.9, 4.0, 0.247, 0.241}, {2.4, 4.7, 0.320, 0.226}}};
+    const double steps = static_cast<double>((K + BK - 1) / BK);
+    MidPlan best{0, 0, 0, 0.0};
+    for (int c = 0; c < 4; ++c) {
+        const Cost& k = b_is_kn ? cfg[c].kn : cfg[c].nk;
+        const int64_t tm = (M + cfg[c].bm - 1) / cfg[c].bm, tn = (N + cfg[c].bn - 1) / cfg[c].bn;
+        const int own = r ? own_columns(tm, tn, r, cfg[c].bn) : 0;
+        const int64_t tiles = tm * (tn + own);
+        const double busy = tiles < kMidCus ? static_cast<double>(tiles) / kMidCus : 1.0;
+        const double us = k.launch + (r && !own ? 1.0 : 0.0) +
+                          static_cast<double>((tiles + kMidCus - 1) / kMidCus) *
+                              (k.round + steps * (r && !own ? 1.7 : 1.0) * (k.step + k.step_full * busy));
+        if (c == 0 || us < best.us) best = MidPlan{c, cfg[c].bm, tn, us};
     }
     return best;
 }
 
-int mid_tile_rows(int64_t M, int64_t N, int64_t K)
-{
-    const int rows[kMidConfigs] = {32, 64, 64, 128};
-    return rows[mid_config(M, N, K)];
-}
-
-int64_t mid_tile_columns(int64_t M, int64_t N, int64_t K)
-{
-    const int cols[kMidConfigs] = {64, 64, 128, 128};
-    const int64_t c = cols[mid_config(M, N, K)];
-    return (N + c - 1) / c;
-}
-
-hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, int cfg, hipStream_t stream)
+hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, hipStream_t stream)
 {
     MidArgs t;
     t.g = g; t.side = side.rows; t.r = side.r; t.oaq = side.oaq; t.db_partial = side.db_partial;
-    switch (cfg < 0 ? mid_config(g.M, g.N, g.K) : cfg) {
+    switch (plan_mid(g.M, g.N, g.K, g.b_is_kn != 0, side.rows ? side.r : 0).config) {
         case 0: return launch_cfg<1, 1, 8, 8, 8>(t, stream);
         case 1: return launch_cfg<2, 1, 7, 8, 8>(t, stream);
         case 2: return launch_cfg<2, 2, 5, 6, 6>(t, stream);

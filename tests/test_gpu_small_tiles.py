@@ -1,10 +1,13 @@
 """The products on tiles smaller than 256x256: every tile configuration, with the adapter
 product as tile columns of its own or riding on the backbone's, and the adapter gradient formed inside the
 input-gradient tiles, on exact-integer data (fp32 outputs bit for bit)."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2510_24061_amd as fq
+from gpu_common import np_of
 from test_gpu_layer import _exact_integer_layer
 
 pytestmark = pytest.mark.gpu
@@ -26,6 +29,9 @@ pytestmark = pytest.mark.gpu
     (1000, 4112, 400, 16),        # 128 x 128 tiles in the input gradient
     (1500, 272, 4112, 128),       # more than one round of tiles
     (9000, 272, 144, 256),        # the adapter gradient in a launch of its own
+    (4000, 1024, 512, 256),       # ... beside an input gradient on 128 x 128 tiles, two per CU
+    (5000, 144, 1008, 16),        # adapter columns inside the last column of 128 x 128 tiles
+    (5000, 4112, 1024, 112),      # two rounds of 128 x 128 tiles, adapter columns of their own inside the second
 ])
 def test_exact_integer_layer_is_bit_exact(T, n, m, r):
     _exact_integer_layer(T, n, m, r)
@@ -75,3 +81,25 @@ def test_backward_also_works_in_the_smallest_workspace(T, n, m, r):
     layer.backward(dy, accumulate=False)
     assert torch.equal(layer.dx, dx)
     assert float((layer.d_b - d_b).norm() / d_b.norm()) < 1e-4      # fp32 matrix-core sums: 2e-5 of the result
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (40, 64, 144),                # 32 x 64 tiles
+    (500, 1040, 272),             # 64 x 64
+    (500, 2064, 272),             # 64 x 128
+    (3900, 1008, 144),            # 128 x 128, two workgroups per CU: short K, no room in one round for smaller tiles
+    (5990, 784, 400),             # ... more than 256 of them
+    (2600, 1040, 6160),           # 128 x 128 on a deep ring: long K
+    (2600, 1552, 6160),           # 128 x 256: long K and more than 256 tiles of 128 x 128
+])
+@pytest.mark.parametrize("kn", [False, True])
+@pytest.mark.parametrize("fmt", [fq.E4M3, fq.E5M2])
+def test_plain_product_of_integers_is_exact_on_every_kind_of_tile(M, N, K, kn, fmt):
+    g = np.random.default_rng(M + N)
+    ai, bi = (g.integers(-v, v + 1, size=s).astype(np.float32) for v, s in ((4, (M, K)), (8, (K, N) if kn else (N, K))))
+    c = torch.empty(M, N, dtype=torch.float32, device="cuda")
+    scale = [torch.tensor([v], device="cuda") for v in (2.0, 0.5)]
+    fq.fp8_gemm(torch.from_numpy(oracle.fp8_encode(ai, fmt)).cuda(), fmt, torch.from_numpy(oracle.fp8_encode(bi, fq.E4M3)).cuda(),
+                kn, *scale, c)
+    want = ai.astype(np.float64) @ (bi if kn else bi.T).astype(np.float64)
+    assert np.max(np.abs(want)) < 2.0 ** 24 and np.array_equal(np_of(c).astype(np.float64), want)
