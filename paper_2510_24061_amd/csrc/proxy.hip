@@ -84,7 +84,7 @@ __device__ __forceinline__ uint32_t encode4_e4m3(const double (&acc)[4])
 // by bisection on its own, two maxima per lane).  The rows that reach tau, a few dozen, contain the k selected
 // ones; they are ranked pairwise.
 //
-// tau has 12 bits from the first one in which the maxima differ: the exponent and some bits behind it where the
+// tau has 12 bits of the range that the maxima span: the exponent and some bits behind it where the
 // rows have learned at different rates, bits far behind it where they are alike (the first step of AdamW moves
 // every element by about the learning rate).  If far more rows than are looked for reach tau, 12 more bits,
 // until tau is the k-th maximum itself; what is left then are equal scores (an untouched buffer), and the row is
@@ -95,67 +95,53 @@ __device__ __forceinline__ uint32_t encode4_e4m3(const double (&acc)[4])
 // workgroup repeats the comparisons; nothing is exchanged.  Whole update in us (graph of 20, n = 256), against
 // ranking 16 rows per workgroup or, beyond 4096 rows, whole blocks:
 //                       rows learned at different rates   after the first AdamW step   untouched
-//   512 x 16, k = 8              8.5 (9.0)                        8.5 (9.0)              8.0 (9.4)
-//   4096 x 64, k = 32           12.0 (15.1)                      12.0 (15.0)            10.5 (15.2)
-//   11008 x 64, k = 32          14.6 (25.7)                      14.8 (25.7)            12.5 (132)
-// Slower than before only where many of few rows are equal and reach tau: 256 of 512 rows 10.7 (9.4), a third of
-// 2000 rows 12.8 (12.3).
+//   512 x 16, k = 8              8.5 (9.1)                        8.5 (9.1)              8.4 (9.4)
+//   4096 x 64, k = 32           12.1 (15.0)                      12.1 (14.9)            10.9 (15.2)
+//   11008 x 64, k = 32          14.8 (25.6)                      14.9 (25.6)            12.9 (132)
+// Slower than before only where many of few rows are equal and reach tau: 256 of 512 rows 10.9 (9.4), a third of
+// 2000 rows 13.2 (12.4).
 // (Requantizing in the same launch was built too: the workgroups that share a row have to agree on when
 // its buffer row may be cleared, and their device-scope atomics cost more, 6 us, than the launch saved.)
 constexpr int kSelectGroups = 128, kSelectMaxK = 96, kSelectCands = 2 * kSelectMaxK + 32, kSelectMaxRows = 64 * kThreads;
 constexpr int kTauBits = 12;                                         // bits of tau found at a time
 constexpr int kTauRounds = 6;                                        // that many cover a key
 
-// bitwise or over the wave, the same in every lane
-__device__ __forceinline__ uint32_t wave_or(uint32_t x)
+// a combination over the wave that leaves `none` unchanged, the same in every lane
+template <typename F>
+__device__ __forceinline__ uint32_t wave_combine(uint32_t x, uint32_t none, F f)
 {
-    const auto v = [](uint32_t u) { return static_cast<int>(u); };
-    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8: rows of 16 lanes
-    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x112, 0xf, 0xf, true);
-    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x114, 0xf, 0xf, true);
-    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x118, 0xf, 0xf, true);
-    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x142, 0xa, 0xf, true);   // row_bcast 15, 31: across rows
-    x |= __builtin_amdgcn_update_dpp(0, v(x), 0x143, 0xc, 0xf, true);
-    return static_cast<uint32_t>(__builtin_amdgcn_readlane(v(x), 63));
+    const int o = static_cast<int>(none);
+    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x111, 0xf, 0xf, false)));   // row_shr 1, 2,
+    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x112, 0xf, 0xf, false)));   // 4, 8: rows of
+    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x114, 0xf, 0xf, false)));   // 16 lanes
+    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x118, 0xf, 0xf, false)));
+    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x142, 0xa, 0xf, false)));   // row_bcast 15,
+    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x143, 0xc, 0xf, false)));   // 31: across rows
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
 }
 
-__device__ __forceinline__ uint64_t read_lane64(uint64_t x, int lane)
+// kTauBits more bits of the k-th largest of 128 maxima, two per lane (a, b): it lies in [tau, tau + 2^open), and so it
+// does afterwards; open = 0: it is tau.
+__device__ __forceinline__ void extend_tau(uint64_t a, uint64_t b, int k, uint64_t& tau, int& open)
 {
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x)), lane);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x >> 32)), lane);
-    return static_cast<uint64_t>(hi) << 32 | lo;
-}
-
-// The next kTauBits bits of the k-th largest of 128 maxima, two per lane (a, b).  tau: its bits outside `open`,
-// zeros inside; open: the low bits not yet known.
-template <bool FIRST>                                                // nothing is known yet
-__device__ __forceinline__ void extend_tau(uint64_t a, uint64_t b, int k, uint64_t& tau, uint64_t& open)
-{
-    bool in_a = true, in_b = true;                                   // maxima that share what is known, and one of them
-    uint64_t ref;
-    if constexpr (FIRST) {
-        ref = read_lane64(a, 0);
-    } else {
-        in_a = ((a ^ tau) & ~open) == 0; in_b = ((b ^ tau) & ~open) == 0;
-        const uint64_t mask_a = __ballot(in_a), mask_b = __ballot(in_b);
-        ref = mask_a ? read_lane64(a, __builtin_ctzll(mask_a)) : mask_b ? read_lane64(b, __builtin_ctzll(mask_b)) : tau;
-    }
-    const uint64_t diff = (in_a ? a ^ ref : 0) | (in_b ? b ^ ref : 0);
-    const uint64_t all = static_cast<uint64_t>(wave_or(static_cast<uint32_t>(diff >> 32))) << 32 | wave_or(static_cast<uint32_t>(diff));
-    if (all == 0) { tau = ref; open = 0; return; }
-    const int top = 63 - __builtin_clzll(all), low = top < kTauBits ? 0 : top - (kTauBits - 1);
-    const uint64_t below_top = (uint64_t(2) << top) - 1;             // (keys have no sign bit: top <= 62)
-    // the window [low, top] of each maximum; those above or below what is known count always or never
-    const uint32_t wa = in_a ? static_cast<uint32_t>((a & below_top) >> low) : a > tau ? ~0u : 0u;
-    const uint32_t wb = in_b ? static_cast<uint32_t>((b & below_top) >> low) : b > tau ? ~0u : 0u;
+    const uint64_t da = a - tau, db = b - tau;
+    const bool in_a = a >= tau && (open > 63 || da >> open == 0), in_b = b >= tau && (open > 63 || db >> open == 0);
+    const uint64_t diff = (in_a ? da : 0) | (in_b ? db : 0);
+    const auto either = [](uint32_t x, uint32_t y) { return x | y; };
+    const uint64_t all = static_cast<uint64_t>(wave_combine(static_cast<uint32_t>(diff >> 32), 0, either)) << 32 |
+                         wave_combine(static_cast<uint32_t>(diff), 0, either);
+    const int bits = all ? 64 - __builtin_clzll(all) : 0;
+    open = bits > kTauBits ? bits - kTauBits : 0;
+    // the leading bits of each distance from tau; maxima above the interval always count, those below never
+    const uint32_t wa = in_a ? static_cast<uint32_t>(da >> open) : a > tau ? ~0u : 0u;
+    const uint32_t wb = in_b ? static_cast<uint32_t>(db >> open) : b > tau ? ~0u : 0u;
     uint32_t w = 0;
 #pragma unroll
     for (int bit = kTauBits - 1; bit >= 0; --bit) {
         const uint32_t trial = w | (1u << bit);
         if (__popcll(__ballot(wa >= trial)) + __popcll(__ballot(wb >= trial)) >= k) w = trial;
     }
-    tau = (ref & ~below_top) | static_cast<uint64_t>(w) << low;
-    open = (uint64_t(1) << low) - 1;
+    tau += static_cast<uint64_t>(w) << open;
 }
 
 template <int U>                                                     // U keys per thread: m <= 256 U
@@ -271,15 +257,18 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
         if (eq && before == left) s_row = u * kThreads + t;
     };
 
-    uint64_t tau = 0, open = ~uint64_t(0);
-    int nc;
+    uint64_t tau;
+    int nc, open = 64;
     {
         const uint64_t a = s_max[lane], b = s_max[lane + 64];
-        extend_tau<true>(a, b, static_cast<int>(k), tau, open);
-        nc = tau ? list_rows(tau, std::false_type{}, 0) : limit + 1;                // (every row reaches 0)
+        const uint32_t ha = static_cast<uint32_t>(a >> 32), hb = static_cast<uint32_t>(b >> 32);
+        const auto smaller = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
+        tau = static_cast<uint64_t>(wave_combine(smaller(ha, hb), ~0u, smaller)) << 32;   // no maximum is below it
+        extend_tau(a, b, static_cast<int>(k), tau, open);
+        nc = tau ? list_rows(tau, std::false_type{}, 0) : limit + 1;     // (every row reaches 0)
         for (int round = 1; nc > limit && open != 0 && round < kTauRounds; ++round) {
             const uint64_t before = tau;
-            extend_tau<false>(a, b, static_cast<int>(k), tau, open);
+            extend_tau(a, b, static_cast<int>(k), tau, open);
             if (tau != before) nc = list_rows(tau, std::false_type{}, round);
         }
     }
