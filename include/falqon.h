@@ -222,10 +222,11 @@ falqon_status falqon_proxy_update_static(float* delta_buf, uint8_t* wq, int64_t 
  *   b_is_kn = 1 (melded backward; a = dy~ E5M2 [T, m], b = backbone rows [m, n]):
  *       side = O_A cast to E4M3 [T, r]; partials of dy~^T O_A~ over groups of tokens
  *   side_ws  scratch of at least falqon_workspace_bytes(T, n, m, r) bytes
- * Only for shapes at which the melded calls use this launch (large products, the adapter columns
+ * Only for shapes at which the melded calls can use this launch (large products, the adapter columns
  * not inside the backbone's last tile column, r <= 64 unless the forward product is finished in
- * the launch); FALQON_ERR_SHAPE otherwise.  What side_ws holds afterwards is internal; the entry
- * exists so that this launch can be timed on its own.
+ * the launch; a melded forward with r > 64 and few tile columns may prefer tiles of its own for the adapter);
+ * FALQON_ERR_SHAPE otherwise.  What side_ws holds afterwards is internal; the entry exists so that this
+ * launch can be timed on its own.
  */
 falqon_status falqon_fp8_gemm(const uint8_t* a, falqon_fmt a_fmt, const uint8_t* b, int b_is_kn,
                               int64_t M, int64_t N, int64_t K, const float* s_a, const float* s_b,

@@ -43,7 +43,8 @@ __device__ __forceinline__ float buffer_step(float buf, float lr, float g)
 // A workgroup owns 64 rows of dB, a thread U runs of four columns at a time.  With `score` set (only
 // together with delta_buf) it keeps the new rows in LDS and leaves their L1 norms and the largest one
 // (row_scores.h).  Bound by latency: 1024 threads, so that all of a workgroup's loads are in flight at once
-// up to rank 64 (a quarter of the threads took four round trips, 7.0 against 4.4 us at 4096 x 64 x 8 splits).
+// up to rank 64 (a quarter of the threads took four round trips: 9.5 against 6.5 us at 4096 x 64 with 8 partials and
+// scores, 24.9 against 17.4 at r = 256, kernel trace).
 constexpr int kReduceThreads = 1024;
 
 template <int U>

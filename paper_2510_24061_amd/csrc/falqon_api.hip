@@ -50,8 +50,8 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least)
     w.scores = off;        off = align_up(off + sizeof(double) * static_cast<size_t>(m + (m + 63) / 64), 256);
     w.delta_sel = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r), 256);
     // The partials of O_A follow (sizes of [m, r] floats are multiples of 1 KB, so without a gap).  No call uses
-    // them beside more partials of dB than the least layout has, and a forward and a backward call cannot share a
-    // workspace at one time anyway (amax_partials): what dB needs beyond its own room lies there first.
+    // them beside more partials of dB than the least layout has, and calls that share a workspace are ordered by the
+    // caller: what dB needs beyond its own room lies there first.
     const size_t db_one = sizeof(float) * static_cast<size_t>(m) * static_cast<size_t>(r);
     const size_t oa_bytes = sizeof(float) * static_cast<size_t>(oa_parts) * static_cast<size_t>(T) * static_cast<size_t>(r);
     size_t db_bytes = db_one * static_cast<size_t>(db_parts);

@@ -9,16 +9,17 @@
 namespace falqon {
 
 // ---- workspace -------------------------------------------------------------------------
-// One layout serves all four calls; the regions never overlap so a forward, a backward
-// and an update of the same layer may share one workspace when run in stream order.
+// One layout serves all calls.  Nothing in it outlives a call, so a forward, a backward and an update of the
+// same layer may share one workspace when run in stream order.  The regions that one call uses do not overlap; the
+// partials of dB may reach into the room of those of O_A, which no call uses beside them.
 constexpr int kMaxAmaxBlocks = 1024;   // per-block partial maxima written by the amax pass
-constexpr int kDbSplitMax = 32;        // upper bound on the token splits of the dB contraction
+constexpr int kDbSplitMax = 32;        // most token splits of dB in launches of its own and beside wide dX tiles
 
 struct WsLayout {
     size_t amax_partials;   // float[kMaxAmaxBlocks]
     size_t scores;          // double[m + ceil(m / 64)]: row scores of the proxy buffer and their block maxima
     size_t delta_sel;       // float[m][r]: buffer rows picked by the proxy update, in rank order
-    size_t db_partials;     // float[splits][m][r]
+    size_t db_partials;     // float[splits][m][r] (up to 64 where small dX tiles leave one per tile row)
     size_t oa_partials;     // float[splits][T][r]
     size_t oa_codes;        // uint8[T][r]: the saved O_A cast to E4M3 for the adapter gradient
     size_t total;
@@ -59,7 +60,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // [N,K], E4M3.  Results are those of launch_gemm(g) and launch_gemm(h).
 hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t stream);
 
-// What every 256x256 backbone tile does for the adapter besides its own tile (gemm.hip).
+// What every backbone tile of 256 columns does for the adapter besides its own tile (gemm.hip).
 //   forward launch:        side = adapter rows A~ [r][K] (row stride g.ldb).
 //                          splits > 0: partial[splits][M][r], rescaled; tile columns in sets of
 //                          row_parts: set s < splits covers K-steps [s * steps_per_split,

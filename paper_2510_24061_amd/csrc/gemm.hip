@@ -52,20 +52,6 @@ __device__ __forceinline__ void dma16_to_lds(const uint8_t* src, uint8_t* dst_wa
     __builtin_amdgcn_global_load_lds(FQ_GLOBAL_PTR(src), FQ_LDS_PTR(dst_wave_uniform), 16, 0, 0);
 }
 
-// 32x32x64 operand of lane `lane` from a K-contiguous tile (128-byte rows, swizzle swz_kc)
-__device__ __forceinline__ v8i read_kc_tile(const uint8_t* tile, int row, int kh, int lane)
-{
-    const int cb = kh * 4 + (lane >> 5) * 2;
-    const int sw = swz_kc(row);
-    const uint8_t* base = tile + row * BK;
-    const v4i lo = *reinterpret_cast<const v4i*>(base + ((cb ^ sw) << 4));
-    const v4i hi = *reinterpret_cast<const v4i*>(base + (((cb + 1) ^ sw) << 4));
-    v8i r;
-    r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
-    r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
-    return r;
-}
-
 // Forward: the tile columns of a tile row are taken in sets of Q (Q = t.row_parts, 1 or 2).  Set s
 // < splits covers K-steps [s * steps_per_split, +steps_per_split); member h of the set multiplies
 // token rows [h * 256 / Q, +256 / Q) of the tile row with the adapter rows over those K-steps and
@@ -239,7 +225,7 @@ __device__ __forceinline__ void db_side_fetch_oa(const TailArgs& t, const DbTail
 
 // Feature step 0 and the first 64 ranks of O_A~ have been issued by the caller, followed by the tile's first
 // stage.  Ranks beyond 64 take a round trip for each further 64 of them, with dy~ kept: at 4096 x 4096 x 4096
-// and r = 256 the launch takes 73.8 us (66.5 at r = 64, same run), 85 with tiles of their own for dB.
+// and r = 256 the launch takes 76.3 us (66.6 at r = 64), 87.1 with tiles of their own for dB (kernel trace).
 template <int BM>
 __device__ __forceinline__ void db_side_run(const TailArgs& t, const GemmArgs& g, const DbTailGeom& q,
                                             uint8_t* lds_dy, uint8_t* lds_oa, int wave, int lane)
@@ -449,18 +435,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     };
 
     // ---- LDS -> matrix-core operands ----------------------------------------------------------
-    // 32x32x64: lane l holds row (l % 32) and the 32 K-bytes [32*(l/32), +32) of the 64-deep slice.
-    auto read_kc = [&](const uint8_t* tile, int row, int kh) -> v8i {
-        const int cb = kh * 4 + (lane >> 5) * 2;
-        const int s = swz_kc(row);
-        const uint8_t* base = tile + row * BK;
-        const v4i lo = *reinterpret_cast<const v4i*>(base + ((cb ^ s) << 4));
-        const v4i hi = *reinterpret_cast<const v4i*>(base + (((cb + 1) ^ s) << 4));
-        v8i r;
-        r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
-        r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
-        return r;
-    };
     // [K][N] tile: ds_read_b64_tr_b8 works on groups of 16 lanes.  Lane s of a group supplies
     // the address of 8 bytes; lane L receives byte (L % 8) of the eight lanes 2q + (L % 16) / 8.
     // Pointing lane s at K-row (s % 16) / 2, column block 8 * (s % 2) therefore returns to
@@ -509,10 +483,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     // a half to land, right-tile fetches a full half-step after the last one is issued.  The
     // barrier is reached with MFMAs still in flight, and no LDS latency is exposed.
     auto read_a = [&](const uint8_t* sA, int mi, int kh) -> v8i {
-        return read_kc(sA, wm * MB * 32 + mi * 32 + (lane & 31), kh);
+        return read_kc_tile(sA, wm * MB * 32 + mi * 32 + (lane & 31), kh, lane);
     };
     auto read_b = [&](const uint8_t* sB, int ni, int kh) -> v8i {
-        if (!B_KN) return read_kc(sB, wn * NB * 32 + ni * 32 + (lane & 31), kh);
+        if (!B_KN) return read_kc_tile(sB, wn * NB * 32 + ni * 32 + (lane & 31), kh, lane);
         return read_kn(sB, wn * NB * 32 + ni * 32, kh);
     };
     constexpr bool RIDE = TAIL == 3 || TAIL == 4 || TAIL == 5;
@@ -999,7 +973,7 @@ bool use_big_tiles(int64_t M, int64_t N)
 // (round + K-steps x step), a last round that fills only a part p of the CUs counting 0.75 to 0.8 + 0.1 p (fewer
 // busy CUs, higher clock).  ride: rank blocks per wave that ride along (0: none); what they add to a step they add in
 // any round, since it is latency: with four, and with two beside 192 and 256 rows, the adapter operands come straight from
-// memory, 16 bytes of a row per lane (256 rows: two blocks spill 19 registers and four 38, too).  Fitted to 16 sizes from
+// memory, 16 bytes of a row per lane (256 rows: two blocks spill 18 registers and four 37, too).  Fitted to 16 sizes from
 // 1024 x 4096 to 8192 x 5120 with K from 256 to 8192, within 3 to 4 %; the choice by it is 0.4 % slower than the best
 // on average.
 static double wide_us(int64_t M, int64_t N, int64_t K, int rows, int ride = 0)

@@ -1,5 +1,5 @@
-// Device helpers shared by the two families of FP8 product kernels (gemm.hip: tiles of 256 and more
-// tokens; gemm_mid.hip: small tiles on deep rings).
+// Device helpers shared by the two families of FP8 product kernels (gemm.hip: tiles of 128 to 256 tokens on rings two and
+// three stages deep; gemm_mid.hip: tiles of 32 to 128 tokens on deep rings).
 #pragma once
 #include "falqon_internal.h"
 
@@ -27,6 +27,21 @@ __device__ __forceinline__ int swz_kc(int row) { return ((row >> 1) ^ ((row & 1)
 // Swizzle of a [K][N] tile with CH chunks of 16 B per K-row.
 template <int CH>
 __device__ __forceinline__ int swz_kn(int krow) { return CH >= 16 ? ((krow & 7) << 1) : (krow & (CH - 1)); }
+
+// Operand of lane `lane` for a 32x32x64 instruction from half kh of a K-contiguous tile (128-byte rows, swizzle swz_kc):
+// lane l holds row (l % 32), which the caller names, and the 32 K-bytes [32 (l / 32), +32) of the 64-deep half.
+__device__ __forceinline__ v8i read_kc_tile(const uint8_t* tile, int row, int kh, int lane)
+{
+    const int cb = kh * 4 + (lane >> 5) * 2;
+    const int sw = swz_kc(row);
+    const uint8_t* base = tile + row * BK;
+    const v4i lo = *reinterpret_cast<const v4i*>(base + ((cb ^ sw) << 4));
+    const v4i hi = *reinterpret_cast<const v4i*>(base + (((cb + 1) ^ sw) << 4));
+    v8i r;
+    r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
+    r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
+    return r;
+}
 
 __device__ __forceinline__ const uint8_t* opaque_uniform(const uint8_t* p)
 {

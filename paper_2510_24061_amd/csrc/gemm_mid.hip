@@ -17,10 +17,10 @@
 //     multiply one more 32-column block, or, where a tile row has too few tile columns or the chip has
 //     idle CUs, the adapter has tile columns of its own.  O_A and its maximum leave the launch finished.
 //   - input gradient: the stages of the left operand also hold what dB needs (see db_stage below).
-// Measured against the 128x128 tiles used before plus their launches for the adapter (us, kernel trace of
-// both in one run): 512 x 4096 x 4096, r = 64: forward 18.5 (19.9 + 7.5 + 3.8), input gradient with dB 21.1
-// (20.3 + 7.2); 8 x 4096 x 11008 forward 10.7 (19.3 + 5.9 + 3.9); 256 x 512 x 512 forward 5.2 (6.8 + 5.4 + 3.1),
-// input gradient with dB 5.8 (6.9 + 6.1).
+// Measured against the 128x128 tiles of gemm.hip plus their launches for the adapter (us, kernel trace of
+// both in one run): 512 x 4096 x 4096, r = 64: forward 18.4 (20.1 + 7.0 + 3.9), input gradient with dB 20.4
+// (20.9 + 7.4); 8 x 4096 x 11008 forward 10.6 (19.4 + 5.8 + 3.1); 256 x 512 x 512 forward 5.2 (6.5 + 5.4 + 3.2),
+// input gradient with dB 5.9 (6.7 + 6.2).
 #include <type_traits>
 
 #include "falqon_internal.h"
@@ -173,17 +173,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     };
 
     // ---- LDS -> matrix-core operands (layouts as in the large tiles) ----------------------------
-    auto read_kc = [&](const uint8_t* tile, int row) -> v8i {
-        const int cb = kh * 4 + (lane >> 5) * 2;
-        const int s = swz_kc(row);
-        const uint8_t* base = tile + row * BK;
-        const v4i lo = *reinterpret_cast<const v4i*>(base + ((cb ^ s) << 4));
-        const v4i hi = *reinterpret_cast<const v4i*>(base + (((cb + 1) ^ s) << 4));
-        v8i x;
-        x[0] = lo[0]; x[1] = lo[1]; x[2] = lo[2]; x[3] = lo[3];
-        x[4] = hi[0]; x[5] = hi[1]; x[6] = hi[2]; x[7] = hi[3];
-        return x;
-    };
+    auto read_kc = [&](const uint8_t* tile, int row) { return read_kc_tile(tile, row, kh, lane); };
     // The transposing read goes out as inline assembly (through the builtin the compiler makes it wait
     // for every fetch in flight), so the compiler takes its results as there at once.  It copies registers
     // where control flow meets, so no read stays in flight across a branch: the reads of a stage, the matrix

@@ -651,7 +651,7 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     // The requantize is bound by its fp64 conversions and sums, so two columns per thread while workgroups of
-    // four would leave CUs idle (32 rows of 4096: 5.9 -> 5.4 us at r = 64, 14.5 -> 13.1 at r = 256).
+    // four would leave CUs idle (32 rows of 4096: 6.1 -> 5.4 us at r = 64, 14.4 -> 13.8 at r = 256).
     const int64_t groups = (n / 4 + kThreads - 1) / kThreads;
     if (k * groups <= 128) {
         const dim3 grid(static_cast<unsigned>(k), static_cast<unsigned>((n / 2 + kThreads - 1) / kThreads));
