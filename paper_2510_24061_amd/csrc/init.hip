@@ -6,12 +6,14 @@
 // This runs once per layer, before training; it is off the hot path.  The SVD is a randomized
 // subspace iteration (the paper only says "SVD"; a truncated factor is all it needs):
 //   Z0 = orth(Omega)                         l = r + 8 rows of length n, Omega Gaussian (caller's);
-//                                            orth = Cholesky QR applied twice
+//                                            orth = Cholesky QR (the last one twice)
 //   repeat q times:  Y = orth(Z E^T);  Z = orth(Y E)
-//   Y = Z E^T;  H = Y Y^T (l x l, fp64);  H = P diag(lambda) P^T  (cyclic Jacobi, fp64)
+//   Y = Z E^T;  H = Y Y^T (l x l, fp64);  H = P diag(lambda) P^T  (Cholesky factor, one-sided Jacobi, fp64)
 //   A^[i,:] = lambda_i^(1/4) * sum_c P[c,i] Z[c,:]      for the r largest lambda_i = sigma_i^2
 // Products with E accumulate in fp32 (matrix cores, slices of the contraction added in order);
 // everything l x l (Gram matrices, Cholesky factors, the eigenproblem) is fp64.
+#include <type_traits>
+
 #include "falqon_internal.h"
 #include "jacobi_rotation.h"
 
@@ -39,136 +41,162 @@ init_residual_kernel(const float* __restrict__ w, const uint8_t* __restrict__ wq
     }
 }
 
-__global__ void __launch_bounds__(kThreads)
-copy_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t count)
-{
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < count; i += stride) dst[i] = src[i];
-}
-
 constexpr int kMaxL = 128;                 // vectors in the subspace (r + 8 <= 128)
-constexpr int kMaxSlices = 16;             // slices of the contracted dimension in the two products
+constexpr int kMaxSlices = 12;             // slices of the contracted dimension in the two products
 
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 
-// The two products with E run on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), operands loaded
-// straight from memory into the instruction's layout: lane t supplies row (t % 32) of its
-// operand and depth index (t / 32).  A contraction does not care in which order its terms are
-// taken as long as both operands agree, so depth index h of four consecutive instructions stands
-// for four consecutive memory elements 4 h .. 4 h + 3 of an eight-element step: one 16-byte load
-// per lane and operand where the operand is contiguous along the contracted dimension.
-// The accumulator of (first, second) operand holds, in lane t, column (t % 32) = the second
-// operand's row, and in register v the first operand's row 8 (v / 4) + 4 (t / 32) + v % 4.
-// One wave owns 32 rows (or columns) of E and all l <= 32 NBV vectors over one slice of the
-// contracted dimension; the slices' results are added in order by sum_slices_kernel.
+// Vectors as the products read them: blocks of 16 elements x 16 vectors in the operand layout of
+// v_mfma_f32_16x16x4_f32, so that a wave reads 1 KB in a row.  Lane t of the instruction holds row t % 16 of an operand
+// and depth index t / 16; a contraction may take its terms in any order as long as both operands agree, so depth index
+// h of four consecutive instructions stands for the elements 4 h .. 4 h + 3 of the block.  Element j of vector c lies
+// in block (j / 16, c / 16) at lane c % 16 + 16 (j % 16 / 4), component j % 4.  Vectors are padded to whole blocks of
+// 16, elements to blocks of 32, both with zeros.
 
-// part[s][c][i] = sum over columns j of slice s of Z[c][j] E[i][j]
-template <int NBV>
+// The two products with E run on the fp32 matrix cores.  At 4096 x 4096, l = 72 (80 with the padding) these need
+// 17 us at 2.4 GHz, and a launch takes 30 us (50 and 75 us with 32 x 32 x 2 instructions and 16 bytes of a row per lane
+// for both operands, a partial result per wave and no packing; 41 us with two waves of 32 rows in place of one of 64).
+// The vectors are packed, and every operand of E comes with 64 or 256 bytes of its row.  The next step's operands are requested before this step's products.
+// The four waves of a workgroup share out the steps of a slice and add up in LDS, which leaves a quarter of the partial
+// sums in memory.  The accumulator of (first, second) operand holds, in lane t, column t % 16 = the second operand's
+// row, and in register v the first operand's row 4 (t / 16) + v.
+
+// part[s][c][i] = sum over columns j of slice s of Z[c][j] E[i][j]; a workgroup owns 64 rows of E
+template <int CB>
 __global__ void __launch_bounds__(kThreads)
-apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* __restrict__ z, int l,
+apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* __restrict__ zp, int l,
                float* __restrict__ part, int64_t per_slice)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane >> 5;
-    const int64_t i0 = (static_cast<int64_t>(blockIdx.x) * (kThreads / 64) + wave) * 32;
-    if (i0 >= m) return;                                             // (no barrier in this kernel)
-    const int64_t j_begin = static_cast<int64_t>(blockIdx.y) * per_slice;
-    const int64_t j_end = j_begin + per_slice < n ? j_begin + per_slice : n;
-    const int64_t row = i0 + (lane & 31);
-    const float* const erow = e + (row < m ? row : m - 1) * n;
-    v16f acc[NBV];
+    constexpr int PITCH = 68;
+    __shared__ __attribute__((aligned(16))) float s_sum[4][CB * 16 * PITCH];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (n + 15) / 16;
+    const int64_t begin = static_cast<int64_t>(blockIdx.y) * per_slice;
+    const int64_t end = begin + per_slice < steps ? begin + per_slice : steps;
+    const float* erow[4];
 #pragma unroll
-    for (int b = 0; b < NBV; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
-    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-
-    for (int64_t j0 = j_begin; j0 < j_end; j0 += 8) {
-        const int64_t jj = j0 + 4 * h;                               // n and per_slice are multiples of 4 and 8
-        const bool in = jj < j_end;
-        const float4 ev = (in && row < m) ? *reinterpret_cast<const float4*>(erow + jj) : zero;
-#pragma unroll
-        for (int b = 0; b < NBV; ++b) {
-            const int c = b * 32 + (lane & 31);
-            const float4 zv = (in && c < l) ? *reinterpret_cast<const float4*>(z + static_cast<int64_t>(c) * n + jj) : zero;
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(zv.x, ev.x, acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(zv.y, ev.y, acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(zv.z, ev.z, acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(zv.w, ev.w, acc[b], 0, 0, 0);
-        }
+    for (int x = 0; x < 4; ++x) {
+        const int64_t row = i0 + 16 * x + row16;
+        erow[x] = e + (row < m ? row : m - 1) * n;                   // rows beyond E are computed and not stored
     }
-    if (row >= m) return;
+    v4f acc[4][CB];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[x][cb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    auto fetch = [&](int64_t b, v4f (&ef)[4], v4f (&zf)[CB]) {
+        int64_t j = b * 16 + 4 * quad;
+        if (j >= n) j = n - 4;                                       // (the vectors are zero there)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) ef[x] = *reinterpret_cast<const v4f*>(erow[x] + j);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) zf[cb] = *reinterpret_cast<const v4f*>(zp + (b * CB + cb) * 256 + lane * 4);
+    };
+    auto multiply = [&](const v4f (&ef)[4], const v4f (&zf)[CB]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(zf[cb][u], ef[x][u], acc[x][cb], 0, 0, 0);
+    };
+    v4f ef[4], ef2[4], zf[CB], zf2[CB];
+    int64_t b = begin + wave;
+    if (b < end) fetch(b, ef, zf);
+    for (; b < end; b += 8) {
+        fetch(b + 4 < end ? b + 4 : b, ef2, zf2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ef, zf);
+        if (b + 4 >= end) break;
+        fetch(b + 8 < end ? b + 8 : b, ef, zf);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ef2, zf2);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + x * 16 + row16] = acc[x][cb][v];
+    __syncthreads();
     float* const out = part + static_cast<int64_t>(blockIdx.y) * l * m;
+    for (int q = threadIdx.x; q < l * 16; q += kThreads) {
+        const int c = q >> 4, i4 = (q & 15) * 4;
+        if (i0 + i4 >= m) continue;                                  // m is a multiple of 4
+        v4f s = *reinterpret_cast<const v4f*>(&s_sum[0][c * PITCH + i4]);
 #pragma unroll
-    for (int b = 0; b < NBV; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int c = b * 32 + 8 * (v / 4) + 4 * h + v % 4;
-            if (c < l) out[static_cast<int64_t>(c) * m + row] = acc[b][v];
-        }
+        for (int w = 1; w < 4; ++w) s += *reinterpret_cast<const v4f*>(&s_sum[w][c * PITCH + i4]);
+        *reinterpret_cast<v4f*>(out + static_cast<int64_t>(c) * m + i0 + i4) = s;
+    }
 }
 
-// part[s][c][j] = sum over rows i of slice s of Y[c][i] E[i][j]
-template <int NBV>
+// part[s][c][j] = sum over rows i of slice s of Y[c][i] E[i][j]; a workgroup owns 64 columns of E: lane t reads four
+// columns 4 (t % 16) + x of one row, one for each of four column blocks
+template <int CB>
 __global__ void __launch_bounds__(kThreads)
-apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* __restrict__ y, int l,
+apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* __restrict__ yp, int l,
                 float* __restrict__ part, int64_t per_slice)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane >> 5;
-    const int64_t j0 = (static_cast<int64_t>(blockIdx.x) * (kThreads / 64) + wave) * 32;
-    if (j0 >= n) return;                                             // (no barrier in this kernel)
-    const int64_t i_begin = static_cast<int64_t>(blockIdx.y) * per_slice;
-    const int64_t i_end = i_begin + per_slice < m ? i_begin + per_slice : m;
-    const int64_t col = j0 + (lane & 31);
-    const float* const ecol = e + (col < n ? col : n - 1);
-    v16f acc[NBV];
+    constexpr int PITCH = 68;
+    __shared__ __attribute__((aligned(16))) float s_sum[4][CB * 16 * PITCH];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
+    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (m + 15) / 16;
+    const int64_t begin = static_cast<int64_t>(blockIdx.y) * per_slice;
+    const int64_t end = begin + per_slice < steps ? begin + per_slice : steps;
+    const int64_t col = j0 + 4 * row16 < n ? j0 + 4 * row16 : n - 4; // columns beyond E are computed and not stored
+    v4f acc[4][CB];
 #pragma unroll
-    for (int b = 0; b < NBV; ++b)
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
-    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-
-    // Operands of the next step are requested before this step's products (92 -> 76 us at 4096 x 4096, l = 72; the
-    // other product, whose loads are 16 bytes of a row each, is faster without, 50 against 100 us).
-    float ev[4], ev2[4];
-    float4 yv[NBV], yv2[NBV];
-    auto fetch = [&](int64_t i0, float (&ef)[4], float4 (&yf)[NBV]) {
-        const int64_t ii = i0 + 4 * h;                               // m and per_slice are multiples of 4 and 8
-        const bool in = ii < i_end;
+        for (int cb = 0; cb < CB; ++cb) acc[x][cb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    auto fetch = [&](int64_t b, v4f (&ef)[4], v4f (&yf)[CB]) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) ef[t] = (in && col < n) ? ecol[(ii + t) * n] : 0.0f;
-#pragma unroll
-        for (int b = 0; b < NBV; ++b) {
-            const int c = b * 32 + (lane & 31);
-            yf[b] = (in && c < l) ? *reinterpret_cast<const float4*>(y + static_cast<int64_t>(c) * m + ii) : zero;
+        for (int v = 0; v < 4; ++v) {
+            const int64_t i = b * 16 + 4 * quad + v;
+            ef[v] = *reinterpret_cast<const v4f*>(e + (i < m ? i : m - 1) * n + col);   // (the vectors are zero beyond)
         }
-    };
-    auto multiply = [&](const float (&ef)[4], const float4 (&yf)[NBV]) {
 #pragma unroll
-        for (int b = 0; b < NBV; ++b) {
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].x, ef[0], acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].y, ef[1], acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].z, ef[2], acc[b], 0, 0, 0);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(yf[b].w, ef[3], acc[b], 0, 0, 0);
-        }
+        for (int cb = 0; cb < CB; ++cb) yf[cb] = *reinterpret_cast<const v4f*>(yp + (b * CB + cb) * 256 + lane * 4);
     };
-    fetch(i_begin, ev, yv);
-    for (int64_t i0 = i_begin; i0 < i_end; i0 += 16) {
-        fetch(i0 + 8, ev2, yv2);                                     // (zeros beyond the slice)
+    auto multiply = [&](const v4f (&ef)[4], const v4f (&yf)[CB]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(yf[cb][v], ef[v][x], acc[x][cb], 0, 0, 0);
+    };
+    v4f ef[4], ef2[4], yf[CB], yf2[CB];
+    int64_t b = begin + wave;
+    if (b < end) fetch(b, ef, yf);
+    for (; b < end; b += 8) {
+        fetch(b + 4 < end ? b + 4 : b, ef2, yf2);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ev, yv);
-        fetch(i0 + 16, ev, yv);
+        multiply(ef, yf);
+        if (b + 4 >= end) break;
+        fetch(b + 8 < end ? b + 8 : b, ef, yf);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ev2, yv2);
+        multiply(ef2, yf2);
     }
-    if (col >= n) return;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            *reinterpret_cast<v4f*>(&s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + 4 * row16]) =
+                v4f{acc[0][cb][v], acc[1][cb][v], acc[2][cb][v], acc[3][cb][v]};
+    __syncthreads();
     float* const out = part + static_cast<int64_t>(blockIdx.y) * l * n;
+    for (int q = threadIdx.x; q < l * 16; q += kThreads) {
+        const int c = q >> 4, j4 = (q & 15) * 4;
+        if (j0 + j4 >= n) continue;                                  // n is a multiple of 4
+        v4f s = *reinterpret_cast<const v4f*>(&s_sum[0][c * PITCH + j4]);
 #pragma unroll
-    for (int b = 0; b < NBV; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int c = b * 32 + 8 * (v / 4) + 4 * h + v % 4;
-            if (c < l) out[static_cast<int64_t>(c) * n + col] = acc[b][v];
-        }
+        for (int w = 1; w < 4; ++w) s += *reinterpret_cast<const v4f*>(&s_sum[w][c * PITCH + j4]);
+        *reinterpret_cast<v4f*>(out + static_cast<int64_t>(c) * n + j0 + j4) = s;
+    }
 }
 
 // out[i] = part[0][i] + part[1][i] + ... in that order
@@ -185,28 +213,31 @@ sum_slices_kernel(const float* __restrict__ part, int slices, int64_t count, flo
     *reinterpret_cast<float4*>(out + i) = s;
 }
 
-// Orthonormalisation of the l rows of V[l][len] by Cholesky QR, applied twice: G = V V^T (fp64,
-// gram_kernel), G = L L^T and its inverse factor (inverse_factor_kernel), V <- L^-1 V
-// (apply_lower_kernel).  Everything of size len runs over the whole chip; only the l x l factorisation is
-// one workgroup.  The second application brings the rows to orthonormal at the precision they are stored in
-// whenever cond(V) < 1e8, which a product with E of a set of orthonormal vectors is far from reaching.  A
-// row whose pivot is not positive (a vector in the span of the earlier ones) is set to zero.
+// Orthonormalisation of the l rows of V[l][len] by Cholesky QR: G = V V^T (fp64, gram_kernel), G = L L^T and its
+// inverse factor (factor_kernel), V <- L^-1 V (apply_lower_kernel).  Everything of size len runs over the whole chip;
+// only the l x l factorisation is one workgroup.  A row whose pivot is not positive (a vector in the span of the
+// earlier ones) is set to zero.  Between two products one application is enough: the iteration needs the span of the
+// rows and a basis of it that is well conditioned, and with everything in fp64 one application leaves the rows
+// orthonormal to 1e-16 cond(V)^2 before they are rounded to fp32 (a product with E of orthonormal vectors has its
+// condition limited by the rounding of the product to about 1e7).  The last basis, which the Rayleigh-Ritz step and
+// A^ take as orthonormal, gets a second one: orthonormal at the precision it is stored in while cond(V) < 1e8.
 //
-// L^-1 by elimination on [G | I]: step c subtracts G[k][c] / d_c times row c from every row k > c, d_c the
-// pivot; the right half becomes the inverse of the unit factor L', and L = L' D^(1/2).  Column j of the left
-// half is finished in step j, where column j of the right one begins, so one lower triangle of registers
-// holds both, in blocks of 4 x 4, one per thread: a step reads eight LDS values per sixteen updates (one
-// element per thread and update reads two for each, and the LDS then takes longer than the arithmetic:
-// 55 us at l = 72).  A step publishes row c of the right half and column c of the left one in one LDS vector
-// and costs a barrier, a reciprocal and the update: a chain of l of them is all there is: 29 us at l = 72, where a factorisation with its trailing block in LDS took
-// 130 us and a forward substitution per column of V another 113 us.
+// L^-1 by elimination on [G | I] in blocks of 4 x 4, one per thread.  Step b, with D the pivot block, P(k) the blocks
+// below it and V(j) those of its row, subtracts P(k) D^-1 V(j) from block (k, j), k > b.  Column b of the left half is
+// finished in step b, where column b of the right one begins, so one lower triangle of registers holds both.  D is
+// factored by every thread for itself (W = inverse of its unit factor, D^-1 = W^T diag(1/d) W), so a step costs one
+// exchange through LDS, one barrier, a chain of four reciprocals and the update.  (With a scalar pivot per step the
+// chain of barriers and reciprocals was four times as long: 29 us at l = 72 against 23.)
+// FACTOR: L^T itself instead (its upper triangle; nothing else is written); pivots below the rounding of G are null.
 constexpr int kFactorThreads = 576;                                   // 32 * 33 / 2 blocks at l = 128, in whole waves
 
+template <bool FACTOR>
 __global__ void __launch_bounds__(kFactorThreads)
-inverse_factor_kernel(const double* __restrict__ g, int l, double* __restrict__ linv)
+factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
 {
-    __shared__ __attribute__((aligned(32))) double s_vec[2][kMaxL];
-    __shared__ double s_root[kMaxL];
+    constexpr int BP = 18;                                            // doubles per block: 16 at an odd number of 16 bytes
+    __shared__ __attribute__((aligned(16))) double s_p[2][kMaxL / 4 * BP], s_q[2][kMaxL / 4 * BP];
+    __shared__ __attribute__((aligned(16))) double s_w[kMaxL / 4 * BP];
     const int t = threadIdx.x, nb = l / 4;                            // l is a multiple of 8
     int R = static_cast<int>((sqrtf(8.0f * static_cast<float>(t) + 1.0f) - 1.0f) * 0.5f);
     if (R * (R + 1) / 2 > t) --R;
@@ -218,249 +249,344 @@ inverse_factor_kernel(const double* __restrict__ g, int l, double* __restrict__ 
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[i][j] = live ? g[(4 * R + i) * l + 4 * C + j] : 0.0;
-    const double tiny = 1e-28 * fmax(g[0], 1e-300);
+    double tiny = 1e-28 * fmax(g[0], 1e-300);
+    if (FACTOR) {
+        double top = 1e-300;
+        for (int i = t & 63; i < l; i += 64) top = fmax(top, g[i * l + i]);
+        for (int off = 32; off > 0; off >>= 1) top = fmax(top, __shfl_xor(top, off, 64));
+        tiny = 1e-15 * top;
+    }
     for (int cb = 0; cb < nb; ++cb) {
+        double* const pc = s_p[cb & 1];                               // P(R); the buffers alternate: one barrier per step
+        double* const vr = s_q[cb & 1];                               // V(C) of either half; the identity for C = cb
+        if (live && C == cb) {
 #pragma unroll
-        for (int ci = 0; ci < 4; ++ci) {
-            const int c = 4 * cb + ci;
-            double* const vec = s_vec[ci & 1];                        // (the buffers alternate: one barrier per step)
-            if (live && C == cb) {                                    // the pivot and the column below it
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (R > cb || i >= ci) vec[4 * R + i] = x[i][ci];
-            }
-            if (live && R == cb) {                                    // L'^-1[c][.] before the pivot
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (C < cb || j < ci) vec[4 * C + j] = x[ci][j];
-            }
-            __syncthreads();
-            const double d = vec[c];
-            double dinv = __builtin_amdgcn_rcp(d);                    // and two Newton steps: full precision
-            dinv = fma(fma(-d, dinv, 1.0), dinv, dinv);
-            dinv = fma(fma(-d, dinv, 1.0), dinv, dinv);
-            if (!(d > tiny)) dinv = 0.0;                              // a dead row takes no part
-            if (t == 0) s_root[c] = dinv;
-            if (live && R >= cb) {
-                double f[4], v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { f[i] = vec[4 * R + i] * dinv; v[i] = vec[4 * C + i]; }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (R == cb && i <= ci) continue;                 // rows up to c are finished
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[i][j] = C == cb && j == ci ? -f[i] : x[i][j] - f[i] * v[j];
+                for (int j = 0; j < 4; ++j) {
+                    pc[R * BP + 4 * i + j] = x[i][j];
+                    vr[R * BP + 4 * i + j] = R == cb ? (i == j ? 1.0 : 0.0) : x[j][i];
                 }
-                if (R == cb && C == cb) x[ci][ci] = 1.0;
+        }
+        if (!FACTOR && live && R == cb && C < cb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) vr[C * BP + 4 * i + j] = x[i][j];
+        }
+        __syncthreads();
+        if (!live || R < cb || (FACTOR && C < cb)) continue;
+        double f[4][4], v[4][4], d[4][4], w[4][4], inv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                d[i][j] = pc[cb * BP + 4 * i + j];
+                f[i][j] = pc[R * BP + 4 * i + j];
+                v[i][j] = vr[C * BP + 4 * i + j];
+                w[i][j] = i == j ? 1.0 : 0.0;
+            }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double p = d[c][c];
+            double r = __builtin_amdgcn_rcp(p);                       // and two Newton steps: full precision
+            r = fma(fma(-p, r, 1.0), r, r);
+            r = fma(fma(-p, r, 1.0), r, r);
+            inv[c] = p > tiny ? r : 0.0;                              // a dead row takes no part
+#pragma unroll
+            for (int k = c + 1; k < 4; ++k) {
+                const double u = d[k][c] * inv[c];
+#pragma unroll
+                for (int j = c + 1; j <= k; ++j) d[k][j] = fma(-u, d[j][c], d[k][j]);
+#pragma unroll
+                for (int j = 0; j <= c; ++j) w[k][j] = fma(-u, w[c][j], w[k][j]);
             }
         }
+        // f <- P(R) W^T, v <- W V(C)
+#pragma unroll
+        for (int j = 3; j > 0; --j)
+#pragma unroll
+            for (int k = 0; k < j; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    f[i][j] = fma(f[i][k], w[j][k], f[i][j]);
+                    v[j][i] = fma(w[j][k], v[k][i], v[j][i]);
+                }
+        if (FACTOR && C == cb) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double root = sqrt(inv[j]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    out[(4 * cb + j) * l + 4 * R + i] = R > cb || j <= i ? f[i][j] * root : 0.0;
+            }
+        }
+        if (!FACTOR && R == cb && C == cb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s_w[cb * BP + 4 * i + j] = i == j ? inv[i] : w[i][j];
+        }
+        // rows of the pivot block are finished; its column starts the right half from zero (the pivot block from one)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                double a = C == cb ? (R == cb && i == j ? 1.0 : 0.0) : x[i][j];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) a = fma(R > cb ? -f[i][k] * inv[k] : 0.0, v[k][j], a);
+                x[i][j] = a;
+            }
     }
-    __syncthreads();
-    if (t < l) s_root[t] = sqrt(s_root[t]);
+    if (FACTOR) return;
     __syncthreads();
     if (!live) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+        const double* const w = s_w + R * BP + 4 * i;
+        const double root = sqrt(w[i]);                               // of 1 / d_i
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (R > C || j <= i) linv[(4 * R + i) * l + 4 * C + j] = x[i][j] * s_root[4 * R + i];
-}
-
-// V <- L^-1 V in place: a workgroup owns 64 columns of V, a wave four rows of the result at a time, whose
-// factors are uniform over the wave (scalar loads) and share each element of V read from LDS: 9.6 us at
-// 72 x 4096.
-constexpr int kLowerCols = 64, kLowerThreads = 1024;
-
-__global__ void __launch_bounds__(kLowerThreads)
-apply_lower_kernel(float* __restrict__ v, int l, int64_t len, const double* __restrict__ linv)
-{
-    extern __shared__ double s_v[];                                   // [l][64]
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * kLowerCols + lane;
-    for (int c = wave; c < l; c += kLowerThreads / 64)
-        s_v[c * kLowerCols + lane] = j < len ? static_cast<double>(v[static_cast<int64_t>(c) * len + j]) : 0.0;
-    __syncthreads();
-    for (int c0 = 4 * wave; c0 < l; c0 += 4 * (kLowerThreads / 64)) { // l is a multiple of 8
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        const double* const f = linv + static_cast<int64_t>(c0) * l;
-        for (int p = 0; p < c0; p += 4) {
-            double x[4];
+        for (int j = 0; j < 4; ++j) {
+            double a = x[i][j];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = s_v[(p + u) * kLowerCols + lane];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc[q] = fma(f[q * l + p + u], x[u], acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)                                   // the diagonal block
-#pragma unroll
-            for (int u = 0; u <= q; ++u) acc[q] = fma(f[q * l + c0 + u], s_v[(c0 + u) * kLowerCols + lane], acc[q]);
-        if (j < len) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[static_cast<int64_t>(c0 + q) * len + j] = static_cast<float>(acc[q]);
+            for (int k = 0; k < i; ++k) a = fma(w[k], x[k][j], a);
+            if (R > C || j <= i) out[(4 * R + i) * l + 4 * C + j] = a * root;
         }
     }
 }
 
-// H[a][b] = sum_i Y[a][i] Y[b][i] in fp64; grid (l, l), the upper half leaves, the lower one writes both
+// dst = L^-1 src on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: lane t holds row t % 16 and depth t / 16 of its
+// operand; register v of the accumulator holds row t / 16 + 4 v, column t % 16).  A workgroup owns 16 elements of all
+// vectors, a wave 16 vectors of the result; every load is requested at once, so the launch is one memory round trip
+// and a chain of up to l / 4 instructions.  dst may be src, and may be null if only `packed` is wanted; `packed` gets
+// the layout above with its padding.
+template <int CB>
+__global__ void __launch_bounds__(CB * 64)
+apply_lower_kernel(const float* src, float* dst, float* __restrict__ packed, int l, int64_t len,
+                   const double* __restrict__ linv)
+{
+    const int R = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * 16 + row16;
+    const int64_t jr = j < len ? j : len - 1;
+    const int c = 16 * R + row16, cr = c < l ? c : l - 1;
+    double a[4 * CB];
+    float b[4 * CB];
+#pragma unroll
+    for (int q = 0; q < 4 * CB; ++q) {
+        const int p = 4 * q + quad, pr = p < l ? p : l - 1;
+        if (q / 4 <= R) {
+            b[q] = src[static_cast<int64_t>(pr) * len + jr];
+            a[q] = linv[cr * l + pr];
+        }
+    }
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4 * CB; ++q) {
+        if (q / 4 > R) continue;
+        const int p = 4 * q + quad;
+        const bool in = p <= c && c < l;                              // (nothing is stored above the diagonal)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[q] : 0.0, p < l ? static_cast<double>(b[q]) : 0.0, acc, 0, 0, 0);
+    }
+    __syncthreads();                                                  // dst may be src
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int cc = quad + 4 * v;
+        const bool in = 16 * R + cc < l && j < len;
+        const float o = static_cast<float>(acc[v]);
+        if (in && dst) dst[static_cast<int64_t>(16 * R + cc) * len + j] = o;
+        packed[(static_cast<int64_t>(blockIdx.x) * CB + R) * 256 + (cc + 16 * (row16 >> 2)) * 4 + (row16 & 3)] = in ? o : 0.0f;
+    }
+}
+
+// H[a][b] = sum_i Y[a][i] Y[b][i] in fp64.  A workgroup forms a block of 4 x 4 sums, so that a row is read l / 4
+// times and not l times, with the next operands in flight (6.1 us at 72 x 4096, 9.7 without); grid (l / 4, l / 4), the upper half leaves, the lower one
+// writes both.
 __global__ void __launch_bounds__(kThreads)
 gram_kernel(const float* __restrict__ y, int l, int64_t m, double* __restrict__ h)
 {
-    __shared__ double s_red[kThreads / 64];
+    __shared__ double s_red[kThreads / 64][16];
     if (blockIdx.y > blockIdx.x) return;
-    const float* ya = y + static_cast<int64_t>(blockIdx.x) * m;
-    const float* yb = y + static_cast<int64_t>(blockIdx.y) * m;
-    double d = 0.0;
-    for (int64_t i = 4 * threadIdx.x; i < m; i += 4 * kThreads) {     // m is a multiple of 4
-        const float4 p = *reinterpret_cast<const float4*>(ya + i), q = *reinterpret_cast<const float4*>(yb + i);
-        d += static_cast<double>(p.x) * static_cast<double>(q.x);
-        d += static_cast<double>(p.y) * static_cast<double>(q.y);
-        d += static_cast<double>(p.z) * static_cast<double>(q.z);
-        d += static_cast<double>(p.w) * static_cast<double>(q.w);
+    const float* const ya = y + static_cast<int64_t>(4 * blockIdx.x) * m;
+    const float* const yb = y + static_cast<int64_t>(4 * blockIdx.y) * m;
+    double d[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) d[q] = 0.0;
+    v4f p[4], q[4], p2[4], q2[4];
+    auto fetch = [&](int64_t i, v4f (&pf)[4], v4f (&qf)[4]) {
+        const int64_t ii = i < m ? i : 0;                             // m is a multiple of 4
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            pf[k] = *reinterpret_cast<const v4f*>(ya + k * m + ii);
+            qf[k] = *reinterpret_cast<const v4f*>(yb + k * m + ii);
+        }
+    };
+    auto add = [&](const v4f (&pf)[4], const v4f (&qf)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int ka = 0; ka < 4; ++ka)
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+                    d[4 * ka + kb] = fma(static_cast<double>(pf[ka][u]), static_cast<double>(qf[kb][u]), d[4 * ka + kb]);
+    };
+    int64_t i = 4 * threadIdx.x;
+    fetch(i, p, q);
+    for (; i < m; i += 8 * kThreads) {
+        fetch(i + 4 * kThreads, p2, q2);
+        __builtin_amdgcn_sched_barrier(0);
+        add(p, q);
+        if (i + 4 * kThreads >= m) break;
+        fetch(i + 8 * kThreads, p, q);
+        __builtin_amdgcn_sched_barrier(0);
+        add(p2, q2);
     }
-    for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off, 64);
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = d;
+    // sixteen sums over a wave: each of four exchanges adds two halves and leaves half as many sums per lane
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int step = 0; step < 4; ++step) {
+        const int half = 8 >> step;
+        const bool upper = (lane >> step) & 1;
+#pragma unroll
+        for (int q = 0; q < half; ++q) {
+            const double keep = upper ? d[q + half] : d[q], give = upper ? d[q] : d[q + half];
+            d[q] = keep + __shfl_xor(give, 1 << step, 64);
+        }
+    }
+    double s = d[0] + __shfl_xor(d[0], 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    // lane bits 0 .. 3 are bits 3 .. 0 of the sum's index
+    if (lane < 16) s_red[threadIdx.x >> 6][(lane & 1) * 8 + (lane & 2) * 2 + (lane & 4) / 2 + (lane & 8) / 8] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 16) {
+        const int a = 4 * blockIdx.x + (threadIdx.x >> 2), b = 4 * blockIdx.y + (threadIdx.x & 3);
         double t = 0.0;
-        for (int w = 0; w < kThreads / 64; ++w) t += s_red[w];
-        h[static_cast<int64_t>(blockIdx.x) * l + blockIdx.y] = t;
-        h[static_cast<int64_t>(blockIdx.y) * l + blockIdx.x] = t;
+        for (int w = 0; w < kThreads / 64; ++w) t += s_red[w][threadIdx.x];
+        if (a >= b) h[static_cast<int64_t>(a) * l + b] = h[static_cast<int64_t>(b) * l + a] = t;
     }
 }
 
-// Symmetric eigen-decomposition of H (l x l, l even, fp64) by two-sided Jacobi with the round-robin
-// ordering: each round rotates l/2 disjoint index pairs at once.  One workgroup; H lives in LDS, the
-// eigenvectors (rows of pt) beside it where both fit (P_IN_LDS, l <= 96: a round then touches no memory), in
-// global memory otherwise.  A round is two phases between barriers: one pass that applies the rotations to H
-// from both sides at once (a thread owns the 2 x 2 block of two pairs, in the lower half, and writes its
-// mirror image too); then the eigenvectors' rotation by fifteen waves, while the first one forms the next
-// round's rotations, a chain of fp64 roots and a division.  Rows of H at an odd pitch: at a pitch of 72
-// doubles a column sits in four LDS banks.  Stops after the first sweep without a rotation, or after
-// `sweeps`.  On exit lambda[i] = H[i][i] and order[k] is the index of the k-th largest eigenvalue.
-// 1024 threads; a chain of l - 1 rounds per sweep, 1.4 us each (l = 72: 0.78 ms for the
-// whole; 2.85 ms with columns, rows and rotations as three phases at an even pitch).
-constexpr int kJacobiThreads = 1024;
+// the sum over each four lanes, the same in all of them
+__device__ __forceinline__ double quad_sum(double v)
+{
+    auto swapped = [](double x, auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), C, 0xf, 0xf, true),
+                                __builtin_amdgcn_mov_dpp(__double2loint(x), C, 0xf, 0xf, true));
+    };
+    v += swapped(v, std::integral_constant<int, 0xB1>{});             // quad_perm [1, 0, 3, 2]
+    return v + swapped(v, std::integral_constant<int, 0x4E>{});       // quad_perm [2, 3, 0, 1]
+}
 
-template <bool P_IN_LDS>
-__global__ void __launch_bounds__(kJacobiThreads)
-jacobi_eig_kernel(const double* __restrict__ h_in, int l, double* __restrict__ pt, double* __restrict__ lambda,
+// Eigen-decomposition H = P diag(lambda) P^T of a symmetric positive semidefinite H = L L^T (l x l, fp64) by one-sided
+// Jacobi: rotations of the columns of L^T that make them orthogonal.  Their dot products are the entries of H, so the
+// rotations are those of the two-sided method on H in the same order, and P is their product; but all that is kept is
+// W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (rotate_kernel).
+// Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: its three dot products
+// are reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.
+// A round is bound by the instructions that a SIMD issues, and those of the rotation count once per wave: four lanes
+// per pair make l / 32 waves, one per SIMD.  (With 16 lanes per pair and up to three waves per SIMD a round took
+// 1.17 us at l = 72; rotating H from both sides, which takes a pass over all of H, the eigenvectors' update and two
+// barriers per round, 1.4 us.)
+// Stops after the first sweep in which no rotation turned its columns by more than 1e-8 radians (what is left of a
+// sweep's off-diagonal parts is of second order in its angles) other than ones between columns that are orthogonal to
+// 1e-14, the rounding level of the products, or after `sweeps`.  Columns that are null stay null.
+// On exit w[i][.] the columns of W, lambda[i] their squared lengths (null below the rounding of H), order[k] the index of the k-th largest.
+template <int L8>                                                      // l / 8: 16-byte parts of a column per lane
+__global__ void __launch_bounds__(256)
+jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double* __restrict__ lambda,
                   int* __restrict__ order, int sweeps)
 {
-    extern __shared__ double s_h[];                                   // [l][l + 1], (pt [l][l],) then rotations and pairs
-    const int pitch = l + 1, t = threadIdx.x;
-    double* const s_p = P_IN_LDS ? s_h + l * pitch : pt;              // the eigenvectors while they are rotated
-    double* const s_cs = s_h + l * pitch + (P_IN_LDS ? l * l : 0);    // two sets of l/2 cosines, l/2 sines
-    int* const s_pairs = reinterpret_cast<int*>(s_cs + 2 * l);        // and of l/2 pairs
-    int* const s_rot = s_pairs + 2 * l;                               // rotations taken in this sweep and the next
-    for (int q = t; q < l * l; q += kJacobiThreads) {
-        s_h[q / l * pitch + q % l] = h_in[q];
-        s_p[q] = (q / l == q % l) ? 1.0 : 0.0;
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    // columns at an odd multiple of 64 bytes: the sixteen pairs of a wave spread over all banks
+    constexpr int l = 8 * L8, PITCH = 8 * (L8 | 1);
+    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], lambda [l], two flags
+    double* const s_lam = s_v + l * PITCH;
+    int* const s_turned = reinterpret_cast<int*>(s_lam + l);
+    const int t = threadIdx.x, pair = t >> 2, e0 = 2 * (t & 3);
+    const bool live = pair < l / 2;
+    for (int q = t; q < l * l; q += blockDim.x) {
+        const int i = q / l, c = q % l;
+        s_v[c * PITCH + i] = i <= c ? lt[i * l + c] : 0.0;
     }
-    const int half = l / 2;
-    // this thread's blocks (k >= j) of H, and its columns of pairs of eigenvectors, as two 16-bit indices
-    constexpr int EB = 3, EP = 9;                                     // l <= 128: 2080 blocks, 8192 columns
-    int blk[EB], vec[EP];
-#pragma unroll
-    for (int e = 0; e < EB; ++e) {
-        const int q = t + e * kJacobiThreads;
-        int k = static_cast<int>((sqrtf(8.0f * static_cast<float>(q) + 1.0f) - 1.0f) * 0.5f);
-        if (k * (k + 1) / 2 > q) --k;
-        if ((k + 1) * (k + 2) / 2 <= q) ++k;
-        blk[e] = k < half ? k << 16 | (q - k * (k + 1) / 2) : -1;
-    }
-#pragma unroll
-    for (int e = 0; e < EP; ++e) {                                    // the first wave forms rotations instead
-        const int q = t - 64 + e * (kJacobiThreads - 64);
-        vec[e] = t >= 64 && q < half * l ? (q / l) << 16 | q % l : -1;
-    }
-    if (t == 0) s_rot[0] = s_rot[1] = 0;
+    if (t < 2) s_turned[t] = 0;
     __syncthreads();
-    // round-robin ordering: position 0 keeps index 0, positions 1 .. l-1 rotate by one per round
+    // position 0 keeps column 0, positions 1 .. l-1 rotate by one per round
     auto at = [&](int pos, int round) { return pos == 0 ? 0 : (pos - 1 >= round ? pos - round : pos - round + l - 1); };
-    // pairs (positions k and l-1-k) of a round and their rotations from the current 2x2 blocks
-    auto form = [&](int round, int set, int* rot) {
-        if (t >= half) return;
-        int a = at(t, round), b = at(l - 1 - t, round);
-        if (a > b) { const int x = a; a = b; b = x; }
-        s_pairs[set * l + 2 * t] = a; s_pairs[set * l + 2 * t + 1] = b;
-        const double haa = s_h[a * pitch + a], hbb = s_h[b * pitch + b], hab = s_h[a * pitch + b];
-        double c, s;
-        if (jacobi_rotation(haa, hbb, hab, c, s)) atomicAdd(rot, 1);
-        s_cs[set * l + t] = c; s_cs[set * l + half + t] = s;
-    };
-    form(0, 0, s_rot);
-    __syncthreads();
-    int set = 0;
     for (int sweep = 0; sweep < sweeps; ++sweep) {
-        for (int round = 0; round < l - 1; ++round, set ^= 1) {
-            const double* const s_c = s_cs + set * l;
-            const double* const s_s = s_c + half;
-            const int* const s_pp = s_pairs + set * l;
-            const bool last = round == l - 2;
-            if (last && t == 0) s_rot[(sweep + 1) & 1] = 0;
-            // H <- J^T H J   (pairs are disjoint, so all of them at once)
+        for (int round = 0; round < l - 1; ++round) {
+            if (round == l - 2 && t == 0) s_turned[(sweep + 1) & 1] = 0;
+            if (live) {
+                v2d* const pa = reinterpret_cast<v2d*>(s_v + at(pair, round) * PITCH + e0);
+                v2d* const pb = reinterpret_cast<v2d*>(s_v + at(l - 1 - pair, round) * PITCH + e0);
+                v2d va[L8], vb[L8], aa = {0.0, 0.0}, bb = {0.0, 0.0}, ab = {0.0, 0.0};
 #pragma unroll
-            for (int e = 0; e < EB; ++e) {
-                if (blk[e] < 0) continue;
-                const int k = blk[e] >> 16, j = blk[e] & 0xffff;
-                const int ak = s_pp[2 * k], bk = s_pp[2 * k + 1], aj = s_pp[2 * j], bj = s_pp[2 * j + 1];
-                const double ck = s_c[k], sk = s_s[k], cj = s_c[j], sj = s_s[j];
-                const double x00 = s_h[ak * pitch + aj], x01 = s_h[ak * pitch + bj];
-                const double x10 = s_h[bk * pitch + aj], x11 = s_h[bk * pitch + bj];
-                const double y00 = cj * x00 - sj * x01, y01 = sj * x00 + cj * x01;
-                const double y10 = cj * x10 - sj * x11, y11 = sj * x10 + cj * x11;
-                const double z00 = ck * y00 - sk * y10, z01 = ck * y01 - sk * y11;
-                const double z10 = sk * y00 + ck * y10, z11 = sk * y01 + ck * y11;
-                s_h[ak * pitch + aj] = z00; s_h[ak * pitch + bj] = z01;
-                s_h[bk * pitch + aj] = z10; s_h[bk * pitch + bj] = z11;
-                if (k != j) {
-                    s_h[aj * pitch + ak] = z00; s_h[bj * pitch + ak] = z01;
-                    s_h[aj * pitch + bk] = z10; s_h[bj * pitch + bk] = z11;
+                for (int e = 0; e < L8; ++e) { va[e] = pa[4 * e]; vb[e] = pb[4 * e]; }
+#pragma unroll
+                for (int e = 0; e < L8; ++e)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        aa[u] = fma(va[e][u], va[e][u], aa[u]);
+                        bb[u] = fma(vb[e][u], vb[e][u], bb[u]);
+                        ab[u] = fma(va[e][u], vb[e][u], ab[u]);
+                    }
+                const double haa = quad_sum(aa[0] + aa[1]), hbb = quad_sum(bb[0] + bb[1]), hab = quad_sum(ab[0] + ab[1]);
+                double c, s;
+                if (jacobi_rotation(haa, hbb, hab, c, s)) {
+#pragma unroll
+                    for (int e = 0; e < L8; ++e) {
+                        v2d na, nb;
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            na[u] = fma(c, va[e][u], -s * vb[e][u]);
+                            nb[u] = fma(s, va[e][u], c * vb[e][u]);
+                        }
+                        pa[4 * e] = na;
+                        pb[4 * e] = nb;
+                    }
+                    if (fabs(s) > 1e-8 && hab * hab > 1e-28 * haa * hbb) s_turned[sweep & 1] = 1;
                 }
             }
             __syncthreads();
-            // the next round's rotations (first wave) beside pt <- J^T pt (the others)
-            form(last ? 0 : round + 1, set ^ 1, s_rot + ((sweep + (last ? 1 : 0)) & 1));
-#pragma unroll
-            for (int e = 0; e < EP; ++e) {
-                if (vec[e] < 0) continue;
-                const int k = vec[e] >> 16, i = vec[e] & 0xffff;
-                double* const pa = s_p + s_pp[2 * k] * l + i;
-                double* const pb = s_p + s_pp[2 * k + 1] * l + i;
-                const double c = s_c[k], s = s_s[k], va = *pa, vb = *pb;
-                *pa = c * va - s * vb;
-                *pb = s * va + c * vb;
-            }
-            __syncthreads();
         }
-        if (s_rot[sweep & 1] == 0) break;                             // converged (same value in every lane)
+        if (s_turned[sweep & 1] == 0) break;                          // (same value in every lane)
     }
-    if (P_IN_LDS)
-        for (int q = t; q < l * l; q += kJacobiThreads) pt[q] = s_p[q];
-    for (int i = t; i < l; i += kJacobiThreads) lambda[i] = s_h[i * pitch + i];
+    for (int i = pair; i < l; i += blockDim.x >> 2) {
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < L8; ++e) {
+            const v2d v = *reinterpret_cast<const v2d*>(s_v + i * PITCH + e0 + 8 * e);
+            *reinterpret_cast<v2d*>(w + i * l + e0 + 8 * e) = v;
+            s = fma(v[0], v[0], fma(v[1], v[1], s));
+        }
+        s = quad_sum(s);
+        if ((t & 3) == 0) s_lam[i] = s;
+    }
     __syncthreads();
     // rank by eigenvalue, larger first, equal values by smaller index.  A NaN (a matrix that is not finite) ranks
     // last: the ranks have to be a permutation, since the entries of `order` are used as indices.
-    auto value = [&](int i) { const double x = s_h[i * pitch + i]; return x == x ? x : -HUGE_VAL; };
-    for (int i = t; i < l; i += kJacobiThreads) {
+    auto value = [&](int i) { const double x = s_lam[i]; return x == x ? x : -HUGE_VAL; };
+    for (int i = t; i < l; i += blockDim.x) {
         const double li = value(i);
         int rank = 0;
+        double top = li;
         for (int j = 0; j < l; ++j) {
             const double lj = value(j);
+            top = fmax(top, lj);
             rank += (lj > li || (lj == li && j < i)) ? 1 : 0;
         }
         order[rank] = i;
+        lambda[i] = s_lam[i] <= 1e-15 * top ? 0.0 : s_lam[i];         // below the rounding of H: null
     }
 }
 
-// A^[k][j] = lambda_k^(1/4) * sum_c pt[order[k]][c] Z[c][j];  sigma[k] = sqrt(lambda_k)
+// A^[k][j] = lambda_k^(1/4) * sum_c P[c][k] Z[c][j], with P's column k = L w_k / lambda_k formed by every workgroup;
+// sigma[k] = sqrt(lambda_k)
 __global__ void __launch_bounds__(kThreads)
-rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __restrict__ pt,
+rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __restrict__ lt, const double* __restrict__ w,
               const double* __restrict__ lambda, const int* __restrict__ order, int r,
               float* __restrict__ a_out, float* __restrict__ sigma_out, int inverse_scale)
 {
+    __shared__ double s_p[kMaxL];
     const int k = blockIdx.y;
     const int col = order[k];
     const double lam = lambda[col] > 0.0 ? lambda[col] : 0.0;
@@ -468,10 +594,17 @@ rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __res
     // z holds E v (length sigma_k u_k after the rotation), row k becomes sqrt(sigma_k) u_k.
     const double root = sqrt(sqrt(lam));
     const double scale = inverse_scale ? (root > 0.0 ? 1.0 / root : 0.0) : root;
+    if (threadIdx.x < l) {
+        const int i = threadIdx.x;
+        double p = 0.0;
+        for (int e = 0; e < l; ++e) p += e <= i ? lt[e * l + i] * w[col * l + e] : 0.0;
+        s_p[i] = lam > 0.0 ? p / lam : 0.0;
+    }
+    __syncthreads();
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     if (j < n) {
         double acc = 0.0;
-        for (int c = 0; c < l; ++c) acc += pt[col * l + c] * static_cast<double>(z[static_cast<int64_t>(c) * n + j]);
+        for (int c = 0; c < l; ++c) acc += s_p[c] * static_cast<double>(z[static_cast<int64_t>(c) * n + j]);
         a_out[static_cast<int64_t>(k) * n + j] = static_cast<float>(scale * acc);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && sigma_out) sigma_out[k] = static_cast<float>(sqrt(lam));
@@ -501,21 +634,39 @@ SvdLayout svd_layout(int64_t m, int64_t n, int64_t r)
     L.p = off;      off = up(off + sizeof(double) * l * l);
     L.lambda = off; off = up(off + sizeof(double) * l);
     L.order = off;  off = up(off + sizeof(int) * l);
-    L.part = off;   off = up(off + sizeof(float) * kMaxSlices * l * static_cast<size_t>(m > n ? m : n));
+    // partial sums of the products and the packed vectors: together no more than the 16 slices of partial sums that
+    // a workspace has had room for (the packed vectors take less than four slices for l >= 24 and max(m, n) >= 32)
+    const size_t longest = static_cast<size_t>(m > n ? m : n), room = sizeof(float) * 16 * l * longest;
+    L.part = off;
+    L.packed = off + sizeof(float) * kMaxSlices * l * longest;
+    off = up(off + room);
     L.total = off;
     return L;
 }
 
-// rows of v[l][len] <- orthonormal (Cholesky QR twice); h and lfac are l x l fp64 scratch
-static hipError_t orthonormalize_rows(float* v, int l, int64_t len, double* h, double* lfac, hipStream_t stream)
+// FQ_BY_BLOCKS(count, F): F<count>() with the number of 16-vector blocks as a constant
+#define FQ_BY_BLOCKS(count, F)                                                                              \
+    switch (count) {                                                                                        \
+        case 2: F(2); break; case 3: F(3); break; case 4: F(4); break; case 5: F(5); break;                 \
+        case 6: F(6); break; case 7: F(7); break; default: F(8); break;                                     \
+    }
+
+// rows of dst[l][len] <- orthonormal basis of the rows of src (Cholesky QR, `passes` times), and the same packed for
+// the products; dst may be src; h and lfac are l x l fp64 scratch
+static hipError_t orthonormalize_rows(const float* src, float* dst, float* packed, int l, int64_t len, double* h,
+                                      double* lfac, int passes, hipStream_t stream)
 {
-    const size_t lds = sizeof(double) * static_cast<size_t>(l) * kLowerCols;                  // 64 KB at most
-    hipError_t err;
-    for (int pass = 0; pass < 2; ++pass) {
-        gram_kernel<<<dim3(l, l), kThreads, 0, stream>>>(v, l, len, h);
-        inverse_factor_kernel<<<1, kFactorThreads, 0, stream>>>(h, l, lfac);
-        apply_lower_kernel<<<static_cast<unsigned>((len + kLowerCols - 1) / kLowerCols), kLowerThreads, lds, stream>>>(v, l, len, lfac);
-        err = hipGetLastError();
+    const int nb = l / 4;
+    const unsigned threads = static_cast<unsigned>((nb * (nb + 1) / 2 + 63) / 64 * 64);
+    const unsigned blocks = static_cast<unsigned>((len + 31) / 32 * 2);
+    for (int pass = 0; pass < passes; ++pass) {
+        const float* const v = pass ? dst : src;
+        gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h);
+        factor_kernel<false><<<1, threads, 0, stream>>>(h, l, lfac);
+#define FQ_APPLY(CB) apply_lower_kernel<CB><<<blocks, CB * 64, 0, stream>>>(v, dst, packed, l, len, lfac)
+        FQ_BY_BLOCKS((l + 15) / 16, FQ_APPLY)
+#undef FQ_APPLY
+        const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
     return hipSuccess;
@@ -533,23 +684,24 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     double* lambda = reinterpret_cast<double*>(ws + L.lambda);
     int* order = reinterpret_cast<int*>(ws + L.order);
     float* part = reinterpret_cast<float*>(ws + L.part);
-    // Y[l][m] = Z E^T (transposed == false) or Z[l][n] = Y E: slices of the contracted dimension so that about
-    // 2048 waves stream E, then the ordered sum of the slices
-    auto product = [&](bool transposed, const float* vec, float* out) -> hipError_t {
+    float* packed = reinterpret_cast<float*>(ws + L.packed);
+    // Y[l][m] = Z E^T (transposed == false) or Z[l][n] = Y E: slices of the contracted dimension so that about 256
+    // workgroups stream E, each with at least one step per wave, then the ordered sum
+    auto product = [&](bool transposed, float* out) -> hipError_t {
         const int64_t rows = transposed ? n : m, depth = transposed ? m : n;
-        const int64_t blocks = (rows + 31) / 32;
-        int64_t slices = 2048 / blocks;
-        if (slices < 1) slices = 1;
+        const int64_t blocks = (rows + 63) / 64, steps = (depth + 15) / 16;
+        int64_t slices = 256 / blocks;
         if (slices > kMaxSlices) slices = kMaxSlices;
-        int64_t per = ((depth + slices - 1) / slices + 7) / 8 * 8;
-        slices = (depth + per - 1) / per;
-        const dim3 grid(static_cast<unsigned>((blocks + kThreads / 64 - 1) / (kThreads / 64)), static_cast<unsigned>(slices));
+        if (slices > (steps + 3) / 4) slices = (steps + 3) / 4;
+        if (slices < 1) slices = 1;
+        const int64_t per = (steps + slices - 1) / slices;
+        slices = (steps + per - 1) / per;
+        const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(slices));
         float* dst = slices > 1 ? part : out;
-        const int nbv = (l + 31) / 32;
-#define FQ_PRODUCT(NBV)                                                                                   \
-        if (transposed) apply_et_kernel<NBV><<<grid, kThreads, 0, stream>>>(e, m, n, vec, l, dst, per);   \
-        else apply_e_kernel<NBV><<<grid, kThreads, 0, stream>>>(e, m, n, vec, l, dst, per)
-        if (nbv == 1) { FQ_PRODUCT(1); } else if (nbv == 2) { FQ_PRODUCT(2); } else if (nbv == 3) { FQ_PRODUCT(3); } else { FQ_PRODUCT(4); }
+#define FQ_PRODUCT(CB)                                                                                       \
+        if (transposed) apply_et_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, packed, l, dst, per);    \
+        else apply_e_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, packed, l, dst, per)
+        FQ_BY_BLOCKS((l + 15) / 16, FQ_PRODUCT)
 #undef FQ_PRODUCT
         hipError_t pe = hipGetLastError();
         if (pe != hipSuccess || slices == 1) return pe;
@@ -559,47 +711,44 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
         return hipGetLastError();
     };
     hipError_t err;
-#define FQ_CHECK_LAUNCH() do { err = hipGetLastError(); if (err != hipSuccess) return err; } while (0)
-    copy_kernel<<<1024, kThreads, 0, stream>>>(omega, z, static_cast<int64_t>(l) * n);
-    FQ_CHECK_LAUNCH();
-    err = orthonormalize_rows(z, l, n, h, p, stream);
-    if (err != hipSuccess) return err;
+#define FQ_CHECK(expr) do { err = (expr); if (err != hipSuccess) return err; } while (0)
+    FQ_CHECK(orthonormalize_rows(omega, z, packed, l, n, h, p, iters ? 1 : 2, stream));
     for (int it = 0; it < iters; ++it) {
-        err = product(false, z, y);
-        if (err != hipSuccess) return err;
-        err = orthonormalize_rows(y, l, m, h, p, stream);
-        if (err != hipSuccess) return err;
-        err = product(true, y, z);
-        if (err != hipSuccess) return err;
-        err = orthonormalize_rows(z, l, n, h, p, stream);
-        if (err != hipSuccess) return err;
+        FQ_CHECK(product(false, y));
+        FQ_CHECK(orthonormalize_rows(y, nullptr, packed, l, m, h, p, 1, stream));
+        FQ_CHECK(product(true, z));
+        FQ_CHECK(orthonormalize_rows(z, z, packed, l, n, h, p, it == iters - 1 ? 2 : 1, stream));
     }
-    err = product(false, z, y);
-    if (err != hipSuccess) return err;
-    gram_kernel<<<dim3(l, l), kThreads, 0, stream>>>(y, l, m, h);
-    FQ_CHECK_LAUNCH();
-    // H, and the eigenvectors too while both fit the LDS (l <= 96; rotated in memory otherwise)
-    const size_t mat = sizeof(double) * static_cast<size_t>(l) * l;
-    const size_t rest = sizeof(double) * 3 * static_cast<size_t>(l) + sizeof(int) * (2 * static_cast<size_t>(l) + 2);
-    const bool p_in_lds = 2 * mat + rest <= 160 * 1024;
-    const size_t lds = (p_in_lds ? 2 : 1) * mat + rest;
-    const void* jacobi = p_in_lds ? reinterpret_cast<const void*>(&jacobi_eig_kernel<true>)
-                                  : reinterpret_cast<const void*>(&jacobi_eig_kernel<false>);
-    err = hipFuncSetAttribute(jacobi, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (err != hipSuccess) return err;
-    if (p_in_lds) jacobi_eig_kernel<true><<<1, kJacobiThreads, lds, stream>>>(h, l, p, lambda, order, 14);
-    else jacobi_eig_kernel<false><<<1, kJacobiThreads, lds, stream>>>(h, l, p, lambda, order, 14);
-    FQ_CHECK_LAUNCH();
+    FQ_CHECK(product(false, y));
+    const int nb = l / 4;
+    gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(y, l, m, h);
+    factor_kernel<true><<<1, static_cast<unsigned>((nb * (nb + 1) / 2 + 63) / 64 * 64), 0, stream>>>(h, l, p);
+    FQ_CHECK(hipGetLastError());
+#define FQ_JACOBI(L8)                                                                                        \
+    case L8: {                                                                                               \
+        const size_t lds = sizeof(double) * 8 * L8 * (8 * (L8 | 1) + 1) + 2 * sizeof(int);                   \
+        FQ_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&jacobi_eig_kernel<L8>),                  \
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));    \
+        jacobi_eig_kernel<L8><<<1, (16 * L8 + 63) / 64 * 64, lds, stream>>>(p, h, lambda, order, 14);        \
+        break;                                                                                               \
+    }
+    switch (l / 8) {
+        FQ_JACOBI(3) FQ_JACOBI(4) FQ_JACOBI(5) FQ_JACOBI(6) FQ_JACOBI(7) FQ_JACOBI(8) FQ_JACOBI(9) FQ_JACOBI(10)
+        FQ_JACOBI(11) FQ_JACOBI(12) FQ_JACOBI(13) FQ_JACOBI(14) FQ_JACOBI(15) FQ_JACOBI(16)
+        default: return hipErrorInvalidValue;
+    }
+#undef FQ_JACOBI
+    FQ_CHECK(hipGetLastError());
     rotate_kernel<<<dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads), static_cast<unsigned>(r)), kThreads, 0,
-                    stream>>>(z, l, n, p, lambda, order, static_cast<int>(r), a_out, sigma_out, 0);
-    FQ_CHECK_LAUNCH();
+                    stream>>>(z, l, n, p, h, lambda, order, static_cast<int>(r), a_out, sigma_out, 0);
+    FQ_CHECK(hipGetLastError());
     if (bt_out) {
         // y still holds E z^T: its rotation by the same eigenvectors is sigma_k u_k, the left singular vectors
         rotate_kernel<<<dim3(static_cast<unsigned>((m + kThreads - 1) / kThreads), static_cast<unsigned>(r)), kThreads, 0,
-                        stream>>>(y, l, m, p, lambda, order, static_cast<int>(r), bt_out, nullptr, 1);
-        FQ_CHECK_LAUNCH();
+                        stream>>>(y, l, m, p, h, lambda, order, static_cast<int>(r), bt_out, nullptr, 1);
+        FQ_CHECK(hipGetLastError());
     }
-#undef FQ_CHECK_LAUNCH
+#undef FQ_CHECK
     return hipSuccess;
 }
 

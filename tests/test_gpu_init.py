@@ -151,3 +151,27 @@ def test_matrix_that_is_not_finite_leaves_the_next_one_alone(r):
     sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)
     sig = np_of(sig).astype(np.float64)
     assert np.all(sig <= sv[:r] * (1 + 1e-4)) and np.sum(sig ** 2) >= 0.9 * np.sum(sv[:r] ** 2)
+
+
+@pytest.mark.parametrize("r", range(16, 121, 8))
+def test_every_subspace_size_on_ragged_matrices(r):
+    """Each number of vectors has kernels of its own; sizes around the 16 and 64 of their tiles, the smallest included.
+    A = sum of s_i u_i v_i^T with a gap of 10^3 behind the r-th: both factors against the known ones.  Bounds: what is
+    left of the gap after q = 3 rounds is below 1e-18, so fp32 products remain, as in the gap cases above."""
+    for m, n in [(r + 8, r + 12), (r + 8 + 4 * (r // 8), 4 * r + 4 * (r // 8 % 5) + 36)]:
+        g = np.random.default_rng(m * n)
+        u, _ = np.linalg.qr(g.normal(size=(m, r)))
+        v, _ = np.linalg.qr(g.normal(size=(n, r)))
+        s = np.linspace(9.0, 2.0, r)
+        e = ((u * s) @ v.T + 2e-3 * g.normal(size=(m, n)) / np.sqrt(m + n)).astype(np.float32)
+        omega = torch.randn(r + 8, n, generator=torch.Generator().manual_seed(r)).cuda()
+        a, bt = torch.full((r, n), 7.0, device="cuda"), torch.full((r, m), 7.0, device="cuda")
+        sig = torch.empty(r, device="cuda")
+        ws = torch.full((fq.svd_workspace_bytes(m, n, r),), 0x7f, dtype=torch.uint8, device="cuda")
+        fq.svd_right_factor(torch.from_numpy(e).cuda(), r, omega, 3, a, sig, ws, bt_out=bt)
+        torch.cuda.synchronize()
+        sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)
+        a, bt, sig = np_of(a).astype(np.float64), np_of(bt).astype(np.float64), np_of(sig).astype(np.float64)
+        assert np.max(np.abs(sig - sv[:r])) <= 1e-4 * sv[0], (m, n)
+        assert np.max(np.abs(a @ a.T - np.diag(sig))) <= 1e-4 * sig[0], (m, n)
+        assert np.linalg.norm(bt.T @ a - (u * s) @ v.T) <= 2e-3 * np.linalg.norm(s), (m, n)
