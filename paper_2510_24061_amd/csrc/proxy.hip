@@ -8,16 +8,18 @@
 //   2. selection: the rank of a row is the number of rows that beat it (larger score, or equal score and
 //      smaller index): exact and order free, so the result is deterministic and already sorted, with no
 //      sort, no atomics on results, no host round trip.  Only rows that can be selected are ranked: the k-th
-//      largest of the maxima of disjoint groups of rows is a lower bound on the k-th largest score.  The
-//      selected buffer row moves to a compact staging array (and is cleared in the buffer), which lets the
-//      third launch spread one row over several workgroups without a hazard on the buffer.
+//      largest of the maxima of disjoint groups of rows is a lower bound on the k-th largest score.
 //   3. requantize: value(W~[i,j]) + sum_p delta[p] * value(A~[p,j]) in fp64 (p ascending), rounded to
 //      fp32, cast to E4M3, written back.  A~ is rows [m, m+r) of the concatenated weight, in the same
 //      scaled domain as W~, so the backbone's scale never enters.
+// Selection and requantize are one launch where the row of a rank is not spread over too many workgroups.  Otherwise
+// the selected buffer row moves to a compact staging array (and is cleared in the buffer), which lets a third launch
+// spread one row over several workgroups without a hazard on the buffer.
 #include <mutex>
 #include <type_traits>
 
 #include "falqon_internal.h"
+#include "gemm_common.h"
 #include "row_scores.h"
 
 namespace falqon {
@@ -53,12 +55,18 @@ row_score_kernel(const float* __restrict__ buf, int64_t m, int r, double* __rest
     score_rows_from_lds(s_rows, r, row0, m, score);
 }
 
+// C adjacent E4M3 codes
+template <int C> struct Codes;
+template <> struct Codes<4> { typedef uint32_t type; };
+template <> struct Codes<2> { typedef uint16_t type; };
+template <> struct Codes<1> { typedef uint8_t type; };
+
 // the first C of four codes
 template <int C>
 __device__ __forceinline__ void decode_e4m3(uint32_t w, double (&d)[4])
 {
     d[0] = static_cast<double>(__builtin_amdgcn_cvt_f32_fp8(static_cast<int>(w), 0));
-    d[1] = static_cast<double>(__builtin_amdgcn_cvt_f32_fp8(static_cast<int>(w), 1));
+    if constexpr (C >= 2) d[1] = static_cast<double>(__builtin_amdgcn_cvt_f32_fp8(static_cast<int>(w), 1));
     if constexpr (C == 4) {
         d[2] = static_cast<double>(__builtin_amdgcn_cvt_f32_fp8(static_cast<int>(w), 2));
         d[3] = static_cast<double>(__builtin_amdgcn_cvt_f32_fp8(static_cast<int>(w), 3));
@@ -77,170 +85,174 @@ __device__ __forceinline__ uint32_t encode4_e4m3(const double (&acc)[4])
 }
 
 // ---- selection ------------------------------------------------------------------------------------------
-// grid (k): workgroup c finds the row of rank c, stages its buffer row and clears it.  Scores are
-// non-negative doubles, so their bit patterns order them as 64-bit integers.  Thread t holds the keys of rows
-// t, t + 256, ...; threads t and t ^ 1 form one of 128 groups.  The k-th largest group maximum bounds the
-// k-th largest key from below, and so does any number below it: tau, its leading bits (every wave finds them
-// by bisection on its own, two maxima per lane).  The rows that reach tau, a few dozen, contain the k selected
-// ones; they are ranked pairwise.
+// A workgroup finds the row of one rank.  Scores are non-negative doubles, so their bit patterns order them as 64-bit integers.  Thread t holds the keys of rows
+// t, t + 512, ...; four threads form one of 128 groups.  The k-th largest group maximum, tau, bounds the
+// k-th largest key from below.  The rows that reach tau, a few dozen, contain the k selected ones; they are
+// ranked pairwise, as are the maxima.  If far more rows than are looked for reach tau, the row is found among
+// those above tau, or by its index among those equal to it (an untouched buffer).  Only where many rows are
+// above tau (all that is large sits in a few threads) is it found by counting over all rows, bit by bit.
 //
-// tau has 12 bits of the range that the maxima span: the exponent and some bits behind it where the
-// rows have learned at different rates, bits far behind it where they are alike (the first step of AdamW moves
-// every element by about the learning rate).  If far more rows than are looked for reach tau, 12 more bits,
-// until tau is the k-th maximum itself; what is left then are equal scores (an untouched buffer), and the row is
-// found among those above tau, or by its index among the equal ones.  Only where many rows are above tau (all that
-// is large sits in a few threads) is it found by counting over all rows, bit by bit.
-//
-// All latency: one round trip for the scores, one for the buffer row, and 2 us of comparisons.  Every
-// workgroup repeats the comparisons; nothing is exchanged.  Whole update in us (graph of 20, n = 256), against
-// ranking 16 rows per workgroup or, beyond 4096 rows, whole blocks:
-//                       rows learned at different rates   after the first AdamW step   untouched
-//   512 x 16, k = 8              8.5 (9.1)                        8.5 (9.1)              8.4 (9.4)
-//   4096 x 64, k = 32           12.1 (15.0)                      12.1 (14.9)            10.9 (15.2)
-//   11008 x 64, k = 32          14.8 (25.6)                      14.9 (25.6)            12.9 (132)
-// Slower than before only where many of few rows are equal and reach tau: 256 of 512 rows 10.9 (9.4), a third of
-// 2000 rows 13.2 (12.4).
-// (Requantizing in the same launch was built too: the workgroups that share a row have to agree on when
-// its buffer row may be cleared, and their device-scope atomics cost more, 6 us, than the launch saved.)
-constexpr int kSelectGroups = 128, kSelectMaxK = 96, kSelectCands = 2 * kSelectMaxK + 32, kSelectMaxRows = 64 * kThreads;
-constexpr int kTauBits = 12;                                         // bits of tau found at a time
-constexpr int kTauRounds = 6;                                        // that many cover a key
+// All latency: a round trip for the scores (0.7 us), then 2.1 us of comparisons (m = 4096: group maxima 0.2, tau 0.5,
+// list 0.8, ranking 0.5; tau bit by bit over ballots took 1.5 us more), most of it chains of LDS accesses and
+// barriers.  512 threads: with 256 a SIMD has one wave, whose instructions it cannot overlap.  Every workgroup repeats
+// the comparisons; nothing is exchanged.
+constexpr int kSelectGroups = 128, kSelectMaxK = 96, kSelectCands = 2 * kSelectMaxK + 32, kSelectThreads = 512;
+constexpr int kSelectMaxRows = 32 * kSelectThreads;
 
-// a combination over the wave that leaves `none` unchanged, the same in every lane
-template <typename F>
-__device__ __forceinline__ uint32_t wave_combine(uint32_t x, uint32_t none, F f)
+// a value of another lane of the same sixteen; 0xB1: lane ^ 1, 0x4E: lane ^ 2 (quad_perm), 0x141 / 0x140: mirrored
+// within eight / sixteen, 0x150 + N: lane N
+template <int CTRL>
+__device__ __forceinline__ int lanes(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true); }
+template <int CTRL>
+__device__ __forceinline__ double lanes(double v)
 {
-    const int o = static_cast<int>(none);
-    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x111, 0xf, 0xf, false)));   // row_shr 1, 2,
-    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x112, 0xf, 0xf, false)));   // 4, 8: rows of
-    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x114, 0xf, 0xf, false)));   // 16 lanes
-    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x118, 0xf, 0xf, false)));
-    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x142, 0xa, 0xf, false)));   // row_bcast 15,
-    x = f(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(o, static_cast<int>(x), 0x143, 0xc, 0xf, false)));   // 31: across rows
-    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
+    return __hiloint2double(lanes<CTRL>(__double2hiint(v)), lanes<CTRL>(__double2loint(v)));
+}
+__device__ __forceinline__ int sum_of_8(int v)                       // over each eight lanes, in all of them
+{
+    v += lanes<0xB1>(v);
+    v += lanes<0x4E>(v);
+    return v + lanes<0x141>(v);                                      // row_half_mirror
 }
 
-// kTauBits more bits of the k-th largest of 128 maxima, two per lane (a, b): it lies in [tau, tau + 2^open), and so it
-// does afterwards; open = 0: it is tau.
-__device__ __forceinline__ void extend_tau(uint64_t a, uint64_t b, int k, uint64_t& tau, int& open)
+// Workgroup barrier behind the wave's LDS accesses; __syncthreads() would also wait for the loads of A~ in flight.
+__device__ __forceinline__ void barrier_lds()
 {
-    const uint64_t da = a - tau, db = b - tau;
-    const bool in_a = a >= tau && (open > 63 || da >> open == 0), in_b = b >= tau && (open > 63 || db >> open == 0);
-    const uint64_t diff = (in_a ? da : 0) | (in_b ? db : 0);
-    const auto either = [](uint32_t x, uint32_t y) { return x | y; };
-    const uint64_t all = static_cast<uint64_t>(wave_combine(static_cast<uint32_t>(diff >> 32), 0, either)) << 32 |
-                         wave_combine(static_cast<uint32_t>(diff), 0, either);
-    const int bits = all ? 64 - __builtin_clzll(all) : 0;
-    open = bits > kTauBits ? bits - kTauBits : 0;
-    // the leading bits of each distance from tau; maxima above the interval always count, those below never
-    const uint32_t wa = in_a ? static_cast<uint32_t>(da >> open) : a > tau ? ~0u : 0u;
-    const uint32_t wb = in_b ? static_cast<uint32_t>(db >> open) : b > tau ? ~0u : 0u;
-    uint32_t w = 0;
-#pragma unroll
-    for (int bit = kTauBits - 1; bit >= 0; --bit) {
-        const uint32_t trial = w | (1u << bit);
-        if (__popcll(__ballot(wa >= trial)) + __popcll(__ballot(wb >= trial)) >= k) w = trial;
-    }
-    tau += static_cast<uint64_t>(w) << open;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    barrier_lds_only();
 }
 
-template <int U>                                                     // U keys per thread: m <= 256 U
-__global__ void __launch_bounds__(kThreads)
-select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int32_t* __restrict__ idx, float* buf,
-              float* __restrict__ delta_sel, int clear_selected)
+// keys of rows t, t + 512, ...
+template <int U>
+__device__ __forceinline__ void load_keys(const double* __restrict__ score, int64_t m, uint64_t (&v)[U])
 {
-    static_assert(U <= 64, "one lane per key of a thread");
-    __shared__ uint64_t s_max[kSelectGroups];
-    __shared__ uint64_t s_ckey[kSelectCands];
-    __shared__ int s_cidx[kSelectCands];
-    __shared__ int s_listed[kTauRounds + 1], s_row, s_count[2][kThreads / 64];
-    __shared__ __attribute__((aligned(16))) int s_equal[64][kThreads / 64];
-    __shared__ unsigned long long s_all, s_any;
     const uint64_t* key = reinterpret_cast<const uint64_t*>(score);
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int rank = static_cast<int>(blockIdx.x);
-
-    uint64_t v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int64_t i = static_cast<int64_t>(u) * kThreads + t;
+        const int64_t i = static_cast<int64_t>(u) * kSelectThreads + threadIdx.x;
         v[u] = i < m ? key[i] : 0;                                   // (0 also stands for the rows behind the last one:
     }                                                                // none is looked for but among equals, by index)
-    if (t <= kTauRounds) s_listed[t] = 0;
+}
+
+// the row of rank `rank` (-1 cannot happen), the same in every thread
+template <int U>                                                     // U keys per thread: m <= 512 U
+__device__ __forceinline__ int select_row(const uint64_t (&v)[U], int64_t k, int rank)
+{
+    static_assert(U <= 32, "one lane per key of a thread");
+    __shared__ __attribute__((aligned(16))) uint64_t s_max[kSelectGroups];
+    __shared__ uint64_t s_tau;
+    __shared__ uint64_t s_ckey[kSelectCands];
+    __shared__ int s_cidx[kSelectCands];
+    __shared__ int s_listed[2], s_row, s_count[2][kSelectThreads / 64];
+    __shared__ __attribute__((aligned(16))) int s_equal[64][kSelectThreads / 64];
+    __shared__ unsigned long long s_all, s_any;
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    if (t < 2) s_listed[t] = 0;
     if (t == 0) s_row = -1;
     double mx = 0.0;                                                 // (a NaN is left out: tau stays a lower bound)
 #pragma unroll
     for (int u = 0; u < U; ++u) mx = fmax(mx, __longlong_as_double(static_cast<long long>(v[u])));
-    mx = fmax(mx, __shfl_xor(mx, 1, 64));
-    if ((t & 1) == 0) s_max[t >> 1] = static_cast<uint64_t>(__double_as_longlong(mx));
-    __syncthreads();
-
-    // Ranking is quadratic: with far more rows listed than are looked for, tau gets more bits, or is the k-th
-    // maximum itself and many of the listed ones equal it.
-    const int limit = 2 * static_cast<int>(k) + 32;
-    // rows with key >= bound > 0 (above: > bound) into the list, as far as it goes; which: the counter, used once per
-    // launch.  Keys are compared as doubles, in one instruction; a NaN counts as above, as its bits do.
-    auto list_rows = [&](uint64_t bound, auto above_tag, int which) __attribute__((always_inline)) {
-        constexpr bool ABOVE = decltype(above_tag)::value;
-        const double reach = __longlong_as_double(static_cast<long long>(bound));
-        uint32_t in[2] = {0, 0};                                     // bit u: key u of this thread
+    mx = fmax(mx, lanes<0xB1>(mx));
+    mx = fmax(mx, lanes<0x4E>(mx));
+    // the group's number in the last bits: no two are equal
+    if ((t & 3) == 0) s_max[t >> 2] = (static_cast<uint64_t>(__double_as_longlong(mx)) & ~uint64_t(127)) | (127 - (t >> 2));
+    barrier_lds();
+    {
+        // tau: the maximum with k - 1 others above it, without its last bits; sixteen threads count for four of them
+        typedef unsigned long long v2u __attribute__((ext_vector_type(2)));
+        const int q = t & 15;
+        uint64_t mine[4];
+        int above[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const double x = __longlong_as_double(static_cast<long long>(v[u]));
-            in[u / 32] |= (ABOVE ? !(x <= reach) : !(x < reach)) ? 1u << (u % 32) : 0u;
+        for (int x = 0; x < 4; ++x) mine[x] = s_max[4 * (t >> 4) + x];
+#pragma unroll
+        for (int u = 0; u < kSelectGroups / 32; ++u) {
+            const v2u o = *reinterpret_cast<const v2u*>(s_max + 2 * (16 * u + q));
+#pragma unroll
+            for (int x = 0; x < 4; ++x) above[x] += (o[0] > mine[x] ? 1 : 0) + (o[1] > mine[x] ? 1 : 0);
         }
-        if (in[0] | in[1]) {
-            int pos = atomicAdd(&s_listed[which], __popc(in[0]) + __popc(in[1]));
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int listed = in[u / 32] >> (u % 32) & 1;
-                if (listed && pos < limit) { s_ckey[pos] = v[u]; s_cidx[pos] = u * kThreads + t; }
-                pos += listed;
+        for (int x = 0; x < 4; ++x) {
+            above[x] = sum_of_8(above[x]);
+            above[x] += lanes<0x140>(above[x]);                      // row_mirror
+            if (q == x && above[x] == static_cast<int>(k) - 1) s_tau = mine[x] & ~uint64_t(127);
+        }
+    }
+    barrier_lds();
+    const uint64_t tau = s_tau;
+
+    // Ranking is quadratic: it ends where far more rows are listed than are looked for.
+    const int limit = 2 * static_cast<int>(k) + 32;
+    // rows with key >= bound into the list, as far as it goes; which: the counter, used once per launch
+    auto list_rows = [&](uint64_t bound, int which) __attribute__((always_inline)) {
+        uint32_t in = 0;                                             // bit u: key u of this thread
+#pragma unroll
+        for (int u = 0; u < U; ++u) in |= v[u] >= bound ? 1u << u : 0u;
+        if (in) {
+            int pos = atomicAdd(&s_listed[which], __popc(in));
+            for (; in && pos < limit; in &= in - 1, ++pos) {
+                const int first = __builtin_ctz(in);
+                uint64_t key = v[0];
+#pragma unroll
+                for (int u = 1; u < U; ++u) {
+                    key = u == first ? v[u] : key;
+                    asm volatile("" : "+v"(key));                    // (else an array in memory)
+                }
+                s_ckey[pos] = key;
+                s_cidx[pos] = first * kSelectThreads + t;
             }
         }
-        __syncthreads();
+        barrier_lds();
         return s_listed[which];
     };
-    // the row of rank `rank` among the nc listed ones: four threads per listed row, four others at a time
+    // the row of rank `rank` among the nc listed ones: eight threads per listed row, eight others at a time
     auto rank_listed = [&](int nc) __attribute__((always_inline)) {
-        for (int c0 = 0; c0 < nc; c0 += kThreads / 4) {
-            const int c = c0 + t / 4;
-            const bool in = c < nc;
-            const uint64_t kc = s_ckey[in ? c : 0];
-            const int ic = s_cidx[in ? c : 0];
-            int beat = 0;
-            for (int j0 = t & 3; j0 < nc; j0 += 16) {
-                uint64_t kj[4];
-                int ij[4];
+        for (int c0 = 0; c0 < nc; c0 += kSelectThreads / 8) {
+            const int c = c0 + t / 8;
+            const uint64_t kc = s_ckey[c < nc ? c : 0];
+            int larger = 0, equal = 0;
+            for (int j0 = t & 7; j0 < nc; j0 += 64) {
+                uint64_t kj[8];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int j = j0 + 4 * q < nc ? j0 + 4 * q : c;  // beyond the list: the row itself, which does not beat itself
-                    kj[q] = s_ckey[in ? j : 0];
-                    ij[q] = s_cidx[in ? j : 0];
+                for (int q = 0; q < 8; ++q) kj[q] = s_ckey[j0 + 8 * q < nc ? j0 + 8 * q : 0];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const bool in = j0 + 8 * q < nc;
+                    larger += in && kj[q] > kc ? 1 : 0;
+                    equal += in && kj[q] == kc ? 1 : 0;              // (itself among them)
                 }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) beat += (kj[q] > kc || (kj[q] == kc && ij[q] < ic)) ? 1 : 0;
             }
-            beat += __shfl_xor(beat, 1, 64);
-            beat += __shfl_xor(beat, 2, 64);
-            if (in && (t & 3) == 0 && beat == rank) s_row = ic;
+            larger = sum_of_8(larger);
+            equal = sum_of_8(equal);
+            if ((t & 7) || c >= nc || rank < larger || rank >= larger + equal) continue;
+            int left = rank - larger;                                // equal keys by index
+            const int ic = s_cidx[c];
+            if (equal > 1)
+                for (int j = 0; j < nc; ++j) left -= s_ckey[j] == kc && s_cidx[j] < ic ? 1 : 0;
+            if (left == 0) s_row = ic;
         }
     };
     // the row with `left` rows of the same key before it
     auto index_among_equal = [&](uint64_t value, int left) __attribute__((always_inline)) {
-        uint64_t equal = 0;                                          // bit u: key u of this thread
+        uint32_t equal = 0;                                          // bit u: key u of this thread
         int mine = 0;                                                // lane u: rows of the wave's share of key u
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool eq = v[u] == value;
             const int count = __popcll(__ballot(eq));
-            equal |= eq ? uint64_t(1) << u : 0;
+            equal |= eq ? 1u << u : 0u;
             mine = lane == u ? count : mine;
         }
         s_equal[lane][wave] = mine;
-        __syncthreads();
-        const int4 c = *reinterpret_cast<const int4*>(s_equal[lane]);
-        int upto = c.x + c.y + c.z + c.w;                            // rows of keys 0 .. lane
+        barrier_lds();
+        int total = 0, earlier = 0;                                  // rows of key `lane`, and those of earlier waves' shares
+#pragma unroll
+        for (int w = 0; w < kSelectThreads / 64; ++w) {
+            const int c = s_equal[lane][w];
+            total += c;
+            earlier += w < wave ? c : 0;
+        }
+        int upto = total;                                            // rows of keys 0 .. lane
         for (int off = 1; off < 64; off <<= 1) {
             const int below = __shfl_up(upto, off, 64);
             if (lane >= off) upto += below;
@@ -248,37 +260,22 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
         const uint64_t reached = __ballot(upto > left);
         if (!reached) return;                                        // (value is a key of more than `left` rows)
         const int u = __builtin_ctzll(reached);
-        int before = __shfl(upto - (c.x + c.y + c.z + c.w), u, 64);
-        before += wave > 0 ? __shfl(c.x, u, 64) : 0;
-        before += wave > 1 ? __shfl(c.y, u, 64) : 0;
-        before += wave > 2 ? __shfl(c.z, u, 64) : 0;
+        int before = __shfl(upto - total + earlier, u, 64);
         const bool eq = equal >> u & 1;
         before += __popcll(__ballot(eq) & ((uint64_t(1) << lane) - 1));
-        if (eq && before == left) s_row = u * kThreads + t;
+        if (eq && before == left) s_row = u * kSelectThreads + t;
     };
 
-    uint64_t tau;
-    int nc, open = 64;
-    {
-        const uint64_t a = s_max[lane], b = s_max[lane + 64];
-        const uint32_t ha = static_cast<uint32_t>(a >> 32), hb = static_cast<uint32_t>(b >> 32);
-        const auto smaller = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
-        tau = static_cast<uint64_t>(wave_combine(smaller(ha, hb), ~0u, smaller)) << 32;   // no maximum is below it
-        extend_tau(a, b, static_cast<int>(k), tau, open);
-        nc = tau ? list_rows(tau, std::false_type{}, 0) : limit + 1;     // (every row reaches 0)
-        for (int round = 1; nc > limit && open != 0 && round < kTauRounds; ++round) {
-            const uint64_t before = tau;
-            extend_tau(a, b, static_cast<int>(k), tau, open);
-            if (tau != before) nc = list_rows(tau, std::false_type{}, round);
-        }
+    // those that reach tau; those above it if they are too many (every row reaches 0)
+    int nc = limit + 1, which = tau ? 0 : 1;
+    for (; which < 2; ++which) {
+        nc = list_rows(tau + which, which);
+        if (nc <= limit) break;
     }
-    const int above = nc > limit ? list_rows(tau, std::true_type{}, kTauRounds) : 0;
-    if (nc <= limit) {
+    if (which == 1 && rank >= nc) {
+        index_among_equal(tau, rank - nc);
+    } else if (nc <= limit) {
         rank_listed(nc);
-    } else if (rank >= above) {
-        index_among_equal(tau, rank - above);
-    } else if (above <= limit) {
-        rank_listed(above);
     } else {
         // largest key that more than `rank` rows reach: the key of the row looked for.  One barrier per count:
         // the sums of a count may still be read while the next one writes, so the two use different buffers, and
@@ -292,13 +289,16 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
                 c += v[u] >= bound ? 1 : 0;
             for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
             if (lane == 0) s_count[which][wave] = c;
-            __syncthreads();
-            return s_count[which][0] + s_count[which][1] + s_count[which][2] + s_count[which][3];
+            barrier_lds();
+            int sum = 0;
+#pragma unroll
+            for (int w = 0; w < kSelectThreads / 64; ++w) sum += s_count[which][w];
+            return sum;
         };
         // bits that all rows from tau on share need no count
         unsigned long long all = ~0ull, any = 0;
         if (t == 0) { s_all = ~0ull; s_any = 0; }
-        __syncthreads();
+        barrier_lds();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (v[u] >= tau) {
@@ -311,7 +311,7 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
             any |= __shfl_xor(any, off, 64);
         }
         if (lane == 0) { atomicAnd(&s_all, all); atomicOr(&s_any, any); }
-        __syncthreads();
+        barrier_lds();
         all = s_all;
         any = s_any;
         uint64_t found = 0;
@@ -321,10 +321,21 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
         }
         index_among_equal(found, rank - count_reaching(found + 1));
     }
-    __syncthreads();
-    const int64_t row = s_row;
-    if (row < 0 || row >= m) return;                                 // cannot happen; keeps every access in range
+    barrier_lds();
+    return s_row;
+}
 
+// grid (k): workgroup c stages the buffer row of rank c and clears it
+template <int U>
+__global__ void __launch_bounds__(kSelectThreads)
+select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int32_t* __restrict__ idx, float* buf,
+              float* __restrict__ delta_sel, int clear_selected)
+{
+    uint64_t v[U];
+    load_keys(score, m, v);
+    const int t = threadIdx.x, rank = static_cast<int>(blockIdx.x);
+    const int64_t row = select_row(v, k, rank);
+    if (row < 0 || row >= m) return;                                 // cannot happen; keeps every access in range
     if (t == 0) idx[rank] = static_cast<int32_t>(row);
     if (t < r) {
         delta_sel[static_cast<int64_t>(rank) * r + t] = buf[row * r + t];
@@ -531,10 +542,6 @@ topk_filtered_kernel(const double* __restrict__ score, int64_t m, int64_t k, int
 }
 
 // grid: (k, ceil(n / (256 C))); a thread owns C adjacent columns of row idx[blockIdx.x]
-template <int C> struct Codes;                                       // C adjacent E4M3 codes
-template <> struct Codes<4> { typedef uint32_t type; };
-template <> struct Codes<2> { typedef uint16_t type; };
-
 template <int C>
 __global__ void __launch_bounds__(kThreads)
 row_requantize_kernel(uint8_t* wq, int64_t n, int64_t m, int64_t r, const int32_t* __restrict__ idx,
@@ -570,6 +577,116 @@ row_requantize_kernel(uint8_t* wq, int64_t n, int64_t m, int64_t r, const int32_
         }
     }
     wrow[c] = static_cast<codes_t>(encode4_e4m3(acc));
+}
+
+// Selection and requantize in one launch, grid (k, parts): every workgroup of a rank finds the row by itself, with
+// its part of A~ on the way into registers meanwhile (then LDS: a thread's bytes of 16 ranks at a time), and writes
+// its C columns per thread of the row.
+//
+// The buffer row may only be cleared when all parts have read it.  Each part has a word in memory: it exchanges the
+// word for `kArrived` once its reads are done, waits for the exchange, and then reads the words of all parts.  The
+// exchange that comes last in memory is followed by reads that find all words set, so at least one part clears
+// the row; parts that find them set at the same time write the same zeros.  Who clears the row also takes the words
+// back, after all have been set, so none is left behind for the next launch or a replay; a word that happens to hold
+// kArrived beforehand is the one thing that must not be (any other 64 bits may stand there).  Nothing waits for
+// another workgroup.  The words of a rank lie in 64 bytes or more of their own, and the exchange hides under the
+// sums; the clear adds 0.7 us to the launch.  (Counters of all ranks in one line took 6 us.)
+//
+// Bound by latency: scores 0.7 us, selection 2.6, row 0.5, sums 1.2 (r = 64; 4.3 at r = 256), end 0.6 at 4096 x 4096,
+// k = 32.  The sums are rolled up to 16 ranks: unrolled over 64 their instructions alone took 0.8 us to arrive.
+// Whole update with its score pass, us (graph of 20, with clear), against selection and requantize in two launches:
+//   512 x 512, r = 16, k = 8          6.8 (8.4)      4096 x 4096, r = 256, k = 32     17.1 (18.8)
+//   2000 x 1040, r = 48, k = 24       9.2 (10.7)     4096 x 11008, r = 64, k = 32     12.3 (13.5)
+//   4096 x 4096, r = 64, k = 32       9.9 (11.4)     11008 x 4096, r = 64, k = 32     12.4 (15.5)
+constexpr unsigned long long kArrived = 0xa57c3e91d20b68f5ull;
+
+template <int N, typename F, int I = 0>
+__device__ __forceinline__ void for_each(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        for_each<N, F, I + 1>(f);
+    }
+}
+
+// element N of the sixteen that each row of 16 lanes holds (row_newbcast: no LDS access, no scalar register)
+template <int N>
+__device__ __forceinline__ double of_row(double sixteen) { return lanes<0x150 + N>(sixteen); }
+
+// ROW columns per workgroup, C per thread; NA x 16 bytes of A~ per thread: r ROW <= 8192 NA
+template <int U, int ROW, int NA>
+__global__ void __launch_bounds__(kSelectThreads)
+fold_kernel(uint8_t* wq, int64_t n, int64_t m, int r, const double* __restrict__ score, int64_t k,
+            int32_t* __restrict__ idx, float* buf, unsigned long long* arrived, int clear_selected)
+{
+    constexpr int C = ROW <= 1024 ? 2 : 4, CHUNKS = ROW / 16;
+    typedef typename Codes<C>::type codes_t;
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_a[];    // [r][ROW]
+    __shared__ double s_delta[256];                                  // r <= 256
+    const int t = threadIdx.x, rank = static_cast<int>(blockIdx.x), part = static_cast<int>(blockIdx.y);
+    const int parts = static_cast<int>(gridDim.y);
+    uint64_t v[U];
+    load_keys(score, m, v);
+    __builtin_amdgcn_sched_barrier(0);
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    v4u ahead[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int q = i * kSelectThreads + t, p = q / CHUNKS;
+        const int64_t j = static_cast<int64_t>(part) * ROW + q % CHUNKS * 16;         // n is a multiple of 16
+        ahead[i] = *reinterpret_cast<const v4u*>(wq + (m + (p < r ? p : r - 1)) * n + (j < n ? j : n - 16));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int64_t row = select_row(v, k, rank);
+    if (row < 0 || row >= m) return;                                 // cannot happen; keeps every access in range
+    const int64_t col = static_cast<int64_t>(part) * ROW + t * C;     // the first of this thread's columns
+    const bool mine = t * C < ROW && col < n;
+    codes_t* const w = reinterpret_cast<codes_t*>(wq + row * n + col);
+    float delta = 0.0f;
+    if (t < r) delta = buf[row * r + t];
+    codes_t old = 0;
+    if (mine) old = *w;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int q = i * kSelectThreads + t;
+        if (q < r * CHUNKS) *reinterpret_cast<v4u*>(s_a + q * 16) = ahead[i];
+    }
+    if (t == 0 && part == 0) idx[rank] = static_cast<int32_t>(row);
+    if (t < 256) s_delta[t] = static_cast<double>(delta);            // (waits for it)
+    barrier_lds();                                              // all waves have read the row
+    unsigned long long* const words = arrived + static_cast<int64_t>(rank) * (r / 2);
+    unsigned long long before = 0;
+    if (clear_selected && parts > 1 && t == 0) before = atomicExch(&words[part], kArrived);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    decode_e4m3<C>(old, acc);
+    const uint8_t* column = s_a + (mine ? t * C : 0);
+    if (t < ROW / C) {                                               // (whole waves)
+        const double* d16 = s_delta + (t & 15);
+#pragma unroll 1
+        for (int p = 0; p < r; p += 16, column += 16 * ROW, d16 += 16) {   // r is a multiple of 16
+            codes_t a[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) a[u] = *reinterpret_cast<const codes_t*>(column + u * ROW);
+            const double d = *d16;
+            auto add = [&](auto tag) {
+                constexpr int N = decltype(tag)::value;
+                double x[4];
+                decode_e4m3<C>(a[N], x);
+                const double dn = of_row<N>(d);
+#pragma unroll
+                for (int e = 0; e < C; ++e) acc[e] = fma(dn, x[e], acc[e]);      // product is exact in fp64
+            };
+            for_each<16>(add);
+        }
+    }
+    if (mine) *w = static_cast<codes_t>(encode4_e4m3(acc));
+    if (!clear_selected || t >= 64) return;
+    if (parts > 1) {
+        if (t == 0) asm volatile("s_waitcnt vmcnt(0)" : : "v"(before) : "memory");
+        if (__ballot(t < parts && atomicOr(&words[t < parts ? t : 0], 0ull) != kArrived) != 0) return;
+    }
+    for (int p = t; p < r; p += 64) buf[row * r + p] = 0.0f;
+    if (parts > 1 && t < parts) atomicExch(&words[t], 0ull);
 }
 
 }  // namespace
@@ -625,18 +742,53 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
         if (e != hipSuccess) return e;
         scores_in = scores;
     }
+    // One launch where its workgroups, each of which repeats the selection, find room on the 256 CUs at one per CU (two
+    // rounds of them, 4096 x 4096 at r = 64, k = 64 with 512 columns each: 12.2 us for the update against 10.8 with 1024),
+    // their part of A~ fits into registers and LDS, and a rank's words fit into the room of its staged row.
+    if (k <= kSelectMaxK && m <= kSelectMaxRows) {
+        int64_t row = 512, parts = 0;
+        for (; row <= 2048; row *= 2) {
+            parts = (n + row - 1) / row;
+            if (k * parts <= 256) break;
+        }
+        if (row <= 2048 && r * row <= 128 * 1024 && parts <= 64 && 2 * parts <= r) {
+            auto go = [&](auto kernel) -> hipError_t {
+                const size_t lds = static_cast<size_t>(r * row);
+                if (lds > 48 * 1024) {
+                    const hipError_t fe = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+                    if (fe != hipSuccess) return fe;
+                }
+                kernel<<<dim3(static_cast<unsigned>(k), static_cast<unsigned>(parts)), kSelectThreads, lds, stream>>>(
+                    wq, n, m, static_cast<int>(r), scores_in, k, idx_out, delta_buf,
+                    reinterpret_cast<unsigned long long*>(delta_sel), clear_selected);
+                return hipGetLastError();
+            };
+            auto pick = [&](auto keys) -> hipError_t {
+                constexpr int U = decltype(keys)::value;
+                const bool few = r * row <= 4 * 8192;
+                if (row == 512) return few ? go(fold_kernel<U, 512, 4>) : go(fold_kernel<U, 512, 16>);
+                if (row == 1024) return few ? go(fold_kernel<U, 1024, 4>) : go(fold_kernel<U, 1024, 16>);
+                return few ? go(fold_kernel<U, 2048, 4>) : go(fold_kernel<U, 2048, 16>);
+            };
+            if (m <= 2 * kSelectThreads) return pick(std::integral_constant<int, 2>{});
+            if (m <= 8 * kSelectThreads) return pick(std::integral_constant<int, 8>{});
+            if (m <= 22 * kSelectThreads) return pick(std::integral_constant<int, 22>{});
+            return pick(std::integral_constant<int, 32>{});
+        }
+    }
     // The selection that finds one rank per workgroup, while the scores fit a workgroup's registers and the
     // group maxima bound the k-th score well (k of 128 groups).
     // Figures at the kernel; at the edge, 16384 rows and k = 96: 22.9 us against 31.4 for the whole update.
     if (k <= kSelectMaxK && m <= kSelectMaxRows) {
         auto go = [&](auto kernel) {
-            kernel<<<static_cast<unsigned>(k), kThreads, 0, stream>>>(scores_in, m, k, static_cast<int>(r), idx_out, delta_buf,
+            kernel<<<static_cast<unsigned>(k), kSelectThreads, 0, stream>>>(scores_in, m, k, static_cast<int>(r), idx_out, delta_buf,
                                                                       delta_sel, clear_selected);
         };
-        if (m <= 4 * kThreads) go(select_kernel<4>);
-        else if (m <= 16 * kThreads) go(select_kernel<16>);
-        else if (m <= 44 * kThreads) go(select_kernel<44>);
-        else go(select_kernel<64>);
+        if (m <= 2 * kSelectThreads) go(select_kernel<2>);
+        else if (m <= 8 * kSelectThreads) go(select_kernel<8>);
+        else if (m <= 42 * kSelectThreads) go(select_kernel<22>);
+        else go(select_kernel<32>);
     } else if (m > kChunk) {
         constexpr size_t lds_sel = sizeof(uint64_t) * kChunkFiltered;
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(&topk_filtered_kernel),

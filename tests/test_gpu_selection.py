@@ -67,3 +67,25 @@ def test_rows_and_order_are_the_oracles(m, k, kind):
     if "infinite" not in kind:                      # non-finite values: selection and buffer only
         idx_ref, w_ref, buf_ref = oracle.proxy_update(buf, wcat, m, r, k, True)
         assert np.array_equal(idx_ref, want) and np.array_equal(np_of(layer.wq), w_ref)
+
+
+# one launch up to 256 workgroups of 512, 1024 or 2048 columns and 128 KB of A~ each; beyond, two launches
+@pytest.mark.parametrize("m,n,r,k", [(304, 16, 16, 8), (1024, 528, 16, 96), (1040, 512, 48, 32), (96, 4096, 16, 32), (4096, 4112, 64, 28),
+                                     (704, 4096, 64, 64), (704, 4096, 64, 65), (512, 13824, 48, 36), (512, 13824, 64, 37), (400, 6160, 128, 40),
+                                     (272, 2064, 256, 50), (272, 2064, 256, 52), (272, 4096, 256, 33), (11280, 1040, 32, 9), (96, 8192, 16, 32)])
+def test_folded_rows_over_several_workgroups(m, n, r, k):
+    g = np.random.default_rng(m + n + r + k)
+    wcat = oracle.fp8_encode(g.integers(-8, 9, size=(m + r, n)).astype(np.float32), oracle.E4M3)
+    buf = (g.normal(size=(m, r)) * np.exp(1.5 * g.normal(size=(m, 1)))).astype(np.float32)
+    layer = layer_on_gpu(4, n, m, r, k, wcat, np.float32(1.0))
+    layer.ws.fill_(0x7f)
+    w, b = wcat, buf
+    for clear in (True, False, True):              # the second update sees what the first one has left
+        layer.delta_buf.copy_(torch.from_numpy(b))
+        layer.update(clear_selected=clear)
+        torch.cuda.synchronize()
+        idx_ref, w, left = oracle.proxy_update(b, w, m, r, k, clear)
+        assert np.array_equal(np_of(layer.idx), idx_ref)
+        assert np.array_equal(np_of(layer.wq), w)
+        assert np.array_equal(np_of(layer.delta_buf), left)
+        b = np.where(left == 0, np.float32(0.25), left)
