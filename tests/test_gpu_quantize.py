@@ -191,3 +191,23 @@ def test_one_launch_and_two_launches_match_the_oracle(fmt, dtype, rows, cols):
     q_ref, _, _ = oracle.quantize(x.float().numpy(), fmt, scale_in=np.float32(3.7))
     assert np.array_equal(np_of(q)[:, :cols], q_ref) and not np_of(q)[:, cols:].any()
     assert s.item() == given.item()
+
+
+# around the lines between one launch and two (256 KB) and between ordinary stores and ones past the caches (12 MB), the
+# largest value in the last piece
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("kb,pad", [(16, 0), (64, 16), (256, 0), (257, 0), (257, 32), (12 * 1024 - 1, 0), (12 * 1024, 0), (12 * 1024 + 5, 16)])
+def test_quantize_at_the_edges_of_its_launches(dtype, kb, pad):
+    es = 2 if dtype == torch.bfloat16 else 4
+    cols = 1024 // es                                        # a kilobyte per row
+    x = torch.randn(kb, cols + pad, generator=torch.Generator().manual_seed(kb)).to(dtype)
+    x[:, cols:] = 1e6                                        # must not be read
+    x[-1, cols - 1] = -37.5
+    q = torch.full((kb, cols + pad), 0xAB, dtype=torch.uint8, device="cuda")
+    s, amax = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    ws = torch.empty(8192, dtype=torch.uint8, device="cuda")
+    fq.quantize(x.cuda()[:, :cols], fq.E4M3, q[:, :cols], s, ws, amax_out=amax)
+    torch.cuda.synchronize()
+    ref, s_ref, amax_ref = oracle.quantize(x[:, :cols].float().numpy(), fq.E4M3)
+    assert np.float32(s.item()) == s_ref and amax.item() == 37.5
+    assert np.array_equal(np_of(q)[:, :cols], ref) and np.all(np_of(q)[:, cols:] == 0xAB)
