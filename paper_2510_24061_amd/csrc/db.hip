@@ -40,33 +40,35 @@ __device__ __forceinline__ float buffer_step(float buf, float lr, float g)
 }
 
 // dB = (sum of partials, split ascending) / (s_dy * s_oa);  delta_buf += -lr * dB.
-// A workgroup owns 64 rows of dB, a thread U runs of four columns at a time.  With `score` set (only
-// together with delta_buf) it keeps the new rows in LDS and leaves their L1 norms and the largest one
-// (row_scores.h).  Bound by latency: 1024 threads, so that all of a workgroup's loads are in flight at once
-// up to rank 64 (a quarter of the threads took four round trips: 9.5 against 6.5 us at 4096 x 64 with 8 partials and
-// scores, 24.9 against 17.4 at r = 256, kernel trace).
+// A workgroup owns ROWS rows of dB, a thread U runs of four columns at a time.  With `score` set (only
+// together with delta_buf) it keeps the new rows in LDS and leaves their L1 norms (row_scores.h).  Bound by latency and
+// by what one CU gets from memory.  Beyond 4096 rows a workgroup has 64 rows and 1024 threads, so that all its loads are
+// in flight at once up to rank 64 (a quarter of the threads took four round trips).  Ranks beyond 64 with up to 4096 rows:
+// 16 rows and 4 r threads, one run each, on four times as many CUs; the block maxima, which the caller has
+// cleared, are raised by four workgroups each (4096 x 256, 8 partials: 10.9 us, 17.3 in blocks of 64).
 constexpr int kReduceThreads = 1024;
 
-template <int U>
+template <int U, int ROWS>
 __global__ void __launch_bounds__(kReduceThreads)
 db_reduce_kernel(const float* __restrict__ partial, int splits, int64_t m, int r,
                  const float* __restrict__ s_dy, const float* __restrict__ amax_oa,
                  float* __restrict__ d_b, float* delta_buf, float lr, double* __restrict__ score)
 {
-    extern __shared__ float s_rows[];                                              // 64 x (r + 4) floats when score is set
+    extern __shared__ float s_rows[];                                              // ROWS x (r + 4) floats when score is set
     const int64_t count = m * r;
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kScoreRows;
+    const int threads = static_cast<int>(blockDim.x);
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
     const int64_t e0 = row0 * r;
-    int64_t e_end = e0 + static_cast<int64_t>(kScoreRows) * r;
+    int64_t e_end = e0 + static_cast<int64_t>(ROWS) * r;
     if (e_end > count) e_end = count;
     const int r4 = r / 4, pitch = r + 4;
     constexpr int B = 8;                                           // splits per batch
-    for (int64_t base = e0 + threadIdx.x * 4; base < e_end; base += static_cast<int64_t>(U) * kReduceThreads * 4) {
+    for (int64_t base = e0 + threadIdx.x * 4; base < e_end; base += static_cast<int64_t>(U) * threads * 4) {
         float4 s[U], d[U];
         if (delta_buf) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t e = base + static_cast<int64_t>(u) * kReduceThreads * 4;
+                const int64_t e = base + static_cast<int64_t>(u) * threads * 4;
                 if (e < e_end) d[u] = *reinterpret_cast<const float4*>(delta_buf + e);
             }
         }
@@ -74,7 +76,7 @@ db_reduce_kernel(const float* __restrict__ partial, int splits, int64_t m, int r
             float4 v[U][B];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t e = base + static_cast<int64_t>(u) * kReduceThreads * 4;
+                const int64_t e = base + static_cast<int64_t>(u) * threads * 4;
                 const int64_t ee = e < e_end ? e : e0;                   // beyond the block: a valid address, value unused
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
@@ -94,7 +96,7 @@ db_reduce_kernel(const float* __restrict__ partial, int splits, int64_t m, int r
         const float inv = 1.0f / ((*s_dy) * s_oa_scale);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t e = base + static_cast<int64_t>(u) * kReduceThreads * 4;
+            const int64_t e = base + static_cast<int64_t>(u) * threads * 4;
             if (e >= e_end) continue;
             float4 g = s[u];
             g.x *= inv; g.y *= inv; g.z *= inv; g.w *= inv;
@@ -115,7 +117,7 @@ db_reduce_kernel(const float* __restrict__ partial, int splits, int64_t m, int r
     }
     if (score) {
         __syncthreads();
-        score_rows_from_lds(s_rows, r, row0, m, score);
+        score_rows_from_lds<ROWS, ROWS != kScoreRows>(s_rows, r, row0, m, score);
     }
 }
 
@@ -157,26 +159,31 @@ hipError_t launch_db_partial(const DbArgs& d, hipStream_t stream)
     return hipGetLastError();
 }
 
+bool db_reduce_raises(int64_t m, int64_t r) { return r > 64 && m <= kScoreFew; }
+
 hipError_t launch_db_reduce(const DbArgs& d, const float* s_dy, float* d_b, float* delta_buf, float lr,
                             hipStream_t stream, double* score)
 {
     if (d.splits < 1) return hipErrorInvalidValue;
     if (!delta_buf) score = nullptr;                              // the scores are those of the buffer the step leaves
-    const size_t lds = score ? sizeof(float) * kScoreRows * (static_cast<size_t>(d.r) + 4) : 0;
-    const dim3 grid(static_cast<unsigned>(score_blocks(d.m)));
-    if (d.r <= 64) {
-        db_reduce_kernel<1><<<grid, kReduceThreads, lds, stream>>>(d.partial, d.splits, d.m, static_cast<int>(d.r), s_dy,
-                                                                   d.amax_oa, d_b, delta_buf, lr, score);
+    const bool few = db_reduce_raises(d.m, d.r);
+    const int rows = few ? kScoreRowsFew : kScoreRows;
+    const size_t lds = score ? sizeof(float) * rows * (static_cast<size_t>(d.r) + 4) : 0;
+    const dim3 grid(static_cast<unsigned>((d.m + rows - 1) / rows));
+    const unsigned threads = few ? static_cast<unsigned>(4 * d.r) : kReduceThreads;
+    auto go = [&](auto kernel) -> hipError_t {
+        if (lds > 64 * 1024) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+            if (e != hipSuccess) return e;
+        }
+        kernel<<<grid, threads, lds, stream>>>(d.partial, d.splits, d.m, static_cast<int>(d.r), s_dy, d.amax_oa, d_b, delta_buf,
+                                               lr, score);
         return hipGetLastError();
-    }
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&db_reduce_kernel<2>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-        if (e != hipSuccess) return e;
-    }
-    db_reduce_kernel<2><<<grid, kReduceThreads, lds, stream>>>(d.partial, d.splits, d.m, static_cast<int>(d.r), s_dy,
-                                                               d.amax_oa, d_b, delta_buf, lr, score);
-    return hipGetLastError();
+    };
+    if (few) return go(db_reduce_kernel<1, kScoreRowsFew>);
+    if (d.r <= 64) return go(db_reduce_kernel<1, kScoreRows>);
+    return go(db_reduce_kernel<2, kScoreRows>);
 }
 
 }  // namespace falqon

@@ -133,7 +133,7 @@ falqon_status falqon_quantize(const void* x, falqon_dtype xt, int64_t rows, int6
     if (!ws || ws_bytes < sizeof(float) * kMaxAmaxBlocks) return FALQON_ERR_WORKSPACE;
     if (misaligned(ws)) return FALQON_ERR_ALIGN;
     hipError_t e = launch_quantize(x, xt, empty ? 0 : rows, cols > 0 ? cols : 16, ld_x, fmt, scale_in, q, ld_q,
-                                   scale_out, amax_out, static_cast<float*>(ws), nullptr,
+                                   scale_out, amax_out, static_cast<float*>(ws), ZeroWords{nullptr, 0},
                                    static_cast<hipStream_t>(stream));
     return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
 }
@@ -162,7 +162,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     // caller's x~ and s_x are used as they are (several layers reading one input quantize it once).
     hipError_t e = x ? launch_quantize(x, FALQON_BF16, T, n, n, FALQON_E4M3, nullptr, xq, n, s_x, nullptr,
                                        reinterpret_cast<float*>(w8 + L.amax_partials),
-                                       reinterpret_cast<uint32_t*>(amax_oa), st)
+                                       ZeroWords{reinterpret_cast<uint32_t*>(amax_oa), 1}, st)
                      : launch_zero_word(reinterpret_cast<uint32_t*>(amax_oa), st);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
@@ -259,8 +259,10 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     const DbTailPlan pd = dx && !(least && r > 64) ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
     const int mid_parts = dx && !least ? mid_db_parts(T, n, m, r) : 0;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
+    ZeroWords zero{nullptr, 0};
+    if (row_scores && delta_buf && db_reduce_raises(m, r)) zero = {reinterpret_cast<uint32_t*>(row_scores + m), static_cast<int>(2 * score_blocks(m))};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
-                                   reinterpret_cast<float*>(w8 + L.amax_partials), nullptr, st, pd.use || mid_parts ? &sc : nullptr);
+                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || mid_parts ? &sc : nullptr);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
     // dX <- dy~ W~ / (s_dy s_w): the backbone rows of the concatenated weight, read as [K = m, N = n]

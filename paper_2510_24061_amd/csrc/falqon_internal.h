@@ -28,14 +28,15 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least);
 int db_splits(int64_t T, int64_t m);
 
 // ---- quantizer (quantize.hip) ------------------------------------------------------------
-// Two launches, per-block partial maxima, then scale + cast; one for small tensors.  `zero_word` (nullable)
-// is a device word that the call clears, used to reset the running maximum of O_A.
+// Two launches, per-block partial maxima, then scale + cast; one for small tensors.  `zero` names device words (up to
+// 256) that the call clears: the running maximum of O_A, or block maxima of row scores.
 // `side` (nullable): a small dense bf16 tensor of `count` elements (a multiple of 16) with a known
 // maximum that the cast pass casts to E4M3 along the way, q = cast(x * (448 / max(*amax, 1e-12f))).
 struct SideCast { const uint16_t* x; const float* amax; uint8_t* q; int64_t count; };
+struct ZeroWords { uint32_t* words; int count; };
 hipError_t launch_quantize(const void* x, falqon_dtype xt, int64_t rows, int64_t cols, int64_t ld_x,
                            falqon_fmt fmt, const float* scale_in, uint8_t* q, int64_t ld_q,
-                           float* scale_out, float* amax_out, float* partials, uint32_t* zero_word,
+                           float* scale_out, float* amax_out, float* partials, ZeroWords zero,
                            hipStream_t stream, const SideCast* side = nullptr);
 // Clears one device word with a kernel (a memset node is not safe inside a captured graph here).
 hipError_t launch_zero_word(uint32_t* w, hipStream_t stream);
@@ -101,7 +102,9 @@ DbArgs make_db_args(const uint8_t* dyq, const void* o_a, const float* amax_oa, i
                     float* partials, int splits);
 hipError_t launch_db_partial(const DbArgs& d, hipStream_t stream);
 // score (nullable, used only with delta_buf): row scores of the buffer after the step, in the layout
-// of row_scores.h (m scores, then one maximum per block of 64 rows).
+// of row_scores.h (m scores, then one maximum per block of 64 rows; these must be zero before where
+// db_reduce_raises(m, r)).
+bool db_reduce_raises(int64_t m, int64_t r);
 hipError_t launch_db_reduce(const DbArgs& d, const float* s_dy, float* d_b, float* delta_buf, float lr,
                             hipStream_t stream, double* score = nullptr);
 // Variant with O_A kept in bf16 (db_wide.hip): d.amax_oa is not read and may be null, also in the reduce.

@@ -35,24 +35,27 @@ constexpr size_t kStaticScoreBytes = sizeof(double) * (kStaticMaxRows + kStaticM
 constexpr size_t kStaticBytes = kStaticScoreBytes + sizeof(float) * kStaticMaxSelected;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
-// grid: ceil(m / 64); dynamic LDS: 64 * (r + 4) floats.  1024 threads: one round trip up to rank 64.
+// grid: ceil(m / ROWS); dynamic LDS: ROWS * (r + 4) floats.  Blocks of 64 rows: 1024 threads, one round trip up to rank
+// 64; blocks of 16, up to 4096 rows: 4 r threads, one always (update at 4096 x 256 16.2 us, 17.1 in blocks of 64; x 64
+// 9.7 and 9.9).
 constexpr int kScoreThreads = 1024;
 
+template <int ROWS>
 __global__ void __launch_bounds__(kScoreThreads)
 row_score_kernel(const float* __restrict__ buf, int64_t m, int r, double* __restrict__ score)
 {
     extern __shared__ float s_rows[];
     const int pitch = r + 4;                                         // +16 B: rows start on different banks
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kScoreRows;
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
     const int r4 = r / 4;
-    for (int e = threadIdx.x; e < kScoreRows * r4; e += kScoreThreads) {
+    for (int e = threadIdx.x; e < ROWS * r4; e += blockDim.x) {
         const int row = e / r4, c4 = e - row * r4;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (row0 + row < m) v = *reinterpret_cast<const float4*>(buf + (row0 + row) * r + c4 * 4);
         *reinterpret_cast<float4*>(s_rows + row * pitch + c4 * 4) = v;
     }
     __syncthreads();
-    score_rows_from_lds(s_rows, r, row0, m, score);
+    score_rows_from_lds<ROWS>(s_rows, r, row0, m, score);
 }
 
 // C adjacent E4M3 codes
@@ -344,6 +347,7 @@ select_kernel(const double* __restrict__ score, int64_t m, int64_t k, int r, int
 }
 
 constexpr int kChunk = 4096;                                         // scores that fit the small selection's LDS (32 KB)
+static_assert(kScoreFew <= kChunk, "the block maxima are there where the selection for larger buffers runs");
 static_assert(65536 / kScoreRows <= kChunk, "the block maxima of the largest buffer (m <= 65536) fit the LDS chunk");
 
 // Selection for buffers of up to kChunk rows.  A workgroup ranks 16 rows (4 waves x 4 consecutive
@@ -730,14 +734,17 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
 {
     hipError_t e;
     if (!scores_in) {
-        const size_t lds = sizeof(float) * kScoreRows * (static_cast<size_t>(r) + 4);
+        const bool few = m <= kScoreFew;
+        const int rows = few ? kScoreRowsFew : kScoreRows;
+        const size_t lds = sizeof(float) * rows * (static_cast<size_t>(r) + 4);
         if (lds > 64 * 1024) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&row_score_kernel),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&row_score_kernel<kScoreRows>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
             if (e != hipSuccess) return e;
         }
-        row_score_kernel<<<static_cast<unsigned>(score_blocks(m)), kScoreThreads, lds, stream>>>(delta_buf, m,
-                                                                                                 static_cast<int>(r), scores);
+        const unsigned blocks = static_cast<unsigned>((m + rows - 1) / rows);
+        if (few) row_score_kernel<kScoreRowsFew><<<blocks, static_cast<unsigned>(4 * r), lds, stream>>>(delta_buf, m, static_cast<int>(r), scores);
+        else row_score_kernel<kScoreRows><<<blocks, kScoreThreads, lds, stream>>>(delta_buf, m, static_cast<int>(r), scores);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         scores_in = scores;

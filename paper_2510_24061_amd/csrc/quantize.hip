@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(kThreads)
 scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, int64_t ld_x,
                   const float* __restrict__ partials, int n_partials, const float* __restrict__ scale_in,
                   uint8_t* __restrict__ q, int64_t ld_q, float* __restrict__ scale_out,
-                  float* __restrict__ amax_out, uint32_t* __restrict__ zero_word, const SideCast side, int side_blocks)
+                  float* __restrict__ amax_out, const ZeroWords zero, const SideCast side, int side_blocks)
 {
     __shared__ float smem[kThreads / 64];
     constexpr int E = Piece<T>::E;
@@ -207,8 +207,8 @@ scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, in
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *scale_out = s;
         if (amax_out) *amax_out = amax;
-        if (zero_word) *zero_word = 0u;
     }
+    if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < zero.count) zero.words[threadIdx.x] = 0u;
 }
 
 // Both passes in one launch for small tensors: every workgroup takes the maximum of the whole tensor itself
@@ -223,7 +223,7 @@ template <typename T, int FMT, bool DENSE>
 __global__ void __launch_bounds__(kOneThreads)
 quantize_one_kernel(const T* __restrict__ x, int n_pieces, int64_t per_row, int64_t ld_x,
                     const float* __restrict__ scale_in, uint8_t* __restrict__ q, int64_t ld_q, float* __restrict__ scale_out,
-                    float* __restrict__ amax_out, uint32_t* __restrict__ zero_word, const SideCast side, int side_blocks)
+                    float* __restrict__ amax_out, const ZeroWords zero, const SideCast side, int side_blocks)
 {
     __shared__ float smem[kOneThreads / 64];
     constexpr int E = Piece<T>::E, SHARE = kVec / E;                 // pieces of its share per thread
@@ -267,8 +267,8 @@ quantize_one_kernel(const T* __restrict__ x, int n_pieces, int64_t per_row, int6
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *scale_out = s;
         if (amax_out) *amax_out = amax;
-        if (zero_word) *zero_word = 0u;
     }
+    if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < zero.count) zero.words[threadIdx.x] = 0u;
 }
 
 __global__ void zero_word_kernel(uint32_t* w) { *w = 0u; }
@@ -276,7 +276,7 @@ __global__ void zero_word_kernel(uint32_t* w) { *w = 0u; }
 template <typename T>
 hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt fmt, const float* scale_in,
                uint8_t* q, int64_t ld_q, float* scale_out, float* amax_out, float* partials,
-               uint32_t* zero_word, const SideCast* side_job, hipStream_t stream)
+               ZeroWords zero, const SideCast* side_job, hipStream_t stream)
 {
     SideCast side{nullptr, nullptr, nullptr, 0};
     if (side_job) side = *side_job;                                  // (count: a multiple of 16)
@@ -290,7 +290,7 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
         const dim3 grid(static_cast<unsigned>(main_blocks + side_blocks));
         auto go = [&](auto kernel) {
             kernel<<<grid, kOneThreads, 0, stream>>>(x, static_cast<int>(n_pieces), per_row, ld_x, scale_in, q, ld_q, scale_out,
-                                                     amax_out, zero_word, side, side_blocks);
+                                                     amax_out, zero, side, side_blocks);
         };
         if (fmt == FALQON_E4M3) { if (dense) go(quantize_one_kernel<T, FALQON_E4M3, true>); else go(quantize_one_kernel<T, FALQON_E4M3, false>); }
         else { if (dense) go(quantize_one_kernel<T, FALQON_E5M2, true>); else go(quantize_one_kernel<T, FALQON_E5M2, false>); }
@@ -313,7 +313,7 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     const dim3 grid(static_cast<unsigned>(blocks + side_blocks));
     auto go = [&](auto kernel) {
         kernel<<<grid, kThreads, 0, stream>>>(x, n_pieces, per_row, ld_x, partials, n_partials, scale_in, q, ld_q, scale_out,
-                                              amax_out, zero_word, side, side_blocks);
+                                              amax_out, zero, side, side_blocks);
     };
     // A product that follows finds small tensors' codes in the caches, and is bound by getting them: with stores past the
     // caches the step with tensors of 4 MB takes 65.0 us, with ordinary ones 60.8.  From 16 MB on the large tiles hide
@@ -339,14 +339,14 @@ hipError_t launch_zero_word(uint32_t* w, hipStream_t stream)
 
 hipError_t launch_quantize(const void* x, falqon_dtype xt, int64_t rows, int64_t cols, int64_t ld_x,
                            falqon_fmt fmt, const float* scale_in, uint8_t* q, int64_t ld_q,
-                           float* scale_out, float* amax_out, float* partials, uint32_t* zero_word,
+                           float* scale_out, float* amax_out, float* partials, ZeroWords zero,
                            hipStream_t stream, const SideCast* side)
 {
     if (xt == FALQON_BF16)
         return run(static_cast<const uint16_t*>(x), rows, cols, ld_x, fmt, scale_in, q, ld_q, scale_out,
-                   amax_out, partials, zero_word, side, stream);
+                   amax_out, partials, zero, side, stream);
     return run(static_cast<const float*>(x), rows, cols, ld_x, fmt, scale_in, q, ld_q, scale_out, amax_out,
-               partials, zero_word, side, stream);
+               partials, zero, side, stream);
 }
 
 }  // namespace falqon
