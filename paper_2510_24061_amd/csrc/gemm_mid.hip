@@ -191,6 +191,9 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 
     constexpr int RBK = RIDE ? mid_max(MB / 2, 1) : 0;           // 32x32 blocks of O_A per wave
     constexpr int NBK = MB * NB + RBK;
+    // The wave's token blocks in the order mi ^ perm, so that its blocks of O_A are on its first ones whatever wn is (a
+    // branch on wn in the steady loop made the compiler move accumulators about: a step took 1.7 times as long).
+    const int perm = RIDE && MB > 1 ? wn * RBK : 0;
     v16f acc[NBK];
 #pragma unroll
     for (int b = 0; b < NBK; ++b)
@@ -207,7 +210,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
             if constexpr (B_KN) read_kn(st + A_BYTES, wn * NB * 32 + f * 32, bt[P][f]);
             else bf[P][f] = read_kc(st + A_BYTES, wn * NB * 32 + f * 32 + (lane & 31));
         } else if (f < NB + MB) {
-            af[P][f - NB] = read_kc(st, (f - NB) * 32 + (lane & 31));
+            af[P][f - NB] = read_kc(st, ((f - NB) ^ perm) * 32 + (lane & 31));
         } else if (RIDE) {
             rf[P] = read_kc(st + A_BYTES + B_BYTES, lane & 31);
         }
@@ -334,12 +337,8 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         if constexpr (RIDE) {
             // wave column wn takes token blocks [wn * RBK, +RBK) of the tile (MB = 1: both form the one)
 #pragma unroll
-            for (int j = 0; j < RBK; ++j) {
-                if (MB > 1 && wn) acc[MB * NB + j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                    rf[P], af[P][MB > 1 ? RBK + j : 0], acc[MB * NB + j], 0, 0, 0, 0, 0, 0);
-                else acc[MB * NB + j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                    rf[P], af[P][j], acc[MB * NB + j], 0, 0, 0, 0, 0, 0);
-            }
+            for (int j = 0; j < RBK; ++j)
+                acc[MB * NB + j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(rf[P], af[P][j], acc[MB * NB + j], 0, 0, 0, 0, 0, 0);
         }
         landed(std::integral_constant<int, 1 - P>{});
     };
@@ -435,7 +434,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 #pragma unroll
             for (int ni = 0; ni < NB; ++ni) {
                 if (((mi * NB + ni) & 1) != kh) continue;
-                uint8_t* srow = lds + (mi * 32 + (lane & 31)) * PITCH;
+                uint8_t* srow = lds + ((mi ^ perm) * 32 + (lane & 31)) * PITCH;
                 const v16f& a = acc[mi * NB + ni];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -506,7 +505,7 @@ gemm_mid_kernel(const MidArgs t)
 }
 
 // Adapter columns of their own cost nothing while they make no further round over the CUs; a step of a tile that
-// carries them along takes 1.7 times as long.  Returns the extra tile columns, 0: they ride.
+// carries them along takes 1.15 times as long.  Returns the extra tile columns, 0: they ride.
 int own_columns(int64_t tiles_m, int64_t tiles_n, int64_t r, int bn)
 {
     const int64_t own = (r + bn - 1) / bn;
@@ -548,7 +547,8 @@ bool gemm_mid_supported(int64_t M, int64_t N)
 // us = launch + rounds over the CUs x (round + K-steps x (step + step_full x part of the CUs that are busy)): a
 // workgroup is alone on its CU, so every round pays the way into its rings and out again, and a step takes longer
 // the more CUs draw on the memory.  Fitted to products of 20 sizes with K from 64 to 8192 (graphs of 10; the fit is
-// within 5 %, and the choice by it 0.2 % slower than the best of all on average).  Tiles that find room in one
+// within 5 %, and the choice by it 0.2 % slower than the best of all on average; with the riding steps at 1.15 and 1.0 us
+// for their way out, forwards of 44 drawn layers are 0.1 % off the best on average, 3 % at worst).  Tiles that find room in one
 // round win; 2 to 8 rounds of smaller ones take up to twice as long (1024 x 4096, K = 128: 12.2 us in four rounds of
 // 64x64, 7.7 with 128x128).
 MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_is_kn, int64_t r)
@@ -569,7 +569,7 @@ MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_is_kn, int64_t r)
         const double busy = tiles < kMidCus ? static_cast<double>(tiles) / kMidCus : 1.0;
         const double us = k.launch + (r && !own ? 1.0 : 0.0) +
                           static_cast<double>((tiles + kMidCus - 1) / kMidCus) *
-                              (k.round + steps * (r && !own ? 1.7 : 1.0) * (k.step + k.step_full * busy));
+                              (k.round + steps * (r && !own ? 1.15 : 1.0) * (k.step + k.step_full * busy));
         if (c == 0 || us < best.us) best = MidPlan{c, cfg[c].bm, tn, us};
     }
     return best;
