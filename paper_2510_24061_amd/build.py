@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfalqon.so")
-SOURCES = ["falqon_api.hip", "quantize.hip", "gemm.hip", "gemm_mid.hip", "partials.hip", "db.hip", "proxy.hip", "optimizer.hip", "init.hip",
+SOURCES = ["falqon_api.hip", "quantize.hip", "gemm.hip", "gemm_mid.hip", "gemm_thin.hip", "partials.hip", "db.hip", "proxy.hip", "optimizer.hip", "init.hip",
            "db_wide.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -158,6 +158,12 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t* w8 = static_cast<uint8_t*>(ws);
 
+    // A few tokens: everything in one launch.
+    if (x && fwd_thin_supported(T, n, m, r)) {
+        const hipError_t te = launch_fwd_thin(x, wq, s_w, T, n, m, r, xq, s_x, y, yt == FALQON_F32, o_a, amax_oa, w8 + L.amax_partials, st);
+        return te == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    }
+
     // x~, s_x <- Q_E4M3(x); the cast pass also resets the running maximum of O_A.  Without x the
     // caller's x~ and s_x are used as they are (several layers reading one input quantize it once).
     hipError_t e = x ? launch_quantize(x, FALQON_BF16, T, n, n, FALQON_E4M3, nullptr, xq, n, s_x, nullptr,

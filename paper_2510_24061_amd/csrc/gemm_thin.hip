@@ -1,0 +1,234 @@
+// Forward of a few tokens (a step of generation): quantizer, backbone product and O_A in one launch.
+//
+// With T <= 16 the weight is all there is to move, and in two launches it waits for the quantizer.  Here every
+// workgroup quantizes the whole input for itself (at most 64 KB of bf16 from the L2: maximum, scale, codes into LDS),
+// while its weights, which do not depend on it, are already on the way.  They go straight from memory into operand
+// registers, each byte to one wave: no LDS ring, and no barrier between the steps.
+//
+// v_mfma_f32_16x16x128: lane t holds row t % 16 of an operand and 32 of its 128 K-bytes; as long as both operands
+// agree it does not matter which, so it takes bytes [16 q, +16) and [64 + 16 q, +16), q = t / 16, and a load covers 64
+// bytes of a row.  First operand: output columns, second: tokens, so a lane ends with four adjacent columns of one
+// token.  Eight waves: NCB column blocks of 16 x KS shares of the K-steps (3 x 2: six waves multiply), which meet in LDS.
+// NCB is the smallest that gives every CU one workgroup.  The first ones form O_A.  Its maximum needs no clear before:
+// each of them exchanges a word in the workspace for its own maximum under a mark, waits for the exchange and reads the
+// words of all; the one whose exchange is the last finds all marked (so may others, which then write the same),
+// writes the maximum and takes the words back.  The mark is a NaN's bits, which no maximum in the workspace has.
+//
+// Against quantizer and product in two launches (gemm_mid.hip), us per forward call, four layers in turn:
+//   1 x 4096 -> 4096, r = 64    9.2 (11.0)     2 x 4096 -> 1024, r = 64    6.9 (11.0)     3 x 1040 -> 2000, r = 48   5.8 (8.4)
+//   4 x 4096 -> 4096, r = 32    9.2 (12.2)     16 x 2048 -> 2048, r = 64   9.8 (10.4)     1 x 4096 -> 11008, r = 64 11.9 (13.3)
+//   8 x 4096 -> 4096, r = 64   12.1 (12.3)     16 x 256 -> 256, r = 16     6.1 (6.6)      8 x 4096 -> 11008, r = 64 15.1 (15.1)
+#include "falqon_internal.h"
+#include "gemm_common.h"
+#include "quantize_common.h"
+
+namespace falqon {
+namespace {
+
+constexpr int64_t kThinNarrow = 254 * 32;                  // m + r up to which a workgroup has 16 or 32 columns
+typedef unsigned short v2s __attribute__((ext_vector_type(2)));
+
+constexpr int kThinThreads = 512, kThinMaxTokens = 16, kThinMaxRank = 64;
+constexpr int64_t kThinMaxCodes = 32 * 1024, kThinMaxK = 4096;     // T n, n
+constexpr unsigned long long kThinArrived = 0x7fa57c3eull;
+constexpr int kThinPieces = 8;                             // 16-byte pieces of x per thread: 512 x 8 x 8 elements
+
+struct ThinArgs {
+    const uint16_t* x; const uint8_t* wq; const float* s_w;
+    int T; int64_t n, m; int r;
+    uint8_t* xq; float* s_x; void* y; int y_is_f32; uint16_t* o_a; float* amax_oa;
+    unsigned long long* words;                             // one per workgroup of O_A, any contents without kThinArrived
+    int pad;                                               // K-bytes per token in LDS, zeros behind n
+};
+
+// K-steps (128 bytes) in flight per wave
+constexpr int thin_depth(int ks) { return ks == 2 ? 8 : 4; }
+constexpr int thin_unit(int ks) { return ks * thin_depth(ks) * BK; }
+
+// accumulates 16 NCB columns (weight rows from `first` on, `last` the last valid one) of all tokens; the result is in the
+// waves of share 0, one block of 16 x 16 each
+template <int NCB, int KS, typename Codes>
+__device__ __forceinline__ v4f thin_columns(const ThinArgs& a, int64_t first, int64_t last, const uint8_t* lds_x, v4f* exchange,
+                                            Codes&& codes)
+{
+    constexpr int D = thin_depth(KS);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int cb = wave % NCB, kh = wave / NCB;
+    const bool works = kh < KS;
+    int64_t row = first + 16 * cb + (lane & 15);
+    row = row < last ? row : last;
+    const uint8_t* const w = a.wq + row * a.n;
+    const int q16 = (lane >> 4) * 16;
+    const int batches = static_cast<int>((a.n + thin_unit(KS) - 1) / thin_unit(KS));
+    v4i lo[D], hi[D];
+    // step i of this wave: K-bytes from 128 (kh + KS i) on; beyond n the tokens are zero, and the row's first bytes stand in
+    auto fetch = [&](int i, int d) {
+        const int64_t k = static_cast<int64_t>(kh + KS * i) * BK + q16;
+        lo[d] = *reinterpret_cast<const v4i*>(w + (k < a.n ? k : 0));
+        hi[d] = *reinterpret_cast<const v4i*>(w + (k + 64 < a.n ? k + 64 : 0));
+    };
+    if (works) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) fetch(d, d);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    codes();                                               // the tokens' codes are in LDS behind this
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (works) {
+        const int token = (lane & 15) < a.T ? lane & 15 : a.T - 1;
+        const uint8_t* const xrow = lds_x + token * (a.pad + 16) + q16;
+        for (int b = 0; b < batches; ++b) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int k = (kh + KS * (b * D + d)) * BK;
+                const v4i xl = *reinterpret_cast<const v4i*>(xrow + k), xh = *reinterpret_cast<const v4i*>(xrow + k + 64);
+                v8i wv, xv;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { wv[u] = lo[d][u]; wv[4 + u] = hi[d][u]; xv[u] = xl[u]; xv[4 + u] = xh[u]; }
+                acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wv, xv, acc, 0, 0, 0, 0, 0, 0);
+                if (b + 1 < batches) fetch((b + 1) * D + d, d);
+            }
+        }
+        if (kh > 0) exchange[(wave - NCB) * 64 + lane] = acc;
+    }
+    __syncthreads();
+    if (kh == 0)
+        for (int s = 1; s < KS; ++s) acc += exchange[((s - 1) * NCB + cb) * 64 + lane];
+    __syncthreads();                                       // the exchange may be written again
+    return acc;
+}
+
+template <int NCB, int KS>
+__global__ void __launch_bounds__(kThinThreads)
+fwd_thin_kernel(const ThinArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_x[];       // [T][pad + 16]
+    __shared__ float s_max[kThinThreads / 64];
+    __shared__ __attribute__((aligned(16))) v4f s_exchange[6 * 64 + 64];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int pieces = static_cast<int>(a.T * a.n / 8), per_row = static_cast<int>(a.n / 8);
+    v4u xr[kThinPieces];
+#pragma unroll
+    for (int i = 0; i < kThinPieces; ++i) {
+        if (i * kThinThreads >= pieces) break;                            // uniform
+        const int p = i * kThinThreads + t;
+        xr[i] = *reinterpret_cast<const v4u*>(a.x + static_cast<int64_t>(p < pieces ? p : pieces - 1) * 8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float s = 1.0f;
+    auto codes = [&]() {
+        v2s top = {0, 0};                                                 // bf16 without signs order as integers
+        auto largest = [](v4u w, v2s m) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m = __builtin_elementwise_max(m, __builtin_bit_cast(v2s, w[u] & 0x7fff7fffu));
+            return m;
+        };
+#pragma unroll
+        for (int i = 0; i < kThinPieces; ++i) {
+            if (i * kThinThreads >= pieces) break;
+            top = largest(xr[i], top);
+        }
+        const float m = __uint_as_float(static_cast<uint32_t>(top[0] > top[1] ? top[0] : top[1]) << 16);
+        const float amax = block_max<kThinThreads / 64>(m, s_max);
+        s = 448.0f / fmaxf(amax, 1e-12f);                                 // the quantizer's scale
+#pragma unroll
+        for (int i = 0; i < kThinPieces; ++i) {
+            if (i * kThinThreads >= pieces) break;
+            const int p = i * kThinThreads + t;
+            if (p >= pieces) continue;
+            const Piece<uint16_t>::codes_t c = cast_piece<uint16_t, FALQON_E4M3>(xr[i], s);
+            const int token = p / per_row, col = (p - token * per_row) * 8;
+            *reinterpret_cast<Piece<uint16_t>::codes_t*>(lds_x + token * (a.pad + 16) + col) = c;
+            // the workgroups share out the codes in memory
+            if (static_cast<unsigned>(i * (kThinThreads / 64) + wave) % gridDim.x == blockIdx.x)
+                *reinterpret_cast<Piece<uint16_t>::codes_t*>(a.xq + static_cast<int64_t>(p) * 8) = c;
+        }
+        const int fill = (a.pad - static_cast<int>(a.n)) / 16;
+        for (int q = t; q < a.T * fill; q += kThinThreads)
+            *reinterpret_cast<v4u*>(lds_x + (q / fill) * (a.pad + 16) + a.n + (q % fill) * 16) = v4u{0, 0, 0, 0};
+        if (blockIdx.x == 0 && t == 0) *a.s_x = s;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        barrier_lds_only();
+    };
+    const int token = lane & 15, quad = lane >> 4, adapters = (a.r + 16 * NCB - 1) / (16 * NCB);
+    const bool adapter = static_cast<int>(blockIdx.x) < adapters;
+    const int64_t first = adapter ? a.m + static_cast<int64_t>(blockIdx.x) * 16 * NCB
+                                  : (static_cast<int64_t>(blockIdx.x) - adapters) * 16 * NCB;
+    const v4f acc = thin_columns<NCB, KS>(a, first, adapter ? a.m + a.r - 1 : a.m - 1, lds_x, s_exchange, codes);
+    if (adapter) {
+        const float inv = 1.0f / (s * (*a.s_w));
+        float top = 0.0f;
+        const int64_t col = first - a.m + 16 * (wave % NCB) + 4 * quad;
+        if (wave < NCB && token < a.T && col < a.r) {
+            uint2 pk;
+            pk.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+            pk.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+            *reinterpret_cast<uint2*>(a.o_a + static_cast<int64_t>(token) * a.r + col) = pk;
+            top = fmaxf(fmaxf(fabsf(__uint_as_float(pk.x << 16)), fabsf(__uint_as_float(pk.x & 0xffff0000u))),
+                        fmaxf(fabsf(__uint_as_float(pk.y << 16)), fabsf(__uint_as_float(pk.y & 0xffff0000u))));
+        }
+        top = block_max<kThinThreads / 64>(top, s_max);
+        if (adapters == 1) {
+            if (t == 0) *a.amax_oa = top;
+            return;
+        }
+        if (t >= 64) return;
+        if (t == 0) {
+            const unsigned long long before = atomicExch(&a.words[blockIdx.x], kThinArrived << 32 | __float_as_uint(top));
+            asm volatile("s_waitcnt vmcnt(0)" : : "v"(before) : "memory");
+        }
+        const unsigned long long word = t < adapters ? atomicOr(&a.words[t], 0ull) : kThinArrived << 32;
+        if (__ballot(word >> 32 != kThinArrived)) return;
+        const float all = wave_max(__uint_as_float(static_cast<uint32_t>(word)));
+        if (t == 0) *a.amax_oa = all;
+        if (t < adapters) atomicExch(&a.words[t], 0ull);
+        return;
+    }
+    const float inv = 1.0f / (s * (*a.s_w));
+    const int64_t col = first + 16 * (wave % NCB) + 4 * quad;
+    if (wave >= NCB || token >= a.T || col >= a.m) return;
+    if (a.y_is_f32) {
+        *reinterpret_cast<v4f*>(static_cast<float*>(a.y) + token * a.m + col) = v4f{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+    } else {
+        uint2 pk;
+        pk.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+        pk.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.y) + token * a.m + col) = pk;
+    }
+}
+
+}  // namespace
+
+// Every workgroup pays for quantizing the whole input: at T n = 64 K that takes longer than a launch (16 x 4096 -> 4096 15.2
+// us against 12.4), at 32 K as long.  Beyond n = 4096 the workgroups' rows get too long for the loads a wave has in flight
+// (4 x 11008 -> 4096 20.4 against 18.8).  Wide layers take their K in units of 2048, which a short one does not fill (1 x 256
+// -> 13824 7.4 against 6.7).
+bool fwd_thin_supported(int64_t T, int64_t n, int64_t m, int64_t r)
+{
+    return (n >= 512 || m + r <= kThinNarrow) && T <= kThinMaxTokens && T * n <= kThinMaxCodes && n <= kThinMaxK && r <= kThinMaxRank;
+}
+
+hipError_t launch_fwd_thin(const void* x, const uint8_t* wq, const float* s_w, int64_t T, int64_t n, int64_t m, int64_t r,
+                           uint8_t* xq, float* s_x, void* y, bool y_is_f32, void* o_a, float* amax_oa, void* words, hipStream_t stream)
+{
+    ThinArgs a;
+    a.x = static_cast<const uint16_t*>(x); a.wq = wq; a.s_w = s_w; a.T = static_cast<int>(T); a.n = n; a.m = m; a.r = static_cast<int>(r);
+    a.xq = xq; a.s_x = s_x; a.y = y; a.y_is_f32 = y_is_f32; a.o_a = static_cast<uint16_t*>(o_a); a.amax_oa = amax_oa;
+    a.words = static_cast<unsigned long long*>(words);
+    auto go = [&](auto kernel, int ncb, int ks) -> hipError_t {
+        const int64_t pad = (n + thin_unit(ks) - 1) / thin_unit(ks) * thin_unit(ks);
+        a.pad = static_cast<int>(pad);
+        const size_t lds = static_cast<size_t>(T) * (pad + 16);           // 32 KB of codes and up to one unit per token
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 static_cast<int>(lds));
+        if (e != hipSuccess) return e;
+        kernel<<<static_cast<unsigned>((m + 16 * ncb - 1) / (16 * ncb) + (r + 16 * ncb - 1) / (16 * ncb)), kThinThreads, lds, stream>>>(a);
+        return hipGetLastError();
+    };
+    if (m + r <= 256 * 16) return go(fwd_thin_kernel<1, 8>, 1, 8);
+    if (m + r <= kThinNarrow) return go(fwd_thin_kernel<2, 4>, 2, 4);
+    if (m + r <= 254 * 48) return go(fwd_thin_kernel<3, 2>, 3, 2);
+    return go(fwd_thin_kernel<4, 2>, 4, 2);
+}
+
+}  // namespace falqon

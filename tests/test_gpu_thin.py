@@ -1,0 +1,44 @@
+"""Forward of up to 16 tokens in one launch: every split of its workgroups (16 to 64 columns, two to eight shares of the
+K-steps), ragged tokens, columns and K, ranks up to 64 in it and beyond it, on exact-integer data (fp32 outputs bit for
+bit) and against the same call on codes quantized beforehand, which takes other launches."""
+import pytest
+import torch
+
+import paper_2510_24061_amd as fq
+from gpu_common import relf, np_of
+from test_gpu_layer import _exact_integer_layer
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 16, 16, 16), (1, 4096, 4096, 64), (2, 144, 272, 48), (7, 1040, 4080, 64), (8, 2064, 4096, 16), (8, 4096, 528, 64),
+          (15, 2064, 8160, 32), (16, 2048, 8176, 64), (9, 2048, 12240, 64), (3, 272, 12256, 48), (10, 3264, 144, 64), (13, 400, 16400, 16),
+          (17, 400, 528, 64), (7, 4112, 144, 32), (5, 1024, 1040, 80)]
+
+
+@pytest.mark.parametrize("T,n,m,r", [s for s in SHAPES if s[0] >= 10] + [(10, 16, 16, 16), (10, 3008, 4080, 64), (12, 272, 12256, 48)])
+def test_exact_integer_layer_is_bit_exact(T, n, m, r):
+    _exact_integer_layer(T, n, m, r)
+
+
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,n,m,r", SHAPES[:12])
+def test_matches_the_call_on_quantized_input(T, n, m, r, out_dtype):
+    g = torch.Generator().manual_seed(T + n)
+    layer = fq.MeldedLinear(T, n, m, r, 8, out_dtype=out_dtype)
+    layer.init_weights((torch.randn(m, n, generator=g) * 0.02).cuda(), (torch.randn(r, n, generator=g) / r).cuda())
+    x = torch.randn(T, n, generator=g).to(torch.bfloat16)
+    x[T - 1, n - 1] = -9.0
+    for b in (layer.y, layer.o_a):
+        b.fill_(7.0)
+    layer.forward(x.cuda())
+    y, o_a, amax = layer.y.clone(), layer.o_a.clone(), layer.amax_oa.clone()
+    xq, s = torch.empty_like(layer.xq), torch.zeros(1, device="cuda")
+    fq.quantize(x.cuda(), fq.E4M3, xq, s, layer.ws)
+    torch.cuda.synchronize()
+    assert torch.equal(xq, layer.xq) and torch.equal(s, layer.s_x)                # bit for bit the quantizer's
+    assert float(amax) == float(o_a.float().abs().max())
+    fq.melded_fwd(None, layer.wq, layer.s_w, m, r, xq, s, layer.y, layer.o_a, layer.amax_oa, layer.ws)
+    torch.cuda.synchronize()
+    # sums in another order: fp32 rounding of up to n terms, or half a unit of bf16 on either side of a tie
+    assert relf(np_of(y), np_of(layer.y)) <= (1e-5 if out_dtype == torch.float32 else 1e-3)
+    assert relf(np_of(o_a), np_of(layer.o_a)) <= 1e-3
