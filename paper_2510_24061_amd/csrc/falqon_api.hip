@@ -159,7 +159,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     uint8_t* w8 = static_cast<uint8_t*>(ws);
 
     // A few tokens: everything in one launch.
-    if (x && fwd_thin_supported(T, n, m, r)) {
+    if (x && fwd_thin_supported(T, n, r)) {
         const hipError_t te = launch_fwd_thin(x, wq, s_w, T, n, m, r, xq, s_x, y, yt == FALQON_F32, o_a, amax_oa, w8 + L.amax_partials, st);
         return te == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
     }

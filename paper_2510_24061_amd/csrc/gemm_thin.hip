@@ -15,9 +15,9 @@
 // writes the maximum and takes the words back.  The mark is a NaN's bits, which no maximum in the workspace has.
 //
 // Against quantizer and product in two launches (gemm_mid.hip), us per forward call, four layers in turn:
-//   1 x 4096 -> 4096, r = 64    9.2 (11.0)     2 x 4096 -> 1024, r = 64    6.9 (11.0)     3 x 1040 -> 2000, r = 48   5.8 (8.4)
-//   4 x 4096 -> 4096, r = 32    9.2 (12.2)     16 x 2048 -> 2048, r = 64   9.8 (10.4)     1 x 4096 -> 11008, r = 64 11.9 (13.3)
-//   8 x 4096 -> 4096, r = 64   12.1 (12.3)     16 x 256 -> 256, r = 16     6.1 (6.6)      8 x 4096 -> 11008, r = 64 15.1 (15.1)
+//   1 x 4096 -> 4096, r = 64    9.6 (11.0)     2 x 4096 -> 1024, r = 64    6.7 (11.0)     3 x 1040 -> 2000, r = 48   5.0 (8.4)
+//   4 x 4096 -> 4096, r = 32    9.1 (12.2)     16 x 2048 -> 2048, r = 64   7.4 (10.4)     1 x 4096 -> 11008, r = 64 11.5 (13.3)
+//   8 x 4096 -> 4096, r = 64   11.5 (12.3)     16 x 256 -> 256, r = 16     3.8 (6.6)      8 x 4096 -> 11008, r = 64 13.7 (15.1)
 #include "falqon_internal.h"
 #include "gemm_common.h"
 #include "quantize_common.h"
@@ -38,12 +38,13 @@ struct ThinArgs {
     int T; int64_t n, m; int r;
     uint8_t* xq; float* s_x; void* y; int y_is_f32; uint16_t* o_a; float* amax_oa;
     unsigned long long* words;                             // one per workgroup of O_A, any contents without kThinArrived
+    uint32_t per_row_inverse;                              // ceil(2^32 / (n / 8)): quotients below 2^16 are exact
     int pad;                                               // K-bytes per token in LDS, zeros behind n
 };
 
-// K-steps (128 bytes) in flight per wave
-constexpr int thin_depth(int ks) { return ks == 2 ? 8 : 4; }
-constexpr int thin_unit(int ks) { return ks * thin_depth(ks) * BK; }
+// K-steps (128 bytes) of a wave, all of them in flight before the input is quantized (with half of them, 8 x 4096 -> 11008
+// took 15.1 us)
+constexpr int thin_steps(int ks) { return static_cast<int>(kThinMaxK) / (ks * BK); }
 
 // accumulates 16 NCB columns (weight rows from `first` on, `last` the last valid one) of all tokens; the result is in the
 // waves of share 0, one block of 16 x 16 each
@@ -51,46 +52,40 @@ template <int NCB, int KS, typename Codes>
 __device__ __forceinline__ v4f thin_columns(const ThinArgs& a, int64_t first, int64_t last, const uint8_t* lds_x, v4f* exchange,
                                             Codes&& codes)
 {
-    constexpr int D = thin_depth(KS);
+    constexpr int D = thin_steps(KS);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int cb = wave % NCB, kh = wave / NCB;
-    const bool works = kh < KS;
     int64_t row = first + 16 * cb + (lane & 15);
     row = row < last ? row : last;
+    const int n = static_cast<int>(a.n), q16 = (lane >> 4) * 16;
     const uint8_t* const w = a.wq + row * a.n;
-    const int q16 = (lane >> 4) * 16;
-    const int batches = static_cast<int>((a.n + thin_unit(KS) - 1) / thin_unit(KS));
+    // step d of this wave: K-bytes from 128 (kh + KS d) on; beyond n the tokens are zero, and the row's first bytes stand in
+    const int steps = kh < KS ? ((n + BK - 1) / BK - kh + KS - 1) / KS : 0;
     v4i lo[D], hi[D];
-    // step i of this wave: K-bytes from 128 (kh + KS i) on; beyond n the tokens are zero, and the row's first bytes stand in
-    auto fetch = [&](int i, int d) {
-        const int64_t k = static_cast<int64_t>(kh + KS * i) * BK + q16;
-        lo[d] = *reinterpret_cast<const v4i*>(w + (k < a.n ? k : 0));
-        hi[d] = *reinterpret_cast<const v4i*>(w + (k + 64 < a.n ? k + 64 : 0));
-    };
-    if (works) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) fetch(d, d);
+    for (int d = 0; d < D; ++d) {
+        const int k = (kh + KS * d) * BK + q16;
+        if (d < steps) {                                   // uniform
+            lo[d] = *reinterpret_cast<const v4i*>(w + (k < n ? k : 0));
+            hi[d] = *reinterpret_cast<const v4i*>(w + (k + 64 < n ? k + 64 : 0));
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
     codes();                                               // the tokens' codes are in LDS behind this
     v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (works) {
-        const int token = (lane & 15) < a.T ? lane & 15 : a.T - 1;
-        const uint8_t* const xrow = lds_x + token * (a.pad + 16) + q16;
-        for (int b = 0; b < batches; ++b) {
+    const int token = (lane & 15) < a.T ? lane & 15 : a.T - 1;
+    const uint8_t* const xrow = lds_x + token * (a.pad + 16) + q16;
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                const int k = (kh + KS * (b * D + d)) * BK;
-                const v4i xl = *reinterpret_cast<const v4i*>(xrow + k), xh = *reinterpret_cast<const v4i*>(xrow + k + 64);
-                v8i wv, xv;
+    for (int d = 0; d < D; ++d) {
+        if (d >= steps) continue;
+        const int k = (kh + KS * d) * BK;
+        const v4i xl = *reinterpret_cast<const v4i*>(xrow + k), xh = *reinterpret_cast<const v4i*>(xrow + k + 64);
+        v8i wv, xv;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { wv[u] = lo[d][u]; wv[4 + u] = hi[d][u]; xv[u] = xl[u]; xv[4 + u] = xh[u]; }
-                acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wv, xv, acc, 0, 0, 0, 0, 0, 0);
-                if (b + 1 < batches) fetch((b + 1) * D + d, d);
-            }
-        }
-        if (kh > 0) exchange[(wave - NCB) * 64 + lane] = acc;
+        for (int u = 0; u < 4; ++u) { wv[u] = lo[d][u]; wv[4 + u] = hi[d][u]; xv[u] = xl[u]; xv[4 + u] = xh[u]; }
+        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wv, xv, acc, 0, 0, 0, 0, 0, 0);
     }
+    if (kh > 0 && kh < KS) exchange[(wave - NCB) * 64 + lane] = acc;
     __syncthreads();
     if (kh == 0)
         for (int s = 1; s < KS; ++s) acc += exchange[((s - 1) * NCB + cb) * 64 + lane];
@@ -137,10 +132,11 @@ fwd_thin_kernel(const ThinArgs a)
             const int p = i * kThinThreads + t;
             if (p >= pieces) continue;
             const Piece<uint16_t>::codes_t c = cast_piece<uint16_t, FALQON_E4M3>(xr[i], s);
-            const int token = p / per_row, col = (p - token * per_row) * 8;
+            const int token = static_cast<int>(__umulhi(static_cast<uint32_t>(p), a.per_row_inverse)), col = (p - token * per_row) * 8;
             *reinterpret_cast<Piece<uint16_t>::codes_t*>(lds_x + token * (a.pad + 16) + col) = c;
             // the workgroups share out the codes in memory
-            if (static_cast<unsigned>(i * (kThinThreads / 64) + wave) % gridDim.x == blockIdx.x)
+            const unsigned share = i * (kThinThreads / 64) + wave;
+            if ((gridDim.x >= kThinPieces * kThinThreads / 64 ? share : share % gridDim.x) == blockIdx.x)
                 *reinterpret_cast<Piece<uint16_t>::codes_t*>(a.xq + static_cast<int64_t>(p) * 8) = c;
         }
         const int fill = (a.pad - static_cast<int>(a.n)) / 16;
@@ -199,13 +195,12 @@ fwd_thin_kernel(const ThinArgs a)
 
 }  // namespace
 
-// Every workgroup pays for quantizing the whole input: at T n = 64 K that takes longer than a launch (16 x 4096 -> 4096 15.2
-// us against 12.4), at 32 K as long.  Beyond n = 4096 the workgroups' rows get too long for the loads a wave has in flight
-// (4 x 11008 -> 4096 20.4 against 18.8).  Wide layers take their K in units of 2048, which a short one does not fill (1 x 256
-// -> 13824 7.4 against 6.7).
-bool fwd_thin_supported(int64_t T, int64_t n, int64_t m, int64_t r)
+// Every workgroup pays for quantizing the whole input: built for T n = 64 K that took longer than a launch (16 x 4096 ->
+// 4096 15.2 us against 12.4; 8 tokens 11.5 against 12.3).  Beyond n = 4096 a wave's share of the rows does not fit its registers
+// (in two batches 4 x 11008 -> 4096 20.4 us against 18.8).
+bool fwd_thin_supported(int64_t T, int64_t n, int64_t r)
 {
-    return (n >= 512 || m + r <= kThinNarrow) && T <= kThinMaxTokens && T * n <= kThinMaxCodes && n <= kThinMaxK && r <= kThinMaxRank;
+    return T <= kThinMaxTokens && T * n <= kThinMaxCodes && n <= kThinMaxK && r <= kThinMaxRank;
 }
 
 hipError_t launch_fwd_thin(const void* x, const uint8_t* wq, const float* s_w, int64_t T, int64_t n, int64_t m, int64_t r,
@@ -215,20 +210,21 @@ hipError_t launch_fwd_thin(const void* x, const uint8_t* wq, const float* s_w, i
     a.x = static_cast<const uint16_t*>(x); a.wq = wq; a.s_w = s_w; a.T = static_cast<int>(T); a.n = n; a.m = m; a.r = static_cast<int>(r);
     a.xq = xq; a.s_x = s_x; a.y = y; a.y_is_f32 = y_is_f32; a.o_a = static_cast<uint16_t*>(o_a); a.amax_oa = amax_oa;
     a.words = static_cast<unsigned long long*>(words);
-    auto go = [&](auto kernel, int ncb, int ks) -> hipError_t {
-        const int64_t pad = (n + thin_unit(ks) - 1) / thin_unit(ks) * thin_unit(ks);
+    a.per_row_inverse = static_cast<uint32_t>(((uint64_t(1) << 32) + n / 8 - 1) / (n / 8));       // n >= 16
+    auto go = [&](auto kernel, int ncb) -> hipError_t {
+        const int64_t pad = (n + BK - 1) / BK * BK;
         a.pad = static_cast<int>(pad);
-        const size_t lds = static_cast<size_t>(T) * (pad + 16);           // 32 KB of codes and up to one unit per token
+        const size_t lds = static_cast<size_t>(T) * (pad + 16);           // 32 KB of codes and up to one K-step per token
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  static_cast<int>(lds));
         if (e != hipSuccess) return e;
         kernel<<<static_cast<unsigned>((m + 16 * ncb - 1) / (16 * ncb) + (r + 16 * ncb - 1) / (16 * ncb)), kThinThreads, lds, stream>>>(a);
         return hipGetLastError();
     };
-    if (m + r <= 256 * 16) return go(fwd_thin_kernel<1, 8>, 1, 8);
-    if (m + r <= kThinNarrow) return go(fwd_thin_kernel<2, 4>, 2, 4);
-    if (m + r <= 254 * 48) return go(fwd_thin_kernel<3, 2>, 3, 2);
-    return go(fwd_thin_kernel<4, 2>, 4, 2);
+    if (m + r <= 256 * 16) return go(fwd_thin_kernel<1, 8>, 1);
+    if (m + r <= kThinNarrow) return go(fwd_thin_kernel<2, 4>, 2);
+    if (m + r <= 254 * 48) return go(fwd_thin_kernel<3, 2>, 3);
+    return go(fwd_thin_kernel<4, 2>, 4);
 }
 
 }  // namespace falqon
