@@ -168,7 +168,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     // caller's x~ and s_x are used as they are (several layers reading one input quantize it once).
     hipError_t e = x ? launch_quantize(x, FALQON_BF16, T, n, n, FALQON_E4M3, nullptr, xq, n, s_x, nullptr,
                                        reinterpret_cast<float*>(w8 + L.amax_partials),
-                                       ZeroWords{reinterpret_cast<uint32_t*>(amax_oa), 1}, st)
+                                       ZeroWords{reinterpret_cast<uint32_t*>(amax_oa), 1}, st, nullptr, m)
                      : launch_zero_word(reinterpret_cast<uint32_t*>(amax_oa), st);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
@@ -268,7 +268,7 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
     ZeroWords zero{nullptr, 0};
     if (row_scores && delta_buf && db_reduce_raises(m, r)) zero = {reinterpret_cast<uint32_t*>(row_scores + m), static_cast<int>(2 * score_blocks(m))};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
-                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || mid_parts ? &sc : nullptr);
+                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || mid_parts ? &sc : nullptr, dx ? n : r);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
     // dX <- dy~ W~ / (s_dy s_w): the backbone rows of the concatenated weight, read as [K = m, N = n]

@@ -28,6 +28,7 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least);
 int db_splits(int64_t T, int64_t m);
 
 // ---- quantizer (quantize.hip) ------------------------------------------------------------
+// next_width: columns of the product that reads the codes next, 0 if unknown.
 // Two launches, per-block partial maxima, then scale + cast; one for small tensors.  `zero` names device words (up to
 // 256) that the call clears: the running maximum of O_A, or block maxima of row scores.
 // `side` (nullable): a small dense bf16 tensor of `count` elements (a multiple of 16) with a known
@@ -37,7 +38,7 @@ struct ZeroWords { uint32_t* words; int count; };
 hipError_t launch_quantize(const void* x, falqon_dtype xt, int64_t rows, int64_t cols, int64_t ld_x,
                            falqon_fmt fmt, const float* scale_in, uint8_t* q, int64_t ld_q,
                            float* scale_out, float* amax_out, float* partials, ZeroWords zero,
-                           hipStream_t stream, const SideCast* side = nullptr);
+                           hipStream_t stream, const SideCast* side = nullptr, int64_t next_width = 0);
 // Clears one device word with a kernel (a memset node is not safe inside a captured graph here).
 hipError_t launch_zero_word(uint32_t* w, hipStream_t stream);
 

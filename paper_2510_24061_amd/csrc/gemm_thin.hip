@@ -214,10 +214,7 @@ hipError_t launch_fwd_thin(const void* x, const uint8_t* wq, const float* s_w, i
     auto go = [&](auto kernel, int ncb) -> hipError_t {
         const int64_t pad = (n + BK - 1) / BK * BK;
         a.pad = static_cast<int>(pad);
-        const size_t lds = static_cast<size_t>(T) * (pad + 16);           // 32 KB of codes and up to one K-step per token
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 static_cast<int>(lds));
-        if (e != hipSuccess) return e;
+        const size_t lds = static_cast<size_t>(T) * (pad + 16);           // 35 KB at most
         kernel<<<static_cast<unsigned>((m + 16 * ncb - 1) / (16 * ncb) + (r + 16 * ncb - 1) / (16 * ncb)), kThinThreads, lds, stream>>>(a);
         return hipGetLastError();
     };

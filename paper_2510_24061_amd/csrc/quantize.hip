@@ -187,7 +187,7 @@ __global__ void zero_word_kernel(uint32_t* w) { *w = 0u; }
 template <typename T>
 hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt fmt, const float* scale_in,
                uint8_t* q, int64_t ld_q, float* scale_out, float* amax_out, float* partials,
-               ZeroWords zero, const SideCast* side_job, hipStream_t stream)
+               ZeroWords zero, const SideCast* side_job, int64_t next_width, hipStream_t stream)
 {
     SideCast side{nullptr, nullptr, nullptr, 0};
     if (side_job) side = *side_job;                                  // (count: a multiple of 16)
@@ -229,13 +229,14 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     // A product that follows finds small tensors' codes in the caches, and is bound by getting them: with stores past the
     // caches the step with tensors of 4 MB takes 65.0 us, with ordinary ones 60.8.  From 16 MB on the large tiles hide
     // the way from memory and the cast gains: three layers on 17 MB 340.5 against 343 to 348, steps with 33 MB 163.2
-    // against 166.
+    // against 166.  A narrow product (next_width columns) does not: 5314 x 2928 -> 496 57.9 against 55.8.  Its time per code
+    // is that of reading it at about 250 columns; the line is at eight times that.
     auto by_rows = [&](auto past) {
         constexpr bool P = decltype(past)::value;
         if (fmt == FALQON_E4M3) { if (dense) go(scale_cast_kernel<T, FALQON_E4M3, true, P>); else go(scale_cast_kernel<T, FALQON_E4M3, false, P>); }
         else { if (dense) go(scale_cast_kernel<T, FALQON_E5M2, true, P>); else go(scale_cast_kernel<T, FALQON_E5M2, false, P>); }
     };
-    if (n_pieces * 16 >= (12 << 20)) by_rows(std::true_type{});
+    if (n_pieces * 16 >= (12 << 20) && (next_width == 0 || next_width >= 2048)) by_rows(std::true_type{});
     else by_rows(std::false_type{});
     return hipGetLastError();
 }
@@ -251,13 +252,13 @@ hipError_t launch_zero_word(uint32_t* w, hipStream_t stream)
 hipError_t launch_quantize(const void* x, falqon_dtype xt, int64_t rows, int64_t cols, int64_t ld_x,
                            falqon_fmt fmt, const float* scale_in, uint8_t* q, int64_t ld_q,
                            float* scale_out, float* amax_out, float* partials, ZeroWords zero,
-                           hipStream_t stream, const SideCast* side)
+                           hipStream_t stream, const SideCast* side, int64_t next_width)
 {
     if (xt == FALQON_BF16)
         return run(static_cast<const uint16_t*>(x), rows, cols, ld_x, fmt, scale_in, q, ld_q, scale_out,
-                   amax_out, partials, zero, side, stream);
+                   amax_out, partials, zero, side, next_width, stream);
     return run(static_cast<const float*>(x), rows, cols, ld_x, fmt, scale_in, q, ld_q, scale_out, amax_out,
-               partials, zero, side, stream);
+               partials, zero, side, next_width, stream);
 }
 
 }  // namespace falqon
