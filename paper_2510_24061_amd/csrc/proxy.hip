@@ -102,6 +102,20 @@ __device__ __forceinline__ uint32_t encode4_e4m3(const double (&acc)[4])
 constexpr int kSelectGroups = 128, kSelectMaxK = 96, kSelectCands = 2 * kSelectMaxK + 32, kSelectThreads = 512;
 constexpr int kSelectMaxRows = 32 * kSelectThreads;
 
+// f(U) with the fewest keys per thread, of those that the kernels are built for, that hold m <= kSelectMaxRows rows
+template <int U, int... More, typename F>
+hipError_t first_that_holds(int64_t m, F f)
+{
+    if constexpr (sizeof...(More) > 0) {
+        if (m > static_cast<int64_t>(U) * kSelectThreads) return first_that_holds<More...>(m, f);
+    } else {
+        static_assert(U * kSelectThreads >= kSelectMaxRows, "every row has a thread that holds its key");
+    }
+    return f(std::integral_constant<int, U>{});
+}
+template <typename F>
+hipError_t with_keys(int64_t m, F f) { return first_that_holds<2, 8, 22, 32>(m, f); }
+
 // a value of another lane of the same sixteen; 0xB1: lane ^ 1, 0x4E: lane ^ 2 (quad_perm), 0x141 / 0x140: mirrored
 // within eight / sixteen, 0x150 + N: lane N
 template <int CTRL>
@@ -778,24 +792,19 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
                 if (row == 1024) return few ? go(fold_kernel<U, 1024, 4>) : go(fold_kernel<U, 1024, 16>);
                 return few ? go(fold_kernel<U, 2048, 4>) : go(fold_kernel<U, 2048, 16>);
             };
-            if (m <= 2 * kSelectThreads) return pick(std::integral_constant<int, 2>{});
-            if (m <= 8 * kSelectThreads) return pick(std::integral_constant<int, 8>{});
-            if (m <= 22 * kSelectThreads) return pick(std::integral_constant<int, 22>{});
-            return pick(std::integral_constant<int, 32>{});
+            return with_keys(m, pick);
         }
     }
     // The selection that finds one rank per workgroup, while the scores fit a workgroup's registers and the
     // group maxima bound the k-th score well (k of 128 groups).
     // Figures at the kernel; at the edge, 16384 rows and k = 96: 22.9 us against 31.4 for the whole update.
     if (k <= kSelectMaxK && m <= kSelectMaxRows) {
-        auto go = [&](auto kernel) {
-            kernel<<<static_cast<unsigned>(k), kSelectThreads, 0, stream>>>(scores_in, m, k, static_cast<int>(r), idx_out, delta_buf,
-                                                                      delta_sel, clear_selected);
-        };
-        if (m <= 2 * kSelectThreads) go(select_kernel<2>);
-        else if (m <= 8 * kSelectThreads) go(select_kernel<8>);
-        else if (m <= 42 * kSelectThreads) go(select_kernel<22>);
-        else go(select_kernel<32>);
+        e = with_keys(m, [&](auto keys) -> hipError_t {
+            select_kernel<decltype(keys)::value><<<static_cast<unsigned>(k), kSelectThreads, 0, stream>>>(
+                scores_in, m, k, static_cast<int>(r), idx_out, delta_buf, delta_sel, clear_selected);
+            return hipGetLastError();
+        });
+        if (e != hipSuccess) return e;
     } else if (m > kChunk) {
         constexpr size_t lds_sel = sizeof(uint64_t) * kChunkFiltered;
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(&topk_filtered_kernel),

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import oracle
+import paper_2510_24061_amd as fq
 from gpu_common import layer_on_gpu, np_of
 
 pytestmark = pytest.mark.gpu
@@ -42,6 +43,8 @@ def _buffer(kind, m, r, g):
     elif kind == "half infinite":
         buf[:] = g.normal(size=(m, r))
         buf[1::2, 3] = np.inf
+    elif kind == "last":                           # the largest at the end
+        buf[:] = g.normal(size=(m, r)) + 4.0 * np.arange(m)[:, None] / m
     return buf
 
 
@@ -89,3 +92,33 @@ def test_folded_rows_over_several_workgroups(m, n, r, k):
         assert np.array_equal(np_of(layer.wq), w)
         assert np.array_equal(np_of(layer.delta_buf), left)
         b = np.where(left == 0, np.float32(0.25), left)
+
+
+# never one launch: 128 KB of A~ have room for 512 columns, of which 96 rows would take 288 workgroups
+@pytest.mark.parametrize("m", [112, 1040, 4096, 4112, 11264, 11280, 13824, 16384])
+@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "alike", "outliers", "clustered", "infinite", "half infinite", "last"])
+def test_rows_and_order_in_two_launches(m, kind):
+    n, r, k = 1040, 256, 96
+    g = np.random.default_rng(m + k)
+    buf = _buffer(kind, m, r, g)
+    wcat = oracle.fp8_encode(g.integers(-8, 9, size=(m + r, n)).astype(np.float32), oracle.E4M3)
+    want = np.lexsort((np.arange(m), -oracle.row_scores(buf)))[:k]
+    left = buf.copy()
+    left[want] = 0.0
+    w_ref = None
+    if "infinite" not in kind:
+        idx_ref, w_ref, _ = oracle.proxy_update(buf, wcat, m, r, k, True)
+        assert np.array_equal(idx_ref, want)
+    layer = layer_on_gpu(1, n, m, r, k, wcat, np.float32(1.0))
+    for static in (False, True):
+        layer.wq.copy_(torch.from_numpy(wcat))
+        layer.delta_buf.copy_(torch.from_numpy(buf))
+        layer.idx.fill_(-1)
+        if static:
+            fq.proxy_update_static(layer.delta_buf, layer.wq, m, r, k, layer.idx)
+        else:
+            layer.update()
+        torch.cuda.synchronize()
+        assert np.array_equal(np_of(layer.idx), want), static
+        assert np.array_equal(np_of(layer.delta_buf), left), static
+        assert w_ref is None or np.array_equal(np_of(layer.wq), w_ref), static
