@@ -112,10 +112,15 @@ fwd_thin_kernel(const ThinArgs a)
     __builtin_amdgcn_sched_barrier(0);
     float s = 1.0f;
     auto codes = [&]() {
-        v2s top = {0, 0};                                                 // bf16 without signs order as integers
+        // bf16 without signs order as integers, NaN above all.  Counted from the first NaN and modulo 2^16 it is the NaN
+        // that come below everything else: they leave the maximum of the other values, as in the quantizer.
+        constexpr unsigned short kFirstNan = 0x7f81;
+        constexpr unsigned short kZero = 65536 - kFirstNan;
+        v2s top = {kZero, kZero};
         auto largest = [](v4u w, v2s m) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) m = __builtin_elementwise_max(m, __builtin_bit_cast(v2s, w[u] & 0x7fff7fffu));
+            for (int u = 0; u < 4; ++u)
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(v2s, w[u] & 0x7fff7fffu) - v2s{kFirstNan, kFirstNan});
             return m;
         };
 #pragma unroll
@@ -123,7 +128,8 @@ fwd_thin_kernel(const ThinArgs a)
             if (i * kThinThreads >= pieces) break;
             top = largest(xr[i], top);
         }
-        const float m = __uint_as_float(static_cast<uint32_t>(top[0] > top[1] ? top[0] : top[1]) << 16);
+        const uint32_t bits = ((top[0] > top[1] ? top[0] : top[1]) + kFirstNan) & 0xffffu;
+        const float m = __uint_as_float(bits << 16);
         const float amax = block_max<kThinThreads / 64>(m, s_max);
         s = 448.0f / fmaxf(amax, 1e-12f);                                 // the quantizer's scale
 #pragma unroll

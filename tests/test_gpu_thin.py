@@ -42,3 +42,59 @@ def test_matches_the_call_on_quantized_input(T, n, m, r, out_dtype):
     # sums in another order: fp32 rounding of up to n terms, or half a unit of bf16 on either side of a tie
     assert relf(np_of(y), np_of(layer.y)) <= (1e-5 if out_dtype == torch.float32 else 1e-3)
     assert relf(np_of(o_a), np_of(layer.o_a)) <= 1e-3
+
+
+def _bits(x, values):
+    """x (bf16) with the given positions set to the given bit patterns"""
+    u = x.view(torch.int16)
+    for (t, j), b in values.items():
+        u[t, j] = b - 65536 if b > 32767 else b
+    return x
+
+
+# A maximum is that of the values that are not NaN, as in the quantizer; positions beside and far from one another, so
+# that values of one thread and of several are concerned
+@pytest.mark.parametrize("name", ["beside the largest", "a token", "all", "infinite", "infinite and NaN", "smallest NaNs", "zeros and NaN"])
+@pytest.mark.parametrize("T,n,m,r", [(8, 4096, 272, 64), (1, 4096, 144, 16), (5, 272, 528, 48), (16, 2048, 400, 64), (16, 16, 16, 16)])
+def test_not_finite_inputs_have_the_quantizers_codes(T, n, m, r, name):
+    g = torch.Generator().manual_seed(T + n)
+    layer = fq.MeldedLinear(T, n, m, r, 8)
+    layer.init_weights((torch.randn(m, n, generator=g) * 0.02).cuda(), (torch.randn(r, n, generator=g) / r).cuda())
+    x = torch.full((T, n), 0.5).to(torch.bfloat16) if name == "beside the largest" else torch.randn(T, n, generator=g).to(torch.bfloat16)
+    at, other = (T - 1, n - 12), (0, 3)
+    bad = set()
+    if name == "beside the largest":
+        x[at[0], at[1] + 2] = 50.0
+        _bits(x, {at: 0x7fc0, (at[0], at[1] + 3): 0xffc0})
+        bad = {T - 1}
+    elif name == "a token":
+        _bits(x, {(T - 1, j): 0x7fc0 for j in range(n)})
+        bad = {T - 1}
+    elif name == "all":
+        x.fill_(float("nan"))
+        bad = set(range(T))
+    elif name == "infinite":
+        x[at], x[other] = float("inf"), float("-inf")
+    elif name == "infinite and NaN":
+        _bits(x, {at: 0x7f80, other: 0x7fff, (0, 4): 0xff80})
+    elif name == "smallest NaNs":
+        _bits(x, {at: 0x7f81, other: 0xff81})
+        bad = {T - 1, 0}
+    else:
+        x.zero_()
+        _bits(x, {other: 0x7fc0, at: 0x8000})
+        bad = {0}
+    for b in (layer.y, layer.o_a):
+        b.fill_(7.0)
+    layer.forward(x.cuda())
+    xq, s = torch.empty_like(layer.xq), torch.zeros(1, device="cuda")
+    fq.quantize(x.cuda(), fq.E4M3, xq, s, layer.ws)
+    torch.cuda.synchronize()
+    assert torch.equal(s, layer.s_x) and torch.equal(xq, layer.xq)
+    if "infinite" in name:
+        return                                                                    # (a scale of zero)
+    y, o_a = layer.y.clone(), layer.o_a.clone()
+    fq.melded_fwd(None, layer.wq, layer.s_w, m, r, xq, s, layer.y, layer.o_a, layer.amax_oa, layer.ws)
+    torch.cuda.synchronize()
+    rows = [t for t in range(T) if t not in bad]                                  # the other tokens are what they were
+    assert relf(np_of(y)[rows], np_of(layer.y)[rows]) <= 1e-3 and relf(np_of(o_a)[rows], np_of(layer.o_a)[rows]) <= 1e-3
