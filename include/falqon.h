@@ -113,6 +113,7 @@ falqon_status falqon_quantize(const void* x, falqon_dtype xt, int64_t rows, int6
  *   y        out  [T, m] of dtype yt
  *   o_a      out  bf16 [T, r]
  *   amax_oa  out  device scalar
+ * y and o_a may lie over x, which the first line alone reads.
  */
 falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s_w,
                                 int64_t T, int64_t n, int64_t m, int64_t r,

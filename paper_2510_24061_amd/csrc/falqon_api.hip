@@ -75,6 +75,12 @@ int oa_splits(int64_t T, int64_t r)
 
 static bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
+static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
+}
+
 static bool bad_layer_shape(int64_t T, int64_t n, int64_t m, int64_t r)
 {
     return T < 1 || n < 16 || m < 16 || r < 16 || (n % 16) || (m % 16) || (r % 16) || r > 256 ||
@@ -158,8 +164,10 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t* w8 = static_cast<uint8_t*>(ws);
 
-    // A few tokens: everything in one launch.
-    if (x && fwd_thin_supported(T, n, r)) {
+    // A few tokens: everything in one launch, unless outputs lie over x: each workgroup reads it, and some begin when
+    // others have written theirs.
+    if (x && fwd_thin_supported(T, n, r) && !overlap(x, 2 * T * n, y, (yt == FALQON_F32 ? 4 : 2) * T * m) &&
+        !overlap(x, 2 * T * n, o_a, 2 * T * r)) {
         const hipError_t te = launch_fwd_thin(x, wq, s_w, T, n, m, r, xq, s_x, y, yt == FALQON_F32, o_a, amax_oa, w8 + L.amax_partials, st);
         return te == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
     }

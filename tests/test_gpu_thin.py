@@ -98,3 +98,24 @@ def test_not_finite_inputs_have_the_quantizers_codes(T, n, m, r, name):
     torch.cuda.synchronize()
     rows = [t for t in range(T) if t not in bad]                                  # the other tokens are what they were
     assert relf(np_of(y)[rows], np_of(layer.y)[rows]) <= 1e-3 and relf(np_of(o_a)[rows], np_of(layer.o_a)[rows]) <= 1e-3
+
+
+@pytest.mark.parametrize("T,n,m", [(8, 4096, 4096), (16, 256, 32000), (3, 1008, 20000), (1, 4096, 8192)])
+def test_outputs_may_lie_over_the_input(T, n, m):
+    """The input is read by the quantizer alone, before anything else is written: y, or O_A, may take its memory."""
+    r, g = 64, torch.Generator().manual_seed(T)
+    layer = fq.MeldedLinear(T, n, m, r, 8)
+    layer.init_weights((torch.randn(m, n, generator=g) * 0.02).cuda(), (torch.randn(r, n, generator=g) / r).cuda())
+    x = torch.randn(T, n, generator=g).to(torch.bfloat16)
+    memory = torch.empty(T * (n + m), dtype=torch.bfloat16, device="cuda")
+    for first, o_a in [(0, layer.o_a), (T * n // 2 // 8 * 8, layer.o_a), (T * n, memory[:T * r].view(T, r))]:
+        memory.fill_(3.0)
+        memory[:T * n] = x.flatten().cuda()
+        xin, y = memory[:T * n].view(T, n), memory[first:first + T * m].view(T, m)
+        fq.melded_fwd(xin, layer.wq, layer.s_w, m, r, layer.xq, layer.s_x, y, o_a, layer.amax_oa, layer.ws)
+        torch.cuda.synchronize()
+        y, o_a = y.clone(), o_a.clone()
+        fq.quantize(x.cuda(), fq.E4M3, layer.xq, layer.s_x, layer.ws)
+        fq.melded_fwd(None, layer.wq, layer.s_w, m, r, layer.xq, layer.s_x, layer.y, layer.o_a, layer.amax_oa, layer.ws)
+        torch.cuda.synchronize()
+        assert relf(np_of(y), np_of(layer.y)) <= 1e-3 and relf(np_of(o_a), np_of(layer.o_a)) <= 1e-3, first
