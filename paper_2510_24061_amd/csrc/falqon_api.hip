@@ -166,7 +166,7 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
 
     // A few tokens: everything in one launch, unless outputs lie over x: each workgroup reads it, and some begin when
     // others have written theirs.
-    if (x && fwd_thin_supported(T, n, r) && !overlap(x, 2 * T * n, y, (yt == FALQON_F32 ? 4 : 2) * T * m) &&
+    if (x && fwd_thin_supported(T, n, m, r) && !overlap(x, 2 * T * n, y, (yt == FALQON_F32 ? 4 : 2) * T * m) &&
         !overlap(x, 2 * T * n, o_a, 2 * T * r)) {
         const hipError_t te = launch_fwd_thin(x, wq, s_w, T, n, m, r, xq, s_x, y, yt == FALQON_F32, o_a, amax_oa, w8 + L.amax_partials, st);
         return te == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;

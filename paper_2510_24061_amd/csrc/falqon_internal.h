@@ -64,7 +64,7 @@ hipError_t launch_gemm_fwd_pair(const GemmArgs& g, const GemmArgs& h, hipStream_
 
 // Forward of a few tokens, quantizer included, in one launch (gemm_thin.hip): x~, s_x, y, O_A and its maximum.
 // words: 32 bytes of scratch.
-bool fwd_thin_supported(int64_t T, int64_t n, int64_t r);
+bool fwd_thin_supported(int64_t T, int64_t n, int64_t m, int64_t r);
 hipError_t launch_fwd_thin(const void* x, const uint8_t* wq, const float* s_w, int64_t T, int64_t n, int64_t m, int64_t r,
                            uint8_t* xq, float* s_x, void* y, bool y_is_f32, void* o_a, float* amax_oa, void* words, hipStream_t stream);
 

@@ -29,7 +29,7 @@ constexpr int64_t kThinNarrow = 254 * 32;                  // m + r up to which 
 typedef unsigned short v2s __attribute__((ext_vector_type(2)));
 
 constexpr int kThinThreads = 512, kThinMaxTokens = 16, kThinMaxRank = 64;
-constexpr int64_t kThinMaxCodes = 32 * 1024, kThinMaxK = 4096;     // T n, n
+constexpr int64_t kThinMaxCodes = 32 * 1024, kThinMaxK = 4096, kThinTwoRoundsK = 1024;     // T n, n, n
 constexpr unsigned long long kThinArrived = 0x7fa57c3eull;
 constexpr int kThinPieces = 8;                             // 16-byte pieces of x per thread: 512 x 8 x 8 elements
 
@@ -204,9 +204,16 @@ fwd_thin_kernel(const ThinArgs a)
 // Every workgroup pays for quantizing the whole input: built for T n = 64 K that took longer than a launch (16 x 4096 ->
 // 4096 15.2 us against 12.4; 8 tokens 11.5 against 12.3).  Beyond n = 4096 a wave's share of the rows does not fit its registers
 // (in two batches 4 x 11008 -> 4096 20.4 us against 18.8).
-bool fwd_thin_supported(int64_t T, int64_t n, int64_t r)
+// And workgroups that find no CU free begin when others have ended, with a quantizer of their own again: in two rounds
+// 1 x 4096 -> 16400 took 22.8 us against 19.7 in two launches, 16 x 2048 -> 24000 19.1 against 16.5, 8 x 2048 -> 32512
+// 18.8 against 18.7; up to n = 1024 they are still ahead (16 x 1024 -> 16400 11.6 against 12.2, -> 32512 13.2 against 13.6,
+// 1 x 256 -> 32512 7.0 against 8.8).  In three or more they are not (16 x 1024 -> 36000 17.5 against 15.8, 16 x 256 -> 49152
+// 12.3 against 11.2).
+bool fwd_thin_supported(int64_t T, int64_t n, int64_t m, int64_t r)
 {
-    return T <= kThinMaxTokens && T * n <= kThinMaxCodes && n <= kThinMaxK && r <= kThinMaxRank;
+    const int64_t workgroups = (m + 63) / 64 + (r + 63) / 64;          // (fewer columns each as long as that makes one round)
+    return T <= kThinMaxTokens && T * n <= kThinMaxCodes && n <= kThinMaxK && r <= kThinMaxRank &&
+           workgroups <= (n <= kThinTwoRoundsK ? 512 : 256);
 }
 
 hipError_t launch_fwd_thin(const void* x, const uint8_t* wq, const float* s_w, int64_t T, int64_t n, int64_t m, int64_t r,

@@ -119,3 +119,9 @@ def test_outputs_may_lie_over_the_input(T, n, m):
         fq.melded_fwd(None, layer.wq, layer.s_w, m, r, layer.xq, layer.s_x, layer.y, layer.o_a, layer.amax_oa, layer.ws)
         torch.cuda.synchronize()
         assert relf(np_of(y), np_of(layer.y)) <= 1e-3 and relf(np_of(o_a), np_of(layer.o_a)) <= 1e-3, first
+
+
+# one round of workgroups of 64 columns, two up to n = 1024, and the first sizes beyond
+@pytest.mark.parametrize("T,n,m,r", [(2, 4096, 16320, 64), (2, 4096, 16336, 64), (3, 1040, 16336, 16), (16, 1024, 32704, 64), (5, 1024, 32720, 48)])
+def test_at_the_most_columns(T, n, m, r):
+    test_matches_the_call_on_quantized_input(T, n, m, r, torch.bfloat16)
