@@ -95,7 +95,7 @@ def test_folded_rows_over_several_workgroups(m, n, r, k):
 
 
 # never one launch: 128 KB of A~ have room for 512 columns, of which 96 rows would take 288 workgroups
-@pytest.mark.parametrize("m", [112, 1040, 4096, 4112, 11264, 11280, 13824, 16384])
+@pytest.mark.parametrize("m", [112, 272, 1040, 4096, 4112, 11264, 11280, 13824, 16384])
 @pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "alike", "outliers", "clustered", "infinite", "half infinite", "last"])
 def test_rows_and_order_in_two_launches(m, kind):
     n, r, k = 1040, 256, 96
@@ -122,3 +122,11 @@ def test_rows_and_order_in_two_launches(m, kind):
         assert np.array_equal(np_of(layer.idx), want), static
         assert np.array_equal(np_of(layer.delta_buf), left), static
         assert w_ref is None or np.array_equal(np_of(layer.wq), w_ref), static
+
+
+# up to 512 rows are spread over 128 groups of four threads
+@pytest.mark.parametrize("m,k", [(32, 20), (112, 30), (128, 40), (144, 48), (208, 64), (240, 96), (272, 80), (304, 96), (384, 96), (496, 96),
+                                 (512, 96), (528, 96)])
+@pytest.mark.parametrize("kind", ["spread", "few", "equal", "last bits", "alike", "clustered", "infinite", "half infinite", "last"])
+def test_rows_and_order_of_small_buffers(m, k, kind):
+    test_rows_and_order_are_the_oracles(m, k, kind)
