@@ -20,23 +20,35 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kVec = 16;          // elements per lane per step
 
-// piece v of a [rows, cols] tensor with row stride ld -> element offset; E elements per piece.  DENSE: no gaps between
-// rows (an instance of its own: the division's code between the loads costs a launch 0.3 us before it ever runs).
-template <int E, bool DENSE>
-__device__ __forceinline__ int64_t piece_offset(int64_t v, int64_t per_row, int64_t ld)
+// Piece v of a [rows, cols] tensor: its row and its place there.  kDense: no gaps between rows, all is one row (an
+// instance of its own: a division's code between the loads costs a launch 0.3 us before it ever runs).  kRows: fewer
+// than 2^32 pieces; with floor(2^32 / per_row) the product's upper half is the quotient or one less.  kFarRows: more
+// (with a 64-bit division per piece 250 KB of fp32 took 7.6 us, 5.5 now).
+enum { kDense, kRows, kFarRows };
+struct RowSplit { int64_t per_row; uint32_t inverse; };
+struct Place { int64_t row, piece; };
+
+template <int ROWS>
+__device__ __forceinline__ Place place_of(int64_t v, RowSplit s)
 {
-    if (DENSE) return v * E;
-    const int64_t row = v / per_row;
-    return row * ld + (v - row * per_row) * E;
+    if (ROWS == kDense) return {0, v};
+    if (ROWS == kFarRows) {
+        const int64_t row = v / s.per_row;
+        return {row, v - row * s.per_row};
+    }
+    const uint32_t u = static_cast<uint32_t>(v), d = static_cast<uint32_t>(s.per_row);
+    uint32_t row = __umulhi(u, s.inverse), piece = u - row * d;
+    if (piece >= d) { ++row; piece -= d; }
+    return {row, piece};
 }
 
 // Both passes go over the tensor in blocks of kBlock pieces per workgroup, block b by a workgroup of index b modulo
 // 8, so by the same XCD: what its L2 still holds from the first pass need not be fetched again.
 constexpr int kAtOnce = 4, kBlock = kThreads * kAtOnce;    // pieces in flight per thread
 
-template <typename T, bool DENSE>
+template <typename T, int ROWS>
 __global__ void __launch_bounds__(kThreads)
-amax_partial_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, int64_t ld_x, float* __restrict__ partials)
+amax_partial_kernel(const T* __restrict__ x, int64_t n_pieces, const RowSplit split, int64_t ld_x, float* __restrict__ partials)
 {
     __shared__ float smem[kThreads / 64];
     float m = 0.0f;
@@ -46,7 +58,8 @@ amax_partial_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, 
 #pragma unroll
         for (int b = 0; b < kAtOnce; ++b) {
             const int64_t v = v0 + b * kThreads < n_pieces ? v0 + b * kThreads : v0;   // beyond the end: one it has already
-            w[b] = *reinterpret_cast<const v4u*>(x + piece_offset<Piece<T>::E, DENSE>(v, per_row, ld_x));
+            const Place p = place_of<ROWS>(v, split);
+            w[b] = *reinterpret_cast<const v4u*>(x + p.row * ld_x + p.piece * Piece<T>::E);
         }
 #pragma unroll
         for (int b = 0; b < kAtOnce; ++b) m = abs_max<T>(w[b], m);
@@ -70,9 +83,9 @@ __device__ __forceinline__ void cast_side(const SideCast& side, int64_t first, i
 // The first pieces are requested before the partial maxima are reduced.
 // Both passes, us, against 32 contiguous bytes per lane, no prefetch and ordinary accesses (bf16, back to back, other
 // tensors in turn): 4 MB 5.2 (5.8), 16 MB 9.0 (10.1), 33 MB 12.6 (15.6), 90 MB 34.6 (37.1), 226 MB 83 (102).
-template <typename T, int FMT, bool DENSE, bool PAST>
+template <typename T, int FMT, int ROWS, bool PAST>
 __global__ void __launch_bounds__(kThreads)
-scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, int64_t ld_x,
+scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, const RowSplit split, int64_t ld_x,
                   const float* __restrict__ partials, int n_partials, const float* __restrict__ scale_in,
                   uint8_t* __restrict__ q, int64_t ld_q, float* __restrict__ scale_out,
                   float* __restrict__ amax_out, const ZeroWords zero, const SideCast side, int side_blocks)
@@ -89,11 +102,13 @@ scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, in
     const int64_t stride = static_cast<int64_t>(main_blocks) * kBlock;
     int64_t v0 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     v4u w[kAtOnce];
+    int64_t to[kAtOnce];                                             // where the codes go
     auto fetch = [&]() {
 #pragma unroll
         for (int b = 0; b < kAtOnce; ++b) {
-            const int64_t v = v0 + b * kThreads < n_pieces ? v0 + b * kThreads : 0;
-            w[b] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(x + piece_offset<E, DENSE>(v, per_row, ld_x)));
+            const Place p = place_of<ROWS>(v0 + b * kThreads < n_pieces ? v0 + b * kThreads : 0, split);
+            to[b] = p.row * ld_q + p.piece * E;
+            w[b] = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(x + p.row * ld_x + p.piece * E));
         }
     };
     if (n_pieces > 0) fetch();
@@ -108,7 +123,7 @@ scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, in
 #pragma unroll
         for (int b = 0; b < kAtOnce; ++b)
             if (v0 + b * kThreads < n_pieces) {
-                codes_t* const dst = reinterpret_cast<codes_t*>(q + piece_offset<E, DENSE>(v0 + b * kThreads, per_row, ld_q));
+                codes_t* const dst = reinterpret_cast<codes_t*>(q + to[b]);
                 if constexpr (PAST) __builtin_nontemporal_store(cast_piece<T, FMT>(w[b], s), dst);
                 else *dst = cast_piece<T, FMT>(w[b], s);
             }
@@ -130,9 +145,9 @@ scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, int64_t per_row, in
 constexpr int kOneThreads = 1024;
 constexpr int64_t kOneLaunchBytes = 256 * 1024;
 
-template <typename T, int FMT, bool DENSE>
+template <typename T, int FMT, int ROWS>
 __global__ void __launch_bounds__(kOneThreads)
-quantize_one_kernel(const T* __restrict__ x, int n_pieces, int64_t per_row, int64_t ld_x,
+quantize_one_kernel(const T* __restrict__ x, int n_pieces, const RowSplit split, int64_t ld_x,
                     const float* __restrict__ scale_in, uint8_t* __restrict__ q, int64_t ld_q, float* __restrict__ scale_out,
                     float* __restrict__ amax_out, const ZeroWords zero, const SideCast side, int side_blocks)
 {
@@ -154,7 +169,8 @@ quantize_one_kernel(const T* __restrict__ x, int n_pieces, int64_t per_row, int6
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const int v = v0 + b * kOneThreads < n_pieces ? v0 + b * kOneThreads : v0;   // beyond the end: one it has already
-                w[b] = *reinterpret_cast<const v4u*>(x + piece_offset<E, DENSE>(v, per_row, ld_x));
+                const Place p = place_of<ROWS>(v, split);
+                w[b] = *reinterpret_cast<const v4u*>(x + p.row * ld_x + p.piece * E);
             }
 #pragma unroll
             for (int b = 0; b < B; ++b) m = abs_max<T>(w[b], m);
@@ -171,9 +187,11 @@ quantize_one_kernel(const T* __restrict__ x, int n_pieces, int64_t per_row, int6
 #pragma unroll
     for (int b = 0; b < SHARE; ++b) {
         const int v = (static_cast<int>(blockIdx.x) * SHARE + b) * kOneThreads + static_cast<int>(threadIdx.x);
-        if (v < n_pieces)
-            *reinterpret_cast<codes_t*>(q + piece_offset<E, DENSE>(v, per_row, ld_q)) =
-                cast_piece<T, FMT>(*reinterpret_cast<const v4u*>(x + piece_offset<E, DENSE>(v, per_row, ld_x)), s);
+        if (v < n_pieces) {
+            const Place p = place_of<ROWS>(v, split);
+            *reinterpret_cast<codes_t*>(q + p.row * ld_q + p.piece * E) =
+                cast_piece<T, FMT>(*reinterpret_cast<const v4u*>(x + p.row * ld_x + p.piece * E), s);
+        }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *scale_out = s;
@@ -192,19 +210,21 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     SideCast side{nullptr, nullptr, nullptr, 0};
     if (side_job) side = *side_job;                                  // (count: a multiple of 16)
     constexpr int E = Piece<T>::E;
-    const int64_t per_row = cols / E, n_pieces = rows * per_row;
-    const bool dense = ld_x == cols && ld_q == cols;
+    const int64_t per_row = cols / E, n_pieces = rows * per_row;     // (per_row is 2 at least)
+    const bool near = n_pieces < (int64_t(1) << 32);
+    const RowSplit split{per_row, near ? static_cast<uint32_t>((int64_t(1) << 32) / per_row) : 0u};
+    const bool dense = rows <= 1 || (ld_x == cols && ld_q == cols);
     if (n_pieces * 16 <= kOneLaunchBytes && side.count / kVec <= 64 * kOneThreads) {
         const int64_t n_vecs = n_pieces * E / kVec;
         const int64_t main_blocks = n_vecs > 0 ? (n_vecs + kOneThreads - 1) / kOneThreads : 1;
         const int side_blocks = static_cast<int>((side.count / kVec + kOneThreads - 1) / kOneThreads);
         const dim3 grid(static_cast<unsigned>(main_blocks + side_blocks));
         auto go = [&](auto kernel) {
-            kernel<<<grid, kOneThreads, 0, stream>>>(x, static_cast<int>(n_pieces), per_row, ld_x, scale_in, q, ld_q, scale_out,
+            kernel<<<grid, kOneThreads, 0, stream>>>(x, static_cast<int>(n_pieces), split, ld_x, scale_in, q, ld_q, scale_out,
                                                      amax_out, zero, side, side_blocks);
         };
-        if (fmt == FALQON_E4M3) { if (dense) go(quantize_one_kernel<T, FALQON_E4M3, true>); else go(quantize_one_kernel<T, FALQON_E4M3, false>); }
-        else { if (dense) go(quantize_one_kernel<T, FALQON_E5M2, true>); else go(quantize_one_kernel<T, FALQON_E5M2, false>); }
+        if (fmt == FALQON_E4M3) { if (dense) go(quantize_one_kernel<T, FALQON_E4M3, kDense>); else go(quantize_one_kernel<T, FALQON_E4M3, kRows>); }
+        else { if (dense) go(quantize_one_kernel<T, FALQON_E5M2, kDense>); else go(quantize_one_kernel<T, FALQON_E5M2, kRows>); }
         return hipGetLastError();
     }
     // The amax pass wants few, long-running workgroups (one partial each); the cast pass is a plain stream.  Both grids
@@ -213,8 +233,10 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     int n_partials = 0;
     if (!scale_in || amax_out) {                                     // (a given scale needs no maximum unless it is asked for)
         n_partials = static_cast<int>(want < kMaxAmaxBlocks ? want : kMaxAmaxBlocks);
-        if (ld_x == cols) amax_partial_kernel<T, true><<<n_partials, kThreads, 0, stream>>>(x, n_pieces, per_row, ld_x, partials);
-        else amax_partial_kernel<T, false><<<n_partials, kThreads, 0, stream>>>(x, n_pieces, per_row, ld_x, partials);
+        auto go = [&](auto kernel) { kernel<<<n_partials, kThreads, 0, stream>>>(x, n_pieces, split, ld_x, partials); };
+        if (dense || ld_x == cols) go(amax_partial_kernel<T, kDense>);
+        else if (near) go(amax_partial_kernel<T, kRows>);
+        else go(amax_partial_kernel<T, kFarRows>);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -223,7 +245,7 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     const int64_t blocks = want < 1 ? 1 : want > 256 * 16 ? 256 * 16 : want;
     const dim3 grid(static_cast<unsigned>(blocks + side_blocks));
     auto go = [&](auto kernel) {
-        kernel<<<grid, kThreads, 0, stream>>>(x, n_pieces, per_row, ld_x, partials, n_partials, scale_in, q, ld_q, scale_out,
+        kernel<<<grid, kThreads, 0, stream>>>(x, n_pieces, split, ld_x, partials, n_partials, scale_in, q, ld_q, scale_out,
                                               amax_out, zero, side, side_blocks);
     };
     // A product that follows finds small tensors' codes in the caches, and is bound by getting them: with stores past the
@@ -231,13 +253,15 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     // the way from memory and the cast gains: three layers on 17 MB 340.5 against 343 to 348, steps with 33 MB 163.2
     // against 166.  A narrow product (next_width columns) does not: 5314 x 2928 -> 496 57.9 against 55.8.  Its time per code
     // is that of reading it at about 250 columns; the line is at eight times that.
-    auto by_rows = [&](auto past) {
-        constexpr bool P = decltype(past)::value;
-        if (fmt == FALQON_E4M3) { if (dense) go(scale_cast_kernel<T, FALQON_E4M3, true, P>); else go(scale_cast_kernel<T, FALQON_E4M3, false, P>); }
-        else { if (dense) go(scale_cast_kernel<T, FALQON_E5M2, true, P>); else go(scale_cast_kernel<T, FALQON_E5M2, false, P>); }
+    const bool past = n_pieces * 16 >= (12 << 20) && (next_width == 0 || next_width >= 2048);
+    auto by_rows = [&](auto rows_tag) {
+        constexpr int R = decltype(rows_tag)::value;
+        if (fmt == FALQON_E4M3) { if (past) go(scale_cast_kernel<T, FALQON_E4M3, R, true>); else go(scale_cast_kernel<T, FALQON_E4M3, R, false>); }
+        else { if (past) go(scale_cast_kernel<T, FALQON_E5M2, R, true>); else go(scale_cast_kernel<T, FALQON_E5M2, R, false>); }
     };
-    if (n_pieces * 16 >= (12 << 20) && (next_width == 0 || next_width >= 2048)) by_rows(std::true_type{});
-    else by_rows(std::false_type{});
+    if (dense) by_rows(std::integral_constant<int, kDense>{});
+    else if (near) by_rows(std::integral_constant<int, kRows>{});
+    else by_rows(std::integral_constant<int, kFarRows>{});
     return hipGetLastError();
 }
 

@@ -211,3 +211,22 @@ def test_quantize_at_the_edges_of_its_launches(dtype, kb, pad):
     ref, s_ref, amax_ref = oracle.quantize(x[:, :cols].float().numpy(), fq.E4M3)
     assert np.float32(s.item()) == s_ref and amax.item() == 37.5
     assert np.array_equal(np_of(q)[:, :cols], ref) and np.all(np_of(q)[:, cols:] == 0xAB)
+
+
+# rows with gaps: few and many pieces per row, odd numbers of them among these, in one launch and in two
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,cols,pad", [(1, 16, 16), (2, 16, 16), (257, 16, 48), (4099, 48, 16), (33, 112, 32), (1021, 1040, 16), (7, 4112, 64),
+                                           (300, 4112, 16), (3, 70000, 16)])
+def test_quantize_rows_with_gaps(dtype, rows, cols, pad):
+    x = torch.randn(rows, cols + pad, generator=torch.Generator().manual_seed(rows + cols)).to(dtype)
+    x[:, cols:] = 1e6                                        # must not be read
+    x[rows // 2, cols // 2] = -37.5
+    for given in (False, True):
+        q = torch.full((rows, cols + 16), 0xAB, dtype=torch.uint8, device="cuda")
+        s, one = torch.zeros(1, device="cuda"), torch.full((1,), 3.7, device="cuda")
+        ws = torch.empty(8192, dtype=torch.uint8, device="cuda")
+        fq.quantize(x.cuda()[:, :cols], fq.E5M2, q[:, :cols], s, ws, scale_in=one if given else None)
+        torch.cuda.synchronize()
+        ref, s_ref, _ = oracle.quantize(x[:, :cols].float().numpy(), fq.E5M2, scale_in=np.float32(3.7) if given else None)
+        assert np.float32(s.item()) == s_ref
+        assert np.array_equal(np_of(q)[:, :cols], ref) and np.all(np_of(q)[:, cols:] == 0xAB)
