@@ -248,12 +248,15 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
         kernel<<<grid, kThreads, 0, stream>>>(x, n_pieces, split, ld_x, partials, n_partials, scale_in, q, ld_q, scale_out,
                                               amax_out, zero, side, side_blocks);
     };
-    // A product that follows finds small tensors' codes in the caches, and is bound by getting them: with stores past the
-    // caches the step with tensors of 4 MB takes 65.0 us, with ordinary ones 60.8.  From 16 MB on the large tiles hide
-    // the way from memory and the cast gains: three layers on 17 MB 340.5 against 343 to 348, steps with 33 MB 163.2
-    // against 166.  A narrow product (next_width columns) does not: 5314 x 2928 -> 496 57.9 against 55.8.  Its time per code
-    // is that of reading it at about 250 columns; the line is at eight times that.
-    const bool past = n_pieces * 16 >= (12 << 20) && (next_width == 0 || next_width >= 2048);
+    // Where the codes go.  A product finds those of ordinary stores in the caches; with stores past them (PAST) it keeps more
+    // of its own operands there.  That gains 1 % on average, from 12 MB on, where the product's tiles are many and read whole
+    // cache lines: at least 2048 rows, of whole lines of 128 bytes (80 calls of 2048 to 12000 tokens 0.992 to 1.034 times as
+    // fast; 4096 x 4096 -> 4096 69.1 us against 70.3).  With fewer rows or rows across lines a product waits for its operands:
+    // 600 x 12000 -> 4064 89.1 us against 71.8 backward, 1907 x 6896 -> 5152 85 against 80, step with tensors of 4 MB 65.0
+    // against 60.8.  So does a narrow one (next_width columns): 5314 x 2928 -> 496 57.9 us against 55.8.  Its time per code is
+    // that of reading it at about 250 columns; the line is at eight times that.
+    const bool past = n_pieces * 16 >= (12 << 20) && rows >= 2048 && ((reinterpret_cast<uintptr_t>(q) | static_cast<uintptr_t>(ld_q)) & 127) == 0 &&
+                      (next_width == 0 || next_width >= 2048);
     auto by_rows = [&](auto rows_tag) {
         constexpr int R = decltype(rows_tag)::value;
         if (fmt == FALQON_E4M3) { if (past) go(scale_cast_kernel<T, FALQON_E4M3, R, true>); else go(scale_cast_kernel<T, FALQON_E4M3, R, false>); }

@@ -230,3 +230,16 @@ def test_quantize_rows_with_gaps(dtype, rows, cols, pad):
         ref, s_ref, _ = oracle.quantize(x[:, :cols].float().numpy(), fq.E5M2, scale_in=np.float32(3.7) if given else None)
         assert np.float32(s.item()) == s_ref
         assert np.array_equal(np_of(q)[:, :cols], ref) and np.all(np_of(q)[:, cols:] == 0xAB)
+
+
+# lines of ordinary stores and ones past the caches: rows (2048), rows of whole lines of 128 bytes, 12 MB
+@pytest.mark.parametrize("rows,cols,pad", [(2047, 3200, 0), (2048, 3200, 0), (2048, 3200, 128), (2049, 3216, 0), (2049, 3200, 64)])
+def test_quantize_past_the_caches(rows, cols, pad):
+    x = torch.randn(rows, cols, generator=torch.Generator().manual_seed(rows + cols)).to(torch.bfloat16)
+    q = torch.full((rows, cols + pad), 0xAB, dtype=torch.uint8, device="cuda")
+    s, ws = torch.zeros(1, device="cuda"), torch.empty(8192, dtype=torch.uint8, device="cuda")
+    fq.quantize(x.cuda(), fq.E4M3, q[:, :cols], s, ws)
+    torch.cuda.synchronize()
+    ref, s_ref, _ = oracle.quantize(x.float().numpy(), fq.E4M3)
+    assert np.float32(s.item()) == s_ref
+    assert np.array_equal(np_of(q)[:, :cols], ref) and np.all(np_of(q)[:, cols:] == 0xAB)
