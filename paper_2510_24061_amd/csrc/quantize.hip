@@ -141,9 +141,10 @@ scale_cast_kernel(const T* __restrict__ x, int64_t n_pieces, const RowSplit spli
 // (it is order free, so all of them and the two-launch form agree to the bit) and casts its share, one vector
 // per thread.  The last side_blocks workgroups cast the side tensor.  Bound by reading the tensor through one CU, so the
 // limit is where the device takes as long as for two launches; the host saves one at any size.  us on the device, one
-// launch (two): 256 KB bf16 4.9 (5.0), fp32 4.5 (4.9).
+// launch (two): 256 KB bf16 4.9 (5.0), fp32 4.5 (4.9).  Without a maximum the other form is one launch too, of more
+// workgroups: 160 KB fp32 3.0 us here, 2.7 there, the same up to 16 KB.
 constexpr int kOneThreads = 1024;
-constexpr int64_t kOneLaunchBytes = 256 * 1024;
+constexpr int64_t kOneLaunchBytes = 256 * 1024, kOneLaunchGivenBytes = 16 * 1024;
 
 template <typename T, int FMT, int ROWS>
 __global__ void __launch_bounds__(kOneThreads)
@@ -214,7 +215,8 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     const bool near = n_pieces < (int64_t(1) << 32);
     const RowSplit split{per_row, near ? static_cast<uint32_t>((int64_t(1) << 32) / per_row) : 0u};
     const bool dense = rows <= 1 || (ld_x == cols && ld_q == cols);
-    if (n_pieces * 16 <= kOneLaunchBytes && side.count / kVec <= 64 * kOneThreads) {
+    const bool wants_max = !scale_in || amax_out;                    // (a given scale needs no maximum unless it is asked for)
+    if (n_pieces * 16 <= (wants_max ? kOneLaunchBytes : kOneLaunchGivenBytes) && side.count / kVec <= 64 * kOneThreads) {
         const int64_t n_vecs = n_pieces * E / kVec;
         const int64_t main_blocks = n_vecs > 0 ? (n_vecs + kOneThreads - 1) / kOneThreads : 1;
         const int side_blocks = static_cast<int>((side.count / kVec + kOneThreads - 1) / kOneThreads);
@@ -231,7 +233,7 @@ hipError_t run(const T* x, int64_t rows, int64_t cols, int64_t ld_x, falqon_fmt 
     // are multiples of 8 where a workgroup has more than one block (see kBlock).
     const int64_t want = (n_pieces + kBlock - 1) / kBlock;
     int n_partials = 0;
-    if (!scale_in || amax_out) {                                     // (a given scale needs no maximum unless it is asked for)
+    if (wants_max) {
         n_partials = static_cast<int>(want < kMaxAmaxBlocks ? want : kMaxAmaxBlocks);
         auto go = [&](auto kernel) { kernel<<<n_partials, kThreads, 0, stream>>>(x, n_pieces, split, ld_x, partials); };
         if (dense || ld_x == cols) go(amax_partial_kernel<T, kDense>);
