@@ -162,25 +162,27 @@ quantize_one_kernel(const T* __restrict__ x, int n_pieces, const RowSplit split,
         return;
     }
     float m = 0.0f;
-    // B pieces in flight per thread, up to 128 KB per workgroup; no more than there are
-    auto sweep = [&](auto at_once) {
+    // B pieces in flight per thread, up to 128 KB per workgroup; no more than there are left (pieces that are not there cost
+    // as much as others: 141 KB 5.1 us with eight for the last 852, 4.3 with one)
+    int begin = 0;
+    auto batch = [&](auto at_once) {
         constexpr int B = decltype(at_once)::value;
-        for (int v0 = static_cast<int>(threadIdx.x); v0 < n_pieces; v0 += B * kOneThreads) {
-            v4u w[B];
+        v4u w[B];
+        const int v0 = begin + static_cast<int>(threadIdx.x);
 #pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int v = v0 + b * kOneThreads < n_pieces ? v0 + b * kOneThreads : v0;   // beyond the end: one it has already
-                const Place p = place_of<ROWS>(v, split);
-                w[b] = *reinterpret_cast<const v4u*>(x + p.row * ld_x + p.piece * E);
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b) m = abs_max<T>(w[b], m);
+        for (int b = 0; b < B; ++b) {
+            const int v = v0 + b * kOneThreads;
+            const Place p = place_of<ROWS>(v < n_pieces ? v : n_pieces - 1, split);      // beyond the end: the last one
+            w[b] = *reinterpret_cast<const v4u*>(x + p.row * ld_x + p.piece * E);
         }
+#pragma unroll
+        for (int b = 0; b < B; ++b) m = abs_max<T>(w[b], m);
+        begin += B * kOneThreads;
     };
     if (!scale_in || amax_out) {                                     // (a given scale needs no maximum unless it is asked for)
-        if (n_pieces <= kOneThreads) sweep(std::integral_constant<int, 1>{});
-        else if (n_pieces <= 4 * kOneThreads) sweep(std::integral_constant<int, 4>{});
-        else sweep(std::integral_constant<int, 8>{});
+        while (n_pieces - begin > 4 * kOneThreads) batch(std::integral_constant<int, 8>{});
+        if (n_pieces - begin > kOneThreads) batch(std::integral_constant<int, 4>{});
+        else if (n_pieces > begin) batch(std::integral_constant<int, 1>{});
     }
     const float amax = block_max<kOneThreads / 64>(m, smem);
     constexpr float mx = FMT == FALQON_E4M3 ? 448.0f : 57344.0f;
