@@ -487,9 +487,12 @@ __device__ __forceinline__ double quad_sum(double v)
 // per pair make l / 32 waves, one per SIMD.  (With 16 lanes per pair and up to three waves per SIMD a round took
 // 1.17 us at l = 72; rotating H from both sides, which takes a pass over all of H, the eigenvectors' update and two
 // barriers per round, 1.4 us.)
-// Stops after the first sweep in which no rotation turned its columns by more than 1e-8 radians (what is left of a
-// sweep's off-diagonal parts is of second order in its angles) other than ones between columns that are orthogonal to
-// 1e-14, the rounding level of the products, or after `sweeps`.  Columns that are null stay null.
+// Stops after `sweeps`, or after the first sweep that found all columns orthogonal to 1e-8 and turned none by more than
+// 1e-8 radians: what such a sweep leaves is of second order, for a short column beside a long one too (these turn by little
+// however far from orthogonal they are, and what a short one keeps of a long one enters P with the ratio of the lengths).
+// Not counted are rotations of columns that are orthogonal to 1e-14, the rounding level of the products.  Nine sweeps for
+// a flat spectrum; 17 to 24 for one that spans the whole range of fp64 before the basis has seen E (no iterations), where
+// 14 left cosines of up to 0.8 and a factor that was wrong altogether.
 // On exit w[i][.] the columns of W, lambda[i] their squared lengths (null below the rounding of H), order[k] the index of the k-th largest.
 template <int L8>                                                      // l / 8: 16-byte parts of a column per lane
 __global__ void __launch_bounds__(256)
@@ -543,7 +546,8 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
                         pa[4 * e] = na;
                         pb[4 * e] = nb;
                     }
-                    if (fabs(s) > 1e-8 && hab * hab > 1e-28 * haa * hbb) s_turned[sweep & 1] = 1;
+                    // (one comparison: orthogonal to 1e-14 where they turn by more than 1e-8, to 1e-8 where not)
+                    if (hab * hab > (fabs(s) > 1e-8 ? 1e-28 : 1e-16) * haa * hbb) s_turned[sweep & 1] = 1;
                 }
             }
             __syncthreads();
@@ -729,7 +733,7 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
         const size_t lds = sizeof(double) * 8 * L8 * (8 * (L8 | 1) + 1) + 2 * sizeof(int);                   \
         FQ_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&jacobi_eig_kernel<L8>),                  \
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));    \
-        jacobi_eig_kernel<L8><<<1, (16 * L8 + 63) / 64 * 64, lds, stream>>>(p, h, lambda, order, 14);        \
+        jacobi_eig_kernel<L8><<<1, (16 * L8 + 63) / 64 * 64, lds, stream>>>(p, h, lambda, order, 48);        \
         break;                                                                                               \
     }
     switch (l / 8) {

@@ -175,3 +175,32 @@ def test_every_subspace_size_on_ragged_matrices(r):
         assert np.max(np.abs(sig - sv[:r])) <= 1e-4 * sv[0], (m, n)
         assert np.max(np.abs(a @ a.T - np.diag(sig))) <= 1e-4 * sig[0], (m, n)
         assert np.linalg.norm(bt.T @ a - (u * s) @ v.T) <= 2e-3 * np.linalg.norm(s), (m, n)
+
+
+def _factors(e, r, omega, iters):
+    m, n = e.shape
+    a, bt, sig = torch.empty(r, n, device="cuda"), torch.empty(r, m, device="cuda"), torch.empty(r, device="cuda")
+    ws = torch.full((fq.svd_workspace_bytes(m, n, r),), 0x7f, dtype=torch.uint8, device="cuda")
+    fq.svd_right_factor(torch.from_numpy(e).cuda(), r, torch.from_numpy(omega).cuda(), iters, a, sig, ws, bt_out=bt)
+    torch.cuda.synchronize()
+    return (np_of(x).astype(np.float64) for x in (a, bt, sig))
+
+
+@pytest.mark.parametrize("r", [16, 32, 64, 120])
+@pytest.mark.parametrize("decades", [3, 7, 9, 20])
+def test_steep_spectrum_without_an_iteration(r, decades):
+    """The first basis is random, so H = (Z E^T)(Z E^T)^T has entries of one size and eigenvalues over the whole range of
+    fp64: the eigenvectors have to be orthogonal to one another all the same, and both factors those of E Z^T Z.  Bounds:
+    Z and the product are exact to some 1e-7 of the largest singular value, and H to l 1e-16 of its square."""
+    g = np.random.default_rng(r + decades)
+    m, n, rank = 200, 300, 160
+    u, _ = np.linalg.qr(g.normal(size=(m, rank)))
+    v, _ = np.linalg.qr(g.normal(size=(n, rank)))
+    e = ((u * np.logspace(0, -decades, rank)) @ v.T).astype(np.float32)
+    omega = g.normal(size=(r + 8, n)).astype(np.float32)
+    a, bt, sig = _factors(e, r, omega, 0)
+    q, _ = np.linalg.qr(omega.T.astype(np.float64))
+    uu, ss, vv = np.linalg.svd(e.astype(np.float64) @ q, full_matrices=False)
+    assert np.all(np.diff(sig) <= 0) and np.max(np.abs(sig - ss[:r])) <= 1e-6 * ss[0]
+    assert np.max(np.abs(a @ a.T - np.diag(sig))) <= 1e-6 * ss[0]
+    assert np.linalg.norm(bt.T @ a - (uu[:, :r] * ss[:r]) @ vv[:r] @ q.T) <= 1e-5 * ss[0]
