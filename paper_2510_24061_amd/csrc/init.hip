@@ -228,7 +228,10 @@ sum_slices_kernel(const float* __restrict__ part, int slices, int64_t count, flo
 // factored by every thread for itself (W = inverse of its unit factor, D^-1 = W^T diag(1/d) W), so a step costs one
 // exchange through LDS, one barrier, a chain of four reciprocals and the update.  (With a scalar pivot per step the
 // chain of barriers and reciprocals was four times as long: 29 us at l = 72 against 23.)
-// FACTOR: L^T itself instead (its upper triangle; nothing else is written); pivots below the rounding of G are null.
+// FACTOR: L^T itself instead (its upper triangle; nothing else is written); pivots below the rounding of their own
+// diagonal entry, which the subtractions cannot fall below, are null.  (Entries of G may differ by the square of the range
+// of singular values: measured against the largest one, all values below 3e-8 of it would be lost, also those of rows
+// that have nothing to do with it.)
 constexpr int kFactorThreads = 576;                                   // 32 * 33 / 2 blocks at l = 128, in whole waves
 
 template <bool FACTOR>
@@ -238,6 +241,7 @@ factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
     constexpr int BP = 18;                                            // doubles per block: 16 at an odd number of 16 bytes
     __shared__ __attribute__((aligned(16))) double s_p[2][kMaxL / 4 * BP], s_q[2][kMaxL / 4 * BP];
     __shared__ __attribute__((aligned(16))) double s_w[kMaxL / 4 * BP];
+    __shared__ double s_least[kMaxL];                                 // pivots up to these are null
     const int t = threadIdx.x, nb = l / 4;                            // l is a multiple of 8
     int R = static_cast<int>((sqrtf(8.0f * static_cast<float>(t) + 1.0f) - 1.0f) * 0.5f);
     if (R * (R + 1) / 2 > t) --R;
@@ -249,13 +253,7 @@ factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[i][j] = live ? g[(4 * R + i) * l + 4 * C + j] : 0.0;
-    double tiny = 1e-28 * fmax(g[0], 1e-300);
-    if (FACTOR) {
-        double top = 1e-300;
-        for (int i = t & 63; i < l; i += 64) top = fmax(top, g[i * l + i]);
-        for (int off = 32; off > 0; off >>= 1) top = fmax(top, __shfl_xor(top, off, 64));
-        tiny = 1e-15 * top;
-    }
+    for (int i = t; i < l; i += static_cast<int>(blockDim.x)) s_least[i] = FACTOR ? 1e-15 * g[i * l + i] : 1e-28 * fmax(g[0], 1e-300);
     for (int cb = 0; cb < nb; ++cb) {
         double* const pc = s_p[cb & 1];                               // P(R); the buffers alternate: one barrier per step
         double* const vr = s_q[cb & 1];                               // V(C) of either half; the identity for C = cb
@@ -292,7 +290,7 @@ factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
             double r = __builtin_amdgcn_rcp(p);                       // and two Newton steps: full precision
             r = fma(fma(-p, r, 1.0), r, r);
             r = fma(fma(-p, r, 1.0), r, r);
-            inv[c] = p > tiny ? r : 0.0;                              // a dead row takes no part
+            inv[c] = p > s_least[4 * cb + c] ? r : 0.0;               // a dead row takes no part
 #pragma unroll
             for (int k = c + 1; k < 4; ++k) {
                 const double u = d[k][c] * inv[c];
@@ -480,7 +478,7 @@ __device__ __forceinline__ double quad_sum(double v)
 // Eigen-decomposition H = P diag(lambda) P^T of a symmetric positive semidefinite H = L L^T (l x l, fp64) by one-sided
 // Jacobi: rotations of the columns of L^T that make them orthogonal.  Their dot products are the entries of H, so the
 // rotations are those of the two-sided method on H in the same order, and P is their product; but all that is kept is
-// W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (rotate_kernel).
+// W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (eigenvector_kernel).
 // Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: its three dot products
 // are reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.
 // A round is bound by the instructions that a SIMD issues, and those of the rotation count once per wave: four lanes
@@ -493,18 +491,16 @@ __device__ __forceinline__ double quad_sum(double v)
 // Not counted are rotations of columns that are orthogonal to 1e-14, the rounding level of the products.  Nine sweeps for
 // a flat spectrum; 17 to 24 for one that spans the whole range of fp64 before the basis has seen E (no iterations), where
 // 14 left cosines of up to 0.8 and a factor that was wrong altogether.
-// On exit w[i][.] the columns of W, lambda[i] their squared lengths (null below the rounding of H), order[k] the index of the k-th largest.
+// On exit w[i][.] the columns of W, lambda[i] their squared lengths.
 template <int L8>                                                      // l / 8: 16-byte parts of a column per lane
 __global__ void __launch_bounds__(256)
-jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double* __restrict__ lambda,
-                  int* __restrict__ order, int sweeps)
+jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double* __restrict__ lambda, int sweeps)
 {
     typedef double v2d __attribute__((ext_vector_type(2)));
     // columns at an odd multiple of 64 bytes: the sixteen pairs of a wave spread over all banks
     constexpr int l = 8 * L8, PITCH = 8 * (L8 | 1);
-    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], lambda [l], two flags
-    double* const s_lam = s_v + l * PITCH;
-    int* const s_turned = reinterpret_cast<int*>(s_lam + l);
+    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], two flags
+    int* const s_turned = reinterpret_cast<int*>(s_v + l * PITCH);
     const int t = threadIdx.x, pair = t >> 2, e0 = 2 * (t & 3);
     const bool live = pair < l / 2;
     for (int q = t; q < l * l; q += blockDim.x) {
@@ -563,55 +559,80 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
             s = fma(v[0], v[0], fma(v[1], v[1], s));
         }
         s = quad_sum(s);
-        if ((t & 3) == 0) s_lam[i] = s;
-    }
-    __syncthreads();
-    // rank by eigenvalue, larger first, equal values by smaller index.  A NaN (a matrix that is not finite) ranks
-    // last: the ranks have to be a permutation, since the entries of `order` are used as indices.
-    auto value = [&](int i) { const double x = s_lam[i]; return x == x ? x : -HUGE_VAL; };
-    for (int i = t; i < l; i += blockDim.x) {
-        const double li = value(i);
-        int rank = 0;
-        double top = li;
-        for (int j = 0; j < l; ++j) {
-            const double lj = value(j);
-            top = fmax(top, lj);
-            rank += (lj > li || (lj == li && j < i)) ? 1 : 0;
-        }
-        order[rank] = i;
-        lambda[i] = s_lam[i] <= 1e-15 * top ? 0.0 : s_lam[i];         // below the rounding of H: null
+        if ((t & 3) == 0) lambda[i] = s;
     }
 }
 
-// A^[k][j] = lambda_k^(1/4) * sum_c P[c][k] Z[c][j], with P's column k = L w_k / lambda_k formed by every workgroup;
-// sigma[k] = sqrt(lambda_k)
-__global__ void __launch_bounds__(kThreads)
-rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __restrict__ lt, const double* __restrict__ w,
-              const double* __restrict__ lambda, const int* __restrict__ order, int r,
-              float* __restrict__ a_out, float* __restrict__ sigma_out, int inverse_scale)
+// w[k][.] <- P's column k = L w_k / lambda_k, for each k a workgroup.  An eigenvalue is as exact as the rounding of the
+// entries of H that its vector weighs, p^T diag(H) p: one that is below it, or not a number, is null, and its vector too.
+// (Measured against the largest of H, those of rows that have nothing to do with the large ones would be lost.)
+__global__ void __launch_bounds__(kMaxL)
+eigenvector_kernel(const double* __restrict__ lt, int l, double* __restrict__ w, double* __restrict__ lambda)
 {
-    __shared__ double s_p[kMaxL];
-    const int k = blockIdx.y;
-    const int col = order[k];
-    const double lam = lambda[col] > 0.0 ? lambda[col] : 0.0;
+    __shared__ double s_sum[2][kMaxL / 64];
+    const int k = blockIdx.x, i = threadIdx.x;
+    const double lam = lambda[k];
+    double p = 0.0, h = 0.0;
+    const int column = i < l ? i : l - 1;
+    for (int e0 = 0; e0 < l; e0 += 8) {                               // l is a multiple of 8: eight loads in flight
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = lt[(e0 + u) * l + column];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (e0 + u > i) x[u] = 0.0;                               // (nothing is stored below the diagonal)
+            p = fma(x[u], w[k * l + e0 + u], p);
+            h = fma(x[u], x[u], h);
+        }
+    }
+    if (i >= l) p = h = 0.0;
+    p = lam > 0.0 ? p / lam : 0.0;
+    double square = p * p, weight = p * p * h;
+    for (int off = 32; off > 0; off >>= 1) {
+        square += __shfl_xor(square, off, 64);
+        weight += __shfl_xor(weight, off, 64);
+    }
+    if ((i & 63) == 0) { s_sum[0][i >> 6] = square; s_sum[1][i >> 6] = weight; }
+    __syncthreads();                                                  // also: w is no longer read
+    square = weight = 0.0;
+    for (int v = 0; v < kMaxL / 64; ++v) { square += s_sum[0][v]; weight += s_sum[1][v]; }
+    const bool live = lam * square > 1e-15 * weight;
+    if (i < l) w[k * l + i] = live ? p : 0.0;
+    if (i == 0) lambda[k] = live ? lam : 0.0;
+}
+
+// A^[k][j] = lambda_k^(1/4) * sum_c P[c][k] Z[c][j], sigma[k] = sqrt(lambda_k), for the k-th largest eigenvalue (equal
+// ones by smaller index); p[i][.]: P's column i
+__global__ void __launch_bounds__(kThreads)
+rotate_kernel(const float* __restrict__ z, int l, int64_t n, const double* __restrict__ p,
+              const double* __restrict__ lambda, float* __restrict__ a_out, float* __restrict__ sigma_out, int inverse_scale)
+{
+    __shared__ double s_p[kMaxL], s_lam[kMaxL];
+    __shared__ int s_col;
+    const int k = blockIdx.y, t = threadIdx.x;
+    if (t < l) s_lam[t] = lambda[t];                                  // (none is a NaN)
+    __syncthreads();
+    if (t < l) {
+        int rank = 0;
+        for (int j = 0; j < l; ++j) rank += (s_lam[j] > s_lam[t] || (s_lam[j] == s_lam[t] && j < t)) ? 1 : 0;
+        if (rank == k) s_col = t;
+    }
+    __syncthreads();
+    const int col = s_col;
+    if (t < l) s_p[t] = p[col * l + t];
+    __syncthreads();
+    const double lam = s_lam[col];
     // right factor: z holds unit vectors, row k becomes sqrt(sigma_k) v_k.  Left factor (inverse_scale):
     // z holds E v (length sigma_k u_k after the rotation), row k becomes sqrt(sigma_k) u_k.
     const double root = sqrt(sqrt(lam));
     const double scale = inverse_scale ? (root > 0.0 ? 1.0 / root : 0.0) : root;
-    if (threadIdx.x < l) {
-        const int i = threadIdx.x;
-        double p = 0.0;
-        for (int e = 0; e < l; ++e) p += e <= i ? lt[e * l + i] * w[col * l + e] : 0.0;
-        s_p[i] = lam > 0.0 ? p / lam : 0.0;
-    }
-    __syncthreads();
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * kThreads + t;
     if (j < n) {
         double acc = 0.0;
         for (int c = 0; c < l; ++c) acc += s_p[c] * static_cast<double>(z[static_cast<int64_t>(c) * n + j]);
         a_out[static_cast<int64_t>(k) * n + j] = static_cast<float>(scale * acc);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && sigma_out) sigma_out[k] = static_cast<float>(sqrt(lam));
+    if (blockIdx.x == 0 && t == 0 && sigma_out) sigma_out[k] = static_cast<float>(sqrt(lam));
 }
 
 }  // namespace
@@ -637,7 +658,6 @@ SvdLayout svd_layout(int64_t m, int64_t n, int64_t r)
     L.h = off;      off = up(off + sizeof(double) * l * l);
     L.p = off;      off = up(off + sizeof(double) * l * l);
     L.lambda = off; off = up(off + sizeof(double) * l);
-    L.order = off;  off = up(off + sizeof(int) * l);
     // partial sums of the products and the packed vectors: together no more than the 16 slices of partial sums that
     // a workspace has had room for (the packed vectors take less than four slices for l >= 24 and max(m, n) >= 32)
     const size_t longest = static_cast<size_t>(m > n ? m : n), room = sizeof(float) * 16 * l * longest;
@@ -686,7 +706,6 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     double* h = reinterpret_cast<double*>(ws + L.h);
     double* p = reinterpret_cast<double*>(ws + L.p);
     double* lambda = reinterpret_cast<double*>(ws + L.lambda);
-    int* order = reinterpret_cast<int*>(ws + L.order);
     float* part = reinterpret_cast<float*>(ws + L.part);
     float* packed = reinterpret_cast<float*>(ws + L.packed);
     // Y[l][m] = Z E^T (transposed == false) or Z[l][n] = Y E: slices of the contracted dimension so that about 256
@@ -730,10 +749,10 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     FQ_CHECK(hipGetLastError());
 #define FQ_JACOBI(L8)                                                                                        \
     case L8: {                                                                                               \
-        const size_t lds = sizeof(double) * 8 * L8 * (8 * (L8 | 1) + 1) + 2 * sizeof(int);                   \
+        const size_t lds = sizeof(double) * 8 * L8 * (8 * (L8 | 1)) + 2 * sizeof(int);                       \
         FQ_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&jacobi_eig_kernel<L8>),                  \
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));    \
-        jacobi_eig_kernel<L8><<<1, (16 * L8 + 63) / 64 * 64, lds, stream>>>(p, h, lambda, order, 48);        \
+        jacobi_eig_kernel<L8><<<1, (16 * L8 + 63) / 64 * 64, lds, stream>>>(p, h, lambda, 48);        \
         break;                                                                                               \
     }
     switch (l / 8) {
@@ -743,13 +762,15 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     }
 #undef FQ_JACOBI
     FQ_CHECK(hipGetLastError());
+    eigenvector_kernel<<<l, kMaxL, 0, stream>>>(p, l, h, lambda);
+    FQ_CHECK(hipGetLastError());
     rotate_kernel<<<dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads), static_cast<unsigned>(r)), kThreads, 0,
-                    stream>>>(z, l, n, p, h, lambda, order, static_cast<int>(r), a_out, sigma_out, 0);
+                    stream>>>(z, l, n, h, lambda, a_out, sigma_out, 0);
     FQ_CHECK(hipGetLastError());
     if (bt_out) {
         // y still holds E z^T: its rotation by the same eigenvectors is sigma_k u_k, the left singular vectors
         rotate_kernel<<<dim3(static_cast<unsigned>((m + kThreads - 1) / kThreads), static_cast<unsigned>(r)), kThreads, 0,
-                        stream>>>(y, l, m, p, h, lambda, order, static_cast<int>(r), bt_out, nullptr, 1);
+                        stream>>>(y, l, m, h, lambda, bt_out, nullptr, 1);
         FQ_CHECK(hipGetLastError());
     }
 #undef FQ_CHECK

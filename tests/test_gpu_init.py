@@ -204,3 +204,19 @@ def test_steep_spectrum_without_an_iteration(r, decades):
     assert np.all(np.diff(sig) <= 0) and np.max(np.abs(sig - ss[:r])) <= 1e-6 * ss[0]
     assert np.max(np.abs(a @ a.T - np.diag(sig))) <= 1e-6 * ss[0]
     assert np.linalg.norm(bt.T @ a - (uu[:, :r] * ss[:r]) @ vv[:r] @ q.T) <= 1e-5 * ss[0]
+
+
+@pytest.mark.parametrize("seed", [5, 6, 7])
+def test_small_singular_values_of_rows_apart_from_the_large(seed):
+    """Two blocks without common rows and columns: what is small beside the other one, here 1e-8 of it, keeps a precision
+    of its own.  (The small block has no gap: its Ritz values come within a few per cent, from below.)"""
+    g = np.random.default_rng(seed)
+    e = np.zeros((400, 600), np.float32)
+    e[:16, :16] = g.normal(size=(16, 16)) + 4.0 * np.eye(16)
+    e[100:, 300:] = 1e-8 * g.normal(size=(300, 300)) * 0.4
+    a, bt, sig = _factors(e, 32, g.normal(size=(40, 600)).astype(np.float32), 6)
+    sv = np.linalg.svd(e.astype(np.float64), compute_uv=False)[:32]
+    assert np.all(np.diff(sig) <= 0) and np.max(np.abs(sig[:16] / sv[:16] - 1.0)) <= 1e-4
+    assert np.all(sig[16:] <= sv[16:] * 1.001) and np.all(sig[16:] >= 0.9 * sv[16:])
+    small = (bt.T @ a)[100:, 300:]
+    assert np.linalg.norm(small, 2) <= sv[16] * 1.01 and np.linalg.norm(small) >= 0.9 * np.linalg.norm(sv[16:])
