@@ -195,7 +195,8 @@ falqon_status falqon_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int6
  * streams, two threads) race; order them.  The first call on a device looks up the array's
  * address (once per device, kept for the life of the process, guarded by a mutex); make that call
  * outside a graph capture.  Nothing in the array needs clearing between calls: each call writes
- * every score and every staged row it later reads.
+ * every score and every staged row it later reads; the words in which the workgroups of a row agree
+ * on its clearing are read for a mark of 64 bits that each call takes back.
  */
 falqon_status falqon_proxy_update_static(float* delta_buf, uint8_t* wq, int64_t n, int64_t m, int64_t r, int64_t k,
                                          int32_t* idx_out, int clear_selected, void* stream);

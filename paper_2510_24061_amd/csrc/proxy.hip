@@ -36,8 +36,8 @@ constexpr size_t kStaticBytes = kStaticScoreBytes + sizeof(float) * kStaticMaxSe
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 // grid: ceil(m / ROWS); dynamic LDS: ROWS * (r + 4) floats.  Blocks of 64 rows: 1024 threads, one round trip up to rank
-// 64; blocks of 16, up to 4096 rows: 4 r threads, one always (update at 4096 x 256 16.2 us, 17.1 in blocks of 64; x 64
-// 9.7 and 9.9).
+// 64; blocks of 16, up to 4096 rows: 4 r threads, one always (update at 4096 x 256 16.7 us, 17.6 in blocks of 64; x 64
+// 9.7 and 10.2).
 constexpr int kScoreThreads = 1024;
 
 template <int ROWS>
@@ -626,9 +626,11 @@ row_requantize_kernel(uint8_t* wq, int64_t n, int64_t m, int64_t r, const int32_
 // Bound by latency: scores 0.7 us, selection 2.6, row 0.5, sums 1.2 (r = 64; 4.3 at r = 256), end 0.6 at 4096 x 4096,
 // k = 32.  The sums are rolled up to 16 ranks: unrolled over 64 their instructions alone took 0.8 us to arrive.
 // Whole update with its score pass, us (graph of 20, with clear), against selection and requantize in two launches:
-//   512 x 512, r = 16, k = 8          6.8 (8.4)      4096 x 4096, r = 256, k = 32     17.1 (18.8)
-//   2000 x 1040, r = 48, k = 24       9.2 (10.7)     4096 x 11008, r = 64, k = 32     12.3 (13.5)
-//   4096 x 4096, r = 64, k = 32       9.9 (11.4)     11008 x 4096, r = 64, k = 32     12.4 (15.5)
+//   512 x 512, r = 16, k = 8          6.8 (8.6)      4096 x 4096, r = 256, k = 32     16.8 (18.7)
+//   2000 x 1040, r = 48, k = 24       8.9 (10.8)     4096 x 11008, r = 64, k = 32     12.0 (13.3)
+//   4096 x 4096, r = 64, k = 32       9.7 (11.3)     11008 x 4096, r = 64, k = 32     12.7 (15.6)
+// Ranks whose part of A~ takes more than 4 of 16 bytes per thread, and less than 16, read the rest for nothing; they are
+// ahead all the same: r = 80 11.1 (12.2), r = 96 11.7 (12.5), r = 128 12.6 (13.6) at 4096 x 4096, k = 32.
 constexpr unsigned long long kArrived = 0xa57c3e91d20b68f5ull;
 
 template <int N, typename F, int I = 0>
@@ -810,8 +812,8 @@ hipError_t launch_proxy_update(float* delta_buf, uint8_t* wq, int64_t n, int64_t
         }
     }
     // The selection that finds one rank per workgroup, while the scores fit a workgroup's registers and the
-    // group maxima bound the k-th score well (k of 128 groups).
-    // Figures at the kernel; at the edge, 16384 rows and k = 96: 22.9 us against 31.4 for the whole update.
+    // group maxima bound the k-th score well (k of 128 groups).  Whole update around the line on k, 1040 columns, r = 256:
+    // 16384 rows 29.9 us at k = 96 and 42.9 at k = 97, 11264 rows 26.0 and 35.5, 4096 rows 23.6 and 24.1.
     if (k <= kSelectMaxK && m <= kSelectMaxRows) {
         e = with_keys(m, [&](auto keys) -> hipError_t {
             select_kernel<decltype(keys)::value><<<static_cast<unsigned>(k), kSelectThreads, 0, stream>>>(

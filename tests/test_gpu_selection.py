@@ -1,5 +1,5 @@
-"""Selection of the proxy update at the edges of its two paths: register counts (1024, 4096, 11264 and
-16384 rows), k on both sides of the limit, long runs of equal scores, scores that share all but a few
+"""Selection of the proxy update, with the requantize in one launch and in two, at the edges of its paths: register counts
+(1024, 4096, 11264 and 16384 rows), k on both sides of the limit, long runs of equal scores, scores that share all but a few
 neighbouring or separate bits, rows that are nearly alike (with and without a few far larger ones), large rows
 that all sit in a few threads, and infinite and zero rows."""
 import numpy as np
