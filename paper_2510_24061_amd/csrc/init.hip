@@ -478,7 +478,7 @@ __device__ __forceinline__ double quad_sum(double v)
 // Eigen-decomposition H = P diag(lambda) P^T of a symmetric positive semidefinite H = L L^T (l x l, fp64) by one-sided
 // Jacobi: rotations of the columns of L^T that make them orthogonal.  Their dot products are the entries of H, so the
 // rotations are those of the two-sided method on H in the same order, and P is their product; but all that is kept is
-// W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (eigenvector_kernel).
+// W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (eigenvector_kernel, settle_kernel).
 // Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: its three dot products
 // are reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.
 // A round is bound by the instructions that a SIMD issues, and those of the rotation count once per wave: four lanes
@@ -563,42 +563,92 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
     }
 }
 
-// w[k][.] <- P's column k = L w_k / lambda_k, for each k a workgroup.  An eigenvalue is as exact as the rounding of the
-// entries of H that its vector weighs, p^T diag(H) p: one that is below it, or not a number, is null, and its vector too.
-// (Measured against the largest of H, those of rows that have nothing to do with the large ones would be lost.)
+// the sums of a and b over the workgroup's kMaxL threads, in all of them
+__device__ __forceinline__ void sums_over_all(double& a, double& b, double (&smem)[2][kMaxL / 64])
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_xor(a, off, 64);
+        b += __shfl_xor(b, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) { smem[0][threadIdx.x >> 6] = a; smem[1][threadIdx.x >> 6] = b; }
+    __syncthreads();
+    a = b = 0.0;
+    for (int v = 0; v < kMaxL / 64; ++v) { a += smem[0][v]; b += smem[1][v]; }
+}
+
+// p[k][.] <- P's column k, L w_k at length 1, for each k a workgroup.  (Its length is lambda_k, which for a null column
+// can be anything down to zero.)
 __global__ void __launch_bounds__(kMaxL)
-eigenvector_kernel(const double* __restrict__ lt, int l, double* __restrict__ w, double* __restrict__ lambda)
+eigenvector_kernel(const double* __restrict__ lt, int l, const double* __restrict__ w, double* __restrict__ p)
 {
     __shared__ double s_sum[2][kMaxL / 64];
-    const int k = blockIdx.x, i = threadIdx.x;
-    const double lam = lambda[k];
-    double p = 0.0, h = 0.0;
-    const int column = i < l ? i : l - 1;
+    const int k = blockIdx.x, i = threadIdx.x, column = i < l ? i : l - 1;
+    double a = 0.0;
     for (int e0 = 0; e0 < l; e0 += 8) {                               // l is a multiple of 8: eight loads in flight
         double x[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) x[u] = lt[(e0 + u) * l + column];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (e0 + u > i) x[u] = 0.0;                               // (nothing is stored below the diagonal)
-            p = fma(x[u], w[k * l + e0 + u], p);
-            h = fma(x[u], x[u], h);
+        for (int u = 0; u < 8; ++u) a = fma(e0 + u <= i ? x[u] : 0.0, w[k * l + e0 + u], a);   // (nothing below the diagonal)
+    }
+    if (i >= l) a = 0.0;
+    double square = a * a, unused = 0.0;
+    sums_over_all(square, unused, s_sum);
+    if (i < l) p[k * l + i] = square > 0.0 && square < HUGE_VAL ? a / sqrt(square) : 0.0;
+}
+
+// L w_k carries the rounding of w_k times the ratio of the largest length to its own: of eigenvalues near the
+// rounding of H, p_k keeps parts of the vectors of larger ones, which the products with E bring up again.  Here these
+// parts are taken out, the vector is brought to length 1, and its eigenvalue becomes |L^T q|^2, so that values, vectors
+// and both factors agree whatever their size.  A vector of which nothing is left is null.
+__global__ void __launch_bounds__(kMaxL)
+settle_kernel(const double* __restrict__ lt, int l, const double* __restrict__ p, const double* __restrict__ lambda,
+              double* __restrict__ q, double* __restrict__ settled)
+{
+    __shared__ double s_p[kMaxL], s_dot[kMaxL], s_sum[2][2][kMaxL / 64];
+    const int k = blockIdx.x, i = threadIdx.x, column = i < l ? i : l - 1;
+    const double own = i < l ? p[k * l + i] : 0.0;
+    s_p[i] = own;
+    __syncthreads();
+    double dot = 0.0;
+    const bool larger = i < l && lambda[i] > lambda[k];
+    if (larger)
+        for (int c0 = 0; c0 < l; c0 += 8) {
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = p[i * l + c0 + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) dot = fma(x[u], s_p[c0 + u], dot);
         }
+    s_dot[i] = dot;
+    __syncthreads();
+    double rest = own;
+    for (int c0 = 0; c0 < l; c0 += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = p[(c0 + u) * l + column];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rest = fma(-s_dot[c0 + u], x[u], rest);
     }
-    if (i >= l) p = h = 0.0;
-    p = lam > 0.0 ? p / lam : 0.0;
-    double square = p * p, weight = p * p * h;
-    for (int off = 32; off > 0; off >>= 1) {
-        square += __shfl_xor(square, off, 64);
-        weight += __shfl_xor(weight, off, 64);
+    if (i >= l) rest = 0.0;
+    double before = own * own, after = rest * rest;
+    sums_over_all(before, after, s_sum[0]);
+    const bool live = after > 1e-4 * before;                          // (not for a NaN)
+    rest = live ? rest / sqrt(after) : 0.0;
+    s_p[i] = rest;                                                    // (all have read it: two barriers ago)
+    __syncthreads();
+    double t = 0.0, unused = 0.0;
+    for (int c0 = 0; c0 < l; c0 += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = lt[column * l + c0 + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t = fma(c0 + u >= i ? x[u] : 0.0, s_p[c0 + u], t);
     }
-    if ((i & 63) == 0) { s_sum[0][i >> 6] = square; s_sum[1][i >> 6] = weight; }
-    __syncthreads();                                                  // also: w is no longer read
-    square = weight = 0.0;
-    for (int v = 0; v < kMaxL / 64; ++v) { square += s_sum[0][v]; weight += s_sum[1][v]; }
-    const bool live = lam * square > 1e-15 * weight;
-    if (i < l) w[k * l + i] = live ? p : 0.0;
-    if (i == 0) lambda[k] = live ? lam : 0.0;
+    t = i < l ? t * t : 0.0;
+    sums_over_all(t, unused, s_sum[1]);
+    if (i < l) q[k * l + i] = rest;
+    if (i == 0) settled[k] = live && t < HUGE_VAL ? t : 0.0;
 }
 
 // A^[k][j] = lambda_k^(1/4) * sum_c P[c][k] Z[c][j], sigma[k] = sqrt(lambda_k), for the k-th largest eigenvalue (equal
@@ -762,15 +812,20 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     }
 #undef FQ_JACOBI
     FQ_CHECK(hipGetLastError());
-    eigenvector_kernel<<<l, kMaxL, 0, stream>>>(p, l, h, lambda);
+    // the products' partial sums are no longer needed: their room holds the vectors before they are settled
+    double* const vectors = reinterpret_cast<double*>(part);
+    double* const settled = vectors + l * l;
+    eigenvector_kernel<<<l, kMaxL, 0, stream>>>(p, l, h, vectors);
+    FQ_CHECK(hipGetLastError());
+    settle_kernel<<<l, kMaxL, 0, stream>>>(p, l, vectors, lambda, h, settled);
     FQ_CHECK(hipGetLastError());
     rotate_kernel<<<dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads), static_cast<unsigned>(r)), kThreads, 0,
-                    stream>>>(z, l, n, h, lambda, a_out, sigma_out, 0);
+                    stream>>>(z, l, n, h, settled, a_out, sigma_out, 0);
     FQ_CHECK(hipGetLastError());
     if (bt_out) {
         // y still holds E z^T: its rotation by the same eigenvectors is sigma_k u_k, the left singular vectors
         rotate_kernel<<<dim3(static_cast<unsigned>((m + kThreads - 1) / kThreads), static_cast<unsigned>(r)), kThreads, 0,
-                        stream>>>(y, l, m, h, lambda, bt_out, nullptr, 1);
+                        stream>>>(y, l, m, h, settled, bt_out, nullptr, 1);
         FQ_CHECK(hipGetLastError());
     }
 #undef FQ_CHECK

@@ -220,3 +220,19 @@ def test_small_singular_values_of_rows_apart_from_the_large(seed):
     assert np.all(sig[16:] <= sv[16:] * 1.001) and np.all(sig[16:] >= 0.9 * sv[16:])
     small = (bt.T @ a)[100:, 300:]
     assert np.linalg.norm(small, 2) <= sv[16] * 1.01 and np.linalg.norm(small) >= 0.9 * np.linalg.norm(sv[16:])
+
+
+@pytest.mark.parametrize("m,n,r,rank,iters", [(128, 128, 120, 100, 0), (92, 64, 56, 40, 1), (128, 192, 120, 70, 4), (104, 156, 96, 90, 2)])
+def test_both_factors_where_the_rank_is_lower_than_asked_for(m, n, r, rank, iters):
+    """What is left of the matrix there is rounding: its rows have to be as small, and as orthogonal, in either factor.
+    Bound: 16 roundings of fp32 of the largest value."""
+    g = np.random.default_rng(m + n)
+    u, _ = np.linalg.qr(g.normal(size=(m, rank)))
+    v, _ = np.linalg.qr(g.normal(size=(n, rank)))
+    e = ((u * g.uniform(0.1, 1.0, rank)) @ v.T).astype(np.float32)
+    a, bt, sig = _factors(e, r, g.normal(size=(r + 8, n)).astype(np.float32), iters)
+    assert np.all(np.diff(sig) <= 0)
+    for f in (a, bt):
+        assert np.max(np.abs(f @ f.T - np.diag(sig))) <= 1e-6 * sig[0]
+    if iters:
+        assert np.linalg.norm(bt.T @ a - e) <= 1e-6 * np.linalg.norm(e) * np.sqrt(rank)
