@@ -30,17 +30,22 @@ __device__ __forceinline__ int swz_kn(int krow) { return CH >= 16 ? ((krow & 7) 
 
 // Operand of lane `lane` for a 32x32x64 instruction from half kh of a K-contiguous tile (128-byte rows, swizzle swz_kc):
 // lane l holds row (l % 32), which the caller names, and the 32 K-bytes [32 (l / 32), +32) of the 64-deep half.
-__device__ __forceinline__ v8i read_kc_tile(const uint8_t* tile, int row, int kh, int lane)
+// Its two 16-byte chunks may come from two tiles.
+__device__ __forceinline__ v8i read_kc_tiles(const uint8_t* tile_lo, const uint8_t* tile_hi, int row, int kh, int lane)
 {
     const int cb = kh * 4 + (lane >> 5) * 2;
     const int sw = swz_kc(row);
-    const uint8_t* base = tile + row * BK;
-    const v4i lo = *reinterpret_cast<const v4i*>(base + ((cb ^ sw) << 4));
-    const v4i hi = *reinterpret_cast<const v4i*>(base + (((cb + 1) ^ sw) << 4));
+    const v4i lo = *reinterpret_cast<const v4i*>(tile_lo + row * BK + ((cb ^ sw) << 4));
+    const v4i hi = *reinterpret_cast<const v4i*>(tile_hi + row * BK + (((cb + 1) ^ sw) << 4));
     v8i r;
     r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
     r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
     return r;
+}
+
+__device__ __forceinline__ v8i read_kc_tile(const uint8_t* tile, int row, int kh, int lane)
+{
+    return read_kc_tiles(tile, tile, row, kh, lane);
 }
 
 __device__ __forceinline__ const uint8_t* opaque_uniform(const uint8_t* p)

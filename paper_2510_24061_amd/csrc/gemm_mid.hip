@@ -71,14 +71,29 @@ constexpr int mid_lds_bytes()
     return mid_max(ring, mid_max(exchange, rows));
 }
 
+// Rows of an operand that begin anywhere in a cache line (row length no multiple of 128 bytes): fetched from their own
+// first byte on, 128 of them lie across two lines, and in long rows the operands take half as long again to arrive.  SKEW
+// ([N,K] operands): a stage holds one whole line of every row instead.  A row begins `shift` chunks of 16 bytes into
+// its line 0, so chunk c of K-step k lies in stage k + (c + shift) / 8: a step's operands are in two stages, and one more
+// of the ring has landed.  In LDS a chunk keeps the place that it has without SKEW.  Rows eight apart have the same
+// shift, whatever their length.  (Lanes of a fetch that only changed places, so that every four lay in one half of a line,
+// gained nothing.)
+struct Skew {
+    int first, length;                                           // first row's place in its line, row length: chunks, modulo 8
+    __device__ Skew(const uint8_t* p, int64_t ld)
+        : first(static_cast<int>(reinterpret_cast<uintptr_t>(p) >> 4) & 7), length(static_cast<int>(ld >> 4) & 7) {}
+    __device__ int shift(int row) const { return (first + row * length) & 7; }
+};
+
 // One tile.  RIDE: the stages carry 32 adapter rows too and the tile writes its 32 MB x 32 block of O_A.
 // ADAPTER (run time): the tile is one of the adapter's own columns (output to c1, bf16, with its maximum).
-template <int MB, int NB, int S, bool B_KN, int A_FMT, bool RIDE, bool DB>
+template <int MB, int NB, int S, bool B_KN, int A_FMT, bool RIDE, bool DB, bool SKEW>
 __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, const int tile_n, const bool adapter,
                                          uint8_t* const lds)
 {
     static_assert(!RIDE || (!B_KN && A_FMT == 0), "the adapter product belongs to the forward product");
     static_assert(!DB || (B_KN && A_FMT == 1), "the adapter gradient belongs to the input-gradient product");
+    static_assert(!SKEW || !B_KN, "whole lines of rows are for operands whose rows run along K");
     const GemmArgs& g = t.g;
     constexpr int BM = 32 * MB, BN = 64 * NB;
     constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = A_BYTES + B_BYTES + (RIDE ? 32 * BK : 0);
@@ -97,19 +112,31 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     constexpr int CH = BN / 16, RPI = 64 / CH;                 // [K][N] tile: chunks per K-row, K-rows per fetch
     const int rows_a = static_cast<int>((M - m0) < BM ? (M - m0) : BM);
     const int rows_b = static_cast<int>((N - n0) < BN ? (N - n0) : BN);
+    const int r0 = tile_n * 32;                                 // first adapter row that rides on this tile
+    const uint8_t* const base_a = g.a + m0 * g.lda;
+    const uint8_t* const base_b = B_KN ? gb + n0 : gb + n0 * g.ldb;
+    const uint8_t* const base_r = RIDE ? t.side + static_cast<int64_t>(r0) * g.ldb : nullptr;
+    const Skew skew_a(base_a, g.lda), skew_b(base_b, g.ldb), skew_r(base_r, g.ldb);
+    // K-contiguous operand: what this lane fetches of LDS row `row`, which holds row rr: chunks behind the row's K-byte 128 s
+    auto chunk_kc = [&](const Skew& k, int row, int rr) {
+        const int c = (lane & 7) ^ swz_kc(row);
+        return SKEW && c + k.shift(rr) >= 8 ? c - 8 : c;
+    };
+    // (SKEW: stages begin one line before a row's line 0, so that the offset is not negative)
+    auto offset_kc = [&](const Skew& k, int row, int rr, int64_t ld) {
+        return static_cast<uint32_t>(rr) * static_cast<uint32_t>(ld) + static_cast<uint32_t>(chunk_kc(k, row, rr) * 16 + (SKEW ? BK : 0));
+    };
     uint32_t off_a[IT_A], off_b[IT_B], off_r = 0;
 #pragma unroll
     for (int it = 0; it < IT_A; ++it) {
         const int row = (it * 4 + wave) * 8 + (lane >> 3);
-        const int rr = row < rows_a ? row : rows_a - 1;
-        off_a[it] = static_cast<uint32_t>(rr) * static_cast<uint32_t>(g.lda) + (((lane & 7) ^ swz_kc(row)) << 4);
+        off_a[it] = offset_kc(skew_a, row, row < rows_a ? row : rows_a - 1, g.lda);
     }
 #pragma unroll
     for (int it = 0; it < IT_B; ++it) {
         if (!B_KN) {
             const int row = (it * 4 + wave) * 8 + (lane >> 3);
-            const int rr = row < rows_b ? row : rows_b - 1;
-            off_b[it] = static_cast<uint32_t>(rr) * static_cast<uint32_t>(g.ldb) + (((lane & 7) ^ swz_kc(row)) << 4);
+            off_b[it] = offset_kc(skew_b, row, row < rows_b ? row : rows_b - 1, g.ldb);
         } else {
             const int krow = (it * 4 + wave) * RPI + lane / CH;
             int c = (lane % CH) ^ swz_kn<CH>(krow);
@@ -117,15 +144,8 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
             off_b[it] = static_cast<uint32_t>(krow) * static_cast<uint32_t>(g.ldb) + c * 16;
         }
     }
-    const int r0 = tile_n * 32;                                 // first adapter row that rides on this tile
-    if constexpr (RIDE) {
-        const int row = wave * 8 + (lane >> 3);
-        const int rr = r0 + row < t.r ? row : static_cast<int>(t.r) - 1 - r0;
-        off_r = static_cast<uint32_t>(rr) * static_cast<uint32_t>(g.ldb) + (((lane & 7) ^ swz_kc(row)) << 4);
-    }
-    const uint8_t* const base_a = g.a + m0 * g.lda;
-    const uint8_t* const base_b = B_KN ? gb + n0 : gb + n0 * g.ldb;
-    const uint8_t* const base_r = RIDE ? t.side + static_cast<int64_t>(r0) * g.ldb : nullptr;
+    const int row_r = wave * 8 + (lane >> 3), rr_r = r0 + row_r < t.r ? row_r : static_cast<int>(t.r) - 1 - r0;
+    if constexpr (RIDE) off_r = offset_kc(skew_r, row_r, rr_r, g.ldb);
     auto dma16 = [&](const uint8_t* src, uint8_t* dst_wave_uniform) {
         __builtin_amdgcn_global_load_lds(FQ_GLOBAL_PTR(src), FQ_LDS_PTR(dst_wave_uniform), 16, 0, 0);
     };
@@ -135,12 +155,12 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         else if (j < IT_B + IT_A) dma16(pa + off_a[j - IT_B], dst + wave * 1024 + (j - IT_B) * 4096);
         else if (RIDE) dma16(pr + off_r, dst + A_BYTES + B_BYTES + wave * 1024);
     };
-    auto inside_a = [&](int s) { return opaque_uniform(base_a + static_cast<int64_t>(s) * BK); };
-    auto inside_b = [&](int s) { return opaque_uniform(base_b + static_cast<int64_t>(s) * BK * (B_KN ? g.ldb : 1)); };
-    auto inside_r = [&](int s) { return RIDE ? opaque_uniform(base_r + static_cast<int64_t>(s) * BK) : nullptr; };
+    auto inside_a = [&](int s) { return opaque_uniform(base_a + static_cast<int64_t>(SKEW ? s - 1 : s) * BK); };
+    auto inside_b = [&](int s) { return opaque_uniform(base_b + static_cast<int64_t>(SKEW ? s - 1 : s) * BK * (B_KN ? g.ldb : 1)); };
+    auto inside_r = [&](int s) { return RIDE ? opaque_uniform(base_r + static_cast<int64_t>(SKEW ? s - 1 : s) * BK) : nullptr; };
     auto fetch = [&](int s, uint8_t* dst) {
         const int64_t k0 = static_cast<int64_t>(s) * BK;
-        if (k0 + BK <= K) {
+        if (k0 + BK <= K && (!SKEW || s > 0)) {
             const uint8_t *pa = inside_a(s), *pb = inside_b(s), *pr = inside_r(s);
 #pragma unroll
             for (int j = 0; j < LPW; ++j) fetch_one(pa, pb, pr, dst, j);
@@ -148,12 +168,16 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         }
         uint8_t* const da = dst + wave * 1024;
         uint8_t* const db = dst + A_BYTES + wave * 1024;
+        // a lane's 16 bytes of a K-contiguous row, zeros where they lie outside the row
+        auto row_chunk = [&](const uint8_t* base, uint32_t off, int chunk) {
+            const int64_t gk = k0 + chunk * 16;
+            return gk < K && (!SKEW || gk >= 0) ? base + (SKEW ? k0 - BK : k0) + off : g_zero16;
+        };
 #pragma unroll
         for (int it = 0; it < IT_B; ++it) {
             if (!B_KN) {
                 const int row = (it * 4 + wave) * 8 + (lane >> 3);
-                const int64_t gk = k0 + (((lane & 7) ^ swz_kc(row)) << 4);
-                dma16(gk < K ? base_b + k0 + off_b[it] : g_zero16, db + it * 4096);
+                dma16(row_chunk(base_b, off_b[it], chunk_kc(skew_b, row, row < rows_b ? row : rows_b - 1)), db + it * 4096);
             } else {
                 const int krow = (it * 4 + wave) * RPI + lane / CH;
                 dma16(k0 + krow < K ? base_b + k0 * g.ldb + off_b[it] : g_zero16, db + it * 4096);
@@ -162,18 +186,17 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 #pragma unroll
         for (int it = 0; it < IT_A; ++it) {
             const int row = (it * 4 + wave) * 8 + (lane >> 3);
-            const int64_t gk = k0 + (((lane & 7) ^ swz_kc(row)) << 4);
-            dma16(gk < K ? base_a + k0 + off_a[it] : g_zero16, da + it * 4096);
+            dma16(row_chunk(base_a, off_a[it], chunk_kc(skew_a, row, row < rows_a ? row : rows_a - 1)), da + it * 4096);
         }
-        if constexpr (RIDE) {
-            const int row = wave * 8 + (lane >> 3);
-            const int64_t gk = k0 + (((lane & 7) ^ swz_kc(row)) << 4);
-            dma16(gk < K ? base_r + k0 + off_r : g_zero16, dst + A_BYTES + B_BYTES + wave * 1024);
-        }
+        if constexpr (RIDE) dma16(row_chunk(base_r, off_r, chunk_kc(skew_r, row_r, rr_r)), dst + A_BYTES + B_BYTES + wave * 1024);
     };
 
     // ---- LDS -> matrix-core operands (layouts as in the large tiles) ----------------------------
-    auto read_kc = [&](const uint8_t* tile, int row) { return read_kc_tile(tile, row, kh, lane); };
+    // K-contiguous operand: rows 32 block + lane % 32 of the tile at `offset` of a stage (SKEW: of two)
+    auto read_kc = [&](const uint8_t* st, const uint8_t* st_next, int offset, const Skew& k, int block) {
+        const int c = kh * 4 + (lane >> 5) * 2 + (SKEW ? k.shift(lane & 31) : 0), row = block * 32 + (lane & 31);
+        return read_kc_tiles((SKEW && c >= 8 ? st_next : st) + offset, (SKEW && c >= 7 ? st_next : st) + offset, row, kh, lane);
+    };
     // The transposing read goes out as inline assembly (through the builtin the compiler makes it wait
     // for every fetch in flight), so the compiler takes its results as there at once.  It copies registers
     // where control flow meets, so no read stays in flight across a branch: the reads of a stage, the matrix
@@ -202,22 +225,23 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     v8i af[2][MB], bf[2][NB], rf[2];
     v2i bt[2][NB][4];
 
-    const int KT = static_cast<int>((K + BK - 1) / BK);
+    const int KT = static_cast<int>((K + BK - 1) / BK), stages = KT + (SKEW ? 1 : 0);
     constexpr int N_FRAG = NB + MB + (RIDE ? 1 : 0);
-    auto read_frag = [&](auto parity, const uint8_t* st, int f) {
+    // (st_next: the stage behind st, looked at if SKEW)
+    auto read_frag = [&](auto parity, const uint8_t* st, const uint8_t* st_next, int f) {
         constexpr int P = decltype(parity)::value;
         if (f < NB) {
             if constexpr (B_KN) read_kn(st + A_BYTES, wn * NB * 32 + f * 32, bt[P][f]);
-            else bf[P][f] = read_kc(st + A_BYTES, wn * NB * 32 + f * 32 + (lane & 31));
+            else bf[P][f] = read_kc(st, st_next, A_BYTES, skew_b, wn * NB + f);
         } else if (f < NB + MB) {
-            af[P][f - NB] = read_kc(st, ((f - NB) ^ perm) * 32 + (lane & 31));
+            af[P][f - NB] = read_kc(st, st_next, 0, skew_a, (f - NB) ^ perm);
         } else if (RIDE) {
-            rf[P] = read_kc(st + A_BYTES + B_BYTES, lane & 31);
+            rf[P] = read_kc(st, st_next, A_BYTES + B_BYTES, skew_r, 0);
         }
     };
-    auto read_stage = [&](auto parity, const uint8_t* st) {
+    auto read_stage = [&](auto parity, const uint8_t* st, const uint8_t* st_next) {
 #pragma unroll
-        for (int f = 0; f < N_FRAG; ++f) read_frag(parity, st, f);
+        for (int f = 0; f < N_FRAG; ++f) read_frag(parity, st, st_next, f);
     };
     auto landed = [&](auto parity) {
         if constexpr (B_KN) {
@@ -288,6 +312,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
             }
         }
     };
+    constexpr int NEED = SKEW ? 2 : 1;                            // operands of step kt + 1 lie in stages up to kt + NEED
     int slot = 0;                                                 // ring slot of stage kt
     // STEADY: stage kt + S exists and lies inside K, so that the body carries no branch.  The others read a
     // stage kt + 1 too where there is none (bytes of the ring that nothing uses): a branch around the reads
@@ -295,27 +320,29 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     auto step = [&](auto parity, auto steady_tag, int kt) {
         constexpr int P = decltype(parity)::value;
         constexpr bool STEADY = decltype(steady_tag)::value;
-        // the operands of kt are in registers, stage kt + 1 has landed (of the stages behind it, those already
+        // the operands of kt are in registers, stage kt + NEED has landed (of the stages behind it, those already
         // fetched stay in flight) ...
         if constexpr (STEADY) {
-            __builtin_amdgcn_s_waitcnt((((S - 2) * LPW) & 15) | (7 << 4) | ((((S - 2) * LPW) >> 4) << 14));
+            __builtin_amdgcn_s_waitcnt((((S - 1 - NEED) * LPW) & 15) | (7 << 4) | ((((S - 1 - NEED) * LPW) >> 4) << 14));
         } else {
-            const int out = (KT - 1 < kt + S - 1 ? KT - 1 : kt + S - 1) - (kt + 1);
-            WaitStages<S - 2>::template run<LPW>(out > 0 ? out : 0);
+            const int out = (stages - 1 < kt + S - 1 ? stages - 1 : kt + S - 1) - (kt + NEED);
+            WaitStages<S - 1 - NEED>::template run<LPW>(out > 0 ? out : 0);
         }
         barrier_lds_only();                                       // ... for every wave: the slot of stage kt is free
         uint8_t* const freed = lds + slot * STAGE;
         slot = slot + 1 == S ? 0 : slot + 1;
+        const uint8_t* const st = lds + slot * STAGE;
+        const uint8_t* const st_next = SKEW ? lds + (slot + 1 == S ? 0 : slot + 1) * STAGE : st;
         const uint8_t *pa = nullptr, *pb = nullptr, *pr = nullptr;
         if constexpr (STEADY) {
             pa = inside_a(kt + S); pb = inside_b(kt + S); pr = inside_r(kt + S);
         } else {
-            if (kt + S < KT) fetch(kt + S, freed);
+            if (kt + S < stages) fetch(kt + S, freed);
         }
         if constexpr (DB) {
-            if (kt + 1 >= db_begin && kt + 1 < db_end) db_stage(lds + slot * STAGE, kt + 1);
+            if (kt + 1 >= db_begin && kt + 1 < db_end) db_stage(st, kt + 1);
         }
-        if constexpr (!STEADY) read_stage(std::integral_constant<int, 1 - P>{}, lds + slot * STAGE);
+        if constexpr (!STEADY) read_stage(std::integral_constant<int, 1 - P>{}, st, st_next);
         // The fetches are spread over the matrix instructions: a wave that issues them back to back, ahead
         // of its LDS reads, stalls on the CU's 64 B/clk vector-memory path.
         constexpr int PER = (LPW + MB * NB - 1) / (MB * NB), FPER = (N_FRAG + MB * NB - 1) / (MB * NB);
@@ -327,7 +354,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 #pragma unroll
                 for (int u = 0; u < (PER > FPER ? PER : FPER); ++u) {
                     if (u < FPER && b * FPER + u < N_FRAG)
-                        read_frag(std::integral_constant<int, 1 - P>{}, lds + slot * STAGE, b * FPER + u);
+                        read_frag(std::integral_constant<int, 1 - P>{}, st, st_next, b * FPER + u);
                     if (u < PER && b * PER + u < LPW) fetch_one(pa, pb, pr, freed, b * PER + u);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -344,7 +371,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     };
     float inv;
     {
-        const int first = KT < S ? KT : S;
+        const int first = stages < S ? stages : S;
         if constexpr (DB) {
             if (db_begin < db_end) {                              // 4 token rows of 256 bytes per wave instruction
 #pragma unroll
@@ -358,9 +385,9 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         for (int s = 0; s < first; ++s) fetch(s, lds + s * STAGE);
         // rescale factor: read behind the first fetches, so that its memory round trip hides under theirs
         inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / ((*g.sa) * (*g.sb)))));
-        WaitStages<S - 1>::template run<LPW>(first - 1);
+        WaitStages<S - NEED>::template run<LPW>(first - NEED);
         barrier_lds_only();
-        read_stage(std::integral_constant<int, 0>{}, lds);
+        read_stage(std::integral_constant<int, 0>{}, lds, lds + STAGE);
         landed(std::integral_constant<int, 0>{});
         if constexpr (DB) {
             if (db_begin == 0 && db_end > 0) db_stage(lds, 0);
@@ -480,7 +507,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 // Workgroup -> tile: XCD x (workgroup index modulo 8) takes tiles [x * chunk, (x + 1) * chunk) of a raster
 // that walks panels of PH tile rows, tile column by tile column: the token panel of an XCD stays in its
 // L2 and every weight column is fetched by one XCD per panel.
-template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB>
+template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB, bool SKEW>
 __global__ void __launch_bounds__(256)
 gemm_mid_kernel(const MidArgs t)
 {
@@ -497,11 +524,11 @@ gemm_mid_kernel(const MidArgs t)
     const int tile_n = rem / ph, tile_m = panel * PH + (rem - tile_n * ph);
     if constexpr (FWD) {
         if (tile_n < t.ride) {
-            mid_tile<MB, NB, S, B_KN, A_FMT, true, DB>(t, tile_m, tile_n, false, lds);
+            mid_tile<MB, NB, S, B_KN, A_FMT, true, DB, SKEW>(t, tile_m, tile_n, false, lds);
             return;
         }
     }
-    mid_tile<MB, NB, S, B_KN, A_FMT, false, DB>(t, tile_m, tile_n, tile_n >= t.tiles_n, lds);
+    mid_tile<MB, NB, S, B_KN, A_FMT, false, DB, SKEW>(t, tile_m, tile_n, tile_n >= t.tiles_n, lds);
 }
 
 // Adapter columns of their own cost nothing while they make no further round over the CUs; a step of a tile that
@@ -513,8 +540,9 @@ int own_columns(int64_t tiles_m, int64_t tiles_n, int64_t r, int bn)
     return tiles_n < (r + 31) / 32 || fits ? static_cast<int>(own) : 0;
 }
 
+// SKEW is for K from long_rows steps on (launch_gemm_mid).
 template <int MB, int NB, int S_FWD, int S_KN, int S_DB>
-hipError_t launch_cfg(MidArgs t, hipStream_t stream)
+hipError_t launch_cfg(MidArgs t, int long_rows, hipStream_t stream)
 {
     constexpr int BM = 32 * MB, BN = 64 * NB;
     t.tiles_m = static_cast<int>((t.g.M + BM - 1) / BM);
@@ -526,13 +554,20 @@ hipError_t launch_cfg(MidArgs t, hipStream_t stream)
     }
     t.chunk = (t.tiles_m * (t.tiles_n + t.tiles_a) + 7) / 8;
     const dim3 grid(static_cast<unsigned>(8 * t.chunk)), block(256);
+    // rows that do not all begin with a cache line (of a single row only its place counts)
+    auto across = [](const uint8_t* p, int64_t ld) { return ((reinterpret_cast<uintptr_t>(p) | static_cast<uintptr_t>(ld)) & (BK - 1)) != 0; };
+    const bool skew = t.g.K >= long_rows * BK && (across(t.g.a, t.g.lda) || across(t.g.b, t.g.ldb) || (t.side && across(t.side, t.g.ldb)));
+    auto go = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(t); };
     if (t.g.b_is_kn) {
-        if (t.g.a_fmt == 0) gemm_mid_kernel<MB, NB, S_KN, true, 0, false><<<grid, block, 0, stream>>>(t);
-        else if (t.oaq) gemm_mid_kernel<MB, NB, S_DB, true, 1, true><<<grid, block, 0, stream>>>(t);
-        else gemm_mid_kernel<MB, NB, S_KN, true, 1, false><<<grid, block, 0, stream>>>(t);
+        if (t.g.a_fmt == 0) go(gemm_mid_kernel<MB, NB, S_KN, true, 0, false, false>);
+        else if (t.oaq) go(gemm_mid_kernel<MB, NB, S_DB, true, 1, true, false>);
+        else go(gemm_mid_kernel<MB, NB, S_KN, true, 1, false, false>);
+    } else if (t.g.a_fmt == 0) {
+        if (skew) go(gemm_mid_kernel<MB, NB, S_FWD, false, 0, false, true>);
+        else go(gemm_mid_kernel<MB, NB, S_FWD, false, 0, false, false>);
     } else {
-        if (t.g.a_fmt == 0) gemm_mid_kernel<MB, NB, S_FWD, false, 0, false><<<grid, block, 0, stream>>>(t);
-        else gemm_mid_kernel<MB, NB, S_KN, false, 1, false><<<grid, block, 0, stream>>>(t);
+        if (skew) go(gemm_mid_kernel<MB, NB, S_KN, false, 1, false, true>);
+        else go(gemm_mid_kernel<MB, NB, S_KN, false, 1, false, false>);
     }
     return hipGetLastError();
 }
@@ -579,11 +614,19 @@ hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, hipStream_t s
 {
     MidArgs t;
     t.g = g; t.side = side.rows; t.r = side.r; t.oaq = side.oaq; t.db_partial = side.db_partial;
+    // The last argument of a configuration: K-steps from which rows across cache lines are fetched by whole lines.  Where the
+    // rows are shorter or the tiles smaller, the line that one step leaves half used is still near when the next one asks for
+    // it, and the stage more costs 0.3 to 1 us.  Plain products, us, by whole lines (from the rows' first bytes): 128-token
+    // tiles 1500 x 2000, K = 1040 11.5 (11.2), K = 1552 12.8 (13.1), K = 4112 21.0 (25.9), K = 8208 32.9 (41.9); 64 x 128 512 x 4096,
+    // K = 1040 8.4 (8.6), K = 1552 9.2 (10.4), K = 4112 15.2 (18.5), K = 8208 24.6 (32.6); 64 x 64 256 x 4096, K = 4112 10.9 (11.1),
+    // 500 x 1504, K = 4112 10.7 (10.1), K = 6160 14.2 (17.3); 32 x 64 128 x 4096, K = 6160 12.3 (11.7), K = 8208 15.1 (16.6),
+    // 100 x 3008, K = 8208 14.0 (13.1).  [K,N] operands: only the left one has such rows, 0.3 to 0.5 us slower up to K = 2064,
+    // 2 to 5 % faster from 4112 on: not built.
     switch (plan_mid(g.M, g.N, g.K, g.b_is_kn != 0, side.rows ? side.r : 0).config) {
-        case 0: return launch_cfg<1, 1, 8, 8, 8>(t, stream);
-        case 1: return launch_cfg<2, 1, 7, 8, 8>(t, stream);
-        case 2: return launch_cfg<2, 2, 5, 6, 6>(t, stream);
-        default: return launch_cfg<4, 2, 4, 5, 4>(t, stream);
+        case 0: return launch_cfg<1, 1, 8, 8, 8>(t, 64, stream);
+        case 1: return launch_cfg<2, 1, 7, 8, 8>(t, 40, stream);
+        case 2: return launch_cfg<2, 2, 5, 6, 6>(t, 12, stream);
+        default: return launch_cfg<4, 2, 4, 5, 4>(t, 12, stream);
     }
 }
 

@@ -55,6 +55,47 @@ def test_tiles_of_128_and_192_rows_exact_integer_layer_is_bit_exact(T, n, m, r):
     _exact_integer_layer(T, n, m, r)
 
 
+@pytest.mark.parametrize("T,n,m,r", [
+    (20, 8208, 144, 32),          # 32 x 64 tiles, rows one chunk of 16 bytes further into their lines each
+    (33, 8288, 272, 48),          # ... six chunks, two tile rows
+    (250, 5152, 4000, 64),        # 64 x 64, two chunks
+    (512, 1552, 4096, 64),        # 64 x 128, adapter rows riding, one chunk
+    (500, 1600, 3984, 48),        # ... four chunks, ragged
+    (500, 1648, 4080, 256),       # ... seven chunks, the largest rank
+    (1024, 1584, 4000, 96),       # 128 x 128, three chunks
+    (1500, 1616, 2000, 16),       # ... five chunks, adapter columns of their own
+])
+def test_long_rows_across_cache_lines_exact_integer_layer_is_bit_exact(T, n, m, r):
+    _exact_integer_layer(T, n, m, r)
+
+
+@pytest.mark.parametrize("M,N,K,a_at,b_at", [
+    (20, 144, 8192, 16, 0),       # rows of whole lines that begin inside one
+    (256, 2048, 5120, 0, 112),
+    (512, 4096, 1536, 64, 48),
+    (1000, 4000, 1552, 96, 32),
+    (1, 64, 8200 // 16 * 16, 80, 16),
+])
+@pytest.mark.parametrize("a_fmt", [fq.E4M3, fq.E5M2])
+def test_operands_that_begin_inside_a_cache_line(M, N, K, a_at, b_at, a_fmt):
+    """Codes of integers up to 4 in size: sums below 2^24 are exact in fp32 in any order."""
+    g = torch.Generator().manual_seed(M + N + K)
+    kind = torch.float8_e4m3fn if a_fmt == fq.E4M3 else torch.float8_e5m2
+    a = torch.randint(-4, 5, (M, K), generator=g).float()
+    b = torch.randint(-4, 5, (N, K), generator=g).float()
+
+    def placed(codes, at):
+        buf = torch.full((codes.numel() + at + 16,), 0x7f, dtype=torch.uint8, device="cuda")     # NaN around the operand
+        view = buf[at:at + codes.numel()].view(codes.shape)
+        view.copy_(codes.view(torch.uint8))
+        return view
+
+    one = torch.ones(1, device="cuda")
+    c = torch.empty(M, N, device="cuda")
+    fq.fp8_gemm(placed(a.to(kind), a_at), a_fmt, placed(b.to(torch.float8_e4m3fn), b_at), False, one, one, c)
+    assert torch.equal(c.cpu(), a @ b.T)
+
+
 @pytest.mark.parametrize("T,n,m,r", [(512, 1024, 1040, 64), (1900, 4096, 8208, 48)])
 def test_backward_also_works_in_the_smallest_workspace(T, n, m, r):
     """A workspace without room for the partial sums that the small or 128- and 192-row tiles would leave: the call
