@@ -122,6 +122,29 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
                                 void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * The melded forward of several layers that read one activation (the q, k and v projections, gate and up): x is
+ * quantized once, and the results of each layer are those of falqon_melded_fwd with x = NULL on these codes.
+ *
+ *   x        in   bf16 [T, n]; it may not lie over an output
+ *   layers   in   host array of `count` (1 .. FALQON_GROUP_MAX) descriptions; a workspace may serve several layers
+ *   xq, s_x  out  E4M3 [T, n] and its scale
+ *   amax_oa  out  [count] device scalars, one per layer
+ *   yt            dtype of every y
+ */
+#define FALQON_GROUP_MAX 256
+typedef struct falqon_group_layer {
+    const uint8_t* wq;      /* E4M3 [(m+r), n] */
+    const float* s_w;
+    void* y;                /* [T, m] */
+    void* o_a;              /* bf16 [T, r] */
+    int64_t m, r;
+    void* ws;               /* of at least falqon_workspace_bytes(T, n, m, r) */
+    size_t ws_bytes;
+} falqon_group_layer;
+falqon_status falqon_melded_fwd_group(const void* x, int64_t T, int64_t n, const falqon_group_layer* layers, int64_t count,
+                                      uint8_t* xq, float* s_x, float* amax_oa, falqon_dtype yt, void* stream);
+
+/*
  * Melded backward (first two lines of the backward-and-update loop, plus the input
  * gradient that an FP8 linear layer owes its predecessor; gradients are E5M2):
  *
@@ -152,6 +175,15 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
                                 uint8_t* dyq, float* s_dy, void* dx, falqon_dtype dxt,
                                 float* d_b, float* delta_buf, float lr, double* row_scores,
                                 void* ws, size_t ws_bytes, void* stream);
+
+/* The same with dx [T, n] bf16 in and out: the rounded product is added to what dx holds and the sum rounded again, as
+ * adding the tensor of falqon_melded_bwd would (layers that read one activation owe it the sum). */
+falqon_status falqon_melded_bwd_add(const void* dy, const uint8_t* wq, const float* s_w,
+                                    const void* o_a, const float* amax_oa,
+                                    int64_t T, int64_t n, int64_t m, int64_t r,
+                                    uint8_t* dyq, float* s_dy, void* dx,
+                                    float* d_b, float* delta_buf, float lr, double* row_scores,
+                                    void* ws, size_t ws_bytes, void* stream);
 
 /* Bytes of a row-score array for m buffer rows (host function); 0 if m is out of range. */
 size_t falqon_row_score_bytes(int64_t m);

@@ -19,6 +19,15 @@ _LIB_PATH = os.path.join(_HERE, "libfalqon.so")
 _lib = None
 
 
+GROUP_MAX = 256                 # FALQON_GROUP_MAX
+
+
+class GroupLayer(ctypes.Structure):
+    """falqon_group_layer"""
+    _fields_ = [("wq", ctypes.c_void_p), ("s_w", ctypes.c_void_p), ("y", ctypes.c_void_p), ("o_a", ctypes.c_void_p),
+                ("m", ctypes.c_int64), ("r", ctypes.c_int64), ("ws", ctypes.c_void_p), ("ws_bytes", ctypes.c_size_t)]
+
+
 class FalqonError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -52,6 +61,11 @@ def lib():
         L.falqon_melded_bwd.restype = c.c_int
         L.falqon_melded_bwd.argtypes = [vp, vp, f32p, vp, f32p, i64, i64, i64, i64, vp, f32p, vp, c.c_int,
                                         f32p, f32p, c.c_float, vp, vp, c.c_size_t, vp]
+        L.falqon_melded_bwd_add.restype = c.c_int
+        L.falqon_melded_bwd_add.argtypes = [vp, vp, f32p, vp, f32p, i64, i64, i64, i64, vp, f32p, vp,
+                                            f32p, f32p, c.c_float, vp, vp, c.c_size_t, vp]
+        L.falqon_melded_fwd_group.restype = c.c_int
+        L.falqon_melded_fwd_group.argtypes = [vp, i64, i64, c.POINTER(GroupLayer), i64, vp, f32p, f32p, c.c_int, vp]
         L.falqon_row_score_bytes.restype = c.c_size_t
         L.falqon_row_score_bytes.argtypes = [i64]
         L.falqon_proxy_update.restype = c.c_int
@@ -147,6 +161,22 @@ def melded_fwd(x, wq, s_w, m: int, r: int, xq, s_x, y, o_a, amax_oa, ws) -> None
     _check(st, "falqon_melded_fwd")
 
 
+def melded_fwd_group(x, layers, xq, s_x, amax_oa) -> None:
+    """layers: (wq, s_w, m, r, y, o_a, ws) of each; x is quantized once.  amax_oa: one element per layer."""
+    if amax_oa.numel() != len(layers) or any(l[4].dtype != layers[0][4].dtype for l in layers):
+        raise ValueError("one maximum per layer, outputs of one type")
+    _dev(x, xq, s_x, amax_oa)
+    T, n = xq.shape
+    described = (GroupLayer * len(layers))()
+    for d, (wq, s_w, m, r, y, o_a, ws) in zip(described, layers):
+        _dev(wq, s_w, y, o_a, ws)
+        d.wq, d.s_w, d.y, d.o_a, d.m, d.r = _p(wq), _p(s_w), _p(y), _p(o_a), m, r
+        d.ws, d.ws_bytes = _p(ws), ws.numel() * ws.element_size()
+    st = lib().falqon_melded_fwd_group(_p(x), T, n, described, len(layers), _p(xq), _p(s_x), _p(amax_oa),
+                                       _dtype_code(layers[0][4]), _stream())
+    _check(st, "falqon_melded_fwd_group")
+
+
 def row_score_bytes(m: int) -> int:
     return int(lib().falqon_row_score_bytes(m))
 
@@ -162,6 +192,19 @@ def melded_bwd(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b, de
                                  _p(row_scores),
                                  _p(ws), ws.numel() * ws.element_size(), _stream())
     _check(st, "falqon_melded_bwd")
+
+
+def melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b, delta_buf, lr: float, ws,
+                   row_scores=None) -> None:
+    """melded_bwd whose input gradient is added to what dx (bf16) holds."""
+    _dev(dy, wq, s_w, o_a, amax_oa, dyq, s_dy, dx, d_b, delta_buf, ws, row_scores)
+    if dx.dtype != torch.bfloat16:
+        raise TypeError("the sum of input gradients is bf16")
+    T, m = dy.shape
+    st = lib().falqon_melded_bwd_add(_p(dy), _p(wq), _p(s_w), _p(o_a), _p(amax_oa), T, n, m, r, _p(dyq), _p(s_dy),
+                                     _p(dx), _p(d_b), _p(delta_buf), float(lr), _p(row_scores),
+                                     _p(ws), ws.numel() * ws.element_size(), _stream())
+    _check(st, "falqon_melded_bwd_add")
 
 
 def proxy_update(delta_buf, wq, m: int, r: int, k: int, idx_out, ws, clear_selected: bool = True,

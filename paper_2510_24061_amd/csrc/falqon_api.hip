@@ -87,6 +87,145 @@ static bool bad_layer_shape(int64_t T, int64_t n, int64_t m, int64_t r)
            T > (int64_t(1) << 24) || n > (int64_t(1) << 20) || m > (int64_t(1) << 20);
 }
 
+// The forward call behind the quantizer: y and O_A from x~; *amax_oa has been reset.
+static falqon_status fwd_products(const uint8_t* wq, const float* s_w, int64_t T, int64_t n, int64_t m, int64_t r,
+                                  const uint8_t* xq, const float* s_x, void* y, falqon_dtype yt, void* o_a, float* amax_oa,
+                                  uint8_t* w8, const WsLayout& L, hipStream_t st)
+{
+    hipError_t e;
+    // O_merged <- x~ W~'^T / (s_w s_x), split into y and O_A.  Small and medium products run on small tiles
+    // that finish O_A in the same launch.  On the large tiles the r adapter columns ride along in the one
+    // GEMM, whose epilogue splits them off, when they fit into the last, partly empty tile column of the
+    // backbone product; otherwise they would add a whole, almost empty tile column (a second round over
+    // the CUs) and are formed by the backbone tiles' workgroups or by tiles of their own.
+    const OaTailPlan po = plan_oa_tail(T, n, m, r);
+    const bool fits = (m + r + 255) / 256 == (m + 255) / 256;
+    const bool mid = gemm_mid_supported(T, m) || (!use_big_tiles(T, m) && !fits && !po.use);
+    const bool merged = !mid && fits;
+    GemmArgs g;
+    g.a = xq; g.lda = n; g.a_fmt = 0;
+    g.b = wq; g.ldb = n; g.b_is_kn = 0;
+    g.M = T; g.N = merged ? m + r : m; g.K = n;
+    g.sa = s_x; g.sb = s_w;
+    g.c0 = y; g.ldc0 = m; g.c0_is_f32 = (yt == FALQON_F32); g.n_split = m;
+    g.c1 = o_a; g.ldc1 = r; g.amax1 = reinterpret_cast<uint32_t*>(amax_oa);
+    if (mid) {
+        MidSide side;
+        side.rows = wq + m * n; side.r = r;
+        e = launch_gemm_mid(g, side, st);
+        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    }
+    if (merged) {
+        e = launch_gemm(g, st);
+        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    }
+    // O_A <- x~ A~^T / (s_w s_x).  On the large tiles the backbone workgroups form it: inside their
+    // own K-steps, finished, where a tile row has enough tile columns to share it out; else as a
+    // side job ahead of the tile that leaves fp32 partials over K slices, which one more pass adds
+    // in order, rounds to bf16 and takes the maximum of.
+    float* part = reinterpret_cast<float*>(w8 + L.oa_partials);
+    if (po.use) {
+        TailArgs t;
+        t.side = wq + m * n; t.r = r; t.partial = part; t.splits = po.splits; t.steps_per_split = po.steps_per_split;
+        t.row_parts = po.row_parts; t.tile_rows = po.tile_rows;
+        e = launch_gemm_fwd_tail(g, t, st);
+        if (e != hipSuccess) return FALQON_ERR_HIP;
+        if (po.splits > 0)                                       // (no partials: the launch wrote O_A and its maximum)
+            e = launch_sum_partials_bf16(part, po.splits, T * r, static_cast<uint16_t*>(o_a),
+                                         reinterpret_cast<uint32_t*>(amax_oa), st);
+        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    }
+    // Otherwise: the same GEMM kernel on the adapter rows, K split over workgroups.  Nothing orders
+    // the two products, so both go out as one launch.
+    const int splits = oa_splits(T, r);
+    int64_t kps = (n + splits - 1) / splits;
+    kps = (kps + 127) / 128 * 128;
+    GemmArgs h;
+    h.a = xq; h.lda = n; h.a_fmt = 0;
+    h.b = wq + m * n; h.ldb = n; h.b_is_kn = 0;
+    h.M = T; h.N = r; h.K = n;
+    h.sa = s_x; h.sb = s_w;
+    h.c0 = part; h.ldc0 = r; h.c0_is_f32 = 1; h.n_split = r;
+    h.c1 = nullptr; h.ldc1 = 0; h.amax1 = nullptr;
+    h.splits = splits; h.k_per_split = kps;
+    e = launch_gemm_fwd_pair(g, h, st);
+    if (e != hipSuccess) return FALQON_ERR_HIP;
+    e = launch_sum_partials_bf16(part, splits, T * r, static_cast<uint16_t*>(o_a),
+                                 reinterpret_cast<uint32_t*>(amax_oa), st);
+    return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+}
+
+static falqon_status melded_bwd(const void* dy, const uint8_t* wq, const float* s_w,
+                                const void* o_a, const float* amax_oa,
+                                int64_t T, int64_t n, int64_t m, int64_t r,
+                                uint8_t* dyq, float* s_dy, void* dx, falqon_dtype dxt,
+                                float* d_b, float* delta_buf, float lr, double* row_scores,
+                                bool dx_adds, void* ws, size_t ws_bytes, void* stream)
+{
+    if (dxt != FALQON_BF16 && dxt != FALQON_F32) return FALQON_ERR_ENUM;
+    if (row_scores && !delta_buf) return FALQON_ERR_NULL;
+    if (row_scores && (reinterpret_cast<uintptr_t>(row_scores) & 7u)) return FALQON_ERR_ALIGN;
+    if (bad_layer_shape(T, n, m, r)) return FALQON_ERR_SHAPE;
+    if (!dy || !wq || !s_w || !o_a || !amax_oa || !dyq || !s_dy || !d_b) return FALQON_ERR_NULL;   // dx may be NULL
+    if (misaligned(dy) || misaligned(wq) || misaligned(o_a) || misaligned(dyq) || (dx && misaligned(dx)) ||
+        misaligned(d_b) || (delta_buf && misaligned(delta_buf)))
+        return FALQON_ERR_ALIGN;
+    if ((reinterpret_cast<uintptr_t>(s_w) & 3u) || (reinterpret_cast<uintptr_t>(s_dy) & 3u) ||
+        (reinterpret_cast<uintptr_t>(amax_oa) & 3u))
+        return FALQON_ERR_ALIGN;
+    WsLayout L = ws_layout(T, n, m, r, false);
+    const bool least = ws_bytes < L.total;
+    if (least) L = ws_layout(T, n, m, r, true);
+    if (!ws || ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
+    if (misaligned(ws)) return FALQON_ERR_ALIGN;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    uint8_t* w8 = static_cast<uint8_t*>(ws);
+
+    // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
+    // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
+    const DbTailPlan pd = dx && !(least && r > 64) ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
+    const int mid_parts = dx && !least ? mid_db_parts(T, n, m, r) : 0;
+    SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
+    ZeroWords zero{nullptr, 0};
+    if (row_scores && delta_buf && db_reduce_raises(m, r)) zero = {reinterpret_cast<uint32_t*>(row_scores + m), static_cast<int>(2 * score_blocks(m))};
+    hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
+                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || mid_parts ? &sc : nullptr, dx ? n : r);
+    if (e != hipSuccess) return FALQON_ERR_HIP;
+
+    // dX <- dy~ W~ / (s_dy s_w): the backbone rows of the concatenated weight, read as [K = m, N = n]
+    GemmArgs g;
+    g.a = dyq; g.lda = m; g.a_fmt = 1;
+    g.b = wq; g.ldb = n; g.b_is_kn = 1;
+    g.M = T; g.N = n; g.K = m;
+    g.sa = s_dy; g.sb = s_w;
+    g.c0 = dx; g.ldc0 = n; g.c0_is_f32 = (dxt == FALQON_F32); g.n_split = n; g.c0_adds = dx_adds;
+    g.c1 = nullptr; g.ldc1 = 0; g.amax1 = nullptr;
+    // dB <- dy~^T O_A~ / (s_dy s_oa);  DeltaBuffer += -lr dB.  Its partial pass reads only dy~ and
+    // O_A, so nothing orders it against the dX product: on the large tiles both go out as one launch.
+    const DbArgs d = make_db_args(dyq, o_a, amax_oa, T, m, r, reinterpret_cast<float*>(w8 + L.db_partials),
+                                  pd.use ? pd.groups : mid_parts ? mid_parts : db_splits(T, m));
+    if (mid_parts) {
+        MidSide side;
+        side.r = r; side.oaq = w8 + L.oa_codes; side.db_partial = d.partial;
+        e = launch_gemm_mid(g, side, st);
+    } else if (pd.use) {
+        TailArgs t;
+        t.side = w8 + L.oa_codes; t.r = r; t.partial = d.partial; t.splits = 0; t.steps_per_split = 0; t.row_parts = 1;
+        t.tile_rows = pd.tile_rows;
+        e = launch_gemm_dx_tail(g, t, st);
+    } else if (!dx) {
+        e = launch_db_partial(d, st);                      // the layer's input needs no gradient
+    } else if (gemm_dx_db_pair_supported(g)) {
+        e = launch_gemm_dx_db_pair(g, d, st);
+    } else {
+        e = launch_gemm(g, st);
+        if (e == hipSuccess) e = launch_db_partial(d, st);
+    }
+    if (e != hipSuccess) return FALQON_ERR_HIP;
+    e = launch_db_reduce(d, s_dy, d_b, delta_buf, lr, st, row_scores);
+    return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+}
+
 }  // namespace falqon
 
 using namespace falqon;
@@ -180,66 +319,42 @@ falqon_status falqon_melded_fwd(const void* x, const uint8_t* wq, const float* s
                      : launch_zero_word(reinterpret_cast<uint32_t*>(amax_oa), st);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
-    // O_merged <- x~ W~'^T / (s_w s_x), split into y and O_A.  Small and medium products run on small tiles
-    // that finish O_A in the same launch.  On the large tiles the r adapter columns ride along in the one
-    // GEMM, whose epilogue splits them off, when they fit into the last, partly empty tile column of the
-    // backbone product; otherwise they would add a whole, almost empty tile column (a second round over
-    // the CUs) and are formed by the backbone tiles' workgroups or by tiles of their own.
-    const OaTailPlan po = plan_oa_tail(T, n, m, r);
-    const bool fits = (m + r + 255) / 256 == (m + 255) / 256;
-    const bool mid = gemm_mid_supported(T, m) || (!use_big_tiles(T, m) && !fits && !po.use);
-    const bool merged = !mid && fits;
-    GemmArgs g;
-    g.a = xq; g.lda = n; g.a_fmt = 0;
-    g.b = wq; g.ldb = n; g.b_is_kn = 0;
-    g.M = T; g.N = merged ? m + r : m; g.K = n;
-    g.sa = s_x; g.sb = s_w;
-    g.c0 = y; g.ldc0 = m; g.c0_is_f32 = (yt == FALQON_F32); g.n_split = m;
-    g.c1 = o_a; g.ldc1 = r; g.amax1 = reinterpret_cast<uint32_t*>(amax_oa);
-    if (mid) {
-        MidSide side;
-        side.rows = wq + m * n; side.r = r;
-        e = launch_gemm_mid(g, side, st);
-        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    return fwd_products(wq, s_w, T, n, m, r, xq, s_x, y, yt, o_a, amax_oa, w8, L, st);
+}
+
+falqon_status falqon_melded_fwd_group(const void* x, int64_t T, int64_t n, const falqon_group_layer* layers, int64_t count,
+                                      uint8_t* xq, float* s_x, float* amax_oa, falqon_dtype yt, void* stream)
+{
+    if (yt != FALQON_BF16 && yt != FALQON_F32) return FALQON_ERR_ENUM;
+    if (count < 1 || count > FALQON_GROUP_MAX) return FALQON_ERR_SHAPE;
+    if (!layers || !x || !xq || !s_x || !amax_oa) return FALQON_ERR_NULL;
+    if (misaligned(x) || misaligned(xq) || ((reinterpret_cast<uintptr_t>(s_x) | reinterpret_cast<uintptr_t>(amax_oa)) & 3u))
+        return FALQON_ERR_ALIGN;
+    int64_t widest = 0;
+    for (int64_t i = 0; i < count; ++i) {
+        const falqon_group_layer& l = layers[i];
+        if (bad_layer_shape(T, n, l.m, l.r)) return FALQON_ERR_SHAPE;
+        if (!l.wq || !l.s_w || !l.y || !l.o_a) return FALQON_ERR_NULL;
+        if (misaligned(l.wq) || misaligned(l.y) || misaligned(l.o_a) || (reinterpret_cast<uintptr_t>(l.s_w) & 3u)) return FALQON_ERR_ALIGN;
+        if (!l.ws || l.ws_bytes < ws_layout(T, n, l.m, l.r, true).total) return FALQON_ERR_WORKSPACE;
+        if (misaligned(l.ws)) return FALQON_ERR_ALIGN;
+        if (l.m > widest) widest = l.m;
     }
-    if (merged) {
-        e = launch_gemm(g, st);
-        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
-    }
-    // O_A <- x~ A~^T / (s_w s_x).  On the large tiles the backbone workgroups form it: inside their
-    // own K-steps, finished, where a tile row has enough tile columns to share it out; else as a
-    // side job ahead of the tile that leaves fp32 partials over K slices, which one more pass adds
-    // in order, rounds to bf16 and takes the maximum of.
-    float* part = reinterpret_cast<float*>(w8 + L.oa_partials);
-    if (po.use) {
-        TailArgs t;
-        t.side = wq + m * n; t.r = r; t.partial = part; t.splits = po.splits; t.steps_per_split = po.steps_per_split;
-        t.row_parts = po.row_parts; t.tile_rows = po.tile_rows;
-        e = launch_gemm_fwd_tail(g, t, st);
-        if (e != hipSuccess) return FALQON_ERR_HIP;
-        if (po.splits > 0)                                       // (no partials: the launch wrote O_A and its maximum)
-            e = launch_sum_partials_bf16(part, po.splits, T * r, static_cast<uint16_t*>(o_a),
-                                         reinterpret_cast<uint32_t*>(amax_oa), st);
-        return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
-    }
-    // Otherwise: the same GEMM kernel on the adapter rows, K split over workgroups.  Nothing orders
-    // the two products, so both go out as one launch.
-    const int splits = oa_splits(T, r);
-    int64_t kps = (n + splits - 1) / splits;
-    kps = (kps + 127) / 128 * 128;
-    GemmArgs h;
-    h.a = xq; h.lda = n; h.a_fmt = 0;
-    h.b = wq + m * n; h.ldb = n; h.b_is_kn = 0;
-    h.M = T; h.N = r; h.K = n;
-    h.sa = s_x; h.sb = s_w;
-    h.c0 = part; h.ldc0 = r; h.c0_is_f32 = 1; h.n_split = r;
-    h.c1 = nullptr; h.ldc1 = 0; h.amax1 = nullptr;
-    h.splits = splits; h.k_per_split = kps;
-    e = launch_gemm_fwd_pair(g, h, st);
+    // one cast for all layers; it also resets the running maxima of their O_A (a launch of 3.6 us for each layer otherwise)
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    uint8_t* const w0 = static_cast<uint8_t*>(layers[0].ws);
+    const WsLayout L0 = ws_layout(T, n, layers[0].m, layers[0].r, true);
+    const hipError_t e = launch_quantize(x, FALQON_BF16, T, n, n, FALQON_E4M3, nullptr, xq, n, s_x, nullptr,
+                                         reinterpret_cast<float*>(w0 + L0.amax_partials),
+                                         ZeroWords{reinterpret_cast<uint32_t*>(amax_oa), static_cast<int>(count)}, st, nullptr, widest);
     if (e != hipSuccess) return FALQON_ERR_HIP;
-    e = launch_sum_partials_bf16(part, splits, T * r, static_cast<uint16_t*>(o_a),
-                                 reinterpret_cast<uint32_t*>(amax_oa), st);
-    return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+    for (int64_t i = 0; i < count; ++i) {
+        const falqon_group_layer& l = layers[i];
+        const falqon_status status = fwd_products(l.wq, l.s_w, T, n, l.m, l.r, xq, s_x, l.y, yt, l.o_a, amax_oa + i,
+                                                  static_cast<uint8_t*>(l.ws), ws_layout(T, n, l.m, l.r, true), st);
+        if (status != FALQON_OK) return status;
+    }
+    return FALQON_OK;
 }
 
 falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* s_w,
@@ -249,68 +364,18 @@ falqon_status falqon_melded_bwd(const void* dy, const uint8_t* wq, const float* 
                                 float* d_b, float* delta_buf, float lr, double* row_scores,
                                 void* ws, size_t ws_bytes, void* stream)
 {
-    if (dxt != FALQON_BF16 && dxt != FALQON_F32) return FALQON_ERR_ENUM;
-    if (row_scores && !delta_buf) return FALQON_ERR_NULL;
-    if (row_scores && (reinterpret_cast<uintptr_t>(row_scores) & 7u)) return FALQON_ERR_ALIGN;
-    if (bad_layer_shape(T, n, m, r)) return FALQON_ERR_SHAPE;
-    if (!dy || !wq || !s_w || !o_a || !amax_oa || !dyq || !s_dy || !d_b) return FALQON_ERR_NULL;   // dx may be NULL
-    if (misaligned(dy) || misaligned(wq) || misaligned(o_a) || misaligned(dyq) || (dx && misaligned(dx)) ||
-        misaligned(d_b) || (delta_buf && misaligned(delta_buf)))
-        return FALQON_ERR_ALIGN;
-    if ((reinterpret_cast<uintptr_t>(s_w) & 3u) || (reinterpret_cast<uintptr_t>(s_dy) & 3u) ||
-        (reinterpret_cast<uintptr_t>(amax_oa) & 3u))
-        return FALQON_ERR_ALIGN;
-    WsLayout L = ws_layout(T, n, m, r, false);
-    const bool least = ws_bytes < L.total;
-    if (least) L = ws_layout(T, n, m, r, true);
-    if (!ws || ws_bytes < L.total) return FALQON_ERR_WORKSPACE;
-    if (misaligned(ws)) return FALQON_ERR_ALIGN;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    uint8_t* w8 = static_cast<uint8_t*>(ws);
+    return melded_bwd(dy, wq, s_w, o_a, amax_oa, T, n, m, r, dyq, s_dy, dx, dxt, d_b, delta_buf, lr, row_scores, false, ws, ws_bytes, stream);
+}
 
-    // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
-    // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
-    const DbTailPlan pd = dx && !(least && r > 64) ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
-    const int mid_parts = dx && !least ? mid_db_parts(T, n, m, r) : 0;
-    SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
-    ZeroWords zero{nullptr, 0};
-    if (row_scores && delta_buf && db_reduce_raises(m, r)) zero = {reinterpret_cast<uint32_t*>(row_scores + m), static_cast<int>(2 * score_blocks(m))};
-    hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
-                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || mid_parts ? &sc : nullptr, dx ? n : r);
-    if (e != hipSuccess) return FALQON_ERR_HIP;
-
-    // dX <- dy~ W~ / (s_dy s_w): the backbone rows of the concatenated weight, read as [K = m, N = n]
-    GemmArgs g;
-    g.a = dyq; g.lda = m; g.a_fmt = 1;
-    g.b = wq; g.ldb = n; g.b_is_kn = 1;
-    g.M = T; g.N = n; g.K = m;
-    g.sa = s_dy; g.sb = s_w;
-    g.c0 = dx; g.ldc0 = n; g.c0_is_f32 = (dxt == FALQON_F32); g.n_split = n;
-    g.c1 = nullptr; g.ldc1 = 0; g.amax1 = nullptr;
-    // dB <- dy~^T O_A~ / (s_dy s_oa);  DeltaBuffer += -lr dB.  Its partial pass reads only dy~ and
-    // O_A, so nothing orders it against the dX product: on the large tiles both go out as one launch.
-    const DbArgs d = make_db_args(dyq, o_a, amax_oa, T, m, r, reinterpret_cast<float*>(w8 + L.db_partials),
-                                  pd.use ? pd.groups : mid_parts ? mid_parts : db_splits(T, m));
-    if (mid_parts) {
-        MidSide side;
-        side.r = r; side.oaq = w8 + L.oa_codes; side.db_partial = d.partial;
-        e = launch_gemm_mid(g, side, st);
-    } else if (pd.use) {
-        TailArgs t;
-        t.side = w8 + L.oa_codes; t.r = r; t.partial = d.partial; t.splits = 0; t.steps_per_split = 0; t.row_parts = 1;
-        t.tile_rows = pd.tile_rows;
-        e = launch_gemm_dx_tail(g, t, st);
-    } else if (!dx) {
-        e = launch_db_partial(d, st);                      // the layer's input needs no gradient
-    } else if (gemm_dx_db_pair_supported(g)) {
-        e = launch_gemm_dx_db_pair(g, d, st);
-    } else {
-        e = launch_gemm(g, st);
-        if (e == hipSuccess) e = launch_db_partial(d, st);
-    }
-    if (e != hipSuccess) return FALQON_ERR_HIP;
-    e = launch_db_reduce(d, s_dy, d_b, delta_buf, lr, st, row_scores);
-    return e == hipSuccess ? FALQON_OK : FALQON_ERR_HIP;
+falqon_status falqon_melded_bwd_add(const void* dy, const uint8_t* wq, const float* s_w,
+                                    const void* o_a, const float* amax_oa,
+                                    int64_t T, int64_t n, int64_t m, int64_t r,
+                                    uint8_t* dyq, float* s_dy, void* dx,
+                                    float* d_b, float* delta_buf, float lr, double* row_scores,
+                                    void* ws, size_t ws_bytes, void* stream)
+{
+    if (!dx) return FALQON_ERR_NULL;
+    return melded_bwd(dy, wq, s_w, o_a, amax_oa, T, n, m, r, dyq, s_dy, dx, FALQON_BF16, d_b, delta_buf, lr, row_scores, true, ws, ws_bytes, stream);
 }
 
 falqon_status falqon_db_bf16(const uint8_t* dyq, const float* s_dy, const void* o_a,

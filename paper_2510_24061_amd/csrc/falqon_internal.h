@@ -56,6 +56,7 @@ struct GemmArgs {
     void* c0; int64_t ldc0; int c0_is_f32; int64_t n_split;
     void* c1; int64_t ldc1; uint32_t* amax1;
     int splits = 1; int64_t k_per_split = int64_t(1) << 40;   // split K: c0 becomes [splits][M][ldc0] partials
+    int c0_adds = 0;         // bf16 c0 of an input-gradient product: the rounded product is added to what c0 holds
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // g (large product, 256x256 tiles) and h (a split-K product on 128x128 tiles) in one launch; both

@@ -783,12 +783,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     if constexpr (RIDE) {
         if (lane == 0) ride_max_slot[wave] = ride_max;
     }
-    // the output type is a run-time argument; each of the two bodies is compiled with it fixed
-    auto epilogue = [&](auto is_f32) {
-        constexpr bool F32 = decltype(is_f32)::value;
+    // the output type, and whether the product is added to what the output holds, are run-time arguments; each body is
+    // compiled with them fixed
+    auto epilogue = [&](auto is_f32, auto adds) {
+        constexpr bool F32 = decltype(is_f32)::value, ADDS = decltype(adds)::value;
         constexpr int ES = F32 ? 4 : 2;
         constexpr int PITCH = BN * ES + 16;                       // +16 B: rows start on different banks
         constexpr int SEGS = BN * ES / 16, COLS_PER_SEG = 16 / ES;
+        constexpr int PIECES = WM * 32 * SEGS / (64 * NW);        // 16 bytes per lane each
+        uint4 held[2][ADDS ? PIECES : 1];                         // what a pass adds to, requested a pass ahead
+        auto request = [&](int mi) {
+#pragma unroll
+            for (int it = 0; it < PIECES; ++it) {
+                const int sidx = it * 64 * NW + threadIdx.x;
+                const int64_t row = m0 + ((sidx / SEGS) >> 5) * (MB * 32) + mi * 32 + ((sidx / SEGS) & 31);
+                const int64_t col = n0 + sidx % SEGS * COLS_PER_SEG;
+                if (row < M && col < N) held[mi & 1][it] = *reinterpret_cast<const uint4*>(c0p + (row * g.ldc0 + col) * ES);
+            }
+        };
+        if constexpr (ADDS) request(0);
 #pragma unroll
         for (int mi = 0; mi < MB; ++mi) {
             uint8_t* srow = lds + (wm * 32 + (lane & 31)) * PITCH;
@@ -813,15 +826,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
                     }
                 }
             }
-            __syncthreads();
+            if constexpr (ADDS) {
+                if (mi + 1 < MB) request(mi + 1);
+                barrier_lds_written();
+            } else {
+                __syncthreads();
+            }
 #pragma unroll
-            for (int it = 0; it < WM * 32 * SEGS / (64 * NW); ++it) {
+            for (int it = 0; it < PIECES; ++it) {
                 const int sidx = it * 64 * NW + threadIdx.x;
                 const int srw = sidx / SEGS, seg = sidx % SEGS;
                 const int64_t row = m0 + (srw >> 5) * (MB * 32) + mi * 32 + (srw & 31);
                 const int64_t col = n0 + seg * COLS_PER_SEG;
                 if (row < M && col < N) {
-                    const uint4 d = *reinterpret_cast<const uint4*>(lds + srw * PITCH + seg * 16);
+                    uint4 d = *reinterpret_cast<const uint4*>(lds + srw * PITCH + seg * 16);
+                    if constexpr (ADDS) d = add_bf16x8(held[mi & 1][it], d);
                     if (col < g.n_split) {
                         // streaming store: every workgroup writes 512-byte row segments of its tile at
                         // the same time; the output is not read again by this layer
@@ -853,8 +872,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
             __syncthreads();
         }
     };
-    if (g.c0_is_f32) epilogue(std::true_type{});
-    else epilogue(std::false_type{});
+    // (Adding in the epilogue costs the launch 5.5 us at 2048 x 4096 x 4096, 37.6 -> 43.1: the sum is read at the rate of the
+    // memory while the tiles write theirs.  A pass of its own took 9.2 us and a launch.)
+    constexpr bool MAY_ADD = B_KN && A_FMT == 1;
+    if (g.c0_is_f32) epilogue(std::true_type{}, std::false_type{});
+    else if (MAY_ADD && g.c0_adds) epilogue(std::false_type{}, std::bool_constant<MAY_ADD>{});
+    else epilogue(std::false_type{}, std::false_type{});
     if constexpr (RIDE) {                                         // (the epilogue ends with a barrier)
         if (g.amax1 && threadIdx.x == 0) {
             float mx = ride_max_slot[0];

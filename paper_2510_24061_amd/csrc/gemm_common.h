@@ -68,6 +68,15 @@ __device__ __forceinline__ void barrier_lds_only()
     asm volatile("" ::: "memory");
 }
 
+// The same behind LDS writes of this wave: they have been carried out, loads from memory may still be in flight.
+__device__ __forceinline__ void barrier_lds_written()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt 0 only
+    barrier_lds_only();
+}
+
 // two fp32 -> two bf16 (round to nearest even) in one dword: v_cvt_pk_bf16_f32
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 {
@@ -75,6 +84,16 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
     const v2f f = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
+}
+
+// a + b of eight bf16 each, every sum rounded once (what adding two bf16 tensors gives)
+__device__ __forceinline__ uint4 add_bf16x8(uint4 a, uint4 b)
+{
+    auto add2 = [](uint32_t x, uint32_t y) {
+        return pack_bf16x2(__uint_as_float(x << 16) + __uint_as_float(y << 16),
+                           __uint_as_float(x & 0xffff0000u) + __uint_as_float(y & 0xffff0000u));
+    };
+    return make_uint4(add2(a.x, b.x), add2(a.y, b.y), add2(a.z, b.z), add2(a.w, b.w));
 }
 
 }  // namespace

@@ -87,12 +87,13 @@ struct Skew {
 
 // One tile.  RIDE: the stages carry 32 adapter rows too and the tile writes its 32 MB x 32 block of O_A.
 // ADAPTER (run time): the tile is one of the adapter's own columns (output to c1, bf16, with its maximum).
-template <int MB, int NB, int S, bool B_KN, int A_FMT, bool RIDE, bool DB, bool SKEW>
+template <int MB, int NB, int S, bool B_KN, int A_FMT, bool RIDE, bool DB, bool SKEW, bool ADDS>
 __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, const int tile_n, const bool adapter,
                                          uint8_t* const lds)
 {
     static_assert(!RIDE || (!B_KN && A_FMT == 0), "the adapter product belongs to the forward product");
     static_assert(!DB || (B_KN && A_FMT == 1), "the adapter gradient belongs to the input-gradient product");
+    static_assert(!ADDS || (B_KN && A_FMT == 1), "input gradients are what is added up");
     static_assert(!SKEW || !B_KN, "whole lines of rows are for operands whose rows run along K");
     const GemmArgs& g = t.g;
     constexpr int BM = 32 * MB, BN = 64 * NB;
@@ -455,7 +456,16 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     auto epilogue = [&](auto is_f32, void* out, int64_t ld) {
         constexpr bool F32 = decltype(is_f32)::value;
         constexpr int ES = F32 ? 4 : 2;
-        constexpr int PITCH = BN * ES + 16, SEGS = BN * ES / 16, COLS = 16 / ES;
+        constexpr int PITCH = BN * ES + 16, SEGS = BN * ES / 16, COLS = 16 / ES, PIECES = BM * SEGS / 256;
+        uint4 held[ADDS ? PIECES : 1];                            // on its way while the tile is parked
+        if constexpr (ADDS) {
+#pragma unroll
+            for (int it = 0; it < PIECES; ++it) {
+                const int sidx = it * 256 + static_cast<int>(threadIdx.x);
+                const int64_t row = m0 + sidx / SEGS, col = n0 + sidx % SEGS * COLS;
+                if (row < M && col < N) held[it] = *reinterpret_cast<const uint4*>(static_cast<const uint8_t*>(out) + (row * ld + col) * ES);
+            }
+        }
 #pragma unroll
         for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
@@ -477,7 +487,19 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
                 }
             }
         __syncthreads();
-        for (int it = 0; it < BM * SEGS / 256; ++it) {
+        if constexpr (ADDS) {
+#pragma unroll
+            for (int it = 0; it < PIECES; ++it) {
+                const int sidx = it * 256 + static_cast<int>(threadIdx.x);
+                const int srw = sidx / SEGS, seg = sidx % SEGS;
+                const int64_t row = m0 + srw, col = n0 + seg * COLS;
+                if (row >= M || col >= N) continue;
+                *reinterpret_cast<uint4*>(static_cast<uint8_t*>(out) + (row * ld + col) * ES) =
+                    add_bf16x8(held[it], *reinterpret_cast<const uint4*>(lds + srw * PITCH + seg * 16));
+            }
+            return;
+        }
+        for (int it = 0; it < PIECES; ++it) {
             const int sidx = it * 256 + static_cast<int>(threadIdx.x);
             const int srw = sidx / SEGS, seg = sidx % SEGS;
             const int64_t row = m0 + srw, col = n0 + seg * COLS;
@@ -495,7 +517,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
         }
     };
     if (adapter) epilogue(std::false_type{}, g.c1, g.ldc1);
-    else if (g.c0_is_f32) epilogue(std::true_type{}, g.c0, g.ldc0);
+    else if (!ADDS && g.c0_is_f32) epilogue(std::true_type{}, g.c0, g.ldc0);
     else epilogue(std::false_type{}, g.c0, g.ldc0);
     if ((RIDE || adapter) && g.amax1) {
         for (int off = 32; off > 0; off >>= 1) oa_max = fmaxf(oa_max, __shfl_xor(oa_max, off, 64));
@@ -507,7 +529,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 // Workgroup -> tile: XCD x (workgroup index modulo 8) takes tiles [x * chunk, (x + 1) * chunk) of a raster
 // that walks panels of PH tile rows, tile column by tile column: the token panel of an XCD stays in its
 // L2 and every weight column is fetched by one XCD per panel.
-template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB, bool SKEW>
+template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB, bool SKEW, bool ADDS = false>
 __global__ void __launch_bounds__(256)
 gemm_mid_kernel(const MidArgs t)
 {
@@ -524,11 +546,11 @@ gemm_mid_kernel(const MidArgs t)
     const int tile_n = rem / ph, tile_m = panel * PH + (rem - tile_n * ph);
     if constexpr (FWD) {
         if (tile_n < t.ride) {
-            mid_tile<MB, NB, S, B_KN, A_FMT, true, DB, SKEW>(t, tile_m, tile_n, false, lds);
+            mid_tile<MB, NB, S, B_KN, A_FMT, true, DB, SKEW, false>(t, tile_m, tile_n, false, lds);
             return;
         }
     }
-    mid_tile<MB, NB, S, B_KN, A_FMT, false, DB, SKEW>(t, tile_m, tile_n, tile_n >= t.tiles_n, lds);
+    mid_tile<MB, NB, S, B_KN, A_FMT, false, DB, SKEW, ADDS>(t, tile_m, tile_n, tile_n >= t.tiles_n, lds);
 }
 
 // Adapter columns of their own cost nothing while they make no further round over the CUs; a step of a tile that
@@ -560,6 +582,8 @@ hipError_t launch_cfg(MidArgs t, int long_rows, hipStream_t stream)
     auto go = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(t); };
     if (t.g.b_is_kn) {
         if (t.g.a_fmt == 0) go(gemm_mid_kernel<MB, NB, S_KN, true, 0, false, false>);
+        else if (t.g.c0_adds && t.oaq) go(gemm_mid_kernel<MB, NB, S_DB, true, 1, true, false, true>);
+        else if (t.g.c0_adds) go(gemm_mid_kernel<MB, NB, S_KN, true, 1, false, false, true>);
         else if (t.oaq) go(gemm_mid_kernel<MB, NB, S_DB, true, 1, true, false>);
         else go(gemm_mid_kernel<MB, NB, S_KN, true, 1, false, false>);
     } else if (t.g.a_fmt == 0) {

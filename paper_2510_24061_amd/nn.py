@@ -31,18 +31,21 @@ def _flat_bf16(t: torch.Tensor, width: int) -> torch.Tensor:
     return t2.contiguous()
 
 
-def _layer_backward(layer: "MeldedLoRALinear", dy2: torch.Tensor, o_a, amax_oa, want_dx: bool):
-    """One falqon_melded_bwd call; returns dx (None when the input needs no gradient)."""
+def _layer_backward(layer: "MeldedLoRALinear", dy2: torch.Tensor, o_a, amax_oa, want_dx: bool, total=None):
+    """One falqon_melded_bwd call; returns dx (None when the input needs no gradient), or `total` with dx added to it."""
     T, dev = dy2.shape[0], dy2.device
     dyq = torch.empty(T, layer.out_features, dtype=torch.uint8, device=dev)
     s_dy = torch.empty(1, dtype=torch.float32, device=dev)
-    dx = torch.empty(T, layer.in_features, dtype=torch.bfloat16, device=dev) if want_dx else None
+    dx = total
+    if want_dx and total is None:
+        dx = torch.empty(T, layer.in_features, dtype=torch.bfloat16, device=dev)
     if layer.sgd_lr is not None:
         buf, lr = layer.delta_buf, layer.sgd_lr            # the buffer step happens inside the call
     else:
         buf, lr = layer.grad_acc, -1.0                      # acc += dB, waiting for adamw_step()
-    _b.melded_bwd(dy2, layer.wq, layer.s_w, o_a, amax_oa, layer.in_features, layer.rank, dyq, s_dy, dx,
-                  layer.d_b, buf, lr, layer._workspace(T))
+    call = _b.melded_bwd if total is None else _b.melded_bwd_add
+    call(dy2, layer.wq, layer.s_w, o_a, amax_oa, layer.in_features, layer.rank, dyq, s_dy, dx,
+         layer.d_b, buf, lr, layer._workspace(T))
     layer.backward_calls += 1
     return dx
 
@@ -86,16 +89,17 @@ class _MeldedGroupFn(torch.autograd.Function):
         T, dev = x2.shape[0], x2.device
         xq = torch.empty(T, first.in_features, dtype=torch.uint8, device=dev)
         s_x = torch.empty(1, dtype=torch.float32, device=dev)
-        _b.quantize(x2, _b.E4M3, xq, s_x, first._workspace(T))
-        outs, saved = [], []
-        for layer in layers:
+        amax_oa = torch.empty(len(layers), dtype=torch.float32, device=dev)
+        outs, saved, calls = [], [], []
+        for i, layer in enumerate(layers):
             y = torch.empty(T, layer.out_features, dtype=torch.bfloat16, device=dev)
             o_a = torch.empty(T, layer.rank, dtype=torch.bfloat16, device=dev)
-            amax_oa = torch.empty(1, dtype=torch.float32, device=dev)
-            _b.melded_fwd(None, layer.wq, layer.s_w, layer.out_features, layer.rank, xq, s_x, y, o_a, amax_oa,
-                          layer._workspace(T))
+            calls.append((layer.wq, layer.s_w, layer.out_features, layer.rank, y, o_a, layer._workspace(T)))
             outs.append(y.reshape(*lead, layer.out_features))
-            saved += [o_a, amax_oa]
+            saved += [o_a, amax_oa[i:i + 1]]
+        _b.melded_fwd_group(x2, calls[:_b.GROUP_MAX], xq, s_x, amax_oa[:_b.GROUP_MAX])
+        for i, (wq, s_w, m, r, y, o_a, ws) in enumerate(calls[_b.GROUP_MAX:], _b.GROUP_MAX):
+            _b.melded_fwd(None, wq, s_w, m, r, xq, s_x, y, o_a, amax_oa[i:i + 1], ws)
         ctx.group, ctx.T, ctx.lead = group, T, lead
         ctx.save_for_backward(*saved)
         return tuple(outs)
@@ -112,9 +116,7 @@ class _MeldedGroupFn(torch.autograd.Function):
                 dy2 = torch.zeros(T, layer.out_features, dtype=torch.bfloat16, device=o_a.device)
             else:
                 dy2 = _flat_bf16(dy, layer.out_features)
-            dx = _layer_backward(layer, dy2, o_a, amax_oa, want_dx)
-            if want_dx:
-                total = dx if total is None else total.add_(dx)
+            total = _layer_backward(layer, dy2, o_a, amax_oa, want_dx, total)
         return (total.reshape(*ctx.lead, layers[0].in_features) if want_dx else None), None, None
 
 
