@@ -47,31 +47,98 @@ constexpr int kMaxSlices = 12;             // slices of the contracted dimension
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// Vectors as the products read them: blocks of 16 elements x 16 vectors in the operand layout of
-// v_mfma_f32_16x16x4_f32, so that a wave reads 1 KB in a row.  Lane t of the instruction holds row t % 16 of an operand
-// and depth index t / 16; a contraction may take its terms in any order as long as both operands agree, so depth index
-// h of four consecutive instructions stands for the elements 4 h .. 4 h + 3 of the block.  Element j of vector c lies
-// in block (j / 16, c / 16) at lane c % 16 + 16 (j % 16 / 4), component j % 4.  Vectors are padded to whole blocks of
-// 16, elements to blocks of 32, both with zeros.
+// The two products with E run on the bf16 matrix cores, with both operands in three parts: an fp32 number is the sum of its
+// rounding to bf16, the rounding of what that leaves, and what is left then (8 bits and a sign each, exact).  Six of the
+// nine products of parts are formed (v_mfma_f32_16x16x32_bf16, exact products added in fp32, small ones first); the
+// others are below 2^-26 of the whole, and an instruction adds 32 terms where the fp32 one adds four, so sums come out nearer to
+// 64 bits than on the fp32 matrix cores (3.7e-7 against 5.4e-7 of a sum of 4096 terms of random sign).  At 4096 x 4096,
+// l = 72, the fp32 cores need 17 us for a product, the six on the bf16 ones 6.5, and E, split on the way from memory to the
+// operands, becomes what bounds it: a launch takes 21.6 us (30.5 on the fp32 cores; 25 with the operands of two steps in registers instead of three).
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v8f __attribute__((ext_vector_type(8)));
+constexpr int kParts = 3;
 
-// The two products with E run on the fp32 matrix cores.  At 4096 x 4096, l = 72 (80 with the padding) these need
-// 17 us at 2.4 GHz, and a launch takes 30 us (50 and 75 us with 32 x 32 x 2 instructions and 16 bytes of a row per lane
-// for both operands, a partial result per wave and no packing; 41 us with two waves of 32 rows in place of one of 64).
-// The vectors are packed, and every operand of E comes with 64 or 256 bytes of its row.  The next step's operands are requested before this step's products.
-// The four waves of a workgroup share out the steps of a slice and add up in LDS, which leaves a quarter of the partial
-// sums in memory.  The accumulator of (first, second) operand holds, in lane t, column t % 16 = the second operand's
-// row, and in register v the first operand's row 4 (t / 16) + v.
+__device__ __forceinline__ void split(v8f x, v8bf (&part)[kParts])
+{
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) {
+        part[k] = __builtin_convertvector(x, v8bf);
+        if (k + 1 < kParts) x -= __builtin_convertvector(part[k], v8f);
+    }
+}
 
-// part[s][c][i] = sum over columns j of slice s of Z[c][j] E[i][j]; a workgroup owns 64 rows of E
+// Vectors as the products read them: blocks of 32 elements x 16 vectors, per block its three parts in the operand layout of
+// the instruction, so that a wave reads 1 KB in a row.  Lane t holds row t % 16 of an operand and depths 8 (t / 16) .. + 7:
+// element j of vector c lies in block (j / 32, c / 16) at lane c % 16 + 16 (j % 32 / 8), component j % 8.  Vectors are
+// padded to whole blocks of 16, elements to blocks of 32, both with zeros.
+//
+// The vectors are packed, and every operand of E comes with 128 or 256 bytes of its row.  The next step's operands are
+// requested before this step's products.  The four waves of a workgroup share out the steps of a slice and add up in LDS,
+// which leaves a quarter of the partial sums in memory.  The accumulator of (first, second) operand holds, in lane t,
+// column t % 16 = the second operand's row, and in register v the first operand's row 4 (t / 16) + v.
+template <int CB>
+struct Products {
+    v4f acc[4][CB];
+    static constexpr int DEPTH = CB <= 5 ? 3 : 2;                     // steps whose operands are in registers or on their way
+    v8bf zf[DEPTH][CB][kParts];
+
+    __device__ __forceinline__ Products()
+    {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[x][cb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    // blocks [first, first + CB) of `blocks`
+    __device__ __forceinline__ void fetch(const v8bf* __restrict__ packed, int64_t step, int blocks, int first, int lane, int which)
+    {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int k = 0; k < kParts; ++k) zf[which][cb][k] = packed[((step * blocks + first + cb) * kParts + k) * 64 + lane];
+    }
+    // steps first, first + 4, ... below end
+    template <class F, class M>
+    __device__ __forceinline__ static void run(int64_t first, int64_t end, F fetch, M multiply)
+    {
+#pragma unroll
+        for (int d = 0; d + 1 < DEPTH; ++d)
+            if (first + 4 * d < end) fetch(first + 4 * d, d);
+        for (int64_t b = first; b < end; b += 4 * DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                if (b + 4 * d >= end) break;
+                if (b + 4 * (d + DEPTH - 1) < end) fetch(b + 4 * (d + DEPTH - 1), (d + DEPTH - 1) % DEPTH);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(d);
+            }
+        }
+    }
+    // 16 vectors x CB by 16 rows of E, 32 deep
+    __device__ __forceinline__ void multiply(int x, v8f e, int which)
+    {
+        v8bf ef[kParts];
+        split(e, ef);
+        constexpr int Z[6] = {2, 0, 1, 1, 0, 0}, E[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[which][cb][Z[q]], ef[E[q]], acc[x][cb], 0, 0, 0);
+    }
+};
+
+// part[s][c][i] = sum over columns j of slice s of Z[c][j] E[i][j]; a workgroup owns 64 rows of E and CB blocks of vectors (all
+// up to seven; eight, whose operands would not fit the registers, are two halves)
 template <int CB>
 __global__ void __launch_bounds__(kThreads)
-apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* __restrict__ zp, int l,
+apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ zp, int l,
                float* __restrict__ part, int64_t per_slice)
 {
     constexpr int PITCH = 68;
     __shared__ __attribute__((aligned(16))) float s_sum[4][CB * 16 * PITCH];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (n + 15) / 16;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (n + 31) / 32;
     const int64_t begin = static_cast<int64_t>(blockIdx.y) * per_slice;
     const int64_t end = begin + per_slice < steps ? begin + per_slice : steps;
     const float* erow[4];
@@ -80,49 +147,34 @@ apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* _
         const int64_t row = i0 + 16 * x + row16;
         erow[x] = e + (row < m ? row : m - 1) * n;                   // rows beyond E are computed and not stored
     }
-    v4f acc[4][CB];
+    Products<CB> p;
+    v4f ef[Products<CB>::DEPTH][4][2];
+    auto fetch = [&](int64_t b, int which) {
+        int64_t j[2] = {b * 32 + 8 * quad, b * 32 + 8 * quad + 4};
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+        for (int h = 0; h < 2; ++h)
+            if (j[h] >= n) j[h] = n - 4;                             // (the vectors are zero there)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[x][cb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    auto fetch = [&](int64_t b, v4f (&ef)[4], v4f (&zf)[CB]) {
-        int64_t j = b * 16 + 4 * quad;
-        if (j >= n) j = n - 4;                                       // (the vectors are zero there)
+        for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int x = 0; x < 4; ++x) ef[x] = *reinterpret_cast<const v4f*>(erow[x] + j);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) zf[cb] = *reinterpret_cast<const v4f*>(zp + (b * CB + cb) * 256 + lane * 4);
+            for (int h = 0; h < 2; ++h) ef[which][x][h] = *reinterpret_cast<const v4f*>(erow[x] + j[h]);
+        p.fetch(zp, b, CB * static_cast<int>(gridDim.z), CB * static_cast<int>(blockIdx.z), lane, which);
     };
-    auto multiply = [&](const v4f (&ef)[4], const v4f (&zf)[CB]) {
+    auto multiply = [&](int which) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(zf[cb][u], ef[x][u], acc[x][cb], 0, 0, 0);
+        for (int x = 0; x < 4; ++x) p.multiply(x, __builtin_shufflevector(ef[which][x][0], ef[which][x][1], 0, 1, 2, 3, 4, 5, 6, 7), which);
     };
-    v4f ef[4], ef2[4], zf[CB], zf2[CB];
-    int64_t b = begin + wave;
-    if (b < end) fetch(b, ef, zf);
-    for (; b < end; b += 8) {
-        fetch(b + 4 < end ? b + 4 : b, ef2, zf2);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ef, zf);
-        if (b + 4 >= end) break;
-        fetch(b + 8 < end ? b + 8 : b, ef, zf);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ef2, zf2);
-    }
+    p.run(begin + wave, end, fetch, multiply);
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + x * 16 + row16] = acc[x][cb][v];
+            for (int v = 0; v < 4; ++v) s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + x * 16 + row16] = p.acc[x][cb][v];
     __syncthreads();
-    float* const out = part + static_cast<int64_t>(blockIdx.y) * l * m;
-    for (int q = threadIdx.x; q < l * 16; q += kThreads) {
+    const int c0 = 16 * CB * static_cast<int>(blockIdx.z), vectors = l - c0 < 16 * CB ? l - c0 : 16 * CB;
+    float* const out = part + (static_cast<int64_t>(blockIdx.y) * l + c0) * m;
+    for (int q = threadIdx.x; q < vectors * 16; q += kThreads) {
         const int c = q >> 4, i4 = (q & 15) * 4;
         if (i0 + i4 >= m) continue;                                  // m is a multiple of 4
         v4f s = *reinterpret_cast<const v4f*>(&s_sum[0][c * PITCH + i4]);
@@ -133,63 +185,49 @@ apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* _
 }
 
 // part[s][c][j] = sum over rows i of slice s of Y[c][i] E[i][j]; a workgroup owns 64 columns of E: lane t reads four
-// columns 4 (t % 16) + x of one row, one for each of four column blocks
+// columns 4 (t % 16) + x of eight rows, one for each of four column blocks
 template <int CB>
 __global__ void __launch_bounds__(kThreads)
-apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const float* __restrict__ yp, int l,
+apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ yp, int l,
                 float* __restrict__ part, int64_t per_slice)
 {
     constexpr int PITCH = 68;
     __shared__ __attribute__((aligned(16))) float s_sum[4][CB * 16 * PITCH];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
-    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (m + 15) / 16;
+    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (m + 31) / 32;
     const int64_t begin = static_cast<int64_t>(blockIdx.y) * per_slice;
     const int64_t end = begin + per_slice < steps ? begin + per_slice : steps;
     const int64_t col = j0 + 4 * row16 < n ? j0 + 4 * row16 : n - 4; // columns beyond E are computed and not stored
-    v4f acc[4][CB];
+    Products<CB> p;
+    v4f ef[Products<CB>::DEPTH][8];
+    auto fetch = [&](int64_t b, int which) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[x][cb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    auto fetch = [&](int64_t b, v4f (&ef)[4], v4f (&yf)[CB]) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t i = b * 16 + 4 * quad + v;
-            ef[v] = *reinterpret_cast<const v4f*>(e + (i < m ? i : m - 1) * n + col);   // (the vectors are zero beyond)
+        for (int v = 0; v < 8; ++v) {
+            const int64_t i = b * 32 + 8 * quad + v;
+            ef[which][v] = *reinterpret_cast<const v4f*>(e + (i < m ? i : m - 1) * n + col);   // (the vectors are zero beyond)
         }
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) yf[cb] = *reinterpret_cast<const v4f*>(yp + (b * CB + cb) * 256 + lane * 4);
+        p.fetch(yp, b, CB * static_cast<int>(gridDim.z), CB * static_cast<int>(blockIdx.z), lane, which);
     };
-    auto multiply = [&](const v4f (&ef)[4], const v4f (&yf)[CB]) {
+    auto multiply = [&](int which) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int x = 0; x < 4; ++x) {
+            v8f column;
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(yf[cb][v], ef[v][x], acc[x][cb], 0, 0, 0);
+            for (int v = 0; v < 8; ++v) column[v] = ef[which][v][x];
+            p.multiply(x, column, which);
+        }
     };
-    v4f ef[4], ef2[4], yf[CB], yf2[CB];
-    int64_t b = begin + wave;
-    if (b < end) fetch(b, ef, yf);
-    for (; b < end; b += 8) {
-        fetch(b + 4 < end ? b + 4 : b, ef2, yf2);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ef, yf);
-        if (b + 4 >= end) break;
-        fetch(b + 8 < end ? b + 8 : b, ef, yf);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ef2, yf2);
-    }
+    p.run(begin + wave, end, fetch, multiply);
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             *reinterpret_cast<v4f*>(&s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + 4 * row16]) =
-                v4f{acc[0][cb][v], acc[1][cb][v], acc[2][cb][v], acc[3][cb][v]};
+                v4f{p.acc[0][cb][v], p.acc[1][cb][v], p.acc[2][cb][v], p.acc[3][cb][v]};
     __syncthreads();
-    float* const out = part + static_cast<int64_t>(blockIdx.y) * l * n;
-    for (int q = threadIdx.x; q < l * 16; q += kThreads) {
+    const int c0 = 16 * CB * static_cast<int>(blockIdx.z), vectors = l - c0 < 16 * CB ? l - c0 : 16 * CB;
+    float* const out = part + (static_cast<int64_t>(blockIdx.y) * l + c0) * n;
+    for (int q = threadIdx.x; q < vectors * 16; q += kThreads) {
         const int c = q >> 4, j4 = (q & 15) * 4;
         if (j0 + j4 >= n) continue;                                  // n is a multiple of 4
         v4f s = *reinterpret_cast<const v4f*>(&s_sum[0][c * PITCH + j4]);
@@ -360,7 +398,7 @@ factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
 // the layout above with its padding.
 template <int CB>
 __global__ void __launch_bounds__(CB * 64)
-apply_lower_kernel(const float* src, float* dst, float* __restrict__ packed, int l, int64_t len,
+apply_lower_kernel(const float* src, float* dst, uint32_t* __restrict__ packed, int l, int64_t len,
                    const double* __restrict__ linv)
 {
     const int R = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
@@ -386,13 +424,32 @@ apply_lower_kernel(const float* src, float* dst, float* __restrict__ packed, int
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[q] : 0.0, p < l ? static_cast<double>(b[q]) : 0.0, acc, 0, 0, 0);
     }
     __syncthreads();                                                  // dst may be src
+    float o[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int cc = quad + 4 * v;
         const bool in = 16 * R + cc < l && j < len;
-        const float o = static_cast<float>(acc[v]);
-        if (in && dst) dst[static_cast<int64_t>(16 * R + cc) * len + j] = o;
-        packed[(static_cast<int64_t>(blockIdx.x) * CB + R) * 256 + (cc + 16 * (row16 >> 2)) * 4 + (row16 & 3)] = in ? o : 0.0f;
+        o[v] = in ? static_cast<float>(acc[v]) : 0.0f;
+        if (in && dst) dst[static_cast<int64_t>(16 * R + cc) * len + j] = o[v];
+    }
+    // Elements j and j + 1 share a word: of each two vectors, the lane of the even one writes the first, the odd one the second.
+    const bool odd = row16 & 1;
+    const int element = static_cast<int>(blockIdx.x & 1) * 16 + row16;                   // of the block of 32
+    uint32_t* const block = packed + (static_cast<int64_t>(blockIdx.x >> 1) * CB + R) * (kParts * 256);
+#pragma unroll
+    for (int pair = 0; pair < 2; ++pair) {
+        const float other = __shfl_xor(odd ? o[2 * pair] : o[2 * pair + 1], 1, 64);
+        float lo = odd ? other : o[2 * pair], hi = odd ? o[2 * pair + 1] : other;
+        const int cc = quad + 4 * (2 * pair + (odd ? 1 : 0));
+#pragma unroll
+        for (int k = 0; k < kParts; ++k) {
+            typedef float v2f __attribute__((ext_vector_type(2)));
+            typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+            const uint32_t word = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{lo, hi}, v2bf));
+            block[k * 256 + (cc + 16 * (element >> 3)) * 4 + ((element & 7) >> 1)] = word;
+            lo -= __uint_as_float(word << 16);
+            hi -= __uint_as_float(word & 0xffff0000u);
+        }
     }
 }
 
@@ -729,7 +786,7 @@ SvdLayout svd_layout(int64_t m, int64_t n, int64_t r)
 
 // rows of dst[l][len] <- orthonormal basis of the rows of src (Cholesky QR, `passes` times), and the same packed for
 // the products; dst may be src; h and lfac are l x l fp64 scratch
-static hipError_t orthonormalize_rows(const float* src, float* dst, float* packed, int l, int64_t len, double* h,
+static hipError_t orthonormalize_rows(const float* src, float* dst, uint32_t* packed, int l, int64_t len, double* h,
                                       double* lfac, int passes, hipStream_t stream)
 {
     const int nb = l / 4;
@@ -759,24 +816,29 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     double* p = reinterpret_cast<double*>(ws + L.p);
     double* lambda = reinterpret_cast<double*>(ws + L.lambda);
     float* part = reinterpret_cast<float*>(ws + L.part);
-    float* packed = reinterpret_cast<float*>(ws + L.packed);
+    uint32_t* packed = reinterpret_cast<uint32_t*>(ws + L.packed);
     // Y[l][m] = Z E^T (transposed == false) or Z[l][n] = Y E: slices of the contracted dimension so that about 256
     // workgroups stream E, each with at least one step per wave, then the ordered sum
     auto product = [&](bool transposed, float* out) -> hipError_t {
         const int64_t rows = transposed ? n : m, depth = transposed ? m : n;
-        const int64_t blocks = (rows + 63) / 64, steps = (depth + 15) / 16;
+        const int64_t blocks = (rows + 63) / 64, steps = (depth + 31) / 32;
         int64_t slices = 256 / blocks;
         if (slices > kMaxSlices) slices = kMaxSlices;
         if (slices > (steps + 3) / 4) slices = (steps + 3) / 4;
         if (slices < 1) slices = 1;
         const int64_t per = (steps + slices - 1) / slices;
         slices = (steps + per - 1) / per;
-        const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(slices));
+        const int vector_blocks = (l + 15) / 16, halves = vector_blocks == 8 ? 2 : 1;
+        const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(slices), static_cast<unsigned>(halves));
         float* dst = slices > 1 ? part : out;
+        const v8bf* const vectors = reinterpret_cast<const v8bf*>(packed);
 #define FQ_PRODUCT(CB)                                                                                       \
-        if (transposed) apply_et_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, packed, l, dst, per);    \
-        else apply_e_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, packed, l, dst, per)
-        FQ_BY_BLOCKS((l + 15) / 16, FQ_PRODUCT)
+        if (transposed) apply_et_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, vectors, l, dst, per);   \
+        else apply_e_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, vectors, l, dst, per)
+        switch (vector_blocks / halves) {
+            case 2: FQ_PRODUCT(2); break; case 3: FQ_PRODUCT(3); break; case 4: FQ_PRODUCT(4); break;
+            case 5: FQ_PRODUCT(5); break; case 6: FQ_PRODUCT(6); break; default: FQ_PRODUCT(7); break;
+        }
 #undef FQ_PRODUCT
         hipError_t pe = hipGetLastError();
         if (pe != hipSuccess || slices == 1) return pe;

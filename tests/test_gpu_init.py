@@ -122,6 +122,24 @@ def test_largest_subspaces(m, n, r):
     assert np.max(np.abs(a @ a.T - np.diag(sig))) <= 1e-4 * sig[0]
 
 
+@pytest.mark.parametrize("r,scale", [(16, 1.0), (32, 1e30), (48, 1.0), (64, 1.0), (64, 1e-33), (80, 1e-20), (96, 1.0), (112, 1.0), (120, 1.0)])
+def test_products_of_many_steps_against_64_bits(r, scale):
+    """Every number of vector blocks, on a matrix whose products take several steps per wave and end inside one, against the
+    same iteration in fp64.  A product of fp32 rounding error moves Ritz values by at most its relative size, which for
+    sums of 2500 terms of random sign is about 1e-6 at the very worst (2500 roundings of 6e-8 adding up as a random walk
+    over sums of 2500 terms: 6e-8)."""
+    m, n, iters = 2500, 2420, 1
+    e = np.random.default_rng(r).normal(size=(m, n)).astype(np.float32) * np.float32(scale)
+    a, sig = _factor(e, r, iters=iters, seed=r)
+    e64 = e.astype(np.float64) / scale
+    z = np.linalg.qr(torch.randn(r + 8, n, generator=torch.Generator().manual_seed(r)).numpy().astype(np.float64).T)[0]
+    for _ in range(iters):
+        z = np.linalg.qr(e64.T @ np.linalg.qr(e64 @ z)[0])[0]
+    want = np.linalg.svd(e64 @ z, compute_uv=False)[:r]
+    assert np.max(np.abs(sig / scale - want)) <= 1e-6 * want[0]
+    assert np.max(np.abs((a / scale) @ a.T - np.diag(sig / scale))) <= 1e-5 * want[0]
+
+
 @pytest.mark.parametrize("rank", [0, 5])
 def test_matrix_of_lower_rank_than_asked_for(rank):
     """Vectors in the span of the others drop out (all of them for a zero matrix); nothing becomes NaN."""
