@@ -260,133 +260,164 @@ sum_slices_kernel(const float* __restrict__ part, int slices, int64_t count, flo
 // condition limited by the rounding of the product to about 1e7).  The last basis, which the Rayleigh-Ritz step and
 // A^ take as orthonormal, gets a second one: orthonormal at the precision it is stored in while cond(V) < 1e8.
 //
-// L^-1 by elimination on [G | I] in blocks of 4 x 4, one per thread.  Step b, with D the pivot block, P(k) the blocks
-// below it and V(j) those of its row, subtracts P(k) D^-1 V(j) from block (k, j), k > b.  Column b of the left half is
-// finished in step b, where column b of the right one begins, so one lower triangle of registers holds both.  D is
-// factored by every thread for itself (W = inverse of its unit factor, D^-1 = W^T diag(1/d) W), so a step costs one
-// exchange through LDS, one barrier, a chain of four reciprocals and the update.  (With a scalar pivot per step the
-// chain of barriers and reciprocals was four times as long: 29 us at l = 72 against 23.)
+// L^-1 by elimination on [G | I] in blocks of 16 x 16, all as accumulators of v_mfma_f64_16x16x4_f64, a wave for each (or up to
+// three).  Step b: its pivot block D is factored by one wave (W D W^T diagonal, W unit lower triangular), a row per lane, in 16
+// pivots that pass through no memory (row_newbcast, an instruction per element; moved first and added then: 15.1 us the launch); F(R) = P(R) W^T for the blocks P(R) below it and, transposed, W V(C) for those
+// of its row in the right half; then block (R, C) loses F(R) diag(1/d) F(C)^T, R > b.  Column b of the left half is
+// finished in step b, where column b of the right one begins, so one lower triangle of blocks holds both halves; the rows of
+// step b are finished too, and are written scaled with d^(-1/2).  A step costs the chain of 16 pivots (about 2000 cycles), two barriers
+// and two chains of four matrix instructions: 12.6 us at l = 72.  (Blocks of 4 x 4, one per thread, the pivot block factored by
+// every thread for itself and everything through LDS between steps: 23.3 us; with a scalar pivot per step 29.)
 // FACTOR: L^T itself instead (its upper triangle; nothing else is written); pivots below the rounding of their own
 // diagonal entry, which the subtractions cannot fall below, are null.  (Entries of G may differ by the square of the range
 // of singular values: measured against the largest one, all values below 3e-8 of it would be lost, also those of rows
 // that have nothing to do with it.)
-constexpr int kFactorThreads = 576;                                   // 32 * 33 / 2 blocks at l = 128, in whole waves
+constexpr int factor_blocks(int nb) { return nb * (nb + 1) / 2; }
+constexpr int factor_waves(int nb) { return factor_blocks(nb) < 16 ? factor_blocks(nb) : 16; }
 
-template <bool FACTOR>
-__global__ void __launch_bounds__(kFactorThreads)
+// lane N of the row of 16 lanes
+template <int N>
+__device__ __forceinline__ double of_lane(double v)
+{
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + N, 0xf, 0xf, true);
+}
+
+// v += u times the v of lane N of the row of 16, in one instruction (the compiler takes two and a wait in between).  `first`: v
+// may have been written by the instruction before, which a DPP read has to be two behind.
+template <int N>
+__device__ __forceinline__ void add_of_lane(double& v, double u, bool first)
+{
+    if (first) asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(v) : "v"(u), "n"(N));
+    else asm volatile("v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(v) : "v"(u), "n"(N));
+}
+
+template <int N, int END, typename F>
+__device__ __forceinline__ void for_each(F f)
+{
+    if constexpr (N < END) {
+        f(std::integral_constant<int, N>{});
+        for_each<N + 1, END>(f);
+    }
+}
+
+template <int NB, bool FACTOR>
+__global__ void __launch_bounds__(64 * factor_waves(NB))
 factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
 {
-    constexpr int BP = 18;                                            // doubles per block: 16 at an odd number of 16 bytes
-    __shared__ __attribute__((aligned(16))) double s_p[2][kMaxL / 4 * BP], s_q[2][kMaxL / 4 * BP];
-    __shared__ __attribute__((aligned(16))) double s_w[kMaxL / 4 * BP];
-    __shared__ double s_least[kMaxL];                                 // pivots up to these are null
-    const int t = threadIdx.x, nb = l / 4;                            // l is a multiple of 8
-    int R = static_cast<int>((sqrtf(8.0f * static_cast<float>(t) + 1.0f) - 1.0f) * 0.5f);
-    if (R * (R + 1) / 2 > t) --R;
-    if ((R + 1) * (R + 2) / 2 <= t) ++R;
-    const int C = t - R * (R + 1) / 2;
-    const bool live = R < nb;                                         // block row R, block column C <= R
-    double x[4][4];
+    constexpr int WAVES = factor_waves(NB), PER = (factor_blocks(NB) + WAVES - 1) / WAVES;
+    constexpr int P = 18;                                             // doubles per row of a block: rows spread over the banks
+    __shared__ __attribute__((aligned(16))) double s_in[NB][16 * P], s_f[NB][16 * P], s_w[16 * P], s_inv[2][16];
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), x = t & 15, quad = (t >> 4) & 3;
+    // Blocks wave, wave + WAVES, ... of the lower triangle, row by row; register v of a block holds row quad + 4 v, column x.
+    int R[PER], C[PER];
+    v4d acc[PER];
+    double least[PER];                                                // pivots up to this are null (of row x)
+    const double largest = FACTOR ? 0.0 : fmax(g[0], 1e-300);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int s = 0; s < PER; ++s) {
+        const int q = wave + s * WAVES;
+        int r = 0;
+        while ((r + 1) * (r + 2) / 2 <= q) ++r;
+        R[s] = r;                                                     // (beyond the triangle: never equal to, or below, a step)
+        C[s] = q - r * (r + 1) / 2;
+        if (q >= factor_blocks(NB)) R[s] = -1;
+        const int row = 16 * r + x;
+        least[s] = row >= l ? 0.0 : FACTOR ? 1e-15 * g[row * l + row] : 1e-28 * largest;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[i][j] = live ? g[(4 * R + i) * l + 4 * C + j] : 0.0;
-    for (int i = t; i < l; i += static_cast<int>(blockDim.x)) s_least[i] = FACTOR ? 1e-15 * g[i * l + i] : 1e-28 * fmax(g[0], 1e-300);
-    for (int cb = 0; cb < nb; ++cb) {
-        double* const pc = s_p[cb & 1];                               // P(R); the buffers alternate: one barrier per step
-        double* const vr = s_q[cb & 1];                               // V(C) of either half; the identity for C = cb
-        if (live && C == cb) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    pc[R * BP + 4 * i + j] = x[i][j];
-                    vr[R * BP + 4 * i + j] = R == cb ? (i == j ? 1.0 : 0.0) : x[j][i];
-                }
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * r + quad + 4 * v, j = 16 * C[s] + x;
+            acc[s][v] = R[s] >= 0 && i < l && j < l ? g[i * l + j] : i == j ? 1.0 : 0.0;     // (padded with the identity)
         }
-        if (!FACTOR && live && R == cb && C < cb) {
+    }
+    // of row x of a block in LDS, the elements 4 quad .. + 3: depth index `quad` of four consecutive instructions
+    auto row_part = [&](const double* block, double (&part)[4]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int u = 0; u < 4; ++u) part[u] = block[x * P + 4 * quad + u];
+    };
+    auto product = [&](const double (&a)[4], const double (&b)[4], v4d c) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) vr[C * BP + 4 * i + j] = x[i][j];
+        for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], c, 0, 0, 0);
+        return c;
+    };
+    for (int b = 0; b < NB; ++b) {
+        // what the next products read: the column below the pivot block, its row in the right half transposed
+#pragma unroll
+        for (int s = 0; s < PER; ++s) {
+            if (C[s] == b && R[s] >= b) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s_in[R[s]][(quad + 4 * v) * P + x] = acc[s][v];
+            } else if (!FACTOR && R[s] == b) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s_in[C[s]][x * P + quad + 4 * v] = acc[s][v];
+            }
+            if (R[s] != b || C[s] != b) continue;
+            // the pivot block: lane x holds its row x, four times over, and columns 4 quad .. + 3 of row x of W
+            asm volatile("" ::: "memory");                            // (a wave's LDS accesses are carried out in order)
+            const int row = 16 * b + x;
+            double d[16], w[4], own = 0.0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) d[j] = s_in[b][x * P + j];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[c] = 4 * quad + c == x ? 1.0 : 0.0;
+            for_each<0, 16>([&](auto tag) {
+                constexpr int k = decltype(tag)::value;
+                const double p = of_lane<k>(d[k]);
+                double r = __builtin_amdgcn_rcp(p);                   // and two Newton steps: full precision
+                r = fma(fma(-p, r, 1.0), r, r);
+                r = fma(fma(-p, r, 1.0), r, r);
+                const double inv = p > of_lane<k>(least[s]) ? r : 0.0;   // a dead row takes no part
+                if (x == k) own = inv;
+                const double u = x > k ? -d[k] * inv : 0.0;
+#pragma unroll
+                for (int j = k + 1; j < 16; ++j) add_of_lane<k>(d[j], u, j == k + 1);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) add_of_lane<k>(w[c], u, c == 0);
+            });
+            if (quad == 0) s_inv[b & 1][x] = own;
+            const double root = sqrt(own);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int j = 4 * quad + c;
+                s_w[x * P + j] = w[c];
+                if (!FACTOR && row < l && j <= x) out[row * l + 16 * b + j] = w[c] * root;
+            }
         }
         __syncthreads();
-        if (!live || R < cb || (FACTOR && C < cb)) continue;
-        double f[4][4], v[4][4], d[4][4], w[4][4], inv[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int s = 0; s < PER; ++s) {
+            if (!FACTOR && R[s] == b && C[s] == b) {                  // W itself is what its column loses first
+                double w[4];
+                row_part(s_w, w);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                d[i][j] = pc[cb * BP + 4 * i + j];
-                f[i][j] = pc[R * BP + 4 * i + j];
-                v[i][j] = vr[C * BP + 4 * i + j];
-                w[i][j] = i == j ? 1.0 : 0.0;
+                for (int u = 0; u < 4; ++u) s_f[b][(4 * quad + u) * P + x] = w[u];
             }
+            const bool below = C[s] == b && (FACTOR ? R[s] >= b : R[s] > b), right = !FACTOR && R[s] == b && C[s] < b;
+            if (!below && !right) continue;
+            const int which = below ? R[s] : C[s];
+            double p[4], w[4];
+            row_part(s_in[which], p);
+            row_part(s_w, w);
+            const v4d f = product(p, w, v4d{0.0, 0.0, 0.0, 0.0});
+            const double root = sqrt(s_inv[b & 1][x]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double p = d[c][c];
-            double r = __builtin_amdgcn_rcp(p);                       // and two Newton steps: full precision
-            r = fma(fma(-p, r, 1.0), r, r);
-            r = fma(fma(-p, r, 1.0), r, r);
-            inv[c] = p > s_least[4 * cb + c] ? r : 0.0;               // a dead row takes no part
-#pragma unroll
-            for (int k = c + 1; k < 4; ++k) {
-                const double u = d[k][c] * inv[c];
-#pragma unroll
-                for (int j = c + 1; j <= k; ++j) d[k][j] = fma(-u, d[j][c], d[k][j]);
-#pragma unroll
-                for (int j = 0; j <= c; ++j) w[k][j] = fma(-u, w[c][j], w[k][j]);
+            for (int v = 0; v < 4; ++v) {
+                const int i = quad + 4 * v, j = 16 * b + x;           // element i of the block, column or row j of the result
+                s_f[which][i * P + x] = f[v];
+                if (FACTOR ? j < l && 16 * R[s] + i < l : right && j < l)
+                    out[j * l + 16 * which + i] = FACTOR && R[s] == b && x > i ? 0.0 : f[v] * root;
             }
         }
-        // f <- P(R) W^T, v <- W V(C)
+        __syncthreads();
 #pragma unroll
-        for (int j = 3; j > 0; --j)
+        for (int s = 0; s < PER; ++s) {
+            if (R[s] <= b || (FACTOR && C[s] <= b)) continue;
+            double f[4], h[4];
+            row_part(s_f[R[s]], f);
+            row_part(s_f[C[s]], h);
 #pragma unroll
-            for (int k = 0; k < j; ++k)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    f[i][j] = fma(f[i][k], w[j][k], f[i][j]);
-                    v[j][i] = fma(w[j][k], v[k][i], v[j][i]);
-                }
-        if (FACTOR && C == cb) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double root = sqrt(inv[j]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    out[(4 * cb + j) * l + 4 * R + i] = R > cb || j <= i ? f[i][j] * root : 0.0;
-            }
-        }
-        if (!FACTOR && R == cb && C == cb) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s_w[cb * BP + 4 * i + j] = i == j ? inv[i] : w[i][j];
-        }
-        // rows of the pivot block are finished; its column starts the right half from zero (the pivot block from one)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                double a = C == cb ? (R == cb && i == j ? 1.0 : 0.0) : x[i][j];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) a = fma(R > cb ? -f[i][k] * inv[k] : 0.0, v[k][j], a);
-                x[i][j] = a;
-            }
-    }
-    if (FACTOR) return;
-    __syncthreads();
-    if (!live) return;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const double* const w = s_w + R * BP + 4 * i;
-        const double root = sqrt(w[i]);                               // of 1 / d_i
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            double a = x[i][j];
-#pragma unroll
-            for (int k = 0; k < i; ++k) a = fma(w[k], x[k][j], a);
-            if (R > C || j <= i) out[(4 * R + i) * l + 4 * C + j] = a * root;
+            for (int u = 0; u < 4; ++u) f[u] *= -s_inv[b & 1][4 * quad + u];
+            if (C[s] == b) acc[s] = v4d{0.0, 0.0, 0.0, 0.0};
+            acc[s] = product(f, h, acc[s]);
         }
     }
 }
@@ -790,13 +821,13 @@ static hipError_t orthonormalize_rows(const float* src, float* dst, uint32_t* pa
                                       double* lfac, int passes, hipStream_t stream)
 {
     const int nb = l / 4;
-    const unsigned threads = static_cast<unsigned>((nb * (nb + 1) / 2 + 63) / 64 * 64);
     const unsigned blocks = static_cast<unsigned>((len + 31) / 32 * 2);
     for (int pass = 0; pass < passes; ++pass) {
         const float* const v = pass ? dst : src;
         gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h);
-        factor_kernel<false><<<1, threads, 0, stream>>>(h, l, lfac);
-#define FQ_APPLY(CB) apply_lower_kernel<CB><<<blocks, CB * 64, 0, stream>>>(v, dst, packed, l, len, lfac)
+#define FQ_APPLY(CB)                                                                                         \
+        factor_kernel<CB, false><<<1, 64 * factor_waves(CB), 0, stream>>>(h, l, lfac);                       \
+        apply_lower_kernel<CB><<<blocks, CB * 64, 0, stream>>>(v, dst, packed, l, len, lfac)
         FQ_BY_BLOCKS((l + 15) / 16, FQ_APPLY)
 #undef FQ_APPLY
         const hipError_t err = hipGetLastError();
@@ -859,7 +890,9 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     FQ_CHECK(product(false, y));
     const int nb = l / 4;
     gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(y, l, m, h);
-    factor_kernel<true><<<1, static_cast<unsigned>((nb * (nb + 1) / 2 + 63) / 64 * 64), 0, stream>>>(h, l, p);
+#define FQ_FACTOR(CB) factor_kernel<CB, true><<<1, 64 * factor_waves(CB), 0, stream>>>(h, l, p)
+    FQ_BY_BLOCKS((l + 15) / 16, FQ_FACTOR)
+#undef FQ_FACTOR
     FQ_CHECK(hipGetLastError());
 #define FQ_JACOBI(L8)                                                                                        \
     case L8: {                                                                                               \
