@@ -567,10 +567,14 @@ __device__ __forceinline__ double quad_sum(double v)
 // Jacobi: rotations of the columns of L^T that make them orthogonal.  Their dot products are the entries of H, so the
 // rotations are those of the two-sided method on H in the same order, and P is their product; but all that is kept is
 // W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (eigenvector_kernel, settle_kernel).
-// Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: its three dot products
-// are reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.
-// A round is bound by the instructions that a SIMD issues, and those of the rotation count once per wave: four lanes
-// per pair make l / 32 waves, one per SIMD.  (With 16 lanes per pair and up to three waves per SIMD a round took
+// Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: the dot product of the two is
+// reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.  Their squared
+// lengths follow from the rotation and are formed anew once per sweep (and where little of one is left): with three dot products
+// and a tangent to full precision per pair the launch took 4 % more at l = 72.
+// A round is bound by the columns' way through LDS (writes at 76 B/clk) and the instructions that a SIMD issues, and those of
+// the rotation count once per wave: four lanes per pair make l / 32 waves, one per SIMD.  (Columns that stay in registers and
+// move on by a lane per round, their edges through LDS, took 1.06 us a round at l = 72 against 0.95: a b128 access of four lanes costs
+// what one of 64 does.)  (With 16 lanes per pair and up to three waves per SIMD a round took
 // 1.17 us at l = 72; rotating H from both sides, which takes a pass over all of H, the eigenvectors' update and two
 // barriers per round, 1.4 us.)
 // Stops after `sweeps`, or after the first sweep that found all columns orthogonal to 1e-8 and turned none by more than
@@ -587,8 +591,9 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
     typedef double v2d __attribute__((ext_vector_type(2)));
     // columns at an odd multiple of 64 bytes: the sixteen pairs of a wave spread over all banks
     constexpr int l = 8 * L8, PITCH = 8 * (L8 | 1);
-    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], two flags
-    int* const s_turned = reinterpret_cast<int*>(s_v + l * PITCH);
+    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], squared lengths as followed and as last formed, two flags
+    v2d* const s_length = reinterpret_cast<v2d*>(s_v + l * PITCH);
+    int* const s_turned = reinterpret_cast<int*>(s_length + l);
     const int t = threadIdx.x, pair = t >> 2, e0 = 2 * (t & 3);
     const bool live = pair < l / 2;
     for (int q = t; q < l * l; q += blockDim.x) {
@@ -599,26 +604,40 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
     __syncthreads();
     // position 0 keeps column 0, positions 1 .. l-1 rotate by one per round
     auto at = [&](int pos, int round) { return pos == 0 ? 0 : (pos - 1 >= round ? pos - round : pos - round + l - 1); };
+    auto square = [&](const v2d (&v)[L8]) {
+        v2d s = {0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < L8; ++e)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) s[u] = fma(v[e][u], v[e][u], s[u]);
+        return quad_sum(s[0] + s[1]);
+    };
     for (int sweep = 0; sweep < sweeps; ++sweep) {
+        for (int c = pair; c < l; c += static_cast<int>(blockDim.x >> 2)) {
+            v2d v[L8];
+#pragma unroll
+            for (int e = 0; e < L8; ++e) v[e] = *reinterpret_cast<const v2d*>(s_v + c * PITCH + e0 + 8 * e);
+            const double length = square(v);
+            s_length[c] = v2d{length, length};
+        }
+        __syncthreads();
         for (int round = 0; round < l - 1; ++round) {
             if (round == l - 2 && t == 0) s_turned[(sweep + 1) & 1] = 0;
             if (live) {
-                v2d* const pa = reinterpret_cast<v2d*>(s_v + at(pair, round) * PITCH + e0);
-                v2d* const pb = reinterpret_cast<v2d*>(s_v + at(l - 1 - pair, round) * PITCH + e0);
-                v2d va[L8], vb[L8], aa = {0.0, 0.0}, bb = {0.0, 0.0}, ab = {0.0, 0.0};
+                const int ca = at(pair, round), cb = at(l - 1 - pair, round);
+                v2d* const pa = reinterpret_cast<v2d*>(s_v + ca * PITCH + e0);
+                v2d* const pb = reinterpret_cast<v2d*>(s_v + cb * PITCH + e0);
+                v2d va[L8], vb[L8], ab = {0.0, 0.0};
 #pragma unroll
                 for (int e = 0; e < L8; ++e) { va[e] = pa[4 * e]; vb[e] = pb[4 * e]; }
+                const v2d la = s_length[ca], lb = s_length[cb];
 #pragma unroll
                 for (int e = 0; e < L8; ++e)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        aa[u] = fma(va[e][u], va[e][u], aa[u]);
-                        bb[u] = fma(vb[e][u], vb[e][u], bb[u]);
-                        ab[u] = fma(va[e][u], vb[e][u], ab[u]);
-                    }
-                const double haa = quad_sum(aa[0] + aa[1]), hbb = quad_sum(bb[0] + bb[1]), hab = quad_sum(ab[0] + ab[1]);
-                double c, s;
-                if (jacobi_rotation(haa, hbb, hab, c, s)) {
+                    for (int u = 0; u < 2; ++u) ab[u] = fma(va[e][u], vb[e][u], ab[u]);
+                const double haa = la[0], hbb = lb[0], hab = quad_sum(ab[0] + ab[1]);
+                double c, s, tn;
+                if (jacobi_rotation<JacobiEstimates, false>(haa, hbb, hab, c, s, tn)) {
 #pragma unroll
                     for (int e = 0; e < L8; ++e) {
                         v2d na, nb;
@@ -627,9 +646,18 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
                             na[u] = fma(c, va[e][u], -s * vb[e][u]);
                             nb[u] = fma(s, va[e][u], c * vb[e][u]);
                         }
-                        pa[4 * e] = na;
-                        pb[4 * e] = nb;
+                        pa[4 * e] = va[e] = na;
+                        pb[4 * e] = vb[e] = nb;
                     }
+                    // Lengths follow from the rotation.  A difference keeps the rounding of the larger terms, so where little of
+                    // one is left since it was last formed, both are formed anew: 1e-11 of a length is off at the worst.
+                    v2d na = {c * c * fma(tn, fma(tn, hbb, -2.0 * hab), haa), la[1]}, nb = {c * c * fma(tn, fma(tn, haa, 2.0 * hab), hbb), lb[1]};
+                    if (!(na[0] >= 1e-3 * na[1] && nb[0] >= 1e-3 * nb[1])) {
+                        na[0] = na[1] = square(va);
+                        nb[0] = nb[1] = square(vb);
+                    }
+                    s_length[ca] = na;
+                    s_length[cb] = nb;
                     // (one comparison: orthogonal to 1e-14 where they turn by more than 1e-8, to 1e-8 where not)
                     if (hab * hab > (fabs(s) > 1e-8 ? 1e-28 : 1e-16) * haa * hbb) s_turned[sweep & 1] = 1;
                 }
@@ -896,7 +924,7 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     FQ_CHECK(hipGetLastError());
 #define FQ_JACOBI(L8)                                                                                        \
     case L8: {                                                                                               \
-        const size_t lds = sizeof(double) * 8 * L8 * (8 * (L8 | 1)) + 2 * sizeof(int);                       \
+        const size_t lds = sizeof(double) * 8 * L8 * (8 * (L8 | 1) + 2) + 2 * sizeof(int);                   \
         FQ_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&jacobi_eig_kernel<L8>),                  \
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));    \
         jacobi_eig_kernel<L8><<<1, (16 * L8 + 63) / 64 * 64, lds, stream>>>(p, h, lambda, 48);        \
