@@ -1,6 +1,8 @@
 // Device helpers shared by the two families of FP8 product kernels (gemm.hip: tiles of 128 to 256 tokens on rings two and
 // three stages deep; gemm_mid.hip: tiles of 32 to 128 tokens on deep rings).
 #pragma once
+#include <type_traits>
+
 #include "falqon_internal.h"
 
 namespace falqon {
@@ -75,6 +77,27 @@ __device__ __forceinline__ void barrier_lds_written()
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt 0 only
     barrier_lds_only();
+}
+
+// The maximum over a wave, in all lanes.  Within rows of 16 lanes by DPP, across rows by lane swaps: about 60 cycles; six
+// exchanges through LDS (__shfl_xor) take 600, which a kernel of a few microseconds feels.
+__device__ __forceinline__ float wave_max(float v)
+{
+    auto moved = [](float x, auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        const int i = static_cast<int>(__float_as_uint(x));
+        return __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(i, C, 0xf, 0xf, true)));
+    };
+    v = fmaxf(v, moved(v, std::integral_constant<int, 0xB1>{}));      // quad_perm [1, 0, 3, 2]
+    v = fmaxf(v, moved(v, std::integral_constant<int, 0x4E>{}));      // quad_perm [2, 3, 0, 1]
+    v = fmaxf(v, moved(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
+    v = fmaxf(v, moved(v, std::integral_constant<int, 0x140>{}));     // row_mirror
+    uint32_t u = __float_as_uint(v);
+    const auto rows = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    v = fmaxf(__uint_as_float(rows[0]), __uint_as_float(rows[1]));
+    u = __float_as_uint(v);
+    const auto halves = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
 }
 
 // two fp32 -> two bf16 (round to nearest even) in one dword: v_cvt_pk_bf16_f32

@@ -520,7 +520,7 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
     else if (!ADDS && g.c0_is_f32) epilogue(std::true_type{}, g.c0, g.ldc0);
     else epilogue(std::false_type{}, g.c0, g.ldc0);
     if ((RIDE || adapter) && g.amax1) {
-        for (int off = 32; off > 0; off >>= 1) oa_max = fmaxf(oa_max, __shfl_xor(oa_max, off, 64));
+        oa_max = wave_max(oa_max);
         // non-negative floats order like their bit patterns
         if (lane == 0 && oa_max > 0.0f) atomicMax(g.amax1, __float_as_uint(oa_max));
     }

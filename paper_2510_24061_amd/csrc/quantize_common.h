@@ -7,12 +7,6 @@
 namespace falqon {
 namespace {
 
-__device__ __forceinline__ float wave_max(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
 // the maximum over the workgroup's N waves, in all threads.  The barrier is behind LDS accesses only: loads in flight
 // stay in flight.
 template <int N>
