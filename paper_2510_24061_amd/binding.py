@@ -1,4 +1,5 @@
-"""ctypes binding of libfalqon.so: argument marshalling only.
+"""Binding of libfalqon.so: argument marshalling only, for the calls of a training step in a Python extension
+(csrc/python_calls.cpp), for the others through ctypes.
 
 Every function takes torch tensors that already live on the GPU, passes their device
 pointers and the current HIP stream through the C ABI (include/falqon.h) and returns.
@@ -17,6 +18,7 @@ BF16, F32 = 0, 1
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfalqon.so")
 _lib = None
+_calls = None
 
 
 GROUP_MAX = 256                 # FALQON_GROUP_MAX
@@ -94,16 +96,31 @@ def lib():
     return _lib
 
 
+def _native():
+    """The extension of the calls that a training step makes (built in-tree with the library)."""
+    global _calls
+    if _calls is None:
+        lib()
+        try:
+            from . import _calls as native
+        except ImportError as e:
+            raise ImportError(f"{_HERE}/_calls.so: {e}: build it with `python -m paper_2510_24061_amd.build`") from e
+        _calls = native
+    return _calls
+
+
 def status_string(status: int) -> str:
     return lib().falqon_status_string(int(status)).decode()
 
 
 def workspace_bytes(T: int, n: int, m: int, r: int) -> int:
-    return int(lib().falqon_workspace_bytes(T, n, m, r))
+    return _native().workspace_bytes(T, n, m, r)
 
 
-# A call of a small layer takes less time on the GPU than its arguments take here, so they go to ctypes as
-# plain integers (the prototypes make pointers of them) and the stream comes from the raw accessor.
+# A call of a small layer takes less time on the GPU than its arguments take on the way, so the extension takes those of a
+# step's calls (us on the host for calls and launches, through ctypes in brackets: forward of 8 tokens, one launch, 4.9 (7.5); step of 512 x 512,
+# six launches, 23.5 (28.8); optimizer step over seven layers, 36 launches, 127 (173)), the others go to ctypes as plain
+# integers (the prototypes make pointers of them), and the stream comes from the raw accessor.
 def _p(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
@@ -154,11 +171,7 @@ def quantize(x: torch.Tensor, fmt: int, q: torch.Tensor, scale_out: torch.Tensor
 
 def melded_fwd(x, wq, s_w, m: int, r: int, xq, s_x, y, o_a, amax_oa, ws) -> None:
     """x = None: xq and s_x are inputs (already quantized by another layer's call or by quantize())."""
-    _dev(x, wq, s_w, xq, s_x, y, o_a, amax_oa, ws)
-    T, n = xq.shape
-    st = lib().falqon_melded_fwd(_p(x) if x is not None else None, _p(wq), _p(s_w), T, n, m, r, _p(xq), _p(s_x), _p(y), _dtype_code(y),
-                                 _p(o_a), _p(amax_oa), _p(ws), ws.numel() * ws.element_size(), _stream())
-    _check(st, "falqon_melded_fwd")
+    _check(_native().melded_fwd(x, wq, s_w, m, r, xq, s_x, y, o_a, amax_oa, ws, _stream()), "falqon_melded_fwd")
 
 
 def melded_fwd_group(x, layers, xq, s_x, amax_oa) -> None:
@@ -185,36 +198,24 @@ def melded_bwd(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b, de
                row_scores=None) -> None:
     """dx = None: the input-gradient product is skipped.  delta_buf = None: no buffer step.
     row_scores (uint8/float64 tensor of row_score_bytes(m) bytes): left for a proxy_update that follows."""
-    _dev(dy, wq, s_w, o_a, amax_oa, dyq, s_dy, dx, d_b, delta_buf, ws, row_scores)
-    T, m = dy.shape
-    st = lib().falqon_melded_bwd(_p(dy), _p(wq), _p(s_w), _p(o_a), _p(amax_oa), T, n, m, r, _p(dyq), _p(s_dy),
-                                 _p(dx), _dtype_code(dx) if dx is not None else BF16, _p(d_b), _p(delta_buf), float(lr),
-                                 _p(row_scores),
-                                 _p(ws), ws.numel() * ws.element_size(), _stream())
-    _check(st, "falqon_melded_bwd")
+    _check(_native().melded_bwd(dy, wq, s_w, o_a, amax_oa, n, r, dyq, s_dy, dx, d_b, delta_buf, lr, ws, row_scores, _stream()),
+           "falqon_melded_bwd")
 
 
 def melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b, delta_buf, lr: float, ws,
                    row_scores=None) -> None:
     """melded_bwd whose input gradient is added to what dx (bf16) holds."""
-    _dev(dy, wq, s_w, o_a, amax_oa, dyq, s_dy, dx, d_b, delta_buf, ws, row_scores)
-    if dx.dtype != torch.bfloat16:
+    if dx is not None and dx.dtype != torch.bfloat16:
         raise TypeError("the sum of input gradients is bf16")
-    T, m = dy.shape
-    st = lib().falqon_melded_bwd_add(_p(dy), _p(wq), _p(s_w), _p(o_a), _p(amax_oa), T, n, m, r, _p(dyq), _p(s_dy),
-                                     _p(dx), _p(d_b), _p(delta_buf), float(lr), _p(row_scores),
-                                     _p(ws), ws.numel() * ws.element_size(), _stream())
-    _check(st, "falqon_melded_bwd_add")
+    _check(_native().melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n, r, dyq, s_dy, dx, d_b, delta_buf, lr, ws, row_scores, _stream()),
+           "falqon_melded_bwd_add")
 
 
 def proxy_update(delta_buf, wq, m: int, r: int, k: int, idx_out, ws, clear_selected: bool = True,
                  row_scores=None) -> None:
     """row_scores: the array melded_bwd filled for this very buffer content (else the scores are formed here)."""
-    _dev(delta_buf, wq, idx_out, ws, row_scores)
-    n = wq.shape[1]
-    st = lib().falqon_proxy_update(_p(delta_buf), _p(wq), n, m, r, k, _p(idx_out), 1 if clear_selected else 0,
-                                   _p(row_scores), _p(ws), ws.numel() * ws.element_size(), _stream())
-    _check(st, "falqon_proxy_update")
+    _check(_native().proxy_update(delta_buf, wq, m, r, k, idx_out, ws, 1 if clear_selected else 0, row_scores, _stream()),
+           "falqon_proxy_update")
 
 
 def proxy_update_static(delta_buf, wq, m: int, r: int, k: int, idx_out, clear_selected: bool = True) -> None:
@@ -255,21 +256,14 @@ def db_bf16(dyq, s_dy, o_a, d_b, delta_buf, lr: float, ws) -> None:
 
 def grad_sqnorm(g, sum_sq, ws) -> None:
     """*sum_sq (device fp64 scalar) += sum of squares of g (fp32)."""
-    _dev(g, sum_sq, ws)
-    st = lib().falqon_grad_sqnorm(_p(g), g.numel(), _p(sum_sq), _p(ws), ws.numel() * ws.element_size(), _stream())
-    _check(st, "falqon_grad_sqnorm")
+    _check(_native().grad_sqnorm(g, sum_sq, ws, _stream()), "falqon_grad_sqnorm")
 
 
 def adamw_delta(d_b, exp_avg, exp_avg_sq, delta_buf, step: int, lr: float = 2e-4, beta1: float = 0.9,
                 beta2: float = 0.999, eps: float = 1e-8, sum_sq=None, max_norm: float = 0.3) -> None:
     """AdamW step on the (clipped) adapter gradient, written into the proxy buffer."""
-    _dev(d_b, exp_avg, exp_avg_sq, delta_buf)
-    if sum_sq is not None:
-        _dev(sum_sq)
-    m, r = d_b.shape
-    st = lib().falqon_adamw_delta(_p(d_b), _p(exp_avg), _p(exp_avg_sq), _p(delta_buf), m, r, int(step), lr, beta1,
-                                  beta2, eps, _p(sum_sq) if sum_sq is not None else None, max_norm, _stream())
-    _check(st, "falqon_adamw_delta")
+    _check(_native().adamw_delta(d_b, exp_avg, exp_avg_sq, delta_buf, int(step), lr, beta1, beta2, eps, sum_sq, max_norm, _stream()),
+           "falqon_adamw_delta")
 
 
 def init_residual(w, wq, s_w, e) -> None:

@@ -1,0 +1,44 @@
+"""The extension that takes a step's calls refuses what the binding has always refused, before anything is launched (this
+machine may have no GPU)."""
+import pytest
+import torch
+
+from paper_2510_24061_amd import binding as b
+
+
+@pytest.fixture(autouse=True)
+def _no_device(monkeypatch):
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+
+
+def test_tensors_off_the_gpu_are_refused():
+    t = torch.zeros(16, 16)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.melded_fwd(t, t, t, 16, 16, t, t, t, t, t, t)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.melded_bwd(t, t, t, t, t, 16, 16, t, t, None, t, None, 0.1, t)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.melded_bwd_add(t, t, t, t, t, 16, 16, t, t, t.to(torch.bfloat16), t, None, 0.1, t)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.proxy_update(t, t, 16, 16, 4, t, t)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.grad_sqnorm(t, t, t)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.adamw_delta(t, t, t, t, 1)
+
+
+def test_what_is_no_tensor_and_what_has_no_shape():
+    n = b._native()
+    with pytest.raises(TypeError):
+        n.grad_sqnorm([1.0], None, None, 0)
+    with pytest.raises(TypeError):
+        n.grad_sqnorm(None, None)                                     # too few
+    with pytest.raises(AttributeError):
+        b.proxy_update(None, None, 16, 16, 4, None, None)
+    with pytest.raises(AttributeError):
+        b.grad_sqnorm(None, None, None)
+    with pytest.raises(TypeError):
+        b.workspace_bytes(16, 64.5, 64, 16)
+    with pytest.raises(OverflowError):
+        b.workspace_bytes(16, 1 << 70, 64, 16)
+    assert b.workspace_bytes(16, 64, 64, 16) == b.lib().falqon_workspace_bytes(16, 64, 64, 16) > 0
