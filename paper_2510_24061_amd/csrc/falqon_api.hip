@@ -10,17 +10,25 @@ namespace falqon {
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Partials of dB where the small-tile dX product also forms it (one per tile row); 0: it does not.  The tiles
-// of a tile row share out the steps of 128 features among themselves; a step takes 0.5 us and 0.3 us for each 32 ranks
-// (operands, matrix instructions, stores).  The ordered sum reads one partial per tile row, at 5 TB/s or, as a workgroup
-// owns 64 rows of dB, at 87 GB/s each.  A launch of its own reads dy~ again, once for each 64 ranks, leaves fewer
-// partials, lets the product take any tiles, and costs the host another 2 us at the least.  Fitted to 1100 calls
-// (20 sizes, features 64 to 8192, r = 16, 64, 256; the choice by it is 0.7 % slower than the better one on average).
-// us for the call: 512 x 4096 x 4096, r = 64: 33 inside, 39 apart; 4000 x 1024 x 512, r = 256: 78 inside, 56 apart.
+// How the adapter gradient of a call with small dX tiles is formed, by time:
+//   inside  by the dX tiles: the tiles of a tile row share out the steps of 128 features among themselves; a step takes 0.5 us
+//           and 0.3 us for each 32 ranks (operands, matrix instructions, stores that drain the tile's ring).  The ordered sum
+//           reads one partial per tile row, at 5 TB/s or, as a workgroup owns 64 rows of dB, at 87 GB/s each.
+//   joint   by workgroups of their own in the same launch (128 features x 64 ranks x a split of the tokens), which run beside the
+//           dX tiles on CUs that these leave idle: the longer of the two, where all of them find a CU at once.  Such a
+//           workgroup takes 2.5 us and 4 us for each 512 tokens.
+//   apart   by a launch of its own, which reads dy~ again, once for each 64 ranks, lets the product take any tiles, and costs the host
+//           another 2 us at the least.
+// The first and the last fitted to 1100 calls (20 sizes, features 64 to 8192, r = 16, 64, 256).  us for the call, inside, joint, apart:
+// 777 x 1040 <- 2000, r = 48 26.7, 22.0, 28.8; 158 x 1696 <- 2960, r = 256 32.5, 22.7, 31.0; 86 x 736 <- 1504, r = 32 17.9, 16.4, 21.5;
+// 122 x 256 <- 11024, r = 96 44.0, 36.0, 43.8; 3898 x 736 <- 416, r = 64 28.5, 23.4 (45.5 with one split), 27.3; 1657 x 1040 <- 560,
+// r = 96, where one split is all that finds CUs, 23.7, 28.9, 25.3; 512 x 4096 <- 4096, r = 64 33 inside, 39 apart.
+// 260 drawn calls against the choice between the other two: geometric mean 1.14 times as fast, slowest 0.996, fastest 1.57.
 constexpr int64_t kMidDbMax = 64;
-static int mid_db_parts(int64_t T, int64_t n, int64_t m, int64_t r)
+struct MidDb { enum { APART, INSIDE, JOINT } kind; int parts; };      // partials of dB (but for APART)
+static MidDb plan_mid_db(int64_t T, int64_t n, int64_t m, int64_t r, bool may_join, bool may_inside = true)
 {
-    if (!gemm_mid_supported(T, n)) return 0;
+    if (!gemm_mid_supported(T, n)) return {MidDb::APART, 0};
     const MidPlan p = plan_mid(T, n, m, true, 0);
     const int64_t parts = (T + p.rows - 1) / p.rows, steps = ((m + 127) / 128 + p.columns - 1) / p.columns;
     const double bytes = static_cast<double>(m) * static_cast<double>(r) * 4.0;
@@ -28,7 +36,21 @@ static int mid_db_parts(int64_t T, int64_t n, int64_t m, int64_t r)
     const double inside = p.us + static_cast<double>(steps) * (0.5 + 0.3 * static_cast<double>((r + 31) / 32)) + static_cast<double>(parts) * sum_us;
     const double apart = product_us(T, n, m, true) + 6.7 + static_cast<double>(T * m * ((r + 63) / 64)) / 3e6 +
                          db_splits(T, m) * (bytes / 11.7e6 + sum_us);
-    return parts <= kMidDbMax && inside < apart ? static_cast<int>(parts) : 0;
+    const bool fits = may_inside && parts <= kMidDbMax;
+    MidDb best{fits && inside < apart ? MidDb::INSIDE : MidDb::APART, fits && inside < apart ? static_cast<int>(parts) : 0};
+    if (!may_join) return best;
+    double best_us = fits && inside < apart ? inside : apart;
+    const int64_t tiles = (parts * p.columns + 7) / 8 * 8, jobs = (m + 127) / 128 * ((r + 63) / 64);
+    for (int splits = 1; splits <= db_splits(T, m) && tiles + splits * jobs <= 256; splits *= 2) {
+        const int64_t tokens = ((T + splits - 1) / splits + 127) / 128 * 128;
+        const double beside = 2.5 + 4.0 * static_cast<double>((tokens + 511) / 512);
+        const double us = (beside > p.us ? beside : p.us) + splits * sum_us;
+        if (us < best_us) {
+            best_us = us;
+            best = {MidDb::JOINT, splits};
+        }
+    }
+    return best;
 }
 
 // least: the layout of a workspace that has room for no more partials of dB than the launches need that
@@ -44,7 +66,7 @@ WsLayout ws_layout(int64_t T, int64_t n, int64_t m, int64_t r, bool least)
     int oa_parts = oa_splits(T, r), db_parts = db_splits(T, m);
     if (po.use && po.splits > oa_parts) oa_parts = po.splits;
     if (r <= 64 && p256.use && p256.groups > db_parts) db_parts = p256.groups;
-    int wide_parts = mid_db_parts(T, n, m, r);
+    int wide_parts = plan_mid_db(T, n, m, r, false).parts;
     if (pd.use && pd.groups > wide_parts) wide_parts = pd.groups;
     w.amax_partials = off; off = align_up(off + sizeof(float) * kMaxAmaxBlocks, 256);
     w.scores = off;        off = align_up(off + sizeof(double) * static_cast<size_t>(m + (m + 63) / 64), 256);
@@ -184,12 +206,14 @@ static falqon_status melded_bwd(const void* dy, const uint8_t* wq, const float* 
     // dy~, s_dy <- Q_E5M2(dy).  When the adapter gradient is formed by the workgroups of the dX tiles, the
     // cast pass also casts the saved O_A to E4M3 (its maximum is known from the forward pass).
     const DbTailPlan pd = dx && !(least && r > 64) ? plan_db_tail(T, n, m, r, least ? 256 : 0) : DbTailPlan{false, 0, 256};
-    const int mid_parts = dx && !least ? mid_db_parts(T, n, m, r) : 0;
+    // (a least layout has no room for the partials of dB inside; those of the joint launch are no more than of one apart)
+    const MidDb mid = dx && !pd.use ? plan_mid_db(T, n, m, r, true, !least) : MidDb{MidDb::APART, 0};
+    const bool inside = mid.kind == MidDb::INSIDE;
     SideCast sc{static_cast<const uint16_t*>(o_a), amax_oa, w8 + L.oa_codes, T * r};
     ZeroWords zero{nullptr, 0};
     if (row_scores && delta_buf && db_reduce_raises(m, r)) zero = {reinterpret_cast<uint32_t*>(row_scores + m), static_cast<int>(2 * score_blocks(m))};
     hipError_t e = launch_quantize(dy, FALQON_BF16, T, m, m, FALQON_E5M2, nullptr, dyq, m, s_dy, nullptr,
-                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || mid_parts ? &sc : nullptr, dx ? n : r);
+                                   reinterpret_cast<float*>(w8 + L.amax_partials), zero, st, pd.use || inside ? &sc : nullptr, dx ? n : r);
     if (e != hipSuccess) return FALQON_ERR_HIP;
 
     // dX <- dy~ W~ / (s_dy s_w): the backbone rows of the concatenated weight, read as [K = m, N = n]
@@ -203,8 +227,12 @@ static falqon_status melded_bwd(const void* dy, const uint8_t* wq, const float* 
     // dB <- dy~^T O_A~ / (s_dy s_oa);  DeltaBuffer += -lr dB.  Its partial pass reads only dy~ and
     // O_A, so nothing orders it against the dX product: on the large tiles both go out as one launch.
     const DbArgs d = make_db_args(dyq, o_a, amax_oa, T, m, r, reinterpret_cast<float*>(w8 + L.db_partials),
-                                  pd.use ? pd.groups : mid_parts ? mid_parts : db_splits(T, m));
-    if (mid_parts) {
+                                  pd.use ? pd.groups : mid.parts ? mid.parts : db_splits(T, m));
+    if (mid.kind == MidDb::JOINT) {
+        MidSide side;
+        side.db = &d;
+        e = launch_gemm_mid(g, side, st);
+    } else if (inside) {
         MidSide side;
         side.r = r; side.oaq = w8 + L.oa_codes; side.db_partial = d.partial;
         e = launch_gemm_mid(g, side, st);

@@ -15,6 +15,7 @@ struct MidSide {
     int64_t r = 0;
     const uint8_t* oaq = nullptr;    // input gradient (E5M2 left operand): O_A codes [M][r]; partial sums of
     float* db_partial = nullptr;     // dy~^T O_A~ go to db_partial[tile row][K][r], not rescaled
+    const DbArgs* db = nullptr;      // instead: these tiles of the adapter gradient are workgroups of their own in the launch
 };
 bool gemm_mid_supported(int64_t M, int64_t N);                   // the 128x128 tiles of a product of this size all find a CU
 // Tile configuration of a product, the one of least time; r: rank of the adapter whose O_A it forms along (0: none).

@@ -23,6 +23,7 @@
 // input gradient with dB 5.9 (6.7 + 6.2).
 #include <type_traits>
 
+#include "db_tile.h"
 #include "falqon_internal.h"
 #include "gemm_common.h"
 #include "gemm_mid.h"
@@ -529,13 +530,10 @@ __device__ __forceinline__ void mid_tile(const MidArgs& t, const int tile_m, con
 // Workgroup -> tile: XCD x (workgroup index modulo 8) takes tiles [x * chunk, (x + 1) * chunk) of a raster
 // that walks panels of PH tile rows, tile column by tile column: the token panel of an XCD stays in its
 // L2 and every weight column is fetched by one XCD per panel.
-template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB, bool SKEW, bool ADDS = false>
-__global__ void __launch_bounds__(256)
-gemm_mid_kernel(const MidArgs t)
+template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB, bool SKEW, bool ADDS>
+__device__ __forceinline__ void mid_workgroup(const MidArgs& t, const int bid, uint8_t* const lds)
 {
     constexpr bool FWD = !B_KN && A_FMT == 0;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[mid_lds_bytes<MB, NB, S, FWD, DB>()];
-    const int bid = blockIdx.x;
     const int tile_id = (bid & 7) * t.chunk + (bid >> 3);
     const int cols = t.tiles_n + t.tiles_a;
     if (tile_id >= t.tiles_m * cols) return;
@@ -553,6 +551,32 @@ gemm_mid_kernel(const MidArgs t)
     mid_tile<MB, NB, S, B_KN, A_FMT, false, DB, SKEW, ADDS>(t, tile_m, tile_n, tile_n >= t.tiles_n, lds);
 }
 
+template <int MB, int NB, int S, bool B_KN, int A_FMT, bool DB, bool SKEW, bool ADDS = false>
+__global__ void __launch_bounds__(256)
+gemm_mid_kernel(const MidArgs t)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[mid_lds_bytes<MB, NB, S, !B_KN && A_FMT == 0, DB>()];
+    mid_workgroup<MB, NB, S, B_KN, A_FMT, DB, SKEW, ADDS>(t, blockIdx.x, lds);
+}
+
+// The input-gradient product, and behind its `product` workgroups those of the adapter gradient's tiles (db_tile.h): both
+// read only dy~, the weight and O_A.  For products that leave CUs idle, which then form dB meanwhile.
+template <int MB, int NB, int S, bool ADDS>
+__global__ void __launch_bounds__(256)
+gemm_mid_db_kernel(const MidArgs t, const DbArgs d, const int product)
+{
+    constexpr int LDS = mid_max(mid_lds_bytes<MB, NB, S, false, false>(), static_cast<int>(dbt::kDbLdsBytes));
+    static_assert(dbt::kThreads == 256, "one workgroup shape for both kinds of tile");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS];
+    const int b = static_cast<int>(blockIdx.x) - product;
+    if (b >= 0) {
+        const int bi = b % d.i_tiles, rest = b / d.i_tiles;
+        dbt::db_partial_tile(d, bi, rest % d.splits, rest / d.splits, lds, g_zero16);
+        return;
+    }
+    mid_workgroup<MB, NB, S, true, 1, false, false, ADDS>(t, blockIdx.x, lds);
+}
+
 // Adapter columns of their own cost nothing while they make no further round over the CUs; a step of a tile that
 // carries them along takes 1.15 times as long.  Returns the extra tile columns, 0: they ride.
 int own_columns(int64_t tiles_m, int64_t tiles_n, int64_t r, int bn)
@@ -564,7 +588,7 @@ int own_columns(int64_t tiles_m, int64_t tiles_n, int64_t r, int bn)
 
 // SKEW is for K from long_rows steps on (launch_gemm_mid).
 template <int MB, int NB, int S_FWD, int S_KN, int S_DB>
-hipError_t launch_cfg(MidArgs t, int long_rows, hipStream_t stream)
+hipError_t launch_cfg(MidArgs t, int long_rows, const DbArgs* db, hipStream_t stream)
 {
     constexpr int BM = 32 * MB, BN = 64 * NB;
     t.tiles_m = static_cast<int>((t.g.M + BM - 1) / BM);
@@ -579,6 +603,12 @@ hipError_t launch_cfg(MidArgs t, int long_rows, hipStream_t stream)
     // rows that do not all begin with a cache line (of a single row only its place counts)
     auto across = [](const uint8_t* p, int64_t ld) { return ((reinterpret_cast<uintptr_t>(p) | static_cast<uintptr_t>(ld)) & (BK - 1)) != 0; };
     const bool skew = t.g.K >= long_rows * BK && (across(t.g.a, t.g.lda) || across(t.g.b, t.g.ldb) || (t.side && across(t.side, t.g.ldb)));
+    if (db) {
+        const dim3 both(grid.x + static_cast<unsigned>(db->i_tiles * db->splits * db->p_tiles));
+        if (t.g.c0_adds) gemm_mid_db_kernel<MB, NB, S_KN, true><<<both, block, 0, stream>>>(t, *db, static_cast<int>(grid.x));
+        else gemm_mid_db_kernel<MB, NB, S_KN, false><<<both, block, 0, stream>>>(t, *db, static_cast<int>(grid.x));
+        return hipGetLastError();
+    }
     auto go = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(t); };
     if (t.g.b_is_kn) {
         if (t.g.a_fmt == 0) go(gemm_mid_kernel<MB, NB, S_KN, true, 0, false, false>);
@@ -647,10 +677,10 @@ hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, hipStream_t s
     // 100 x 3008, K = 8208 14.0 (13.1).  [K,N] operands: only the left one has such rows, 0.3 to 0.5 us slower up to K = 2064,
     // 2 to 5 % faster from 4112 on: not built.
     switch (plan_mid(g.M, g.N, g.K, g.b_is_kn != 0, side.rows ? side.r : 0).config) {
-        case 0: return launch_cfg<1, 1, 8, 8, 8>(t, 64, stream);
-        case 1: return launch_cfg<2, 1, 7, 8, 8>(t, 40, stream);
-        case 2: return launch_cfg<2, 2, 5, 6, 6>(t, 12, stream);
-        default: return launch_cfg<4, 2, 4, 5, 4>(t, 12, stream);
+        case 0: return launch_cfg<1, 1, 8, 8, 8>(t, 64, side.db, stream);
+        case 1: return launch_cfg<2, 1, 7, 8, 8>(t, 40, side.db, stream);
+        case 2: return launch_cfg<2, 2, 5, 6, 6>(t, 12, side.db, stream);
+        default: return launch_cfg<4, 2, 4, 5, 4>(t, 12, side.db, stream);
     }
 }
 
