@@ -300,7 +300,7 @@ constexpr int gemm_lds_bytes()
 // gradient dB as a side job ahead of the tile (input-gradient launch); 3, 4, 5: blocks of O_A formed
 // inside the tile's own K-steps, one, two or four per wave, finished and written as bf16 with their
 // maximum (forward).
-template <int WM, int WN, int MB, int NB, bool B_KN, int A_FMT, int TAIL = 0>
+template <int WM, int WN, int MB, int NB, bool B_KN, int A_FMT, int TAIL = 0, bool ADDS = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, const int tiles_n, const int chunk,
                                           const int bid, const int split, uint8_t* const lds,
                                           const TailArgs* const tail = nullptr)
@@ -308,6 +308,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     static_assert(TAIL == 0 || (WM == 2 && WN == 2 && NB == 4), "the adapter's products ride on the 256-column tiles only");
     static_assert(TAIL != 1 || MB == 4, "the O_A side job is laid out for 256 token rows");
     static_assert((TAIL != 1 && TAIL != 3 && TAIL != 4 && TAIL != 5) || (!B_KN && A_FMT == 0), "the adapter product belongs to the forward product");
+    static_assert(!ADDS || (B_KN && A_FMT == 1), "input gradients are what is added up");
     static_assert(TAIL != 2 || (B_KN && A_FMT == 1), "the dB slice belongs to the input-gradient product");
     constexpr int BM = WM * MB * 32, BN = WN * NB * 32, NW = WM * WN;
     constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK;
@@ -783,15 +784,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     if constexpr (RIDE) {
         if (lane == 0) ride_max_slot[wave] = ride_max;
     }
-    // the output type, and whether the product is added to what the output holds, are run-time arguments; each body is
-    // compiled with them fixed
-    auto epilogue = [&](auto is_f32, auto adds) {
-        constexpr bool F32 = decltype(is_f32)::value, ADDS = decltype(adds)::value;
+    // the output type is a run-time argument; each of the two bodies is compiled with it fixed
+    auto epilogue = [&](auto is_f32) {
+        constexpr bool F32 = decltype(is_f32)::value;
         constexpr int ES = F32 ? 4 : 2;
         constexpr int PITCH = BN * ES + 16;                       // +16 B: rows start on different banks
         constexpr int SEGS = BN * ES / 16, COLS_PER_SEG = 16 / ES;
         constexpr int PIECES = WM * 32 * SEGS / (64 * NW);        // 16 bytes per lane each
-        uint4 held[2][ADDS ? PIECES : 1];                         // what a pass adds to, requested a pass ahead
+        uint4 held[2][ADDS ? PIECES : 1];                         // what a pass adds to, requested a pass ahead (ADDS: bf16)
         auto request = [&](int mi) {
 #pragma unroll
             for (int it = 0; it < PIECES; ++it) {
@@ -874,10 +874,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     };
     // (Adding in the epilogue costs the launch 5.5 us at 2048 x 4096 x 4096, 37.6 -> 43.1: the sum is read at the rate of the
     // memory while the tiles write theirs.  A pass of its own took 9.2 us and a launch.)
-    constexpr bool MAY_ADD = B_KN && A_FMT == 1;
-    if (g.c0_is_f32) epilogue(std::true_type{}, std::false_type{});
-    else if (MAY_ADD && g.c0_adds) epilogue(std::false_type{}, std::bool_constant<MAY_ADD>{});
-    else epilogue(std::false_type{}, std::false_type{});
+    if (!ADDS && g.c0_is_f32) epilogue(std::true_type{});
+    else epilogue(std::false_type{});
     if constexpr (RIDE) {                                         // (the epilogue ends with a barrier)
         if (g.amax1 && threadIdx.x == 0) {
             float mx = ride_max_slot[0];
@@ -892,12 +890,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
     }
 }
 
-template <int WM, int WN, int MB, int NB, bool B_KN, int A_FMT>
+template <int WM, int WN, int MB, int NB, bool B_KN, int A_FMT, bool ADDS = false>
 __global__ void __launch_bounds__(64 * WM * WN)
 gemm_fp8_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int chunk)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[gemm_lds_bytes<WM, WN, MB, NB>()];
-    gemm_tile<WM, WN, MB, NB, B_KN, A_FMT>(g, tiles_m, tiles_n, chunk, blockIdx.x, blockIdx.y, lds);
+    gemm_tile<WM, WN, MB, NB, B_KN, A_FMT, 0, ADDS>(g, tiles_m, tiles_n, chunk, blockIdx.x, blockIdx.y, lds);
 }
 
 // The backbone product with the adapter's share as a side job of every tile (TailArgs).
@@ -918,12 +916,12 @@ gemm_fwd_ride_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, con
     gemm_tile<2, 2, MB, 4, false, 0, RB == 4 ? 5 : RB == 2 ? 4 : 3>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
 }
 
-template <int MB>
+template <int MB, bool ADDS>
 __global__ void __launch_bounds__(256)
 gemm_dx_tail_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int chunk, const TailArgs t)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[gemm_lds_bytes<2, 2, MB, 4>()];
-    gemm_tile<2, 2, MB, 4, true, 1, 2>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
+    gemm_tile<2, 2, MB, 4, true, 1, 2, ADDS>(g, tiles_m, tiles_n, chunk, blockIdx.x, 0, lds, &t);
 }
 
 // Forward product and the adapter's split-K product in one launch.  Both read only x~ and the
@@ -949,6 +947,7 @@ gemm_fwd_pair_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, con
 // Input-gradient product and the partial pass of the adapter gradient in one launch, for the same
 // reason: the first n_side workgroups take the adapter-gradient tiles, the rest the 256x256 tiles
 // of dX = dy~ W~.
+template <bool ADDS>
 __global__ void __launch_bounds__(256)
 gemm_dx_db_pair_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int chunk,
                        const DbArgs d, const int n_side)
@@ -962,7 +961,7 @@ gemm_dx_db_pair_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, c
         const int bi = b % d.i_tiles, rest = b / d.i_tiles;
         dbt::db_partial_tile(d, bi, rest % d.splits, rest / d.splits, lds, g_zero16);
     } else {
-        gemm_tile<2, 2, 4, 4, true, 1>(g, tiles_m, tiles_n, chunk, b - n_side, 0, lds);
+        gemm_tile<2, 2, 4, 4, true, 1, 0, ADDS>(g, tiles_m, tiles_n, chunk, b - n_side, 0, lds);
     }
 }
 
@@ -976,6 +975,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream)
     const dim3 grid(static_cast<unsigned>(chunk * 8), static_cast<unsigned>(g.splits)), block(64 * WM * WN);
     if (g.b_is_kn) {
         if (g.a_fmt == 0) gemm_fp8_kernel<WM, WN, MB, NB, true, 0><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
+        else if (g.c0_adds) gemm_fp8_kernel<WM, WN, MB, NB, true, 1, true><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
         else gemm_fp8_kernel<WM, WN, MB, NB, true, 1><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
     } else {
         if (g.a_fmt == 0) gemm_fp8_kernel<WM, WN, MB, NB, false, 0><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
@@ -1171,7 +1171,9 @@ static hipError_t launch_dx_tail(const GemmArgs& g, const TailArgs& t, hipStream
 {
     const int tiles_m = static_cast<int>((g.M + 64 * MB - 1) / (64 * MB)), tiles_n = static_cast<int>((g.N + 255) / 256);
     const int chunk = (tiles_m * tiles_n + 7) / 8;
-    gemm_dx_tail_kernel<MB><<<dim3(static_cast<unsigned>(8 * chunk)), dim3(256), 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    const dim3 grid(static_cast<unsigned>(8 * chunk)), block(256);
+    if (g.c0_adds) gemm_dx_tail_kernel<MB, true><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
+    else gemm_dx_tail_kernel<MB, false><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, t);
     return hipGetLastError();
 }
 
@@ -1192,8 +1194,9 @@ hipError_t launch_gemm_dx_db_pair(const GemmArgs& g, const DbArgs& d, hipStream_
     const int tiles_m = static_cast<int>((g.M + 255) / 256), tiles_n = static_cast<int>((g.N + 255) / 256);
     const int chunk = (tiles_m * tiles_n + 7) / 8;
     const int n_side = (d.i_tiles * d.splits * d.p_tiles + 7) / 8 * 8;
-    gemm_dx_db_pair_kernel<<<dim3(static_cast<unsigned>(n_side + 8 * chunk)), dim3(256), 0, stream>>>(
-        g, tiles_m, tiles_n, chunk, d, n_side);
+    const dim3 grid(static_cast<unsigned>(n_side + 8 * chunk)), block(256);
+    if (g.c0_adds) gemm_dx_db_pair_kernel<true><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, d, n_side);
+    else gemm_dx_db_pair_kernel<false><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk, d, n_side);
     return hipGetLastError();
 }
 
