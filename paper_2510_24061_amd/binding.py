@@ -198,8 +198,8 @@ def melded_bwd(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b, de
                row_scores=None) -> None:
     """dx = None: the input-gradient product is skipped.  delta_buf = None: no buffer step.
     row_scores (uint8/float64 tensor of row_score_bytes(m) bytes): left for a proxy_update that follows."""
-    _check(_native().melded_bwd(dy, wq, s_w, o_a, amax_oa, n, r, dyq, s_dy, dx, d_b, delta_buf, lr, ws, row_scores, _stream()),
-           "falqon_melded_bwd")
+    _check(_native().melded_bwd(dy, wq, s_w, o_a, amax_oa, n, r, dyq, s_dy, dx, d_b, delta_buf, float(lr), ws, row_scores,
+                                _stream()), "falqon_melded_bwd")
 
 
 def melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b, delta_buf, lr: float, ws,
@@ -207,8 +207,8 @@ def melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n: int, r: int, dyq, s_dy, dx, d_b
     """melded_bwd whose input gradient is added to what dx (bf16) holds."""
     if dx is not None and dx.dtype != torch.bfloat16:
         raise TypeError("the sum of input gradients is bf16")
-    _check(_native().melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n, r, dyq, s_dy, dx, d_b, delta_buf, lr, ws, row_scores, _stream()),
-           "falqon_melded_bwd_add")
+    _check(_native().melded_bwd_add(dy, wq, s_w, o_a, amax_oa, n, r, dyq, s_dy, dx, d_b, delta_buf, float(lr), ws, row_scores,
+                                    _stream()), "falqon_melded_bwd_add")
 
 
 def proxy_update(delta_buf, wq, m: int, r: int, k: int, idx_out, ws, clear_selected: bool = True,

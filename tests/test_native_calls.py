@@ -42,3 +42,21 @@ def test_what_is_no_tensor_and_what_has_no_shape():
     with pytest.raises(OverflowError):
         b.workspace_bytes(16, 1 << 70, 64, 16)
     assert b.workspace_bytes(16, 64, 64, 16) == b.lib().falqon_workspace_bytes(16, 64, 64, 16) > 0
+
+
+def test_rates_are_what_float_takes(monkeypatch):
+    """A rate read from a file of settings may be text ("2e-4" is a string to YAML)."""
+    rates = []
+
+    class Calls:
+        @staticmethod
+        def melded_bwd(*args):
+            rates.append(args[12])
+            return 0
+        melded_bwd_add = melded_bwd
+
+    monkeypatch.setattr(b, "_native", lambda: Calls)
+    t = [None] * 5
+    b.melded_bwd(*t, 16, 16, None, None, None, None, None, "2e-4", None)
+    b.melded_bwd_add(*t, 16, 16, None, None, None, None, None, torch.tensor(0.5), None)
+    assert rates == [2e-4, 0.5] and all(type(r) is float for r in rates)
