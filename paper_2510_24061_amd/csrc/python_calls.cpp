@@ -34,12 +34,12 @@ public:
         if (!t.is_cuda() || !t.is_contiguous()) return fail(PyExc_ValueError, "tensors must be contiguous GPU tensors");
         return &t;
     }
-    const at::Tensor* matrix()                                       // its shape is asked for
+    const at::Tensor* matrix(bool longer = false)                    // its shape is asked for; longer: the first two dimensions of it
     {
         const at::Tensor* const t = tensor();
         if (failed_) return nullptr;
         if (!t) return fail(PyExc_AttributeError, "'NoneType' object has no attribute 'shape'");
-        if (t->dim() != 2) return fail(PyExc_ValueError, "a tensor of two dimensions expected");
+        if (longer ? t->dim() < 2 : t->dim() != 2) return fail(PyExc_ValueError, "a tensor of two dimensions expected");
         return t;
     }
     int64_t integer()
@@ -166,7 +166,7 @@ PyObject* proxy_update(PyObject*, PyObject* const* args, Py_ssize_t count)
 {
     return guarded([&]() -> PyObject* {
         Args a(args, count, 10);
-        const at::Tensor *buf = a.tensor(), *wq = a.matrix();
+        const at::Tensor *buf = a.tensor(), *wq = a.matrix(true);
         const int64_t m = a.integer(), r = a.integer(), k = a.integer();
         const at::Tensor *idx = a.tensor(), *ws = a.tensor();
         const int clear = a.integer() != 0;

@@ -60,3 +60,19 @@ def test_rates_are_what_float_takes(monkeypatch):
     b.melded_bwd(*t, 16, 16, None, None, None, None, None, "2e-4", None)
     b.melded_bwd_add(*t, 16, 16, None, None, None, None, None, torch.tensor(0.5), None)
     assert rates == [2e-4, 0.5] and all(type(r) is float for r in rates)
+
+@pytest.mark.gpu
+def test_update_takes_the_width_of_a_weight_of_more_dimensions():
+    m, r, n, k = 32, 16, 64, 4
+    buf = torch.randn(m, r, device="cuda", generator=torch.Generator(device="cuda").manual_seed(0))
+    outs = []
+    for shape in [(m + r, n), (m + r, n, 1)]:
+        wq = torch.full(shape, 0x30, dtype=torch.uint8, device="cuda")
+        idx = torch.empty(k, dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.workspace_bytes(16, n, m, r), dtype=torch.uint8, device="cuda")
+        b.proxy_update(buf.clone(), wq, m, r, k, idx, ws)
+        torch.cuda.synchronize()
+        outs.append((wq.reshape(m + r, n), idx))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    with pytest.raises(ValueError):
+        b.proxy_update(buf, wq.reshape(-1), m, r, k, idx, ws)
