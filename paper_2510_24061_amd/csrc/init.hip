@@ -643,7 +643,7 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
                     for (int u = 0; u < 2; ++u) ab[u] = fma(va[e][u], vb[e][u], ab[u]);
                 const double haa = la[0], hbb = lb[0], hab = quad_sum(ab[0] + ab[1]);
                 double c, s, tn;
-                if (jacobi_rotation<JacobiEstimates, false>(haa, hbb, hab, c, s, tn)) {
+                if (jacobi_rotation(haa, hbb, hab, c, s, tn)) {
 #pragma unroll
                     for (int e = 0; e < L8; ++e) {
                         v2d na, nb;

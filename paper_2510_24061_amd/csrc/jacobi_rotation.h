@@ -23,32 +23,21 @@ struct JacobiEstimates {
     }
 };
 
-// Root, reciprocal and reciprocal root of positive normal numbers to a few 1e-16: an estimate and one step of third
-// order (its error is the cube of the estimate's), a fifth of the instructions of the correctly rounded operations.
+// Reciprocal root of a positive normal number to a few 1e-16: an estimate and one step of third order (its error is the cube
+// of the estimate's), a fifth of the instructions of the correctly rounded operation.
 template <class E = JacobiEstimates>
 __host__ __device__ inline double jacobi_rsqrt(double x)
 {
     const double y = E::rsqrt_of(x), e = fma(-x * y, y, 1.0);
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
-template <class E = JacobiEstimates>
-__host__ __device__ inline double jacobi_sqrt(double x)
-{
-    const double y = jacobi_rsqrt<E>(x), r = x * y;
-    return fma(0.5 * y, fma(-r, r, x), r);
-}
-template <class E = JacobiEstimates>
-__host__ __device__ inline double jacobi_reciprocal(double x)
-{
-    const double y = E::reciprocal_of(x), e = fma(-x, y, 1.0);
-    return fma(y, fma(e, e, e), y);
-}
 
 // Cosine, sine and tangent of the rotation that annihilates hab between the diagonal entries haa and hbb; false (and the
 // identity) for an entry below the rounding level of the two, which is left alone.
-// FULL = false: the tangent straight from the estimates, so that 2^-22 of hab is left; the rotation is as orthogonal as
-// with it, and the chain of dependent instructions, which is what an eigensolver's round waits for, half as long.
-template <class E = JacobiEstimates, bool FULL = true>
+// The tangent comes straight from the estimates: a relative error d of it leaves d hab of the entry, here 2^-23, and the
+// next sweep takes that; the rotation is as orthogonal as with an exact tangent, and the chain of dependent instructions, which is
+// what an eigensolver's round waits for, half as long.
+template <class E = JacobiEstimates>
 __host__ __device__ inline bool jacobi_rotation(double haa, double hbb, double hab, double& c, double& s, double& tn)
 {
     // Entries between directions that are null up to rounding can be so small that their squares underflow: all three
@@ -58,19 +47,12 @@ __host__ __device__ inline bool jacobi_rotation(double haa, double hbb, double h
     const bool turns = fabs(hab) > 1e-300 && (hab * scale) * (hab * scale) > 1e-32 * fabs((haa * scale) * (hbb * scale));
     // tangent of the smaller angle: 2 hab / (d +- sqrt(d^2 + 4 hab^2)), d = hbb - haa
     const double d = (hbb - haa) * scale, x = 2.0 * hab * scale, square = d * d + x * x;
-    const double root = FULL ? jacobi_sqrt<E>(square) : square * E::rsqrt_of(square);
-    const double sum = d >= 0.0 ? d + root : d - root;
-    const double t = x * (FULL ? jacobi_reciprocal<E>(sum) : E::reciprocal_of(sum));
+    const double root = square * E::rsqrt_of(square);
+    const double t = x * E::reciprocal_of(d >= 0.0 ? d + root : d - root);
     tn = turns ? t : 0.0;
     c = turns ? jacobi_rsqrt<E>(1.0 + t * t) : 1.0;
     s = tn * c;
     return turns;
-}
-template <class E = JacobiEstimates>
-__host__ __device__ inline bool jacobi_rotation(double haa, double hbb, double hab, double& c, double& s)
-{
-    double tn;
-    return jacobi_rotation<E>(haa, hbb, hab, c, s, tn);
 }
 
 }  // namespace falqon
