@@ -575,7 +575,7 @@ __device__ __forceinline__ double quad_sum(double v)
 // W = L^T P, whose columns have lengths lambda^(1/2) and give P back as L W diag(1/lambda) (eigenvector_kernel, settle_kernel).
 // Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: the dot product of the two is
 // reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.  Their squared
-// lengths follow from the rotation and are formed anew once per sweep (and where little of one is left): with three dot products
+// lengths follow from the rotation, to 1e-12 of each, and are formed anew once per sweep and where little of one is left: with three dot products
 // and a tangent to full precision per pair the launch took 4 % more at l = 72.
 // A round is bound by the columns' way through LDS (writes at 76 B/clk) and the instructions that a SIMD issues, and those of
 // the rotation count once per wave: four lanes per pair make l / 32 waves, one per SIMD.  (Columns that stay in registers and
@@ -597,8 +597,8 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
     typedef double v2d __attribute__((ext_vector_type(2)));
     // columns at an odd multiple of 64 bytes: the sixteen pairs of a wave spread over all banks
     constexpr int l = 8 * L8, PITCH = 8 * (L8 | 1);
-    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], squared lengths as followed and as last formed, two flags
-    v2d* const s_length = reinterpret_cast<v2d*>(s_v + l * PITCH);
+    extern __shared__ __attribute__((aligned(16))) double s_v[];      // [l][PITCH], squared lengths, two flags
+    JacobiLength* const s_length = reinterpret_cast<JacobiLength*>(s_v + l * PITCH);
     int* const s_turned = reinterpret_cast<int*>(s_length + l);
     const int t = threadIdx.x, pair = t >> 2, e0 = 2 * (t & 3);
     const bool live = pair < l / 2;
@@ -624,7 +624,7 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
 #pragma unroll
             for (int e = 0; e < L8; ++e) v[e] = *reinterpret_cast<const v2d*>(s_v + c * PITCH + e0 + 8 * e);
             const double length = square(v);
-            s_length[c] = v2d{length, length};
+            s_length[c] = JacobiLength{length, length};
         }
         __syncthreads();
         for (int round = 0; round < l - 1; ++round) {
@@ -636,12 +636,12 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
                 v2d va[L8], vb[L8], ab = {0.0, 0.0};
 #pragma unroll
                 for (int e = 0; e < L8; ++e) { va[e] = pa[4 * e]; vb[e] = pb[4 * e]; }
-                const v2d la = s_length[ca], lb = s_length[cb];
+                JacobiLength la = s_length[ca], lb = s_length[cb];
 #pragma unroll
                 for (int e = 0; e < L8; ++e)
 #pragma unroll
                     for (int u = 0; u < 2; ++u) ab[u] = fma(va[e][u], vb[e][u], ab[u]);
-                const double haa = la[0], hbb = lb[0], hab = quad_sum(ab[0] + ab[1]);
+                const double haa = la.now, hbb = lb.now, hab = quad_sum(ab[0] + ab[1]);
                 double c, s, tn;
                 if (jacobi_rotation(haa, hbb, hab, c, s, tn)) {
 #pragma unroll
@@ -655,15 +655,12 @@ jacobi_eig_kernel(const double* __restrict__ lt, double* __restrict__ w, double*
                         pa[4 * e] = va[e] = na;
                         pb[4 * e] = vb[e] = nb;
                     }
-                    // Lengths follow from the rotation.  A difference keeps the rounding of the larger terms, so where little of
-                    // one is left since it was last formed, both are formed anew: 1e-11 of a length is off at the worst.
-                    v2d na = {c * c * fma(tn, fma(tn, hbb, -2.0 * hab), haa), la[1]}, nb = {c * c * fma(tn, fma(tn, haa, 2.0 * hab), hbb), lb[1]};
-                    if (!(na[0] >= 1e-3 * na[1] && nb[0] >= 1e-3 * nb[1])) {
-                        na[0] = na[1] = square(va);
-                        nb[0] = nb[1] = square(vb);
+                    if (!jacobi_follow(c, tn, hab, la, lb)) {
+                        la.now = la.carried = square(va);
+                        lb.now = lb.carried = square(vb);
                     }
-                    s_length[ca] = na;
-                    s_length[cb] = nb;
+                    s_length[ca] = la;
+                    s_length[cb] = lb;
                     // (one comparison: orthogonal to 1e-14 where they turn by more than 1e-8, to 1e-8 where not)
                     if (hab * hab > (fabs(s) > 1e-8 ? 1e-28 : 1e-16) * haa * hbb) s_turned[sweep & 1] = 1;
                 }

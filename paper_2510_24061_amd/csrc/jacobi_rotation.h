@@ -55,4 +55,25 @@ __host__ __device__ inline bool jacobi_rotation(double haa, double hbb, double h
     return turns;
 }
 
+// Squared length of a column as it follows from the rotations since it was last formed from the column itself, and the lengths
+// that went into it: its rounding errors are some 1e-16 of these.
+struct JacobiLength {
+    double now, carried;
+};
+
+// What the rotation makes of the lengths of its two columns; false if they have to be formed anew.  No term of a sum exceeds
+// its column's old length (tn^2 hbb <= haa for the shorter one, as hab^2 <= haa hbb), so a rotation adds some roundings of
+// that; errors of before come with the weights of the lengths, but do not cancel where these do.  Where less than a
+// thousandth of them is left, a length is no longer good.  (Compared with the column's own largest length, errors go from
+// column to column and grow by a thousand on each.)
+__host__ __device__ inline bool jacobi_follow(double c, double tn, double hab, JacobiLength& a, JacobiLength& b)
+{
+    const double haa = a.now, hbb = b.now, carried = a.carried, c2 = c * c, t2 = tn * tn;
+    a.now = c2 * fma(tn, fma(tn, hbb, -2.0 * hab), haa);
+    b.now = c2 * fma(tn, fma(tn, haa, 2.0 * hab), hbb);
+    a.carried = fmax(a.now, c2 * fma(t2, b.carried, carried));
+    b.carried = fmax(b.now, c2 * fma(t2, carried, b.carried));
+    return a.now >= 1e-3 * a.carried && b.now >= 1e-3 * b.carried;
+}
+
 }  // namespace falqon
