@@ -282,13 +282,27 @@ __device__ __forceinline__ double of_lane(double v)
     return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + N, 0xf, 0xf, true);
 }
 
-// v += u times the v of lane N of the row of 16, in one instruction (the compiler takes two and a wait in between).  `first`: v
-// may have been written by the instruction before, which a DPP read has to be two behind.
-template <int N>
-__device__ __forceinline__ void add_of_lane(double& v, double u, bool first)
+// v[i] += u times the v[i] of lane N of the row of 16, COUNT of them, an instruction each (the compiler takes two and a wait in
+// between).  A DPP read has to be two instructions behind a vector write of its source.  The compiler does not look into inline
+// assembly for that, and what it puts before a block (a copy, a reload, the select of a start value) may be such a write: so
+// every block waits by itself, and within one no source is written before it is read.  Nor does it see that a block writes:
+// what it reads by DPP next is a block's first element, so a block of one or two waits at its end, too.
+template <int N, int COUNT>
+__device__ __forceinline__ void add_of_lane(double* v, double u)
 {
-    if (first) asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(v) : "v"(u), "n"(N));
-    else asm volatile("v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(v) : "v"(u), "n"(N));
+    static_assert(COUNT >= 0 && COUNT <= 8, "operands of a block");
+#define FQ_ADD(i) "\n\tv_fmac_f64_dpp %" #i ", %" #i ", %[u] row_newbcast:%[lane] row_mask:0xf bank_mask:0xf"
+#define FQ_BLOCK(adds, ...) asm volatile("s_nop 1" adds : __VA_ARGS__ : [u] "v"(u), [lane] "n"(N))
+    if constexpr (COUNT == 1) FQ_BLOCK(FQ_ADD(0) "\n\ts_nop 1", "+v"(v[0]));
+    if constexpr (COUNT == 2) FQ_BLOCK(FQ_ADD(0) FQ_ADD(1) "\n\ts_nop 1", "+v"(v[0]), "+v"(v[1]));
+    if constexpr (COUNT == 3) FQ_BLOCK(FQ_ADD(0) FQ_ADD(1) FQ_ADD(2), "+v"(v[0]), "+v"(v[1]), "+v"(v[2]));
+    if constexpr (COUNT == 4) FQ_BLOCK(FQ_ADD(0) FQ_ADD(1) FQ_ADD(2) FQ_ADD(3), "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+    if constexpr (COUNT > 4 && COUNT < 8) { add_of_lane<N, 4>(v, u); add_of_lane<N, COUNT - 4>(v + 4, u); }
+    if constexpr (COUNT == 8)
+        FQ_BLOCK(FQ_ADD(0) FQ_ADD(1) FQ_ADD(2) FQ_ADD(3) FQ_ADD(4) FQ_ADD(5) FQ_ADD(6) FQ_ADD(7),
+                 "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+#undef FQ_BLOCK
+#undef FQ_ADD
 }
 
 template <int N, int END, typename F>
@@ -368,10 +382,10 @@ factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
                 const double inv = p > of_lane<k>(least[s]) ? r : 0.0;   // a dead row takes no part
                 if (x == k) own = inv;
                 const double u = x > k ? -d[k] * inv : 0.0;
-#pragma unroll
-                for (int j = k + 1; j < 16; ++j) add_of_lane<k>(d[j], u, j == k + 1);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) add_of_lane<k>(w[c], u, c == 0);
+                constexpr int LEFT = 15 - k, FIRST = LEFT > 8 ? 8 : LEFT;
+                add_of_lane<k, FIRST>(d + k + 1, u);
+                add_of_lane<k, LEFT - FIRST>(d + k + 1 + FIRST, u);
+                add_of_lane<k, 4>(w, u);
             });
             if (quad == 0) s_inv[b & 1][x] = own;
             const double root = sqrt(own);
