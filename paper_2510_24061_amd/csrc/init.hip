@@ -54,6 +54,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // 64 bits than on the fp32 matrix cores (3.7e-7 against 5.4e-7 of a sum of 4096 terms of random sign).  At 4096 x 4096,
 // l = 72, the fp32 cores need 17 us for a product, the six on the bf16 ones 6.5, and E, split on the way from memory to the
 // operands, becomes what bounds it: a launch takes 21.6 us (30.5 on the fp32 cores; 25 with the operands of two steps in registers instead of three).
+// Elements whose parts bf16 does not hold (look_at_range) take the fp32 cores: no packing and no ring there, such matrices are rare.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v8f __attribute__((ext_vector_type(8)));
 constexpr int kParts = 3;
@@ -82,7 +83,8 @@ struct Products {
     static constexpr int DEPTH = CB <= 5 ? 3 : 2;                     // steps whose operands are in registers or on their way
     v8bf zf[DEPTH][CB][kParts];
 
-    __device__ __forceinline__ Products()
+    __device__ __forceinline__ Products() { clear(); }
+    __device__ __forceinline__ void clear()
     {
 #pragma unroll
         for (int x = 0; x < 4; ++x)
@@ -114,6 +116,30 @@ struct Products {
             }
         }
     }
+    // The same from the beginning on the fp32 matrix cores, with the vectors as they are.  (Behind the steps above, so that nothing waits
+    // for the word that asks for it.)  vector: the one of this lane in the first block, of `length`
+    // elements, with `vectors` from it on; operand(i, x): element i of this lane's row or column of E in block x.
+    template <class O>
+    __device__ __forceinline__ void run_fp32(const float* vector, int vectors, int64_t length, int64_t first, int64_t end, int quad, O operand)
+    {
+        clear();
+        for (int64_t b = first; b < end; b += 4) {
+#pragma unroll 1
+            for (int u = 0; u < 8; ++u) {                             // depth index of the instruction: quad
+                const int64_t i = b * 32 + 4 * u + quad;
+                const bool in = i < length;
+                float o[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) o[x] = in ? operand(i, x) : 0.0f;
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    const float z = in && 16 * cb < vectors ? vector[16 * cb * length + i] : 0.0f;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(z, o[x], acc[x][cb], 0, 0, 0);
+                }
+            }
+        }
+    }
     // 16 vectors x CB by 16 rows of E, 32 deep
     __device__ __forceinline__ void multiply(int x, v8f e, int which)
     {
@@ -132,11 +158,12 @@ struct Products {
 // up to seven; eight, whose operands would not fit the registers, are two halves)
 template <int CB>
 __global__ void __launch_bounds__(kThreads)
-apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ zp, int l,
-               float* __restrict__ part, int64_t per_slice)
+apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ zp, const float* __restrict__ z, int l,
+               const int* __restrict__ wide, float* __restrict__ part, int64_t per_slice)
 {
     constexpr int PITCH = 68;
     __shared__ __attribute__((aligned(16))) float s_sum[4][CB * 16 * PITCH];
+    const int outside = *wide;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (n + 31) / 32;
     const int64_t begin = static_cast<int64_t>(blockIdx.y) * per_slice;
@@ -164,7 +191,9 @@ apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __
 #pragma unroll
         for (int x = 0; x < 4; ++x) p.multiply(x, __builtin_shufflevector(ef[which][x][0], ef[which][x][1], 0, 1, 2, 3, 4, 5, 6, 7), which);
     };
+    const int c0 = 16 * CB * static_cast<int>(blockIdx.z);
     p.run(begin + wave, end, fetch, multiply);
+    if (outside) p.run_fp32(z + (c0 + row16) * n, l - c0 - row16, n, begin + wave, end, quad, [&](int64_t j, int x) { return erow[x][j]; });
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
@@ -172,7 +201,7 @@ apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __
 #pragma unroll
             for (int v = 0; v < 4; ++v) s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + x * 16 + row16] = p.acc[x][cb][v];
     __syncthreads();
-    const int c0 = 16 * CB * static_cast<int>(blockIdx.z), vectors = l - c0 < 16 * CB ? l - c0 : 16 * CB;
+    const int vectors = l - c0 < 16 * CB ? l - c0 : 16 * CB;
     float* const out = part + (static_cast<int64_t>(blockIdx.y) * l + c0) * m;
     for (int q = threadIdx.x; q < vectors * 16; q += kThreads) {
         const int c = q >> 4, i4 = (q & 15) * 4;
@@ -188,11 +217,12 @@ apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __
 // columns 4 (t % 16) + x of eight rows, one for each of four column blocks
 template <int CB>
 __global__ void __launch_bounds__(kThreads)
-apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ yp, int l,
-                float* __restrict__ part, int64_t per_slice)
+apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ yp, const float* __restrict__ y, int l,
+                const int* __restrict__ wide, float* __restrict__ part, int64_t per_slice)
 {
     constexpr int PITCH = 68;
     __shared__ __attribute__((aligned(16))) float s_sum[4][CB * 16 * PITCH];
+    const int outside = *wide;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
     const int64_t j0 = static_cast<int64_t>(blockIdx.x) * 64, steps = (m + 31) / 32;
     const int64_t begin = static_cast<int64_t>(blockIdx.y) * per_slice;
@@ -217,7 +247,9 @@ apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* _
             p.multiply(x, column, which);
         }
     };
+    const int c0 = 16 * CB * static_cast<int>(blockIdx.z);
     p.run(begin + wave, end, fetch, multiply);
+    if (outside) p.run_fp32(y + (c0 + row16) * m, l - c0 - row16, m, begin + wave, end, quad, [&](int64_t i, int x) { return e[i * n + col + x]; });
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -225,7 +257,7 @@ apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* _
             *reinterpret_cast<v4f*>(&s_sum[wave][(cb * 16 + 4 * quad + v) * PITCH + 4 * row16]) =
                 v4f{p.acc[0][cb][v], p.acc[1][cb][v], p.acc[2][cb][v], p.acc[3][cb][v]};
     __syncthreads();
-    const int c0 = 16 * CB * static_cast<int>(blockIdx.z), vectors = l - c0 < 16 * CB ? l - c0 : 16 * CB;
+    const int vectors = l - c0 < 16 * CB ? l - c0 : 16 * CB;
     float* const out = part + (static_cast<int64_t>(blockIdx.y) * l + c0) * n;
     for (int q = threadIdx.x; q < vectors * 16; q += kThreads) {
         const int c = q >> 4, j4 = (q & 15) * 4;
@@ -314,10 +346,38 @@ __device__ __forceinline__ void for_each(F f)
     }
 }
 
+// *wide <- 1 where E has entries that the parts of the products do not hold: beyond 2^120, not finite, or below 2^-64 but not
+// zero (the last part of an element is 2^-17 of it, and its product with that of a vector has to stay above 2^-149).
+struct RangeOf {
+    const float* e;
+    int64_t count;                                                    // a multiple of 16
+    int* wide;
+};
+__device__ __forceinline__ void look_at_range(const RangeOf& r, int64_t first, int64_t stride)
+{
+    constexpr uint32_t LEAST = uint32_t{127 - 64} << 23, MOST = uint32_t{127 + 120} << 23;
+    bool outside = false;
+    for (int64_t i = 4 * first; i < r.count; i += 4 * stride) {
+        const uint4 v = *reinterpret_cast<const uint4*>(r.e + i);
+        const uint32_t bits[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t size = bits[u] & 0x7fffffffu;
+            outside |= size != 0 && size - LEAST > MOST - LEAST;
+        }
+    }
+    if (outside) *r.wide = 1;
+}
+
+// Workgroups beyond the first (one takes all of the chain) look at E's range meanwhile.
 template <int NB, bool FACTOR>
 __global__ void __launch_bounds__(64 * factor_waves(NB))
-factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
+factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out, const RangeOf range)
 {
+    if (!FACTOR && blockIdx.x > 0) {
+        look_at_range(range, static_cast<int64_t>(blockIdx.x - 1) * blockDim.x + threadIdx.x, static_cast<int64_t>(gridDim.x - 1) * blockDim.x);
+        return;
+    }
     constexpr int WAVES = factor_waves(NB), PER = (factor_blocks(NB) + WAVES - 1) / WAVES;
     constexpr int P = 18;                                             // doubles per row of a block: rows spread over the banks
     __shared__ __attribute__((aligned(16))) double s_in[NB][16 * P], s_f[NB][16 * P], s_w[16 * P], s_inv[2][16];
@@ -439,13 +499,14 @@ factor_kernel(const double* __restrict__ g, int l, double* __restrict__ out)
 // dst = L^-1 src on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: lane t holds row t % 16 and depth t / 16 of its
 // operand; register v of the accumulator holds row t / 16 + 4 v, column t % 16).  A workgroup owns 16 elements of all
 // vectors, a wave 16 vectors of the result; every load is requested at once, so the launch is one memory round trip
-// and a chain of up to l / 4 instructions.  dst may be src, and may be null if only `packed` is wanted; `packed` gets
-// the layout above with its padding.
+// and a chain of up to l / 4 instructions.  dst may be src, and is written only if *asked where
+// that is given; `packed` gets the layout above with its padding.
 template <int CB>
 __global__ void __launch_bounds__(CB * 64)
 apply_lower_kernel(const float* src, float* dst, uint32_t* __restrict__ packed, int l, int64_t len,
-                   const double* __restrict__ linv)
+                   const double* __restrict__ linv, const int* __restrict__ asked)
 {
+    const bool whole = !asked || *asked;
     const int R = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, row16 = lane & 15, quad = lane >> 4;
     const int64_t j = static_cast<int64_t>(blockIdx.x) * 16 + row16;
     const int64_t jr = j < len ? j : len - 1;
@@ -475,7 +536,7 @@ apply_lower_kernel(const float* src, float* dst, uint32_t* __restrict__ packed, 
         const int cc = quad + 4 * v;
         const bool in = 16 * R + cc < l && j < len;
         o[v] = in ? static_cast<float>(acc[v]) : 0.0f;
-        if (in && dst) dst[static_cast<int64_t>(16 * R + cc) * len + j] = o[v];
+        if (in && whole) dst[static_cast<int64_t>(16 * R + cc) * len + j] = o[v];
     }
     // Elements j and j + 1 share a word: of each two vectors, the lane of the even one writes the first, the odd one the second.
     const bool odd = row16 & 1;
@@ -502,10 +563,11 @@ apply_lower_kernel(const float* src, float* dst, uint32_t* __restrict__ packed, 
 // times and not l times, with the next operands in flight (6.2 us at 72 x 4096, 9.7 without; 5.9 with the first two exchanges of the reduction within four lanes, not through LDS); grid (l / 4, l / 4), the upper half leaves, the lower one
 // writes both.
 __global__ void __launch_bounds__(kThreads)
-gram_kernel(const float* __restrict__ y, int l, int64_t m, double* __restrict__ h)
+gram_kernel(const float* __restrict__ y, int l, int64_t m, double* __restrict__ h, int* wide)
 {
     __shared__ double s_red[kThreads / 64][16];
     if (blockIdx.y > blockIdx.x) return;
+    if (wide && blockIdx.x == 0 && threadIdx.x == 0) *wide = 0;        // for the launch that follows
     const float* const ya = y + static_cast<int64_t>(4 * blockIdx.x) * m;
     const float* const yb = y + static_cast<int64_t>(4 * blockIdx.y) * m;
     double d[16];
@@ -849,6 +911,7 @@ SvdLayout svd_layout(int64_t m, int64_t n, int64_t r)
     L.part = off;
     L.packed = off + sizeof(float) * kMaxSlices * l * longest;
     off = up(off + room);
+    L.wide = off - 256;                                                   // (behind the packed vectors: they leave at least 1.5 KB)
     L.total = off;
     return L;
 }
@@ -861,18 +924,21 @@ SvdLayout svd_layout(int64_t m, int64_t n, int64_t r)
     }
 
 // rows of dst[l][len] <- orthonormal basis of the rows of src (Cholesky QR, `passes` times), and the same packed for
-// the products; dst may be src; h and lfac are l x l fp64 scratch
+// the products; dst may be src, and is written only if *asked where that is given (one pass then); h and lfac are l x l fp64
+// scratch; range: what is looked at beside the first factor
 static hipError_t orthonormalize_rows(const float* src, float* dst, uint32_t* packed, int l, int64_t len, double* h,
-                                      double* lfac, int passes, hipStream_t stream)
+                                      double* lfac, int passes, hipStream_t stream, const int* asked = nullptr,
+                                      RangeOf range = {nullptr, 0, nullptr})
 {
     const int nb = l / 4;
     const unsigned blocks = static_cast<unsigned>((len + 31) / 32 * 2);
     for (int pass = 0; pass < passes; ++pass) {
         const float* const v = pass ? dst : src;
-        gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h);
+        gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h, pass ? nullptr : range.wide);
+        const unsigned lookers = range.wide && !pass ? 1020 : 0;
 #define FQ_APPLY(CB)                                                                                         \
-        factor_kernel<CB, false><<<1, 64 * factor_waves(CB), 0, stream>>>(h, l, lfac);                       \
-        apply_lower_kernel<CB><<<blocks, CB * 64, 0, stream>>>(v, dst, packed, l, len, lfac)
+        factor_kernel<CB, false><<<1 + lookers, 64 * factor_waves(CB), 0, stream>>>(h, l, lfac, range);      \
+        apply_lower_kernel<CB><<<blocks, CB * 64, 0, stream>>>(v, dst, packed, l, len, lfac, asked)
         FQ_BY_BLOCKS((l + 15) / 16, FQ_APPLY)
 #undef FQ_APPLY
         const hipError_t err = hipGetLastError();
@@ -893,6 +959,7 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     double* lambda = reinterpret_cast<double*>(ws + L.lambda);
     float* part = reinterpret_cast<float*>(ws + L.part);
     uint32_t* packed = reinterpret_cast<uint32_t*>(ws + L.packed);
+    int* wide = reinterpret_cast<int*>(ws + L.wide);
     // Y[l][m] = Z E^T (transposed == false) or Z[l][n] = Y E: slices of the contracted dimension so that about 256
     // workgroups stream E, each with at least one step per wave, then the ordered sum
     auto product = [&](bool transposed, float* out) -> hipError_t {
@@ -909,8 +976,8 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
         float* dst = slices > 1 ? part : out;
         const v8bf* const vectors = reinterpret_cast<const v8bf*>(packed);
 #define FQ_PRODUCT(CB)                                                                                       \
-        if (transposed) apply_et_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, vectors, l, dst, per);   \
-        else apply_e_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, vectors, l, dst, per)
+        if (transposed) apply_et_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, vectors, y, l, wide, dst, per); \
+        else apply_e_kernel<CB><<<grid, kThreads, 0, stream>>>(e, m, n, vectors, z, l, wide, dst, per)
         switch (vector_blocks / halves) {
             case 2: FQ_PRODUCT(2); break; case 3: FQ_PRODUCT(3); break; case 4: FQ_PRODUCT(4); break;
             case 5: FQ_PRODUCT(5); break; case 6: FQ_PRODUCT(6); break; default: FQ_PRODUCT(7); break;
@@ -925,17 +992,17 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     };
     hipError_t err;
 #define FQ_CHECK(expr) do { err = (expr); if (err != hipSuccess) return err; } while (0)
-    FQ_CHECK(orthonormalize_rows(omega, z, packed, l, n, h, p, iters ? 1 : 2, stream));
+    FQ_CHECK(orthonormalize_rows(omega, z, packed, l, n, h, p, iters ? 1 : 2, stream, nullptr, RangeOf{e, m * n, wide}));
     for (int it = 0; it < iters; ++it) {
         FQ_CHECK(product(false, y));
-        FQ_CHECK(orthonormalize_rows(y, nullptr, packed, l, m, h, p, 1, stream));
+        FQ_CHECK(orthonormalize_rows(y, y, packed, l, m, h, p, 1, stream, wide));
         FQ_CHECK(product(true, z));
         FQ_CHECK(orthonormalize_rows(z, z, packed, l, n, h, p, it == iters - 1 ? 2 : 1, stream));
     }
     FQ_CHECK(product(false, y));
     const int nb = l / 4;
-    gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(y, l, m, h);
-#define FQ_FACTOR(CB) factor_kernel<CB, true><<<1, 64 * factor_waves(CB), 0, stream>>>(h, l, p)
+    gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(y, l, m, h, nullptr);
+#define FQ_FACTOR(CB) factor_kernel<CB, true><<<1, 64 * factor_waves(CB), 0, stream>>>(h, l, p, RangeOf{nullptr, 0, nullptr})
     FQ_BY_BLOCKS((l + 15) / 16, FQ_FACTOR)
 #undef FQ_FACTOR
     FQ_CHECK(hipGetLastError());

@@ -254,3 +254,36 @@ def test_both_factors_where_the_rank_is_lower_than_asked_for(m, n, r, rank, iter
         assert np.max(np.abs(f @ f.T - np.diag(sig))) <= 1e-6 * sig[0]
     if iters:
         assert np.linalg.norm(bt.T @ a - e) <= 1e-6 * np.linalg.norm(e) * np.sqrt(rank)
+
+
+@pytest.mark.parametrize("largest", [3.3999e38, 1e-3, 1.7e-36])
+def test_entries_at_the_ends_of_the_range(largest):
+    """The products take elements in parts of 8 bits, which hold numbers up to 3.39e38 and, to all their bits, down to 1.5e-33:
+    beyond that the elements have to be taken whole.  Twenty entries in rows and columns of their own are the singular values,
+    and all of them are in a subspace of 24.  Bound: 16 roundings of fp32."""
+    g = np.random.default_rng(1)
+    m, n = 200, 324
+    values = np.sort(largest * g.uniform(0.2, 1.0, 20).astype(np.float32))[::-1].astype(np.float32)
+    values[0] = np.float32(largest)
+    e = np.zeros((m, n), np.float32)
+    e[g.permutation(m)[:20], g.permutation(n)[:20]] = values
+    a, bt, sig = _factors(e, 16, g.normal(size=(24, n)).astype(np.float32), 2)
+    assert np.max(np.abs(sig / values[:16] - 1.0)) <= 1e-6
+    assert np.max(np.abs((a / sig[0]) @ a.T - np.diag(sig / sig[0]))) <= 1e-6
+    assert np.max(np.abs((bt.T / sig[0]) @ a - np.where(e >= values[15], e / sig[0], 0.0))) <= 1e-6
+
+
+@pytest.mark.parametrize("r", [16, 32, 40, 64, 80, 88, 104, 120])
+@pytest.mark.parametrize("scale", [1e-30, 1e36])
+def test_products_of_whole_elements_against_64_bits(r, scale):
+    """Every number of vector blocks with elements beyond the range of the parts, on sizes that end inside steps and tiles.
+    Bounds as in the products of many steps above."""
+    m, n = 300, 412
+    e = np.random.default_rng(r).normal(size=(m, n)).astype(np.float32) * np.float32(scale)
+    a, sig = _factor(e, r, iters=1, seed=r)
+    e64 = e.astype(np.float64) / scale
+    z = np.linalg.qr(torch.randn(r + 8, n, generator=torch.Generator().manual_seed(r)).numpy().astype(np.float64).T)[0]
+    z = np.linalg.qr(e64.T @ np.linalg.qr(e64 @ z)[0])[0]
+    want = np.linalg.svd(e64 @ z, compute_uv=False)[:r]
+    assert np.max(np.abs(sig / scale - want)) <= 1e-6 * want[0]
+    assert np.max(np.abs((a / scale) @ a.T - np.diag(sig / scale))) <= 1e-5 * want[0]
