@@ -79,6 +79,7 @@ __device__ __forceinline__ void split(v8f x, v8bf (&part)[kParts])
 // column t % 16 = the second operand's row, and in register v the first operand's row 4 (t / 16) + v.
 template <int CB>
 struct Products {
+    static_assert(CB <= 7, "eight blocks spill 66 registers");
     v4f acc[4][CB];
     static constexpr int DEPTH = CB <= 5 ? 3 : 2;                     // steps whose operands are in registers or on their way
     v8bf zf[DEPTH][CB][kParts];
@@ -155,7 +156,7 @@ struct Products {
 };
 
 // part[s][c][i] = sum over columns j of slice s of Z[c][j] E[i][j]; a workgroup owns 64 rows of E and CB blocks of vectors (all
-// up to seven; eight, whose operands would not fit the registers, are two halves)
+// up to seven, at 510 of 512 registers; eight would spill 66 and are two halves, which give the same bits)
 template <int CB>
 __global__ void __launch_bounds__(kThreads)
 apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ zp, const float* __restrict__ z, int l,
