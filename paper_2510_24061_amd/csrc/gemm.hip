@@ -791,19 +791,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
         constexpr int PITCH = BN * ES + 16;                       // +16 B: rows start on different banks
         constexpr int SEGS = BN * ES / 16, COLS_PER_SEG = 16 / ES;
         constexpr int PIECES = WM * 32 * SEGS / (64 * NW);        // 16 bytes per lane each
-        uint4 held[2][ADDS ? PIECES : 1];                         // what a pass adds to, requested a pass ahead (ADDS: bf16)
+        uint4 held[ADDS ? PIECES : 1];                            // what a pass adds to, on its way while its rows are parked (ADDS: bf16)
         auto request = [&](int mi) {
 #pragma unroll
             for (int it = 0; it < PIECES; ++it) {
                 const int sidx = it * 64 * NW + threadIdx.x;
                 const int64_t row = m0 + ((sidx / SEGS) >> 5) * (MB * 32) + mi * 32 + ((sidx / SEGS) & 31);
                 const int64_t col = n0 + sidx % SEGS * COLS_PER_SEG;
-                if (row < M && col < N) held[mi & 1][it] = *reinterpret_cast<const uint4*>(c0p + (row * g.ldc0 + col) * ES);
+                if (row < M && col < N) held[it] = *reinterpret_cast<const uint4*>(c0p + (row * g.ldc0 + col) * ES);
             }
         };
-        if constexpr (ADDS) request(0);
 #pragma unroll
         for (int mi = 0; mi < MB; ++mi) {
+            if constexpr (ADDS) request(mi);
             uint8_t* srow = lds + (wm * 32 + (lane & 31)) * PITCH;
 #pragma unroll
             for (int ni = 0; ni < NB; ++ni) {
@@ -827,7 +827,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
                 }
             }
             if constexpr (ADDS) {
-                if (mi + 1 < MB) request(mi + 1);
                 barrier_lds_written();
             } else {
                 __syncthreads();
@@ -840,8 +839,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
                 const int64_t col = n0 + seg * COLS_PER_SEG;
                 if (row < M && col < N) {
                     uint4 d = *reinterpret_cast<const uint4*>(lds + srw * PITCH + seg * 16);
-                    if constexpr (ADDS) d = add_bf16x8(held[mi & 1][it], d);
-                    if (col < g.n_split) {
+                    if constexpr (ADDS) d = add_bf16x8(held[it], d);
+                    if (ADDS || col < g.n_split) {
                         // streaming store: every workgroup writes 512-byte row segments of its tile at
                         // the same time; the output is not read again by this layer
                         typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -873,7 +872,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tiles_m, 
         }
     };
     // (Adding in the epilogue costs the launch 5.5 us at 2048 x 4096 x 4096, 37.6 -> 43.1: the sum is read at the rate of the
-    // memory while the tiles write theirs.  A pass of its own took 9.2 us and a launch.)
+    // memory while the tiles write theirs.  A pass of its own took 9.2 us and a launch.  Whole backward calls, plain and adding, tiles of
+    // 256 rows: 4096 x 4096 <- 4096 82.2 and 86.5 us, 8192 x 4096 <- 4096 149.9 and 167.3, 4096 x 4096 <- 11008, r = 128, 215 and 221; what is
+    // added requested a pass ahead, in twice the registers: 87.6, 168.7 and 220.  These instances spill 16 registers, once per tile
+    // around the last block of the K-loop.)
     if (!ADDS && g.c0_is_f32) epilogue(std::true_type{});
     else epilogue(std::false_type{});
     if constexpr (RIDE) {                                         // (the epilogue ends with a barrier)
@@ -973,9 +975,12 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream)
     const int total = tiles_m * tiles_n;
     const int chunk = (total + 7) / 8;
     const dim3 grid(static_cast<unsigned>(chunk * 8), static_cast<unsigned>(g.splits)), block(64 * WM * WN);
-    if (g.b_is_kn) {
+    if (g.c0_adds) {
+        // (input gradients large enough for 192 or 256 rows leave with dB in their launch; the others are one round of 128)
+        if constexpr (MB == 2) gemm_fp8_kernel<WM, WN, MB, NB, true, 1, true><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
+        else return hipErrorInvalidValue;
+    } else if (g.b_is_kn) {
         if (g.a_fmt == 0) gemm_fp8_kernel<WM, WN, MB, NB, true, 0><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
-        else if (g.c0_adds) gemm_fp8_kernel<WM, WN, MB, NB, true, 1, true><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
         else gemm_fp8_kernel<WM, WN, MB, NB, true, 1><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
     } else {
         if (g.a_fmt == 0) gemm_fp8_kernel<WM, WN, MB, NB, false, 0><<<grid, block, 0, stream>>>(g, tiles_m, tiles_n, chunk);
