@@ -18,11 +18,14 @@ def _layer(T, n, m, r, seed):
     return wq, s_w, ws, g
 
 
-# every kind of tile that an input-gradient product can take: 32 x 64, 64 x 64, 64 x 128, 128 x 128 on rings, with dB inside
-# and apart; 128, 192 and 256 rows of 256 columns; 128 x 128 two to a CU; ragged in rows and columns
+# the kernels that add, by a trace of this list: small tiles of 32 x 64, 64 x 128 and 128 x 128 with dB inside, of 32 x 64, 64 x 64,
+# 64 x 128 and 128 x 128 with dB beside them, of 64 x 128 with dB apart; 128, 192 and 256 rows of 256 columns with dB in the tiles;
+# 256 x 256 with dB in workgroups of its own; 128 x 256 and 128 x 128 two to a CU with dB apart; ragged in rows and columns
 @pytest.mark.parametrize("T,n,m,r", [(17, 272, 144, 16), (200, 1040, 528, 32), (512, 4096, 1024, 64), (777, 1040, 2000, 48),
                                      (1000, 2064, 512, 256), (1024, 4096, 128, 16), (2048, 4096, 512, 64), (1999, 5120, 400, 32),
-                                     (4096, 4112, 272, 64), (4000, 4096, 256, 256), (5000, 1008, 96, 16)])
+                                     (4096, 4112, 272, 64), (4000, 4096, 256, 256), (5000, 1008, 96, 16),
+                                     (285, 4736, 1600, 64), (636, 2688, 9168, 256), (3900, 4096, 2048, 64), (2048, 4096, 4240, 256),
+                                     (2041, 4112, 9168, 128), (5000, 1008, 4240, 64), (3354, 912, 6096, 128)])
 def test_input_gradient_added_in_the_product_is_the_sum_of_the_tensors(T, n, m, r):
     wq, s_w, ws, g = _layer(T, n, m, r, 5)
     dy = torch.randn(T, m, device="cuda", generator=g).mul_(1e-3).to(torch.bfloat16)
