@@ -672,9 +672,13 @@ hipError_t launch_gemm_mid(const GemmArgs& g, const MidSide& side, hipStream_t s
     // rows are shorter or the tiles smaller, the line that one step leaves half used is still near when the next one asks for
     // it, and the stage more costs 0.3 to 1 us.  Plain products, us, by whole lines (from the rows' first bytes): 128-token
     // tiles 1500 x 2000, K = 1040 11.5 (11.2), K = 1552 12.8 (13.1), K = 4112 21.0 (25.9), K = 8208 32.9 (41.9); 64 x 128 512 x 4096,
-    // K = 1040 8.4 (8.6), K = 1552 9.2 (10.4), K = 4112 15.2 (18.5), K = 8208 24.6 (32.6); 64 x 64 256 x 4096, K = 4112 10.9 (11.1),
-    // 500 x 1504, K = 4112 10.7 (10.1), K = 6160 14.2 (17.3); 32 x 64 128 x 4096, K = 6160 12.3 (11.7), K = 8208 15.1 (16.6),
-    // 100 x 3008, K = 8208 14.0 (13.1).  [K,N] operands: only the left one has such rows, 0.3 to 0.5 us slower up to K = 2064,
+    // K = 1040 8.4 (8.6), K = 1552 9.2 (10.4), K = 4112 15.2 (18.5), K = 8208 24.6 (32.6).
+    // The small tiles' lines are for weights that come from memory, as they do in a model, where other layers' calls lie between
+    // two of one layer: 64 x 64 256 x 4096, K = 5136 17.5 (24.2), 500 x 1504, K = 5136 12.9 (16.3); 32 x 64 128 x 4096, K = 8208 19.2
+    // (23.8), 100 x 3008, K = 8208 16.4 (18.9), 64 x 1024, K = 8208 13.8 (15.8).  For calls back to back on one weight that the caches still
+    // hold they can be the slower way: 13.2 (14.6), 12.5 (11.5), 15.4 (16.5), 14.1 (12.5), 13.1 (11.4).  From memory whole lines are ahead
+    // from K = 3088 on in all of 120 products of 17 to 500 tokens (1.02 to 1.49 times as fast), from the caches in 39 of 45 from K = 11024 on (the others down to 0.85).
+    // [K,N] operands: only the left one has such rows, 0.3 to 0.5 us slower up to K = 2064,
     // 2 to 5 % faster from 4112 on: not built.
     switch (plan_mid(g.M, g.N, g.K, g.b_is_kn != 0, side.rows ? side.r : 0).config) {
         case 0: return launch_cfg<1, 1, 8, 8, 8>(t, 64, side.db, stream);
