@@ -70,3 +70,28 @@ def test_group_forward_equals_the_layers_on_the_same_codes(T, n, widths, r, dt):
     assert torch.equal(xq, xq2) and torch.equal(s_x, s_x2) and torch.equal(amax, amax2)
     for p, q in zip(ys + oas, ys2 + oas2):
         assert torch.equal(p, q)
+
+
+def test_group_of_more_layers_than_a_call_takes():
+    """Layers beyond the first 256 run on the same codes in calls of their own."""
+    from paper_2510_24061_amd.nn import MeldedGroup, MeldedLoRALinear
+    T, n, m, r, count = 24, 64, 48, 16, b.GROUP_MAX + 3
+    g = torch.Generator(device="cuda").manual_seed(2)
+    layers = []
+    for _ in range(count):
+        layers.append(MeldedLoRALinear(n, m, r, 4))
+        layers[-1].load_weights(torch.randn(m, n, device="cuda", generator=g).mul_(0.05), torch.randn(r, n, device="cuda", generator=g) / r)
+    x = torch.randn(T, n, device="cuda", generator=g).to(torch.bfloat16)
+    one, all_of_them = x.clone().requires_grad_(True), x.clone().requires_grad_(True)
+    outs = MeldedGroup(*layers)(all_of_them)
+    dys = [torch.randn(T, m, device="cuda", generator=g).mul_(1e-2).to(torch.bfloat16) for _ in range(count)]
+    torch.autograd.backward(outs, dys)
+    d_bs = [layer.d_b.clone() for layer in layers]
+    total = None
+    for layer, y, dy, d_b in zip(layers, outs, dys, d_bs):
+        one.grad = None
+        alone = layer(one)
+        alone.backward(dy)
+        total = one.grad.clone() if total is None else total.add_(one.grad)
+        assert torch.equal(alone, y) and torch.equal(layer.d_b, d_b)
+    assert torch.equal(total, all_of_them.grad)

@@ -228,3 +228,72 @@ def test_da_argument_validation(L):
     assert g(r=8) == 2 and g(n=72) == 2 and g(T=0) == 2
     assert g(xq=odd) == 3 and g(dat=odd) == 3
     assert g(ws=None) == 5 and g(wb=big - 1) == 5
+
+
+def test_adding_backward_argument_validation(L):
+    ok, odd = 0x10000, 0x10004
+    wsb = L.falqon_workspace_bytes(64, 64, 64, 16)
+
+    def f(**kw):
+        a = dict(dy=ok, wq=ok, s_w=ok, o_a=ok, amax=ok, T=64, n=64, m=64, r=16, dyq=ok, s_dy=ok, dx=ok, d_b=ok, buf=ok, sc=None,
+                 ws=ok, wsb=wsb)
+        a.update(kw)
+        return L.falqon_melded_bwd_add(_vp(a["dy"]), _vp(a["wq"]), _vp(a["s_w"]), _vp(a["o_a"]), _vp(a["amax"]), a["T"], a["n"], a["m"],
+                                       a["r"], _vp(a["dyq"]), _vp(a["s_dy"]), _vp(a["dx"]), _vp(a["d_b"]), _vp(a["buf"]),
+                                       ctypes.c_float(1e-3), _vp(a["sc"]), _vp(a["ws"]), a["wsb"], None)
+
+    assert f(dx=None) == 1                                                    # there is nothing to add to
+    assert all(f(**{name: None}) == 1 for name in ("dy", "wq", "s_w", "o_a", "amax", "dyq", "s_dy", "d_b"))
+    assert f(sc=ok, buf=None) == 1
+    assert f(T=0) == 2 and f(n=72) == 2 and f(m=24) == 2 and f(r=8) == 2 and f(r=272) == 2
+    assert all(f(**{name: odd}) == 3 for name in ("dy", "wq", "o_a", "dyq", "dx", "d_b", "buf", "sc", "ws"))
+    assert all(f(**{name: 0x10002}) == 3 for name in ("s_w", "amax", "s_dy"))
+    assert f(ws=None) == 5 and f(wsb=0) == 5
+
+
+def test_group_forward_argument_validation(L):
+    import paper_2510_24061_amd as fq
+    from paper_2510_24061_amd.binding import GroupLayer
+    ok, odd = 0x10000, 0x10004
+    wsb = L.falqon_workspace_bytes(64, 64, 64, 16)
+
+    def layer(**kw):
+        a = dict(wq=ok, s_w=ok, y=ok, o_a=ok, m=64, r=16, ws=ok, ws_bytes=wsb)
+        a.update(kw)
+        return GroupLayer(*(a[name] for name, _ in GroupLayer._fields_))
+
+    def f(*layers, count=None, **kw):
+        a = dict(x=ok, T=64, n=64, xq=ok, s_x=ok, amax=ok, yt=0)
+        a.update(kw)
+        described = (GroupLayer * max(1, len(layers)))(*layers)
+        return L.falqon_melded_fwd_group(_vp(a["x"]), a["T"], a["n"], described if layers else None, len(layers) if count is None else count,
+                                         _vp(a["xq"]), _vp(a["s_x"]), _vp(a["amax"]), a["yt"], None)
+
+    good = layer()
+    assert f(good, yt=2) == 4
+    assert f(good, count=0) == 2 and f(good, count=-1) == 2 and f(*[good] * 257) == 2          # FALQON_GROUP_MAX
+    assert f(count=1) == 1                                                    # no descriptions
+    assert all(f(good, **{name: None}) == 1 for name in ("x", "xq", "s_x", "amax"))
+    assert f(good, x=odd) == 3 and f(good, xq=odd) == 3 and f(good, s_x=0x10002) == 3 and f(good, amax=0x10002) == 3
+    # each layer's own, also behind good ones
+    for before in ([], [good, good]):
+        assert all(f(*before, layer(**{name: None})) == 1 for name in ("wq", "s_w", "y", "o_a"))
+        assert all(f(*before, layer(**kw)) == 2 for kw in (dict(m=0), dict(m=72), dict(r=8), dict(r=272)))
+        assert all(f(*before, layer(**{name: odd})) == 3 for name in ("wq", "y", "o_a", "ws"))
+        assert f(*before, layer(s_w=0x10002)) == 3
+        assert f(*before, layer(ws=None)) == 5 and f(*before, layer(ws_bytes=0)) == 5
+    assert f(good, T=0) == 2 and f(good, n=72) == 2
+    assert fq.binding.GROUP_MAX == 256
+
+
+def test_group_forward_refuses_mixed_outputs_and_tensors_off_the_gpu():
+    import torch
+    from paper_2510_24061_amd import binding as b
+    t, amax = torch.zeros(16, 16), torch.zeros(2)
+    one, other = (t, t, 16, 16, t, t, t), (t, t, 16, 16, t.to(torch.bfloat16), t, t)
+    with pytest.raises(ValueError, match="one type"):
+        b.melded_fwd_group(t, [one, other], t, t, amax)
+    with pytest.raises(ValueError, match="one maximum"):
+        b.melded_fwd_group(t, [one], t, t, amax)
+    with pytest.raises(ValueError, match="contiguous GPU"):
+        b.melded_fwd_group(t, [one, one], t, t, amax)

@@ -61,6 +61,7 @@ def test_rates_are_what_float_takes(monkeypatch):
     b.melded_bwd_add(*t, 16, 16, None, None, None, None, None, torch.tensor(0.5), None)
     assert rates == [2e-4, 0.5] and all(type(r) is float for r in rates)
 
+
 @pytest.mark.gpu
 def test_update_takes_the_width_of_a_weight_of_more_dimensions():
     m, r, n, k = 32, 16, 64, 4
