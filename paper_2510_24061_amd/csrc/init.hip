@@ -49,9 +49,10 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 // The two products with E run on the bf16 matrix cores, with both operands in three parts: an fp32 number is the sum of its
 // rounding to bf16, the rounding of what that leaves, and what is left then (8 bits and a sign each, exact).  Six of the
-// nine products of parts are formed (v_mfma_f32_16x16x32_bf16, exact products added in fp32, small ones first); the
-// others are below 2^-26 of the whole, and an instruction adds 32 terms where the fp32 one adds four, so sums come out nearer to
-// 64 bits than on the fp32 matrix cores (3.7e-7 against 5.4e-7 of a sum of 4096 terms of random sign).  At 4096 x 4096,
+// nine products of parts are formed (v_mfma_f32_16x16x32_bf16, exact products added in fp32, small ones first).  The
+// others are at most 2^-24 of the whole (parts of 2^-8 and 2^-17 of their elements, twice), 2^-27.4 of it in the mean square (the largest of 4
+// million drawn pairs 2^-24.2): what rounding a term to fp32 could cost, which the fp32 cores do not do.  An instruction adds 32
+// terms where the fp32 one adds four, and sums come out nearer to 64 bits all the same (3.7e-7 against 5.4e-7 of a sum of 4096 terms of random sign).  At 4096 x 4096,
 // l = 72, the fp32 cores need 17 us for a product, the six on the bf16 ones 6.5, and E, split on the way from memory to the
 // operands, becomes what bounds it: a launch takes 21.6 us (30.5 on the fp32 cores; 25 with the operands of two steps in registers instead of three).
 // Elements whose parts bf16 does not hold (look_at_range) take the fp32 cores: no packing and no ring there, such matrices are rare.
