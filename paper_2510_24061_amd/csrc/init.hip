@@ -55,7 +55,8 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // terms where the fp32 one adds four, and sums come out nearer to 64 bits all the same (3.7e-7 against 5.4e-7 of a sum of 4096 terms of random sign).  At 4096 x 4096,
 // l = 72, the fp32 cores need 17 us for a product, the six on the bf16 ones 6.5, and E, split on the way from memory to the
 // operands, becomes what bounds it: a launch takes 21.6 us (30.5 on the fp32 cores; 25 with the operands of two steps in registers instead of three).
-// Elements whose parts bf16 does not hold (look_at_range) take the fp32 cores: no packing and no ring there, such matrices are rare.
+// Elements whose parts bf16 does not hold (look_at_range) take the fp32 cores, without packing or a ring: initialization of 4096 x 4096, r = 64,
+// 1460 us (1275 in parts, 1563 with packed vectors on the fp32 cores for all).
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v8f __attribute__((ext_vector_type(8)));
 constexpr int kParts = 3;
@@ -80,13 +81,12 @@ __device__ __forceinline__ void split(v8f x, v8bf (&part)[kParts])
 // column t % 16 = the second operand's row, and in register v the first operand's row 4 (t / 16) + v.
 template <int CB>
 struct Products {
-    static_assert(CB <= 7, "eight blocks spill 66 registers");
+    static_assert(CB <= 7, "eight blocks are two halves");
     v4f acc[4][CB];
     static constexpr int DEPTH = CB <= 5 ? 3 : 2;                     // steps whose operands are in registers or on their way
     v8bf zf[DEPTH][CB][kParts];
 
-    __device__ __forceinline__ Products() { clear(); }
-    __device__ __forceinline__ void clear()
+    __device__ __forceinline__ Products()
     {
 #pragma unroll
         for (int x = 0; x < 4; ++x)
@@ -101,13 +101,14 @@ struct Products {
 #pragma unroll
             for (int k = 0; k < kParts; ++k) zf[which][cb][k] = packed[((step * blocks + first + cb) * kParts + k) * 64 + lane];
     }
-    // steps first, first + 4, ... below end
+    // steps first, first + 4, ... below end; none where the word says so, which is looked at behind the first requests
     template <class F, class M>
-    __device__ __forceinline__ static void run(int64_t first, int64_t end, F fetch, M multiply)
+    __device__ __forceinline__ static void run(int64_t first, int64_t end, int outside, F fetch, M multiply)
     {
 #pragma unroll
         for (int d = 0; d + 1 < DEPTH; ++d)
             if (first + 4 * d < end) fetch(first + 4 * d, d);
+        if (outside) return;
         for (int64_t b = first; b < end; b += 4 * DEPTH) {
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {
@@ -118,27 +119,30 @@ struct Products {
             }
         }
     }
-    // The same from the beginning on the fp32 matrix cores, with the vectors as they are.  (Behind the steps above, so that nothing waits
-    // for the word that asks for it.)  vector: the one of this lane in the first block, of `length`
-    // elements, with `vectors` from it on; operand(i, x): element i of this lane's row or column of E in block x.
-    template <class O>
+    // The same on the fp32 matrix cores, with the vectors as they are.  vector: the one of this lane in the first block, of `length`
+    // elements, with `vectors` from it on; operand(i, k): elements i .. i + 3 of this lane's row of E in block k (ROWS) or those of its
+    // column in all four blocks from row i + k.  Depth index `quad` of four consecutive instructions stands for four elements in a row.
+    template <bool ROWS, class O>
     __device__ __forceinline__ void run_fp32(const float* vector, int vectors, int64_t length, int64_t first, int64_t end, int quad, O operand)
     {
-        clear();
         for (int64_t b = first; b < end; b += 4) {
-#pragma unroll 1
-            for (int u = 0; u < 8; ++u) {                             // depth index of the instruction: quad
-                const int64_t i = b * 32 + 4 * u + quad;
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const int64_t i = b * 32 + 16 * half + 4 * quad;      // (lengths are multiples of 4)
                 const bool in = i < length;
-                float o[4];
+                v4f o[4], z[CB];
 #pragma unroll
-                for (int x = 0; x < 4; ++x) o[x] = in ? operand(i, x) : 0.0f;
+                for (int k = 0; k < 4; ++k) o[k] = in ? operand(i, k) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    const float z = in && 16 * cb < vectors ? vector[16 * cb * length + i] : 0.0f;
+                for (int cb = 0; cb < CB; ++cb)
+                    z[cb] = in && 16 * cb < vectors ? *reinterpret_cast<const v4f*>(vector + 16 * cb * length + i) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(z, o[x], acc[x][cb], 0, 0, 0);
-                }
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb)
+                            acc[x][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[cb][u], ROWS ? o[x][u] : o[u][x], acc[x][cb], 0, 0, 0);
             }
         }
     }
@@ -157,7 +161,7 @@ struct Products {
 };
 
 // part[s][c][i] = sum over columns j of slice s of Z[c][j] E[i][j]; a workgroup owns 64 rows of E and CB blocks of vectors (all
-// up to seven, at 510 of 512 registers; eight would spill 66 and are two halves, which give the same bits)
+// up to seven, at 424 of 512 registers; eight, which spilled 66 where seven took 508, are two halves, which give the same bits)
 template <int CB>
 __global__ void __launch_bounds__(kThreads)
 apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __restrict__ zp, const float* __restrict__ z, int l,
@@ -194,8 +198,10 @@ apply_e_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* __
         for (int x = 0; x < 4; ++x) p.multiply(x, __builtin_shufflevector(ef[which][x][0], ef[which][x][1], 0, 1, 2, 3, 4, 5, 6, 7), which);
     };
     const int c0 = 16 * CB * static_cast<int>(blockIdx.z);
-    p.run(begin + wave, end, fetch, multiply);
-    if (outside) p.run_fp32(z + (c0 + row16) * n, l - c0 - row16, n, begin + wave, end, quad, [&](int64_t j, int x) { return erow[x][j]; });
+    p.run(begin + wave, end, outside, fetch, multiply);
+    if (outside)
+        p.template run_fp32<true>(z + (c0 + row16) * n, l - c0 - row16, n, begin + wave, end, quad,
+                                  [&](int64_t j, int x) { return *reinterpret_cast<const v4f*>(erow[x] + j); });
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
@@ -250,8 +256,10 @@ apply_et_kernel(const float* __restrict__ e, int64_t m, int64_t n, const v8bf* _
         }
     };
     const int c0 = 16 * CB * static_cast<int>(blockIdx.z);
-    p.run(begin + wave, end, fetch, multiply);
-    if (outside) p.run_fp32(y + (c0 + row16) * m, l - c0 - row16, m, begin + wave, end, quad, [&](int64_t i, int x) { return e[i * n + col + x]; });
+    p.run(begin + wave, end, outside, fetch, multiply);
+    if (outside)
+        p.template run_fp32<false>(y + (c0 + row16) * m, l - c0 - row16, m, begin + wave, end, quad,
+                                   [&](int64_t i, int v) { return *reinterpret_cast<const v4f*>(e + (i + v) * n + col); });
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -348,8 +356,9 @@ __device__ __forceinline__ void for_each(F f)
     }
 }
 
-// *wide <- 1 where E has entries that the parts of the products do not hold: beyond 2^120, not finite, or below 2^-64 but not
-// zero (the last part of an element is 2^-17 of it, and its product with that of a vector has to stay above 2^-149).
+// *wide <- 1 where E has entries that the parts of the products do not hold: beyond 2^120 (rounding up must not overflow, nor a sum of
+// what was rounded up), not finite, or below 2^-109 but not zero (bits down to 2^-133 are bf16's; conversion and matrix instruction keep
+// subnormals).  Elements of the vectors, of length 1, lose no more than 2^-134 and are not looked at.
 struct RangeOf {
     const float* e;
     int64_t count;                                                    // a multiple of 16
@@ -357,7 +366,7 @@ struct RangeOf {
 };
 __device__ __forceinline__ void look_at_range(const RangeOf& r, int64_t first, int64_t stride)
 {
-    constexpr uint32_t LEAST = uint32_t{127 - 64} << 23, MOST = uint32_t{127 + 120} << 23;
+    constexpr uint32_t LEAST = uint32_t{127 - 109} << 23, MOST = uint32_t{127 + 120} << 23;
     bool outside = false;
     for (int64_t i = 4 * first; i < r.count; i += 4 * stride) {
         const uint4 v = *reinterpret_cast<const uint4*>(r.e + i);

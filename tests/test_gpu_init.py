@@ -256,7 +256,7 @@ def test_both_factors_where_the_rank_is_lower_than_asked_for(m, n, r, rank, iter
         assert np.linalg.norm(bt.T @ a - e) <= 1e-6 * np.linalg.norm(e) * np.sqrt(rank)
 
 
-@pytest.mark.parametrize("largest", [3.3999e38, 1e-3, 1.7e-36])
+@pytest.mark.parametrize("largest", [3.3999e38, 1.3e36, 1e-3, 8e-33, 1.7e-36])
 def test_entries_at_the_ends_of_the_range(largest):
     """The products take elements in parts of 8 bits, which hold numbers up to 3.39e38 and, to all their bits, down to 1.5e-33:
     beyond that the elements have to be taken whole.  Twenty entries in rows and columns of their own are the singular values,
@@ -274,7 +274,7 @@ def test_entries_at_the_ends_of_the_range(largest):
 
 
 @pytest.mark.parametrize("r", [16, 32, 40, 64, 80, 88, 104, 120])
-@pytest.mark.parametrize("scale", [1e-30, 1e36])
+@pytest.mark.parametrize("scale", [1e-34, 1e36])
 def test_products_of_whole_elements_against_64_bits(r, scale):
     """Every number of vector blocks with elements beyond the range of the parts, on sizes that end inside steps and tiles.
     Bounds as in the products of many steps above."""

@@ -10,7 +10,7 @@ import paper_2510_24061_amd as fq
 from test_lds_waits import _code_objects
 
 READELF = os.environ.get("LLVM_READELF", "/opt/rocm/llvm/bin/llvm-readelf")
-# the initialization's kernels, the products with up to 510 of 512 registers among them
+# the initialization's kernels, the products, which hold operands of several steps, among them
 INIT = ("apply_e_kernel", "apply_et_kernel", "apply_lower_kernel", "eigenvector_kernel", "factor_kernel", "gram_kernel",
         "init_residual_kernel", "jacobi_eig_kernel", "rotate_kernel", "settle_kernel", "sum_slices_kernel")
 
