@@ -1,7 +1,7 @@
 """MI355X-native melded FP8-LoRA linear layer (hot path of FALQON, arXiv 2510.24061).
 
 The compute lives in libfalqon.so (hand-written HIP for gfx950, C ABI in include/falqon.h).
-This package is a thin ctypes binding with the same four names; PyTorch is used only to own
+This package is a thin binding with the same names (a Python extension for a step's calls, ctypes for the others); PyTorch is used only to own
 device memory and streams.
 """
 from .binding import (  # noqa: F401

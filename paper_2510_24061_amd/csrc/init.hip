@@ -572,13 +572,14 @@ apply_lower_kernel(const float* src, float* dst, uint32_t* __restrict__ packed, 
 
 // H[a][b] = sum_i Y[a][i] Y[b][i] in fp64.  A workgroup forms a block of 4 x 4 sums, so that a row is read l / 4
 // times and not l times, with the next operands in flight (6.2 us at 72 x 4096, 9.7 without; 5.9 with the first two exchanges of the reduction within four lanes, not through LDS); grid (l / 4, l / 4), the upper half leaves, the lower one
-// writes both.
+// writes both.  CLEARS: *wide <- 0, for the launch that follows.
+template <bool CLEARS>
 __global__ void __launch_bounds__(kThreads)
 gram_kernel(const float* __restrict__ y, int l, int64_t m, double* __restrict__ h, int* wide)
 {
     __shared__ double s_red[kThreads / 64][16];
     if (blockIdx.y > blockIdx.x) return;
-    if (wide && blockIdx.x == 0 && threadIdx.x == 0) *wide = 0;        // for the launch that follows
+    if (CLEARS && blockIdx.x == 0 && threadIdx.x == 0) *wide = 0;
     const float* const ya = y + static_cast<int64_t>(4 * blockIdx.x) * m;
     const float* const yb = y + static_cast<int64_t>(4 * blockIdx.y) * m;
     double d[16];
@@ -663,7 +664,7 @@ __device__ __forceinline__ double quad_sum(double v)
 // Round-robin ordering, a round rotates l/2 disjoint pairs of columns, each pair in four lanes: the dot product of the two is
 // reduced within the lanes, every lane forms the rotation, and both columns go back to LDS; one barrier per round.  Their squared
 // lengths follow from the rotation, to 1e-12 of each, and are formed anew once per sweep and where little of one is left: with three dot products
-// and a tangent to full precision per pair the launch took 4 % more at l = 72.
+// and a tangent to full precision per pair the launch took 577 us at l = 72, 562 now (flat spectrum, nine sweeps).
 // A round is bound by the columns' way through LDS (writes at 76 B/clk) and the instructions that a SIMD issues, and those of
 // the rotation count once per wave: four lanes per pair make l / 32 waves, one per SIMD.  (Columns that stay in registers and
 // move on by a lane per round, their edges through LDS, took 1.06 us a round at l = 72 against 0.95: a b128 access of four lanes costs
@@ -945,8 +946,10 @@ static hipError_t orthonormalize_rows(const float* src, float* dst, uint32_t* pa
     const unsigned blocks = static_cast<unsigned>((len + 31) / 32 * 2);
     for (int pass = 0; pass < passes; ++pass) {
         const float* const v = pass ? dst : src;
-        gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h, pass ? nullptr : range.wide);
-        const unsigned lookers = range.wide && !pass ? 1020 : 0;
+        const bool looks = range.wide && !pass;
+        const unsigned lookers = looks ? 1020 : 0;
+        if (looks) gram_kernel<true><<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h, range.wide);
+        else gram_kernel<false><<<dim3(nb, nb), kThreads, 0, stream>>>(v, l, len, h, nullptr);
 #define FQ_APPLY(CB)                                                                                         \
         factor_kernel<CB, false><<<1 + lookers, 64 * factor_waves(CB), 0, stream>>>(h, l, lfac, range);      \
         apply_lower_kernel<CB><<<blocks, CB * 64, 0, stream>>>(v, dst, packed, l, len, lfac, asked)
@@ -1012,7 +1015,7 @@ hipError_t launch_svd_right_factor(const float* e, int64_t m, int64_t n, int64_t
     }
     FQ_CHECK(product(false, y));
     const int nb = l / 4;
-    gram_kernel<<<dim3(nb, nb), kThreads, 0, stream>>>(y, l, m, h, nullptr);
+    gram_kernel<false><<<dim3(nb, nb), kThreads, 0, stream>>>(y, l, m, h, nullptr);
 #define FQ_FACTOR(CB) factor_kernel<CB, true><<<1, 64 * factor_waves(CB), 0, stream>>>(h, l, p, RangeOf{nullptr, 0, nullptr})
     FQ_BY_BLOCKS((l + 15) / 16, FQ_FACTOR)
 #undef FQ_FACTOR
